@@ -630,8 +630,8 @@ int emb_cache_select_workspace_bytes(int64_t num_rows, size_t *bytes);
  * emb_cache_select_workspace_bytes, contents irrelevant (EMB_ERR_WORKSPACE
  * otherwise).  info_out_dev (nullable, u64[2], only written when num_hot > 0):
  * [0] = the smallest counter value in the hot set, [1] = how many rows with
- * exactly that value it holds.  Reads the counters six times and writes them
- * once: 1 GB of counters (2.5e8 rows) takes a few milliseconds. */
+ * exactly that value it holds.  Reads the counters three times (six where the
+ * threshold is 2047 or more) and writes those that are not zero once. */
 int emb_cache_select(uint32_t *freq_dev, int64_t num_rows, int64_t num_hot, int32_t decay_shift,
                      void *workspace_dev, size_t workspace_bytes, int64_t *hot_rows_out_dev,
                      uint64_t *info_out_dev, void *stream);
@@ -669,6 +669,17 @@ int emb_cache_rebuild(const void *table_dev, int64_t num_rows, int32_t D, int32_
                       const void *old_cache_rows_dev, const void *old_cache_index_dev,
                       int64_t old_num_hot, const int64_t *hot_rows_dev, int64_t num_hot,
                       void *cache_rows_dev, void *cache_index_dev, uint64_t *moved_dev,
+                      uint32_t *status_dev, void *stream);
+
+/* A whole refresh in one call: emb_cache_select, then emb_cache_rebuild with the
+ * rows it chose.  Same arguments, results and errors as the two calls; the pass
+ * that writes the chosen rows writes the new cache's index and copies its rows as
+ * well. */
+int emb_cache_refresh(uint32_t *freq_dev, int64_t num_rows, int64_t num_hot, int32_t decay_shift,
+                      void *workspace_dev, size_t workspace_bytes, const void *table_dev, int32_t D,
+                      int32_t dtype, const void *old_cache_rows_dev, const void *old_cache_index_dev,
+                      int64_t old_num_hot, int64_t *hot_rows_out_dev, void *cache_rows_dev,
+                      void *cache_index_dev, uint64_t *moved_dev, uint64_t *info_out_dev,
                       uint32_t *status_dev, void *stream);
 
 /* ---- version-tagged table sets (Section 3.3, Algorithms 1 and 2) ----------

@@ -57,7 +57,7 @@ EXPORTS = [
     "emb_version_hosted_latch", "emb_bag_forward_cached_latched", "emb_bag_forward_cached_latched_hashed",
     "emb_cached_tables_init", "emb_bag_forward_cached_tables", "emb_bag_forward_cached_tables_hashed", "emb_bag_forward_cached_tables_hashed_lengths",
     "emb_cache_observe", "emb_cache_observe_hashed", "emb_cache_select_workspace_bytes", "emb_cache_select", "emb_cache_select_static",
-    "emb_cache_rebuild",
+    "emb_cache_rebuild", "emb_cache_refresh",
     "emb_table_fill", "emb_checksum",
 ]
 
@@ -187,6 +187,8 @@ def lib() -> C.CDLL:
     L.emb_cache_select_static.argtypes = [vp, i64, i64, i32, vp, vp, vp]
     L.emb_cache_rebuild.restype = C.c_int
     L.emb_cache_rebuild.argtypes = [vp, i64, i32, i32, vp, vp, i64, vp, i64, vp, vp, vp, vp, vp]
+    L.emb_cache_refresh.restype = C.c_int
+    L.emb_cache_refresh.argtypes = [vp, i64, i64, i32, vp, sz, vp, i32, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     L.emb_version_record_bytes.restype = C.c_int
     L.emb_version_record_bytes.argtypes = [i32, C.POINTER(sz)]
     L.emb_version_latch_bytes.restype = C.c_int
@@ -831,6 +833,23 @@ def emb_cache_rebuild(table_ptr: int, num_rows: int, D: int, dtype: str, old_cac
         _ptr(hot_rows, torch.int64, "hot_rows"), hot_rows.numel(), _ptr(cache_rows, _TABLE_TORCH[dtype], "cache_rows"),
         _ptr(cache_index, torch.uint8, "cache_index"), _ptr(moved, _U64, "moved"), _ptr(status, torch.int32, "status"),
         _stream()))
+
+
+def emb_cache_refresh(freq: torch.Tensor, num_hot: int, decay_shift: int, workspace: torch.Tensor, table_ptr: int, D: int,
+                      dtype: str, old_cache_rows: Optional[torch.Tensor], old_cache_index: torch.Tensor,
+                      old_num_hot: int, hot_rows_out: torch.Tensor, cache_rows: torch.Tensor, cache_index: torch.Tensor,
+                      moved: Optional[torch.Tensor] = None, info_out: Optional[torch.Tensor] = None,
+                      status: Optional[torch.Tensor] = None) -> None:
+    """``emb_cache_select`` followed by ``emb_cache_rebuild`` with the rows it chose, in one call."""
+    if hot_rows_out.numel() < num_hot:
+        raise TypeError("hot_rows_out too small")
+    _check("emb_cache_refresh", lib().emb_cache_refresh(
+        _ptr(freq, _U32, "freq"), freq.numel(), int(num_hot), int(decay_shift), _ptr(workspace, torch.uint8, "workspace"),
+        workspace.numel(), int(table_ptr), int(D), DTYPE[dtype], _ptr(old_cache_rows, _TABLE_TORCH[dtype], "old_cache_rows"),
+        _ptr(old_cache_index, torch.uint8, "old_cache_index"), int(old_num_hot),
+        _ptr(hot_rows_out, torch.int64, "hot_rows_out"), _ptr(cache_rows, _TABLE_TORCH[dtype], "cache_rows"),
+        _ptr(cache_index, torch.uint8, "cache_index"), _ptr(moved, _U64, "moved"), _ptr(info_out, _U64, "info_out"),
+        _ptr(status, torch.int32, "status"), _stream()))
 
 
 def emb_version_record_bytes(T: int) -> int:

@@ -14,17 +14,21 @@ struct CacheEntry {
 };
 static_assert(sizeof(CacheEntry) == 16, "cache index entry must be 16 bytes");
 
-// Slot of row r (0 <= r < num_rows) in the cache, or -1 if the row is not cached.
-__device__ __forceinline__ int64_t cache_probe(const CacheEntry *__restrict__ index, uint64_t r, uint64_t num_hot)
+// Slot in the cache of the row that bit `bit` of an index entry stands for, or -1 if it is not cached.
+__device__ __forceinline__ int64_t cache_slot(const uint4 &entry, int bit, uint64_t num_hot)
 {
-    const uint4 raw = load_chunk(reinterpret_cast<const char *>(index + (r >> 6)));   // device memory
-    const uint64_t bits = ((uint64_t)raw.y << 32) | raw.x;
-    const int bit = (int)(r & 63);
+    const uint64_t bits = ((uint64_t)entry.y << 32) | entry.x;
     if ((bits >> bit) & 1ull) {
-        const uint64_t slot = (uint64_t)raw.z + (uint64_t)__popcll(bits & ((1ull << bit) - 1ull));
+        const uint64_t slot = (uint64_t)entry.z + (uint64_t)__popcll(bits & ((1ull << bit) - 1ull));
         if (slot < num_hot) return (int64_t)slot;   // always true for an index built from a valid hot set
     }
     return -1;
+}
+
+// Slot of row r (0 <= r < num_rows) in the cache, or -1 if the row is not cached.
+__device__ __forceinline__ int64_t cache_probe(const CacheEntry *__restrict__ index, uint64_t r, uint64_t num_hot)
+{
+    return cache_slot(load_chunk(reinterpret_cast<const char *>(index + (r >> 6))), (int)(r & 63), num_hot);   // device memory
 }
 
 // hit_miss[0] += hits, hit_miss[1] += misses, summed over the workgroup first: every thread of the

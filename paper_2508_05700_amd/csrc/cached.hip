@@ -31,74 +31,97 @@ __global__ __launch_bounds__(CB_BLOCK) void cache_clear_kernel(uint4 *index, int
 }
 
 // One thread per hot row: validate the ordering, set its bit, and let the
-// first hot row of every entry record how many hot rows precede it.
+// first hot row of every entry record how many hot rows precede it.  The rows
+// ascend, so neighbouring lanes often share an entry: the lanes of an entry OR
+// their bits by shuffles and one of them adds the word (one atomic per row, up to
+// 64 of them on one word, took 62 us for 1e6 rows).
 __global__ __launch_bounds__(CB_BLOCK) void cache_mark_kernel(const int64_t *__restrict__ hot, int64_t num_hot,
                                                               int64_t num_rows, CacheEntry *index, uint32_t *status)
 {
-    int64_t k = (int64_t)blockIdx.x * CB_BLOCK + threadIdx.x;
-    if (k >= num_hot) return;
-    const int64_t r = hot[k];
-    const int64_t prev = k > 0 ? hot[k - 1] : -1;
-    if (r < 0 || r >= num_rows || r <= prev) {
-        emb_flag(status, EMB_STATUS_BAD_HOT_SET);
-        return;
+    const int64_t k = (int64_t)blockIdx.x * CB_BLOCK + threadIdx.x;
+    const int lane = threadIdx.x & (EMB_WAVE - 1);
+    int64_t entry = -1, prev = -1;
+    uint64_t bits = 0;
+    if (k < num_hot) {
+        const int64_t r = hot[k];
+        prev = k > 0 ? hot[k - 1] : -1;
+        if (r < 0 || r >= num_rows || r <= prev) {
+            emb_flag(status, EMB_STATUS_BAD_HOT_SET);
+        } else {
+            entry = r >> 6;
+            bits = 1ull << (r & 63);
+        }
     }
-    CacheEntry *e = index + (r >> 6);
-    atomicOr(reinterpret_cast<unsigned long long *>(&e->bits), 1ull << (r & 63));
-    if (prev < 0 || (prev >> 6) != (r >> 6)) e->before = (uint32_t)k;
+    const int64_t left = shfl_i64(entry, lane > 0 ? lane - 1 : 0, EMB_WAVE);
+#pragma unroll
+    for (int d = 1; d < EMB_WAVE; d <<= 1) {
+        const int from = lane + d < EMB_WAVE ? lane + d : lane;
+        const int64_t e = shfl_i64(entry, from, EMB_WAVE);
+        const uint64_t b = (uint64_t)shfl_i64((int64_t)bits, from, EMB_WAVE);
+        if (e == entry) bits |= b;
+    }
+    if (entry < 0) return;
+    CacheEntry *e = index + entry;
+    if (lane == 0 || left != entry) atomicOr(reinterpret_cast<unsigned long long *>(&e->bits), (unsigned long long)bits);
+    if (prev < 0 || (prev >> 6) != entry) e->before = (uint32_t)k;
 }
 
-// One thread per 16-byte chunk copies the hot rows into the cache.  With an
-// older cache at hand (a refresh), a row that it holds is taken from there, in
-// HBM, and only newly admitted rows are read from the table.  moved (nullable):
-// [0] += rows taken from the older cache, [1] += rows read from the table.
-__global__ __launch_bounds__(CB_BLOCK) void cache_copy_kernel(const char *__restrict__ table,
-                                                              const char *__restrict__ old_rows,
-                                                              const CacheEntry *__restrict__ old_index,
-                                                              int64_t old_num_hot, const int64_t *__restrict__ hot,
-                                                              int64_t num_hot, int64_t num_rows, int32_t chunks_per_row,
-                                                              char *__restrict__ cache_rows, unsigned long long *moved)
+// One thread per 16-byte chunk copies the hot rows into the cache, COPY_UNROLL
+// chunks at a time.  With an older cache at hand (a refresh), a row that it holds
+// is taken from there, in HBM, and only newly admitted rows are read from the
+// table.  moved (nullable): [0] += rows taken from the older cache, [1] += rows
+// read from the table, summed over the workgroup first: adds to one word are
+// served one at a time, about 24 ns each, so a launch has COPY_GRID workgroups.
+constexpr int COPY_BLOCK = 512;
+constexpr int COPY_UNROLL = 4;
+constexpr int COPY_GRID = 512;
+__global__ __launch_bounds__(COPY_BLOCK) void cache_copy_kernel(const char *__restrict__ table,
+                                                                const char *__restrict__ old_rows,
+                                                                const CacheEntry *__restrict__ old_index,
+                                                                int64_t old_num_hot, const int64_t *__restrict__ hot,
+                                                                int64_t num_hot, int64_t num_rows, int32_t chunks_per_row,
+                                                                char *__restrict__ cache_rows, unsigned long long *moved)
 {
     const int64_t total = num_hot * chunks_per_row;
+    const int64_t stride = (int64_t)gridDim.x * COPY_BLOCK;
     uint32_t kept = 0u, fetched = 0u;
-    for (int64_t i = (int64_t)blockIdx.x * CB_BLOCK + threadIdx.x; i < total; i += (int64_t)gridDim.x * CB_BLOCK) {
-        const int64_t k = i / chunks_per_row;
-        const int64_t c = i - k * chunks_per_row;
-        const int64_t r = hot[k];
-        if (r < 0 || r >= num_rows) continue;
-        const char *src = table + r * chunks_per_row * 16;
-        bool in_old = false;
-        if (old_index) {
-            const uint4 raw = *reinterpret_cast<const uint4 *>(old_index + (r >> 6));
-            const uint64_t bits = ((uint64_t)raw.y << 32) | raw.x;
-            const int bit = (int)(r & 63);
-            if ((bits >> bit) & 1ull) {
-                const int64_t slot = (int64_t)raw.z + __popcll(bits & ((1ull << bit) - 1ull));
-                if (slot < old_num_hot) {
-                    src = old_rows + slot * chunks_per_row * 16;
-                    in_old = true;
-                }
+    for (int64_t i0 = (int64_t)blockIdx.x * COPY_BLOCK + threadIdx.x; i0 < total; i0 += stride * COPY_UNROLL) {
+        int64_t row[COPY_UNROLL], chunk[COPY_UNROLL];
+        uint4 entry[COPY_UNROLL], v[COPY_UNROLL];
+#pragma unroll
+        for (int u = 0; u < COPY_UNROLL; ++u) {
+            const int64_t i = i0 + u * stride;
+            row[u] = -1;
+            chunk[u] = 0;
+            if (i < total) {
+                // (below 2^32 the quotient takes a 32-bit division)
+                const int64_t k = total <= 0xFFFFFFFFll ? (int64_t)((uint32_t)i / (uint32_t)chunks_per_row) : i / chunks_per_row;
+                chunk[u] = i - k * chunks_per_row;
+                row[u] = hot[k];
+                if (row[u] < 0 || row[u] >= num_rows) row[u] = -1;
             }
         }
-        const uint4 v = *reinterpret_cast<const uint4 *>(src + c * 16);
-        *reinterpret_cast<uint4 *>(cache_rows + i * 16) = v;
-        if (c == 0) {
-            kept += in_old ? 1u : 0u;
-            fetched += in_old ? 0u : 1u;
-        }
-    }
-    if (moved) {
-        // the loop has ended for every lane of the wavefront: reduce, then one atomic per wavefront
 #pragma unroll
-        for (int d = EMB_WAVE >> 1; d >= 1; d >>= 1) {
-            kept += __shfl_xor(kept, d, EMB_WAVE);
-            fetched += __shfl_xor(fetched, d, EMB_WAVE);
+        for (int u = 0; u < COPY_UNROLL; ++u) {
+            entry[u] = make_uint4(0u, 0u, 0u, 0u);
+            if (old_index && row[u] >= 0) entry[u] = load_chunk(reinterpret_cast<const char *>(old_index + (row[u] >> 6)));
         }
-        if ((threadIdx.x & (EMB_WAVE - 1)) == 0) {
-            if (kept) atomicAdd(&moved[0], (unsigned long long)kept);
-            if (fetched) atomicAdd(&moved[1], (unsigned long long)fetched);
+#pragma unroll
+        for (int u = 0; u < COPY_UNROLL; ++u) {
+            if (row[u] < 0) continue;
+            const int64_t slot = cache_slot(entry[u], (int)(row[u] & 63), (uint64_t)old_num_hot);
+            const char *src = slot >= 0 ? old_rows + slot * chunks_per_row * 16 : table + row[u] * chunks_per_row * 16;
+            v[u] = load_chunk(src + chunk[u] * 16);
+            if (chunk[u] == 0) {
+                kept += slot >= 0 ? 1u : 0u;
+                fetched += slot >= 0 ? 0u : 1u;
+            }
         }
+#pragma unroll
+        for (int u = 0; u < COPY_UNROLL; ++u)
+            if (row[u] >= 0) *reinterpret_cast<uint4 *>(cache_rows + (i0 + u * stride) * 16) = v[u];
     }
+    cache_add_hit_miss(kept, fetched, moved);
 }
 
 // Rows come from the HBM cache when present, else from the (host) table.
@@ -414,10 +437,9 @@ extern "C" int emb_host_device_pointer(const void *host_ptr, void **dev_ptr_out)
     return EMB_OK;
 }
 
-static int cache_build_entry(const void *table_dev, int64_t num_rows, int32_t D, int32_t dtype,
-                             const void *old_rows_dev, const void *old_index_dev, int64_t old_num_hot,
-                             const int64_t *hot_rows_dev, int64_t num_hot, void *cache_rows_dev, void *cache_index_dev,
-                             uint64_t *moved_dev, uint32_t *status_dev, void *stream)
+int emb_check_cache_build(const void *table_dev, int64_t num_rows, int32_t D, int32_t dtype, const void *old_rows_dev,
+                          const void *old_index_dev, int64_t old_num_hot, const int64_t *hot_rows_dev, int64_t num_hot,
+                          const void *cache_rows_dev, const void *cache_index_dev)
 {
     if (num_rows <= 0 || num_hot < 0 || num_hot > num_rows) return EMB_ERR_INVALID_ARG;
     int rc = cached_row_shape(D, dtype);
@@ -434,6 +456,17 @@ static int cache_build_entry(const void *table_dev, int64_t num_rows, int32_t D,
         if (old_index_dev == cache_index_dev || (old_rows_dev && old_rows_dev == cache_rows_dev))
             return EMB_ERR_INVALID_ARG;
     }
+    return EMB_OK;
+}
+
+static int cache_build_entry(const void *table_dev, int64_t num_rows, int32_t D, int32_t dtype,
+                             const void *old_rows_dev, const void *old_index_dev, int64_t old_num_hot,
+                             const int64_t *hot_rows_dev, int64_t num_hot, void *cache_rows_dev, void *cache_index_dev,
+                             uint64_t *moved_dev, uint32_t *status_dev, void *stream)
+{
+    const int rc = emb_check_cache_build(table_dev, num_rows, D, dtype, old_rows_dev, old_index_dev, old_num_hot,
+                                         hot_rows_dev, num_hot, cache_rows_dev, cache_index_dev);
+    if (rc != EMB_OK) return rc;
     hipStream_t s = emb_stream(stream);
     const int64_t entries = (num_rows + 63) / 64;
     const int64_t cblocks = (entries + CB_BLOCK - 1) / CB_BLOCK;
@@ -447,9 +480,9 @@ static int cache_build_entry(const void *table_dev, int64_t num_rows, int32_t D,
                        num_rows, reinterpret_cast<CacheEntry *>(cache_index_dev), status_dev);
     EMB_RETURN_IF_LAUNCH_FAILED();
     const int chunks = (int)(emb_row_bytes(D, dtype) / 16);   // rows of every storage type are whole 16-byte chunks
-    int64_t want = (num_hot * chunks + CB_BLOCK - 1) / CB_BLOCK;
-    unsigned grid = (unsigned)(want > 65536 ? 65536 : want);
-    hipLaunchKernelGGL(cache_copy_kernel, dim3(grid), dim3(CB_BLOCK), 0, s, reinterpret_cast<const char *>(table_dev),
+    const int64_t want = (num_hot * chunks + COPY_BLOCK - 1) / COPY_BLOCK;
+    const unsigned grid = (unsigned)(want > COPY_GRID ? COPY_GRID : want);
+    hipLaunchKernelGGL(cache_copy_kernel, dim3(grid), dim3(COPY_BLOCK), 0, s, reinterpret_cast<const char *>(table_dev),
                        reinterpret_cast<const char *>(old_rows_dev), reinterpret_cast<const CacheEntry *>(old_index_dev),
                        old_num_hot, hot_rows_dev, num_hot, num_rows, chunks, reinterpret_cast<char *>(cache_rows_dev),
                        reinterpret_cast<unsigned long long *>(moved_dev));

@@ -105,6 +105,11 @@ int emb_forward_cached_unchecked_tables(const emb_cached_table *tables_dev, int3
                                         int32_t mode, float *out_dev, uint64_t *hit_miss_dev, uint32_t *status_dev,
                                         void *stream, bool hashed, int64_t *offsets_out_dev = nullptr);
 
+// Argument checks of everything that builds a cache (cached.hip); old_index_dev == NULL: no older cache.
+int emb_check_cache_build(const void *table_dev, int64_t num_rows, int32_t D, int32_t dtype, const void *old_rows_dev,
+                          const void *old_index_dev, int64_t old_num_hot, const int64_t *hot_rows_dev, int64_t num_hot,
+                          const void *cache_rows_dev, const void *cache_index_dev);
+
 // Row-quantised storage types and the bits of one of their codes (EMB_INT4_ROW64
 // differs from EMB_INT4 in the row stride only).
 static inline bool emb_is_quant(int32_t dtype)

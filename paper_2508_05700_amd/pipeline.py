@@ -229,11 +229,10 @@ class HotRowCache:
     def refresh(self) -> None:
         """Select the most frequently looked-up rows and fill the idle buffers with them, taking the rows the
         active cache already holds from HBM; then swap.  In stream order with the lookups."""
-        emb.emb_cache_select(self.freq, self.capacity, self.decay_shift, self.workspace, self.hot, self.info)
         new = 1 - self.active
-        emb.emb_cache_rebuild(self.table_ptr, self.R, self.D, self.dtype, self.rows[self.active],
-                              self.index[self.active], self.num_hot, self.hot[:self.capacity], self.rows[new],
-                              self.index[new], self.moved, self.status)
+        emb.emb_cache_refresh(self.freq, self.capacity, self.decay_shift, self.workspace, self.table_ptr, self.D,
+                              self.dtype, self.rows[self.active], self.index[self.active], self.num_hot, self.hot,
+                              self.rows[new], self.index[new], self.moved, self.info, self.status)
         self.active, self.num_hot = new, self.capacity
 
     def forward_hashed(self, raw: torch.Tensor, offsets: torch.Tensor, B: int, mode: str, out: torch.Tensor) -> None:

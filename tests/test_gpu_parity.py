@@ -1645,6 +1645,51 @@ def test_cache_rebuild_takes_kept_rows_from_the_old_cache(dtype):
         emb.emb_cache_rebuild(ptr, R, D, dtype, cache_a, idx_b, hot_b.size, H.dev(hot_b), cache_b, idx_b, None, status)
 
 
+@pytest.mark.parametrize("R,num_hot,D,dtype", [(1, 1, 4, "f32"), (63, 0, 64, "f32"), (64, 64, 16, "int4"), (65, 7, 4, "f32"),
+                                               (4095, 300, 48, "bf16"), (4096, 4096, 64, "int4"), (4097, 1, 1024, "f32"),
+                                               (70_001, 9000, 64, "int4"), (300_007, 20_000, 20, "f32")])
+def test_cache_refresh_equals_select_then_rebuild(R, num_hot, D, dtype):
+    # the last pass of the one call makes list, index and rows; counters with many ties, and larger than 2047
+    rng = np.random.default_rng(R)
+    full = (rng.standard_normal((R, D)) * 0.01).astype(np.float32)
+    table = torch.from_numpy(full).to(H.DEV)
+    if dtype == "bf16":
+        table = table.to(torch.bfloat16)
+    elif dtype == "int4":
+        q = torch.empty((R, emb.emb_row_bytes(D, dtype)), dtype=torch.uint8, device=H.DEV)
+        emb.emb_quantize_rows(table, dtype, q)
+        table = q
+    ptr = int(table.data_ptr())
+    ws = torch.full((emb.emb_cache_select_workspace_bytes(R),), 0xA5, dtype=torch.uint8, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    old_hot = np.sort(rng.choice(R, size=R // 3, replace=False)).astype(np.int64)
+    old_rows = torch.empty((max(old_hot.size, 1), table.shape[1]), dtype=table.dtype, device=H.DEV)
+    old_idx = torch.empty(emb.emb_cache_index_bytes(R), dtype=torch.uint8, device=H.DEV)
+    emb.emb_cache_build(ptr, R, D, dtype, H.dev(old_hot), old_rows, old_idx, status)
+    old_rows.view(torch.uint8).bitwise_xor_(0xFF)                     # where a row came from shows in its bytes
+    for freq in (rng.integers(0, 3, size=R), rng.zipf(1.3, size=R).clip(0, 50), 5000 + rng.integers(0, 1 << 20, size=R)):
+        got = []
+        for one in (False, True):
+            fd = _freq_dev(freq.astype(np.uint32))
+            hot = torch.full((max(num_hot, 1),), -9, dtype=torch.int64, device=H.DEV)
+            info = torch.full((2,), -9, dtype=torch.int64, device=H.DEV)
+            rows = torch.zeros((max(num_hot, 1), table.shape[1]), dtype=table.dtype, device=H.DEV)
+            idx = torch.full_like(old_idx, 0x77)
+            moved = torch.full((2,), 5, dtype=torch.int64, device=H.DEV)
+            if one:
+                emb.emb_cache_refresh(fd, num_hot, 1, ws, ptr, D, dtype, old_rows, old_idx, old_hot.size, hot, rows, idx,
+                                      moved, info, status)
+            else:
+                emb.emb_cache_select(fd, num_hot, 1, ws, hot, info)
+                emb.emb_cache_rebuild(ptr, R, D, dtype, old_rows, old_idx, old_hot.size, hot[:num_hot], rows, idx, moved,
+                                      status)
+            torch.cuda.synchronize()
+            got.append((fd, hot, info, rows.view(torch.uint8), idx, moved))
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+        assert status.item() == 0
+
+
 def test_cache_policy_loop_matches_the_oracle_step_by_step():
     # a drifting Zipf stream of raw IDs: observe each batch, refresh every few batches; the hot set, the
     # counters, hits and misses and the pooled output follow the oracle's at every step
