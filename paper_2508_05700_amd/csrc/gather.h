@@ -1,6 +1,8 @@
 // Device helpers shared by the gather-pool kernels: 16-byte row chunks of fp32
 // or bf16 rows, accumulated in fp32.
 #pragma once
+#include <type_traits>
+
 #include "emb_internal.h"
 #include "scan.h"
 
@@ -82,6 +84,69 @@ __device__ __forceinline__ int64_t shfl_i64(int64_t v, int src, int width)
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
+// The value that lane k of every group of LPR lanes holds, in all lanes of the group (up to 16 lanes k is a
+// constant once the caller's loop is unrolled).  Inside 16 lanes this is a data-parallel move of the vector
+// unit, which neither waits for nor loads the LDS pipe that a general lane shuffle goes through.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_upper_half(uint32_t low, uint32_t v)   // lanes 8..15 of every 16 move, the others keep low
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)low, (int)v, CTRL, 0xF, 0xC, false);
+}
+template <int LPR>
+__device__ __forceinline__ uint32_t group_bcast(uint32_t v, int k)
+{
+    if constexpr (LPR == 1) return v;
+    if constexpr (LPR == 2) return k == 0 ? dpp_move<0xA0>(v) : dpp_move<0xF5>(v);   // quad_perm
+    if constexpr (LPR == 4) {
+        switch (k) {   // quad_perm [k, k, k, k]
+            case 0: return dpp_move<0x00>(v);
+            case 1: return dpp_move<0x55>(v);
+            case 2: return dpp_move<0xAA>(v);
+            default: return dpp_move<0xFF>(v);
+        }
+    }
+#define EMB_BC8(K) dpp_upper_half<0x158 + K>(dpp_move<0x150 + K>(v), v)   // row_newbcast, one for each half of a row
+    if constexpr (LPR == 8) {
+        switch (k) {
+            case 0: return EMB_BC8(0);
+            case 1: return EMB_BC8(1);
+            case 2: return EMB_BC8(2);
+            case 3: return EMB_BC8(3);
+            case 4: return EMB_BC8(4);
+            case 5: return EMB_BC8(5);
+            case 6: return EMB_BC8(6);
+            default: return EMB_BC8(7);
+        }
+    }
+#undef EMB_BC8
+#define EMB_BC16(K) case K: return dpp_move<0x150 + K>(v)   // row_newbcast
+    if constexpr (LPR == 16) {
+        switch (k) {
+            EMB_BC16(0); EMB_BC16(1); EMB_BC16(2); EMB_BC16(3); EMB_BC16(4); EMB_BC16(5); EMB_BC16(6); EMB_BC16(7);
+            EMB_BC16(8); EMB_BC16(9); EMB_BC16(10); EMB_BC16(11); EMB_BC16(12); EMB_BC16(13); EMB_BC16(14);
+            default: return dpp_move<0x15F>(v);
+        }
+    }
+#undef EMB_BC16
+    if constexpr (LPR == 32) return (uint32_t)__shfl((int)v, k, LPR);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, k);   // the whole wavefront: a scalar
+}
+template <int LPR>
+__device__ __forceinline__ const char *group_bcast_ptr(uint64_t p, int k)
+{
+    const uint32_t lo = group_bcast<LPR>((uint32_t)p, k), hi = group_bcast<LPR>((uint32_t)(p >> 32), k);
+    return reinterpret_cast<const char *>(((uint64_t)hi << 32) | lo);
+}
+
+// A row of zeros as long as the largest row: what an entry that is skipped reads, so that the row loads need
+// no test of their own (adding +0 to a sum that started at +0 changes no bit).
+static __device__ uint4 emb_zero_row[1024];
+
 // Bounds of bag `bag` (clamped to bag 0 where the caller's lane group has no bag) from offsets kept in two
 // levels: `local` holds the sums of the bag lengths within tiles of EMB_OFFSETS_TILE lengths
 // (emb_offsets_tile_sums), the tile totals standing at the tile ends; the prefix sums of the totals are
@@ -147,15 +212,53 @@ static inline void emb_row_split(int chunks, int &lpr, int &cpl)
 // row reads in flight.  The group's lanes fetch the bag's row indices with one
 // coalesced load; the lane that fetched an index resolves it to the address of
 // the row (Source::resolve: bounds check, and for the cached table the cache
-// probe) and the address is handed round with lane shuffles, so every index is
+// probe) and the address is handed round (group_bcast), so every index is
 // read and resolved exactly once.  No cross-lane reduction is needed: a lane
 // only ever adds the chunks it owns.
+//
+// What bounds it: on narrow rows the instructions around a row load, on wide ones
+// the rate of scattered lines.  So a row costs two moves, one address add, the load
+// and the adds: entries past the bag's end and skipped ones read a row of zeros,
+// lanes past the row read its first chunk and store nothing, and a batch that no
+// bag of the wavefront fills is done at half its length (a short bag would pay for
+// eight loads otherwise).
 //
 // Source must provide
 //   __device__ uint64_t resolve(int64_t v, int64_t j)   address of the row that entry j of
 //                                                       `rows` (value v) selects, 0 = skip it
 // ---------------------------------------------------------------------------
 // STREAM: the rows are read with non-temporal loads (see EMB_ROWS_STREAMING in the header).
+template <int LPR, int CPL, int N, bool BF16, bool STREAM, int IPL>
+__device__ __forceinline__ void gather_rows(ChunkAcc<BF16> (&acc)[CPL], const uint64_t (&mine)[IPL], int k0, const uint32_t (&off)[CPL])
+{
+    uint4 v[N][CPL];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const char *p = group_bcast_ptr<LPR>(mine[IPL == 1 ? 0 : (k0 + i) / LPR], (k0 + i) % LPR);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) v[i][c] = STREAM ? load_chunk_nt(p + off[c]) : load_chunk(p + off[c]);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // every load of the batch before its first add
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c].add(v[i][c]);
+}
+
+// Does `left` entries' worth of a batch of UNROLL at its full length, a half or a quarter: do_rows(n) with n a
+// compile-time constant.  The longest of the wavefront's bags decides (uniform).
+template <int UNROLL, typename Rows>
+__device__ __forceinline__ void gather_batch(int64_t left, const Rows &do_rows)
+{
+    if constexpr (UNROLL >= 4) {
+        if (__ballot(left > UNROLL / 2) != 0) do_rows(std::integral_constant<int, UNROLL>());
+        else if (__ballot(left > UNROLL / 4) != 0) do_rows(std::integral_constant<int, UNROLL / 2>());
+        else do_rows(std::integral_constant<int, UNROLL / 4>());
+    } else {
+        do_rows(std::integral_constant<int, UNROLL>());
+    }
+}
+
 // The bag is given by its bounds: lookups [s, e) of `rows` (ignored unless live).
 template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM = false, typename Source>
 __device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_t s, int64_t e, int l, int64_t nnz,
@@ -175,37 +278,39 @@ __device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_
     }
 
     ChunkAcc<BF16> acc[CPL];
+    uint32_t off[CPL];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c].zero();
+    for (int c = 0; c < CPL; ++c) {
+        acc[c].zero();
+        off[c] = l + c * LPR < chunks_per_row ? (uint32_t)(l + c * LPR) * 16u : 0u;
+    }
 
+    const uint64_t zero_row = reinterpret_cast<uint64_t>(emb_zero_row);
+    // the entries of the batch after the current one are asked for before the current one's rows
+    int64_t next[IPL];
+#pragma unroll
+    for (int m = 0; m < IPL; ++m) {
+        const int64_t j = s + m * LPR + l;
+        next[m] = j < e ? rows[j] : 0;
+    }
     for (int64_t base = s; base < e; base += IB) {
         uint64_t mine[IPL];
 #pragma unroll
         for (int m = 0; m < IPL; ++m) {
             const int64_t j = base + m * LPR + l;
-            mine[m] = (j < e) ? src.resolve(rows[j], j) : 0ull;
+            mine[m] = 0ull;
+            if (j < e) mine[m] = src.resolve(next[m], j);
+            if (mine[m] == 0ull) mine[m] = zero_row;
+            if (j + IB < e) next[m] = rows[j + IB];
         }
-#pragma unroll
+        // (lane numbers of a group of up to 16 must be constants)
+#pragma unroll(LPR <= 16 ? IB / UNROLL : 1)
         for (int u = 0; u < IB / UNROLL; ++u) {
-            if (base + u * UNROLL < e) {
-                uint4 v[UNROLL][CPL];
-#pragma unroll
-                for (int i = 0; i < UNROLL; ++i) {
-                    const int k = u * UNROLL + i;
-                    const uint64_t p = (uint64_t)shfl_i64((int64_t)mine[k / LPR], k % LPR, LPR);
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) {
-                        v[i][c] = make_uint4(0, 0, 0, 0);
-                        if (p != 0 && l + c * LPR < chunks_per_row)
-                            v[i][c] = STREAM ? load_chunk_nt(reinterpret_cast<const char *>(p) + (int64_t)(l + c * LPR) * 16)
-                                             : load_chunk(reinterpret_cast<const char *>(p) + (int64_t)(l + c * LPR) * 16);
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < UNROLL; ++i)
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) acc[c].add(v[i][c]);
-            }
+            const int64_t left = e - base - u * UNROLL;
+            if (left > 0)   // the group's lanes agree
+                gather_batch<UNROLL>(left, [&](auto n) {
+                    gather_rows<LPR, CPL, decltype(n)::value, BF16, STREAM>(acc, mine, u * UNROLL, off);
+                });
         }
     }
 

@@ -35,13 +35,45 @@ __device__ __forceinline__ void codes_to_float(const uint32_t (&w)[BITS == 8 ? 4
     }
 }
 
-// The loop has the shape of gather_pool_bag (gather.h): a group of LPR lanes owns a
-// bag, fetches its indices with one coalesced load, the fetching lane resolves an
-// index to the row's address (Source::resolve, 0 = skip), addresses go round by
-// shuffles, UNROLL rows are requested before the first add.  A row costs every lane
-// the 8-byte header (one request for the group) and its own 8 or 16 code bytes.
-// Each element is dequantised (one fused multiply-add) and then added, so the
-// rounding behaviour is that of summing fp32 rows.  `bag` indexes offsets and out.
+// N rows of a group's batch, from entry k0 on.  A row costs every lane the 8-byte
+// header (one request for the group) and its own 8 or 16 code bytes.  Each element
+// is dequantised (one fused multiply-add) and then added, so the rounding behaviour
+// is that of summing fp32 rows; a row of zeros has scale and bias 0.
+template <int LPR, int BITS, int N, int IPL>
+__device__ __forceinline__ void gather_dequant_rows(float (&acc)[Q_ELEMS], const uint64_t (&mine)[IPL], int k0, uint32_t code_off)
+{
+    constexpr int CW = BITS == 8 ? 4 : 2;                   // code words per lane and row
+    uint2 hdr[N];
+    uint32_t w[N][CW];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const char *row = group_bcast_ptr<LPR>(mine[IPL == 1 ? 0 : (k0 + i) / LPR], (k0 + i) % LPR);
+        hdr[i] = load_u2(row);
+        const uint2 c0 = load_u2(row + code_off);
+        w[i][0] = c0.x;
+        w[i][1] = c0.y;
+        if (BITS == 8) {
+            const uint2 c1 = load_u2(row + code_off + 8);
+            w[i][CW - 2] = c1.x;
+            w[i][CW - 1] = c1.y;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // every load of the batch before its first add
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float scale = __uint_as_float(hdr[i].x), bias = __uint_as_float(hdr[i].y);
+        float f[Q_ELEMS];
+        codes_to_float<BITS>(w[i], f);
+#pragma unroll
+        for (int x = 0; x < Q_ELEMS; ++x) acc[x] += __builtin_fmaf(scale, f[x], bias);
+    }
+}
+
+// The loop has the shape of gather_pool_range (gather.h): a group of LPR lanes owns a
+// bag, fetches its indices with one coalesced load (the next batch's ahead of the
+// current one's rows), the fetching lane resolves an index to the row's address
+// (Source::resolve, 0 = skip: a row of zeros), addresses are handed round, UNROLL
+// rows are requested before the first add.  `bag` indexes offsets and out.
 // The bag is given by its bounds: lookups [s, e) of `rows` (ignored unless live).
 template <int LPR, int BITS, int UNROLL, typename Source>
 __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live, int64_t bag, int64_t s, int64_t e, int l,
@@ -50,10 +82,9 @@ __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live
 {
     constexpr int IPL = (UNROLL > LPR) ? UNROLL / LPR : 1;  // indices fetched per lane per batch
     constexpr int IB = IPL * LPR;                           // indices per batch
-    constexpr int CW = BITS == 8 ? 4 : 2;                   // code words per lane and row
     static_assert(IB % UNROLL == 0, "index batch must be whole unroll groups");
-    const bool mine_elems = l * Q_ELEMS < D;         // lanes past the row (D/16 not a power of two) idle
-    const int code_off = 8 + l * (BITS == 8 ? 16 : 8);
+    const bool mine_elems = l * Q_ELEMS < D;         // lanes past the row (D/16 not a power of two) read its first codes
+    const uint32_t code_off = 8u + (mine_elems ? (uint32_t)l * (BITS == 8 ? 16u : 8u) : 0u);
 
     if (!live) {
         s = e = 0;
@@ -65,47 +96,30 @@ __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live
 #pragma unroll
     for (int i = 0; i < Q_ELEMS; ++i) acc[i] = 0.f;
 
+    const uint64_t zero_row = reinterpret_cast<uint64_t>(emb_zero_row);
+    int64_t next[IPL];
+#pragma unroll
+    for (int m = 0; m < IPL; ++m) {
+        const int64_t j = s + m * LPR + l;
+        next[m] = j < e ? rows[j] : 0;
+    }
     for (int64_t base = s; base < e; base += IB) {
         uint64_t mine[IPL];
 #pragma unroll
         for (int m = 0; m < IPL; ++m) {
             const int64_t j = base + m * LPR + l;
-            mine[m] = (j < e) ? src.resolve(rows[j], j) : 0ull;
+            mine[m] = 0ull;
+            if (j < e) mine[m] = src.resolve(next[m], j);
+            if (mine[m] == 0ull) mine[m] = zero_row;
+            if (j + IB < e) next[m] = rows[j + IB];
         }
-#pragma unroll
+#pragma unroll(LPR <= 16 ? IB / UNROLL : 1)
         for (int u = 0; u < IB / UNROLL; ++u) {
-            if (base + u * UNROLL < e) {
-                uint2 hdr[UNROLL];
-                uint32_t w[UNROLL][CW];
-#pragma unroll
-                for (int i = 0; i < UNROLL; ++i) {
-                    const int k = u * UNROLL + i;
-                    const uint64_t p = (uint64_t)shfl_i64((int64_t)mine[k / LPR], k % LPR, LPR);
-                    hdr[i] = make_uint2(0u, 0u);     // a skipped row counts as scale 0, bias 0
-#pragma unroll
-                    for (int c = 0; c < CW; ++c) w[i][c] = 0u;
-                    if (p != 0 && mine_elems) {
-                        const char *row = reinterpret_cast<const char *>(p);
-                        hdr[i] = load_u2(row);
-                        const uint2 c0 = load_u2(row + code_off);
-                        w[i][0] = c0.x;
-                        w[i][1] = c0.y;
-                        if (BITS == 8) {
-                            const uint2 c1 = load_u2(row + code_off + 8);
-                            w[i][CW - 2] = c1.x;
-                            w[i][CW - 1] = c1.y;
-                        }
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < UNROLL; ++i) {
-                    const float scale = __uint_as_float(hdr[i].x), bias = __uint_as_float(hdr[i].y);
-                    float f[Q_ELEMS];
-                    codes_to_float<BITS>(w[i], f);
-#pragma unroll
-                    for (int x = 0; x < Q_ELEMS; ++x) acc[x] += __builtin_fmaf(scale, f[x], bias);
-                }
-            }
+            const int64_t left = e - base - u * UNROLL;
+            if (left > 0)
+                gather_batch<UNROLL>(left, [&](auto n) {
+                    gather_dequant_rows<LPR, BITS, decltype(n)::value>(acc, mine, u * UNROLL, code_off);
+                });
         }
     }
 
