@@ -290,7 +290,8 @@ int emb_bag_forward_hashed(const emb_table *tables_host, const emb_table *tables
 /* emb_lengths_to_offsets and emb_bag_forward_hashed in one call: the serving
  * form of "bag lengths and raw IDs in, pooled embeddings out" (Sections 2.2,
  * 3.4).  Takes the T*B bag lengths instead of offsets and writes the offsets
- * (i64[T*B+1]) to offsets_out_dev.  Two launches instead of four: the sums of
+ * (i64[T*B+1]) to offsets_out_dev.  One launch for batches of up to 4096 bags
+ * (every workgroup adds up the lengths before its bags), else two: the sums of
  * the lengths within tiles of 4096 go to scratch_dev (caller-owned,
  * emb_offsets_scratch_bytes(T*B) bytes, 16-byte aligned, free again once the
  * call's work has run), and every workgroup of the lookup adds the prefix sums
@@ -307,6 +308,14 @@ int emb_bag_forward_hashed_lengths(const emb_table *tables_host, const emb_table
                                    int32_t mode, float *out_dev, int64_t *offsets_out_dev,
                                    int64_t *rows_out_dev, void *scratch_dev, size_t scratch_bytes,
                                    uint32_t *status_dev, void *stream);
+
+/* The same for lookups by row number: emb_lengths_to_offsets and emb_bag_forward
+ * in one call. */
+int emb_bag_forward_lengths(const emb_table *tables_host, const emb_table *tables_dev, int32_t T,
+                            int32_t D, int32_t dtype, const int64_t *rows_dev,
+                            const int32_t *lengths_dev, int64_t B, int64_t nnz, int32_t mode,
+                            float *out_dev, int64_t *offsets_out_dev, void *scratch_dev,
+                            size_t scratch_bytes, uint32_t *status_dev, void *stream);
 
 /* Shape of one table for emb_bag_forward_mixed.  The caller fills D, dtype,
  * out_offset and out_stride; emb_table_shapes_init derives the rest for a batch

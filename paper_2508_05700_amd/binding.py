@@ -46,7 +46,7 @@ assert SHAPE_DESC.itemsize == 32
 EXPORTS = [
     "emb_status_string", "emb_tables_init", "emb_hash_ids", "emb_hash_ids_tables", "emb_lengths_to_offsets",
     "emb_bag_forward", "emb_bag_forward_hashed", "emb_table_shapes_init", "emb_bag_forward_mixed", "emb_bag_backward_workspace_bytes", "emb_bag_backward_rowwise_adagrad",
-    "emb_bag_backward_sort", "emb_debug_sort_poll_limit", "emb_bag_backward_update", "emb_bag_forward_train", "emb_bag_forward_train_lengths", "emb_offsets_scratch_bytes", "emb_bag_forward_hashed_lengths", "emb_bag_backward_sort_prepared", "emb_row_bytes", "emb_quantize_rows",
+    "emb_bag_backward_sort", "emb_debug_sort_poll_limit", "emb_bag_backward_update", "emb_bag_forward_train", "emb_bag_forward_train_lengths", "emb_offsets_scratch_bytes", "emb_bag_forward_hashed_lengths", "emb_bag_forward_lengths", "emb_bag_backward_sort_prepared", "emb_row_bytes", "emb_quantize_rows",
     "emb_side_stream_create", "emb_side_stream_destroy", "emb_side_stream_join", "emb_bag_forward_train_lengths_after", "emb_event_create", "emb_event_destroy", "emb_event_record",
     "emb_event_elapsed_ms",
     "emb_cache_index_bytes", "emb_cache_build", "emb_bag_forward_cached", "emb_bag_forward_cached_hashed", "emb_bag_forward_cached_hashed_lengths", "emb_host_device_pointer",
@@ -123,6 +123,8 @@ def lib() -> C.CDLL:
     L.emb_offsets_scratch_bytes.argtypes = [i64]
     L.emb_bag_forward_hashed_lengths.restype = C.c_int
     L.emb_bag_forward_hashed_lengths.argtypes = [vp, vp, i32, i32, i32, vp, vp, i64, i64, i32, vp, vp, vp, vp, sz, vp, vp]
+    L.emb_bag_forward_lengths.restype = C.c_int
+    L.emb_bag_forward_lengths.argtypes = [vp, vp, i32, i32, i32, vp, vp, i64, i64, i32, vp, vp, vp, sz, vp, vp]
     L.emb_bag_forward_train_lengths.restype = C.c_int
     L.emb_bag_forward_train_lengths.argtypes = [vp, vp, i32, i32, i32, vp, vp, i64, i64, i32, vp, vp, vp, vp, sz, vp, vp, vp]
     L.emb_bag_backward_sort_prepared.restype = C.c_int
@@ -228,20 +230,32 @@ def lib() -> C.CDLL:
 # ---------------------------------------------------------------------------
 # marshalling helpers
 # ---------------------------------------------------------------------------
+# A small lookup is a few microseconds of work on the device, so what a call costs here counts: the stream
+# handle is asked for directly (a torch.cuda.Stream object takes 2.7 us to make, the handle 0.2) and a tensor
+# that passes its checks passes them in one expression.
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor], dtype=None, name: str = "tensor") -> Optional[int]:
     if t is None:
         return None
+    if t.is_cuda and (dtype is None or t.dtype is dtype or (dtype.__class__ is tuple and t.dtype in dtype)) \
+            and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise TypeError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
-        raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
-    return int(t.data_ptr())
+    raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
+
+
+def _host_address(owner) -> int:
+    """Address of ``owner.host``, a numpy array (asking numpy for it takes 1.2 us, so it is kept with the array)."""
+    known = getattr(owner, "_host_known", None)
+    if known is None or known[0] is not owner.host:
+        known = owner._host_known = (owner.host, int(owner.host.ctypes.data))
+    return known[1]
 
 
 def _check(fn: str, rc: int) -> None:
@@ -296,11 +310,11 @@ class TableSet:
 
     @property
     def host_ptr(self) -> int:
-        return int(self.host.ctypes.data)
+        return _host_address(self)
 
     @property
     def dev_ptr(self) -> int:
-        return int(self.dev.data_ptr())
+        return self.dev.data_ptr()
 
 
 # ---------------------------------------------------------------------------
@@ -391,6 +405,22 @@ def emb_bag_forward_hashed_lengths(tables: TableSet, raw: torch.Tensor, lengths:
         _ptr(scratch, torch.uint8, "scratch"), scratch.numel(), _ptr(status, torch.int32, "status"), _stream()))
 
 
+def emb_bag_forward_lengths(tables: TableSet, rows: torch.Tensor, lengths: torch.Tensor, B: int, mode: str,
+                            out: torch.Tensor, offsets_out: torch.Tensor, scratch: torch.Tensor,
+                            status: Optional[torch.Tensor] = None, streaming: bool = False) -> None:
+    """``emb_lengths_to_offsets`` + ``emb_bag_forward`` in one call: takes the bag lengths, writes the offsets;
+    ``scratch`` holds ``emb_offsets_scratch_bytes(T * B)`` bytes."""
+    n = tables.T * B
+    if lengths.numel() != n or offsets_out.numel() != n + 1 or out.numel() != n * tables.D:
+        raise TypeError("shape mismatch")
+    _check("emb_bag_forward_lengths", lib().emb_bag_forward_lengths(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], _ptr(rows, torch.int64, "rows"),
+        _ptr(lengths, torch.int32, "lengths") if n else None, int(B), rows.numel(),
+        POOL[mode] | (ROWS_STREAMING if streaming else 0), _ptr(out, torch.float32, "out"),
+        _ptr(offsets_out, torch.int64, "offsets_out"), _ptr(scratch, torch.uint8, "scratch"), scratch.numel(),
+        _ptr(status, torch.int32, "status"), _stream()))
+
+
 class MixedTables:
     """Tables of different width / storage type for ``emb_bag_forward_mixed``.
 
@@ -434,7 +464,7 @@ def emb_bag_forward_mixed(mt: MixedTables, rows: torch.Tensor, offsets: torch.Te
     if offsets.numel() != mt.T * mt.B + 1 or out.numel() < mt.out_floats:
         raise TypeError("shape mismatch")
     _check("emb_bag_forward_mixed", lib().emb_bag_forward_mixed(
-        mt.tables.host_ptr, mt.tables.dev_ptr, int(mt.host.ctypes.data), int(mt.dev.data_ptr()), mt.T,
+        mt.tables.host_ptr, mt.tables.dev_ptr, _host_address(mt), mt.dev.data_ptr(), mt.T,
         _ptr(rows, torch.int64, "rows"), _ptr(offsets, torch.int64, "offsets"), mt.B, rows.numel(), POOL[mode],
         _ptr(out, torch.float32, "out"), out.numel(), _ptr(status, torch.int32, "status"), _stream()))
 
@@ -941,7 +971,7 @@ def _forward_cached_tables(fn: str, ct: CachedTables, ids, id_dtype, offsets, B,
     if offsets.numel() != ct.T * B + 1 or out.numel() != ct.T * B * ct.D:
         raise TypeError("shape mismatch")
     _check(fn, getattr(lib(), fn)(
-        int(ct.host.ctypes.data), int(ct.dev.data_ptr()), ct.T, ct.D, DTYPE[ct.dtype], _ptr(ids, id_dtype, "ids"),
+        _host_address(ct), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(ids, id_dtype, "ids"),
         _ptr(offsets, torch.int64, "offsets"), int(B), ids.numel(), POOL[mode], _ptr(out, torch.float32, "out"),
         _ptr(hit_miss, _U64, "hit_miss"), _ptr(status, torch.int32, "status"), _stream()))
 
@@ -970,7 +1000,7 @@ def emb_bag_forward_cached_tables_hashed_lengths(ct: CachedTables, raw: torch.Te
     if lengths.numel() != n or offsets_out.numel() != n + 1 or out.numel() != n * ct.D:
         raise TypeError("shape mismatch")
     _check("emb_bag_forward_cached_tables_hashed_lengths", lib().emb_bag_forward_cached_tables_hashed_lengths(
-        int(ct.host.ctypes.data), int(ct.dev.data_ptr()), ct.T, ct.D, DTYPE[ct.dtype], _ptr(raw, _U64, "raw"),
+        _host_address(ct), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(raw, _U64, "raw"),
         _ptr(lengths, torch.int32, "lengths") if n else None, int(B), raw.numel(), POOL[mode],
         _ptr(out, torch.float32, "out"), _ptr(offsets_out, torch.int64, "offsets_out"),
         _ptr(scratch, torch.uint8, "scratch"), scratch.numel(), _ptr(hit_miss, _U64, "hit_miss"),
@@ -1016,7 +1046,7 @@ def emb_version_hosted_record_write(record: torch.Tensor, ct: CachedTables, vers
     if record.numel() < emb_version_hosted_record_bytes(ct.T):
         raise TypeError("record too small")
     _check("emb_version_hosted_record_write", lib().emb_version_hosted_record_write(
-        _ptr(record, torch.uint8, "record"), int(ct.host.ctypes.data), int(ct.dev.data_ptr()), ct.T,
+        _ptr(record, torch.uint8, "record"), _host_address(ct), ct.dev.data_ptr(), ct.T,
         C.c_uint64(int(version)), _stream()))
 
 

@@ -49,106 +49,106 @@ struct HashedTableSource {
     }
 };
 
-// TWO_LEVEL (emb_bag_forward_hashed_lengths): `offsets` holds the sums of the bag lengths within tiles of
-// EMB_OFFSETS_TILE lengths (emb_offsets_tile_sums); the prefix sums of the tile totals are taken inside the
-// kernel (emb_two_level_bounds, at most FWD_BLOCK tiles) and the final offsets are written to offsets_out.
-template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM, bool TWO_LEVEL = false>
-__global__ __launch_bounds__(FWD_BLOCK) void bag_forward_hashed_kernel(const emb_table *__restrict__ tables, int32_t T,
-                                                                       int64_t B, uint32_t blocks_per_table,
-                                                                       int64_t nnz, const int64_t *__restrict__ raw,
-                                                                       const int64_t *__restrict__ offsets,
-                                                                       int32_t chunks_per_row, int32_t mode,
-                                                                       float *__restrict__ out,
-                                                                       int64_t *__restrict__ rows_out, uint32_t *status,
-                                                                       int64_t *__restrict__ offsets_out = nullptr)
-{
-    __shared__ int64_t tile_prefix[TWO_LEVEL ? FWD_BLOCK : 1];
-    __shared__ int64_t wave_sums[FWD_BLOCK / EMB_WAVE];
-    constexpr int GROUPS = FWD_BLOCK / LPR;
-    const uint32_t lb = emb_xcd_block(blockIdx.x, gridDim.x);
-    const uint32_t t_raw = lb / blocks_per_table;
-    const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
-    const int t = tail ? T - 1 : (int)t_raw;
-    const int l = threadIdx.x % LPR;
-    const int64_t b = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS + threadIdx.x / LPR;
-    const emb_table tb = tables[t];
-    HashedTableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
-                          (int64_t)chunks_per_row * 16, rows_out};
-    constexpr int F = ChunkAcc<BF16>::FLOATS;
-    const int64_t bag = (int64_t)t * B + b;
-    if (TWO_LEVEL) {
-        int64_t s, e;
-        emb_two_level_bounds<FWD_BLOCK>(offsets, (int64_t)T * B, b < B, bag, tile_prefix, wave_sums, s, e);
-        if (b < B && l == 0) {
-            offsets_out[bag + 1] = e;
-            if (bag == 0) offsets_out[0] = 0;
-        }
-        gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM>(src, b < B, s, e, l, nnz, raw, chunks_per_row, mode,
-                                                          out + bag * ((int64_t)chunks_per_row * F), status);
-        return;
-    }
-    gather_pool_bag<LPR, CPL, UNROLL, BF16, STREAM>(src, b < B, bag, l, nnz, raw, offsets, chunks_per_row, mode,
-                                            out + bag * ((int64_t)chunks_per_row * F), status);
-}
-
-template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM>
-__global__ __launch_bounds__(FWD_BLOCK) void bag_forward_kernel(const emb_table *__restrict__ tables, int32_t T, int64_t B,
-                                                                uint32_t blocks_per_table, int64_t nnz,
+// HASHED: `rows` holds raw IDs (HashedTableSource).
+// MAKE_OFFSETS (the calls that take bag lengths): the kernel finds the bags' bounds itself and writes the final
+// offsets to offsets_out.  lengths != NULL: from the lengths (emb_bounds_from_lengths); else `offsets` holds the
+// sums of the bag lengths within tiles of EMB_OFFSETS_TILE lengths (emb_offsets_tile_sums) and the prefix sums of
+// the tile totals are taken inside the kernel (emb_two_level_bounds, at most FWD_BLOCK tiles).
+template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM, bool HASHED, bool MAKE_OFFSETS>
+__global__ __launch_bounds__(FWD_BLOCK) void bag_forward_kernel(const emb_table *__restrict__ tables, int32_t T,
+                                                                int64_t B, uint32_t blocks_per_table, int64_t nnz,
                                                                 const int64_t *__restrict__ rows,
                                                                 const int64_t *__restrict__ offsets,
                                                                 int32_t chunks_per_row, int32_t mode,
-                                                                float *__restrict__ out, uint32_t *status)
+                                                                float *__restrict__ out, int64_t *__restrict__ rows_out,
+                                                                uint32_t *status, int64_t *__restrict__ offsets_out,
+                                                                const int32_t *__restrict__ lengths)
 {
     constexpr int GROUPS = FWD_BLOCK / LPR;
+    __shared__ int64_t tile_prefix[MAKE_OFFSETS ? FWD_BLOCK + 1 : 1];
+    __shared__ int64_t wave_sums[2 * FWD_BLOCK / EMB_WAVE];
     const uint32_t lb = emb_xcd_block(blockIdx.x, gridDim.x);
     const uint32_t t_raw = lb / blocks_per_table;
     const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
     const int t = tail ? T - 1 : (int)t_raw;
     const int l = threadIdx.x % LPR;
-    const int64_t b = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS + threadIdx.x / LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
     const emb_table tb = tables[t];
-    TableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, (int64_t)chunks_per_row * 16,
-                    status};
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     const int64_t bag = (int64_t)t * B + b;
-    gather_pool_bag<LPR, CPL, UNROLL, BF16, STREAM>(src, b < B, bag, l, nnz, rows, offsets, chunks_per_row, mode,
-                                            out + bag * ((int64_t)chunks_per_row * F), status);
+    const bool live = b < B;
+    int64_t s = 0, e = 0;
+    if (MAKE_OFFSETS) {
+        if (lengths) {   // uniform
+            const int64_t left = B - b0;
+            emb_bounds_from_lengths<FWD_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < GROUPS ? (int)left : GROUPS,
+                                                       threadIdx.x / LPR, tile_prefix, wave_sums, status, s, e);
+        } else {
+            emb_two_level_bounds<FWD_BLOCK>(offsets, (int64_t)T * B, live, bag, tile_prefix, wave_sums, s, e);
+        }
+        if (live && l == 0) {
+            offsets_out[bag + 1] = e;
+            if (bag == 0) offsets_out[0] = 0;
+        }
+    } else if (live) {
+        s = offsets[bag];
+        e = offsets[bag + 1];
+    }
+    float *const out_row = out + bag * ((int64_t)chunks_per_row * F);
+    if (HASHED) {
+        HashedTableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
+                              (int64_t)chunks_per_row * 16, rows_out};
+        gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM>(src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row, status);
+    } else {
+        TableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, (int64_t)chunks_per_row * 16,
+                        status};
+        gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM>(src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row, status);
+    }
 }
+
+struct ForwardArgs {
+    const emb_table *tables;
+    int32_t T, mode;
+    int64_t B, nnz;
+    const int64_t *rows, *offsets;   // rows: raw IDs if hashed
+    int32_t chunks;
+    float *out;
+    uint32_t *status;
+    bool hashed, stream;             // stream: non-temporal row reads
+    int64_t *rows_out, *offsets_out; // nullable
+    const int32_t *lengths;
+    hipStream_t s;
+};
 
 template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM>
-void launch_forward_variant(dim3 grid, hipStream_t s, const emb_table *tables, int32_t T, int64_t B, uint32_t per_table,
-                            int64_t nnz, const int64_t *rows, const int64_t *offsets, int32_t chunks, int32_t mode,
-                            float *out, uint32_t *status, bool hashed, int64_t *rows_out, int64_t *offsets_out)
+void launch_forward_variant(dim3 grid, uint32_t per_table, const ForwardArgs &a)
 {
-    if (offsets_out)   // hashed, offsets in two levels
-        hipLaunchKernelGGL((bag_forward_hashed_kernel<LPR, CPL, UNROLL, BF16, STREAM, true>), grid, dim3(FWD_BLOCK), 0, s,
-                           tables, T, B, per_table, nnz, rows, offsets, chunks, mode, out, rows_out, status, offsets_out);
-    else if (hashed)
-        hipLaunchKernelGGL((bag_forward_hashed_kernel<LPR, CPL, UNROLL, BF16, STREAM>), grid, dim3(FWD_BLOCK), 0, s,
-                           tables, T, B, per_table, nnz, rows, offsets, chunks, mode, out, rows_out, status);
-    else
-        hipLaunchKernelGGL((bag_forward_kernel<LPR, CPL, UNROLL, BF16, STREAM>), grid, dim3(FWD_BLOCK), 0, s, tables, T,
-                           B, per_table, nnz, rows, offsets, chunks, mode, out, status);
+#define EMB_FK(HASHED, MAKE)                                                                                          \
+    hipLaunchKernelGGL((bag_forward_kernel<LPR, CPL, UNROLL, BF16, STREAM, HASHED, MAKE>), grid, dim3(FWD_BLOCK), 0, a.s, \
+                       a.tables, a.T, a.B, per_table, a.nnz, a.rows, a.offsets, a.chunks, a.mode, a.out, a.rows_out,  \
+                       a.status, a.offsets_out, a.lengths)
+    if (a.hashed) {
+        if (a.offsets_out) EMB_FK(true, true); else EMB_FK(true, false);
+    } else {
+        if (a.offsets_out) EMB_FK(false, true); else EMB_FK(false, false);
+    }
+#undef EMB_FK
 }
 
-// hashed: `rows` holds raw IDs and the hashing kernel is launched; stream: non-temporal row reads.
 template <int LPR, int CPL, int UNROLL>
-int launch_forward(bool bf16, int32_t T, hipStream_t s, const emb_table *tables, int64_t B, int64_t nnz,
-                   const int64_t *rows, const int64_t *offsets, int32_t chunks, int32_t mode, float *out,
-                   uint32_t *status, bool hashed, int64_t *rows_out, bool stream, int64_t *offsets_out)
+int launch_forward(bool bf16, const ForwardArgs &a)
 {
     constexpr int GROUPS = FWD_BLOCK / LPR;
-    const int64_t per_table = (B + GROUPS - 1) / GROUPS;
-    const int64_t blocks = emb_round_up_xcds(per_table * T);
+    const int64_t per_table = (a.B + GROUPS - 1) / GROUPS;
+    const int64_t blocks = emb_round_up_xcds(per_table * a.T);
     if (blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
-#define EMB_FV(BF, ST)                                                                                              \
-    launch_forward_variant<LPR, CPL, UNROLL, BF, ST>(grid, s, tables, T, B, (uint32_t)per_table, nnz, rows, offsets, \
-                                                     chunks, mode, out, status, hashed, rows_out, offsets_out)
+#define EMB_FV(BF, ST) launch_forward_variant<LPR, CPL, UNROLL, BF, ST>(grid, (uint32_t)per_table, a)
     if (bf16) {
-        if (stream) EMB_FV(true, true); else EMB_FV(true, false);
+        if (a.stream) EMB_FV(true, true); else EMB_FV(true, false);
     } else {
-        if (stream) EMB_FV(false, true); else EMB_FV(false, false);
+        if (a.stream) EMB_FV(false, true); else EMB_FV(false, false);
     }
 #undef EMB_FV
     EMB_RETURN_IF_LAUNCH_FAILED();
@@ -161,7 +161,8 @@ int launch_forward(bool bf16, int32_t T, hipStream_t s, const emb_table *tables,
 static int forward_entry(const emb_table *tables_host, const emb_table *tables_dev, int32_t T, int32_t D,
                          int32_t dtype, const int64_t *rows_dev, const int64_t *offsets_dev, int64_t B, int64_t nnz,
                          int32_t mode, float *out_dev, uint32_t *status_dev, void *stream, bool hashed,
-                         int64_t *rows_out_dev, bool check_tables = true, int64_t *offsets_out_dev = nullptr)
+                         int64_t *rows_out_dev, bool check_tables = true, int64_t *offsets_out_dev = nullptr,
+                         const int32_t *lengths_dev = nullptr)
 {
     if (B < 0 || nnz < 0) return EMB_ERR_INVALID_ARG;
     const bool streaming = (mode & EMB_ROWS_STREAMING) != 0;
@@ -178,22 +179,21 @@ static int forward_entry(const emb_table *tables_host, const emb_table *tables_d
     }
     if (T == 0 || B == 0) return EMB_OK;
     if (T > 65535) return EMB_ERR_UNSUPPORTED;
-    if (!offsets_dev || !out_dev || (nnz > 0 && !rows_dev)) return EMB_ERR_INVALID_ARG;
+    if ((!offsets_dev && !lengths_dev) || !out_dev || (nnz > 0 && !rows_dev)) return EMB_ERR_INVALID_ARG;
     if (!emb_aligned(out_dev, 16)) return EMB_ERR_INVALID_ARG;
     if (B > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
 
     if (quant) {
         return emb_forward_quant(tables_dev, T, D, dtype, rows_dev, offsets_dev, B, nnz, mode, out_dev, status_dev,
-                                 emb_stream(stream), hashed, rows_out_dev, offsets_out_dev);
+                                 emb_stream(stream), hashed, rows_out_dev, offsets_out_dev, lengths_dev);
     }
     const int chunks = D * emb_elem_size(dtype) / 16;
     int lpr, cpl;
     emb_row_split(chunks, lpr, cpl);
     const bool bf16 = dtype == EMB_BF16;
-    hipStream_t s = emb_stream(stream);
-#define EMB_FWD(L, C, U) \
-    return launch_forward<L, C, U>(bf16, T, s, tables_dev, B, nnz, rows_dev, offsets_dev, chunks, mode, out_dev, \
-                                   status_dev, hashed, rows_out_dev, streaming, offsets_out_dev)
+    const ForwardArgs a{tables_dev, T,         mode,         B,               nnz,         rows_dev,          offsets_dev, chunks, out_dev,
+                        status_dev, hashed,    streaming,    rows_out_dev,    offsets_out_dev, lengths_dev,   emb_stream(stream)};
+#define EMB_FWD(L, C, U) return launch_forward<L, C, U>(bf16, a)
     if (cpl == 1) {
         switch (lpr) {
             case 1: EMB_FWD(1, 1, 8);
@@ -236,12 +236,11 @@ extern "C" size_t emb_offsets_scratch_bytes(int64_t num_bags_total)
     return num_bags_total < 0 ? 0 : ((size_t)num_bags_total + 1) * 8;
 }
 
-extern "C" int emb_bag_forward_hashed_lengths(const emb_table *tables_host, const emb_table *tables_dev, int32_t T,
-                                              int32_t D, int32_t dtype, const uint64_t *raw_dev,
-                                              const int32_t *lengths_dev, int64_t B, int64_t nnz, int32_t mode,
-                                              float *out_dev, int64_t *offsets_out_dev, int64_t *rows_out_dev,
-                                              void *scratch_dev, size_t scratch_bytes, uint32_t *status_dev,
-                                              void *stream)
+// The lookups that take bag lengths.  Small batches are one launch (emb_bounds_from_lengths), larger ones two.
+static int forward_lengths_entry(const emb_table *tables_host, const emb_table *tables_dev, int32_t T, int32_t D,
+                                 int32_t dtype, const int64_t *ids_dev, const int32_t *lengths_dev, int64_t B, int64_t nnz,
+                                 int32_t mode, float *out_dev, int64_t *offsets_out_dev, int64_t *rows_out_dev,
+                                 void *scratch_dev, size_t scratch_bytes, uint32_t *status_dev, void *stream, bool hashed)
 {
     if (B < 0 || nnz < 0 || T < 0) return EMB_ERR_INVALID_ARG;
     if (!offsets_out_dev) return EMB_ERR_INVALID_ARG;
@@ -251,17 +250,41 @@ extern "C" int emb_bag_forward_hashed_lengths(const emb_table *tables_host, cons
     if (n > 0 && (!lengths_dev || !scratch_dev || !emb_aligned(scratch_dev, 16) ||
                   scratch_bytes < emb_offsets_scratch_bytes(n)))
         return EMB_ERR_INVALID_ARG;
+    if (n > 0 && n <= EMB_LENGTHS_DIRECT_BAGS)
+        return forward_entry(tables_host, tables_dev, T, D, dtype, ids_dev, nullptr, B, nnz, mode, out_dev, status_dev,
+                             stream, hashed, rows_out_dev, true, offsets_out_dev, lengths_dev);
     // validate everything before the first launch: the sums within tiles go to the scratch array
     // (or, with no bags at all, the single entry 0 straight to the caller's array)
     int64_t *local = n == 0 ? offsets_out_dev : reinterpret_cast<int64_t *>(scratch_dev);
     int rc = forward_entry(tables_host, tables_dev, T, D, dtype, nullptr, nullptr, 0, 0, mode, nullptr, nullptr, nullptr,
-                           true, nullptr);   // shapes, tables and mode only: B == 0 launches nothing
+                           hashed, nullptr);   // shapes, tables and mode only: B == 0 launches nothing
     if (rc != EMB_OK) return rc;
-    if (n > 0 && (!out_dev || !emb_aligned(out_dev, 16) || (nnz > 0 && !raw_dev))) return EMB_ERR_INVALID_ARG;
+    if (n > 0 && (!out_dev || !emb_aligned(out_dev, 16) || (nnz > 0 && !ids_dev))) return EMB_ERR_INVALID_ARG;
     rc = emb_offsets_tile_sums(lengths_dev, n, local, status_dev, emb_stream(stream));
     if (rc != EMB_OK || n == 0) return rc;
-    return forward_entry(tables_host, tables_dev, T, D, dtype, reinterpret_cast<const int64_t *>(raw_dev), local, B, nnz,
-                         mode, out_dev, status_dev, stream, true, rows_out_dev, true, offsets_out_dev);
+    return forward_entry(tables_host, tables_dev, T, D, dtype, ids_dev, local, B, nnz, mode, out_dev, status_dev, stream,
+                         hashed, rows_out_dev, true, offsets_out_dev);
+}
+
+extern "C" int emb_bag_forward_lengths(const emb_table *tables_host, const emb_table *tables_dev, int32_t T, int32_t D,
+                                       int32_t dtype, const int64_t *rows_dev, const int32_t *lengths_dev, int64_t B,
+                                       int64_t nnz, int32_t mode, float *out_dev, int64_t *offsets_out_dev,
+                                       void *scratch_dev, size_t scratch_bytes, uint32_t *status_dev, void *stream)
+{
+    return forward_lengths_entry(tables_host, tables_dev, T, D, dtype, rows_dev, lengths_dev, B, nnz, mode, out_dev,
+                                 offsets_out_dev, nullptr, scratch_dev, scratch_bytes, status_dev, stream, false);
+}
+
+extern "C" int emb_bag_forward_hashed_lengths(const emb_table *tables_host, const emb_table *tables_dev, int32_t T,
+                                              int32_t D, int32_t dtype, const uint64_t *raw_dev,
+                                              const int32_t *lengths_dev, int64_t B, int64_t nnz, int32_t mode,
+                                              float *out_dev, int64_t *offsets_out_dev, int64_t *rows_out_dev,
+                                              void *scratch_dev, size_t scratch_bytes, uint32_t *status_dev,
+                                              void *stream)
+{
+    return forward_lengths_entry(tables_host, tables_dev, T, D, dtype, reinterpret_cast<const int64_t *>(raw_dev), lengths_dev,
+                                 B, nnz, mode, out_dev, offsets_out_dev, rows_out_dev, scratch_dev, scratch_bytes,
+                                 status_dev, stream, true);
 }
 
 int emb_forward_unchecked_tables(const emb_table *tables_dev, int32_t T, int32_t D, int32_t dtype, const int64_t *ids_dev,

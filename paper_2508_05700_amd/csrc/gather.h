@@ -191,6 +191,62 @@ __device__ __forceinline__ void emb_two_level_bounds(const int64_t *__restrict__
     e = a1 + pe;
 }
 
+// Bounds of the workgroup's bags straight from the bag lengths, for batches of up to EMB_LENGTHS_DIRECT_BAGS
+// bags: every workgroup adds up the lengths before its first bag itself (at most 16 KB, from the L2), which
+// saves the launch that would make sums within tiles.  A launch that has to wait for the one before it costs
+// 4.5 us in a full queue and 2 us of host time; reading 4096 lengths costs a workgroup about 1 us, and the
+// total grows with the square of the number of bags.  first: the workgroup's first bag; bags: how many it has
+// (at most BLOCK / LPR); g: the calling thread's.  Every thread of the workgroup calls this.
+constexpr int64_t EMB_LENGTHS_DIRECT_BAGS = 4096;
+template <int BLOCK, int GROUPS>
+__device__ __forceinline__ void emb_bounds_from_lengths(const int32_t *__restrict__ lengths, int64_t first, int bags, int g,
+                                                        int64_t *own /*LDS [GROUPS + 1]*/,
+                                                        int64_t *wave_sums /*LDS [2 * BLOCK / 64]*/, uint32_t *status,
+                                                        int64_t &s, int64_t &e)
+{
+    constexpr int WAVES = BLOCK / EMB_WAVE;
+    constexpr int UNROLL = 8;
+    const int tid = threadIdx.x, lane = tid & (EMB_WAVE - 1), wave = tid / EMB_WAVE;
+    int64_t before = 0, mine = 0;
+    bool bad = false;
+    if (tid < bags) mine = lengths[first + tid];
+    for (int64_t i0 = tid; i0 < first; i0 += BLOCK * UNROLL) {
+        int32_t v[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) v[u] = i0 + u * BLOCK < first ? lengths[i0 + u * BLOCK] : 0;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            bad |= v[u] < 0;
+            before += v[u] < 0 ? 0 : v[u];
+        }
+    }
+    if (mine < 0) {
+        bad = true;
+        mine = 0;
+    }
+    if (bad) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
+#pragma unroll
+    for (int d = EMB_WAVE >> 1; d >= 1; d >>= 1) before += shfl_i64(before, lane ^ d, EMB_WAVE);
+    int64_t inc = mine;
+    if (wave * EMB_WAVE < GROUPS) inc = wave_inclusive_scan(mine);   // uniform over the wavefront
+    if (lane == EMB_WAVE - 1) {
+        wave_sums[wave] = before;
+        wave_sums[WAVES + wave] = inc;
+    }
+    __syncthreads();
+    int64_t base = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        base += wave_sums[w];
+        if (w < wave) inc += wave_sums[WAVES + w];
+    }
+    if (tid < GROUPS) own[tid + 1] = base + inc;
+    if (tid == 0) own[0] = base;
+    __syncthreads();
+    s = own[g];
+    e = own[g + 1];
+}
+
 // Lanes per row (a power of two <= 64) and chunks per lane for a row of
 // `chunks` 16-byte chunks.
 static inline void emb_row_split(int chunks, int &lpr, int &cpl)

@@ -112,8 +112,12 @@ LENGTHS_ROUTE_MAX_BAGS = 1 << 20    # what emb_bag_forward_hashed_lengths accept
 
 def run_index_and_forward_fused(w: Workload, tables: emb.TableSet, db: DeviceBatch, buf: StepBuffers) -> torch.Tensor:
     """Bag offsets, hashing and pooled lookup (one call where the number of bags allows).  Returns the view of the row
-    buffer the kernel filled (for the backward).  Workloads whose IDs are row numbers already take the two-kernel route."""
+    buffer the kernel filled, or the given row numbers (for the backward)."""
     if db.raw is None:
+        if w.T * w.B <= LENGTHS_ROUTE_MAX_BAGS:
+            emb.emb_bag_forward_lengths(tables, db.rows_given, db.lengths, w.B, w.pool, buf.out, buf.offsets,
+                                        buf.offsets_scratch, buf.status, streaming=w.streaming)
+            return db.rows_given
         rows = run_index_stage(w, tables, db, buf)
         run_forward(w, tables, rows, buf)
         return rows

@@ -1006,6 +1006,52 @@ def test_hashed_forward_from_lengths_equals_offsets_then_hashed_forward(T, B, D,
     assert a[3] & emb.STATUS_BAD_OFFSETS and b[3] & emb.STATUS_BAD_OFFSETS and torch.equal(a[0], b[0])
 
 
+@pytest.mark.parametrize("T,B", [(1, 1), (1, 63), (3, 1), (2, 257), (7, 585), (1, 4096), (1, 4097), (3, 2000)])
+@pytest.mark.parametrize("D,dtype", [(4, "f32"), (16, "bf16"), (48, "f32"), (64, "int4"), (160, "int8"), (300, "f32")])
+def test_forward_by_row_number_from_lengths_equals_offsets_then_forward(T, B, D, dtype):
+    # around the batch size up to which every workgroup adds up the lengths itself; short and empty bags, one long one,
+    # lengths at an address that is no multiple of 16, negative lengths and rows out of range
+    rng = np.random.default_rng(T * 10_000 + B + D)
+    R = 300
+    full = [(rng.standard_normal((R, D)) * 0.01).astype(np.float32) for _ in range(T)]
+    w = []
+    for x in full:
+        t = torch.from_numpy(x).to(H.DEV)
+        if dtype in emb.QUANT_DTYPES:
+            q = torch.empty((R, emb.emb_row_bytes(D, dtype)), dtype=torch.uint8, device=H.DEV)
+            emb.emb_quantize_rows(t, dtype, q)
+            t = q
+        elif dtype == "bf16":
+            t = t.to(torch.bfloat16)
+        w.append(t)
+    ts = emb.TableSet(w, D, dtype, device=torch.device(H.DEV))
+    lengths = rng.integers(0, 4, size=T * B).astype(np.int32)
+    lengths[rng.integers(0, T * B)] = 77
+    lengths[rng.integers(0, T * B)] = -5
+    nnz = int(np.maximum(lengths, 0).sum())
+    rows = rng.integers(0, R, size=nnz)
+    rows[:1] = R
+    ld = torch.empty(T * B + 1, dtype=torch.int32, device=H.DEV)[1:]
+    ld.copy_(torch.from_numpy(lengths))
+    rd = H.dev(rows.astype(np.int64))
+    got = []
+    for one in (False, True):
+        out = torch.full((T, B, D), float("nan"), dtype=torch.float32, device=H.DEV)
+        off = torch.full((T * B + 1,), -3, dtype=torch.int64, device=H.DEV)
+        status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+        if one:
+            scratch = torch.empty(emb.emb_offsets_scratch_bytes(T * B), dtype=torch.uint8, device=H.DEV)
+            emb.emb_bag_forward_lengths(ts, rd, ld, B, "mean", out, off, scratch, status)
+        else:
+            emb.emb_lengths_to_offsets(ld, off, status)
+            emb.emb_bag_forward(ts, rd, off, B, "mean", out, status)
+        torch.cuda.synchronize()
+        got.append((out, off, status))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    assert got[0][2].item() & emb.STATUS_BAD_OFFSETS
+
+
 def test_hashed_forward_from_lengths_argument_limits():
     ts = emb.TableSet([torch.zeros((5, 16), dtype=torch.float32, device=H.DEV)], 16, "f32", device=torch.device(H.DEV))
     offs = torch.full((1,), -9, dtype=torch.int64, device=H.DEV)
