@@ -512,6 +512,10 @@ __global__ __launch_bounds__(256) void long_detect_kernel(const KeyT *__restrict
 // per-span run counts.  A run ends where the next run starts: inside its own span
 // (queue_end), else at the first run start of the spans after it, which the
 // wavefront looks up together, 64 spans per round trip.
+// The workgroup is small because the kernel is launched beside update_kernel, whose workgroups of two
+// wavefronts take every place that comes free: one of sixteen wavefronts waits until the update has nearly
+// drained (step of 3 tables x 512 bags of 20: 110 us, with four wavefronts 91 us; at 2.6e6 lookups, where
+// update_kernel bounds the step either way, 413 and 415 us).
 __global__ __launch_bounds__(PREP_BLOCK) void long_prepare_kernel(uint32_t n, BwdCtrl *ctrl,
                                                            const uint32_t *__restrict__ queue,
                                                            const uint32_t *__restrict__ queue_end, uint32_t slots,
