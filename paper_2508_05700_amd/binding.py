@@ -250,12 +250,21 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name: str = "tensor") -> Optiona
     raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
 
 
-def _host_address(owner) -> int:
-    """Address of ``owner.host``, a numpy array (asking numpy for it takes 1.2 us, so it is kept with the array)."""
-    known = getattr(owner, "_host_known", None)
-    if known is None or known[0] is not owner.host:
-        known = owner._host_known = (owner.host, int(owner.host.ctypes.data))
-    return known[1]
+class _HostDescriptors:
+    """A holder of ``host``, the numpy array of descriptors that the library reads on each call."""
+
+    def _host_address(self) -> int:
+        # asking numpy for the address takes 1.1 us, so it is kept with the array
+        known = getattr(self, "_host_known", None)
+        if known is None or known[0] is not self.host:
+            known = self._host_known = (self.host, int(self.host.ctypes.data))
+        return known[1]
+
+    def __getstate__(self):
+        # a copy's array lies elsewhere, and deepcopy or pickle would keep the pair of array and address matching
+        state = self.__dict__.copy()
+        state.pop("_host_known", None)
+        return state
 
 
 def _check(fn: str, rc: int) -> None:
@@ -268,7 +277,7 @@ _TABLE_TORCH = {"f32": torch.float32, "bf16": torch.bfloat16, "int8": torch.uint
                 "int4r64": torch.uint8}
 
 
-class TableSet:
+class TableSet(_HostDescriptors):
     """The ``emb_table`` descriptor array of T tables, on the host and on the device.
 
     ``weights[t]`` is a device tensor ``[R_t, D]`` (fp32 or bf16; uint8
@@ -310,7 +319,7 @@ class TableSet:
 
     @property
     def host_ptr(self) -> int:
-        return _host_address(self)
+        return self._host_address()
 
     @property
     def dev_ptr(self) -> int:
@@ -421,7 +430,7 @@ def emb_bag_forward_lengths(tables: TableSet, rows: torch.Tensor, lengths: torch
         _ptr(status, torch.int32, "status"), _stream()))
 
 
-class MixedTables:
+class MixedTables(_HostDescriptors):
     """Tables of different width / storage type for ``emb_bag_forward_mixed``.
 
     ``weights[t]`` is a device tensor ``[R_t, D_t]`` (fp32 or bf16).  ``layout``: "table_major" puts
@@ -464,7 +473,7 @@ def emb_bag_forward_mixed(mt: MixedTables, rows: torch.Tensor, offsets: torch.Te
     if offsets.numel() != mt.T * mt.B + 1 or out.numel() < mt.out_floats:
         raise TypeError("shape mismatch")
     _check("emb_bag_forward_mixed", lib().emb_bag_forward_mixed(
-        mt.tables.host_ptr, mt.tables.dev_ptr, _host_address(mt), mt.dev.data_ptr(), mt.T,
+        mt.tables.host_ptr, mt.tables.dev_ptr, mt._host_address(), mt.dev.data_ptr(), mt.T,
         _ptr(rows, torch.int64, "rows"), _ptr(offsets, torch.int64, "offsets"), mt.B, rows.numel(), POOL[mode],
         _ptr(out, torch.float32, "out"), out.numel(), _ptr(status, torch.int32, "status"), _stream()))
 
@@ -946,7 +955,7 @@ def emb_bag_forward_latched_hashed(latch: torch.Tensor, T: int, D: int, dtype: s
                      streaming)
 
 
-class CachedTables:
+class CachedTables(_HostDescriptors):
     """The ``emb_cached_table`` descriptor array of T hosted tables with their caches, on the host and on the
     device.  ``entries[t]`` = (table_ptr, num_rows, cache_rows tensor, cache_index tensor, num_hot, salt)."""
 
@@ -971,7 +980,7 @@ def _forward_cached_tables(fn: str, ct: CachedTables, ids, id_dtype, offsets, B,
     if offsets.numel() != ct.T * B + 1 or out.numel() != ct.T * B * ct.D:
         raise TypeError("shape mismatch")
     _check(fn, getattr(lib(), fn)(
-        _host_address(ct), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(ids, id_dtype, "ids"),
+        ct._host_address(), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(ids, id_dtype, "ids"),
         _ptr(offsets, torch.int64, "offsets"), int(B), ids.numel(), POOL[mode], _ptr(out, torch.float32, "out"),
         _ptr(hit_miss, _U64, "hit_miss"), _ptr(status, torch.int32, "status"), _stream()))
 
@@ -1000,7 +1009,7 @@ def emb_bag_forward_cached_tables_hashed_lengths(ct: CachedTables, raw: torch.Te
     if lengths.numel() != n or offsets_out.numel() != n + 1 or out.numel() != n * ct.D:
         raise TypeError("shape mismatch")
     _check("emb_bag_forward_cached_tables_hashed_lengths", lib().emb_bag_forward_cached_tables_hashed_lengths(
-        _host_address(ct), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(raw, _U64, "raw"),
+        ct._host_address(), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(raw, _U64, "raw"),
         _ptr(lengths, torch.int32, "lengths") if n else None, int(B), raw.numel(), POOL[mode],
         _ptr(out, torch.float32, "out"), _ptr(offsets_out, torch.int64, "offsets_out"),
         _ptr(scratch, torch.uint8, "scratch"), scratch.numel(), _ptr(hit_miss, _U64, "hit_miss"),
@@ -1046,7 +1055,7 @@ def emb_version_hosted_record_write(record: torch.Tensor, ct: CachedTables, vers
     if record.numel() < emb_version_hosted_record_bytes(ct.T):
         raise TypeError("record too small")
     _check("emb_version_hosted_record_write", lib().emb_version_hosted_record_write(
-        _ptr(record, torch.uint8, "record"), _host_address(ct), ct.dev.data_ptr(), ct.T,
+        _ptr(record, torch.uint8, "record"), ct._host_address(), ct.dev.data_ptr(), ct.T,
         C.c_uint64(int(version)), _stream()))
 
 

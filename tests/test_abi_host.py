@@ -1,7 +1,9 @@
 """The C ABI without a GPU: the library loads, exports what the header
 declares, and every host-checkable error is reported without a launch."""
+import copy
 import ctypes as C
 import os
+import pickle
 import re
 import subprocess
 
@@ -544,3 +546,14 @@ def test_exact_remainder_on_the_host(tmp_path):
                            os.path.join(ROOT, "tests", "host", "u64mod_check.cpp"), "-o", exe])
     out = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
     assert out.returncode == 0 and out.stdout.startswith("OK"), out.stdout
+
+
+@pytest.mark.parametrize("cls", [b.TableSet, b.MixedTables, b.CachedTables])
+@pytest.mark.parametrize("duplicate", [copy.copy, copy.deepcopy, lambda o: pickle.loads(pickle.dumps(o))])
+def test_copied_descriptors_are_read_where_the_copy_holds_them(cls, duplicate):
+    one = cls.__new__(cls)   # the descriptors alone: the rest of a table set is device memory
+    one.host = np.zeros(3, dtype=b.TABLE_DESC)
+    assert one._host_address() == one.host.ctypes.data
+    two = duplicate(one)
+    assert two._host_address() == two.host.ctypes.data
+    assert one._host_address() == one.host.ctypes.data
