@@ -505,9 +505,18 @@ int launch_update(const BwdArgs &a, const BwdLayout &L, const KeyT *keys, const 
     EMB_MARK(a, 4);
 
     const int64_t pthreads = L.qslots > L.slots ? L.qslots : L.slots;
-    hipLaunchKernelGGL(long_prepare_kernel, dim3((unsigned)((pthreads + PREP_BLOCK - 1) / PREP_BLOCK)), dim3(PREP_BLOCK),
-                       0, ls, n, ctrl, queue, queue_end, (uint32_t)L.qslots, span_head, wave_heads, (uint32_t)L.slots, segs,
-                       multi_list, chunk_tasks, (uint32_t)L.chunk_cap);
+    // Beside update_kernel a workgroup of sixteen wavefronts waits for a whole free CU.  In a small step that wait is
+    // the step's own length (3 tables x 512 bags of 20: 110 us, with four wavefronts 91).  In a large one it keeps
+    // long_reduce_kernel away from the update until the update drains: 2.6e6 lookups, reduce 35 us and update 219,
+    // with four wavefronts 134 and 239 (traces of two cards; the step 413 and 415 us on one), because both then run
+    // at once for the reduce's whole length.
+#define EMB_PREPARE(BLOCK)                                                                                              \
+    hipLaunchKernelGGL(long_prepare_kernel<BLOCK>, dim3((unsigned)((pthreads + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, ls, n, \
+                       ctrl, queue, queue_end, (uint32_t)L.qslots, span_head, wave_heads, (uint32_t)L.slots, segs,     \
+                       multi_list, chunk_tasks, (uint32_t)L.chunk_cap)
+    if (a.nnz <= PREP_SMALL_MAX) EMB_PREPARE(PREP_BLOCK);
+    else EMB_PREPARE(PREP_BLOCK_LARGE);
+#undef EMB_PREPARE
     EMB_RETURN_IF_LAUNCH_FAILED();
 
     // one wavefront per task; enough workgroups to fill the chip, tasks beyond that are strided over

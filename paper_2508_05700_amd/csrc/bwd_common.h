@@ -26,7 +26,9 @@ constexpr int UPD_LOOK = 32;         // records of look-ahead after a span
 constexpr int UPD_SHORT_MAX = 32;    // longest run the short-run kernel sums itself
 constexpr int UPD_QSLOTS = UPD_SPAN / (UPD_SHORT_MAX + 1) + 1;  // runs longer than that which can start in one span
 constexpr int LONG_CHUNK = 256;     // records of a queued run summed by one wavefront
-constexpr int PREP_BLOCK = 256;      // workgroup of the kernel that turns queued runs into tasks (long_prepare_kernel says why)
+constexpr int PREP_BLOCK = 256;      // workgroup of the kernel that turns queued runs into tasks
+constexpr int PREP_BLOCK_LARGE = 1024;            // the same for more than PREP_SMALL_MAX records (launch_update)
+constexpr int64_t PREP_SMALL_MAX = 1 << 20;
 constexpr int UPD_LDS_TABLES = 512; // table directories up to this size are staged in LDS
 
 struct LongSeg {

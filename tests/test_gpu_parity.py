@@ -1155,6 +1155,29 @@ def test_many_tables_take_the_paths_without_lds_staging():
         H.assert_rows_close(w[t].cpu().numpy(), ref_t[t], tables[t], 0.01, what="many tables rows t=%d" % t)
 
 
+@pytest.mark.parametrize("extra", [0, 1])
+@pytest.mark.parametrize("side", [True, False])
+def test_backward_at_the_line_between_the_two_ways_to_prepare_long_runs(extra, side):
+    # up to 2^20 records the queued runs are prepared by workgroups of four wavefronts, beyond by sixteen; the
+    # gradients are small whole numbers, so the sums of the runs (3500 records in table 1) are exact in any order
+    rng = np.random.default_rng(46 + extra)
+    T, B, D, Rs, nnz = 2, 1024, 16, [50_000, 150], (1 << 20) + extra
+    half = [nnz // 2, nnz - nnz // 2]
+    lengths = np.concatenate([rng.multinomial(n, np.full(B, 1.0 / B)) for n in half]).astype(np.int32)
+    off, _ = oracle.lengths_to_offsets(lengths)
+    rows = np.concatenate([rng.integers(0, R, size=n) for R, n in zip(Rs, half)]).astype(np.int64)
+    tables = [(rng.standard_normal((R, D)) * 0.01).astype(np.float32) for R in Rs]
+    dout = rng.integers(-3, 4, size=(T, B, D)).astype(np.float32)
+    ts, w, acc = H.make_tableset(tables, "f32", with_accum=True)
+    g = H.gpu_backward(ts, rows, off, B, "sum", dout, 0.01, 1e-8, side=side)
+    ref_t, ref_a = [t.copy() for t in tables], [np.zeros(R, np.float32) for R in Rs]
+    r = oracle.bag_backward_rowwise_adagrad(ref_t, ref_a, "f32", rows, off, B, "sum", dout, 0.01, 1e-8)
+    assert g["status"] == r["status"] == 0 and np.array_equal(g["unique_keys"], r["unique_keys"])
+    assert np.array_equal(g["unique_counts"], r["unique_counts"])
+    for t in range(T):
+        H.assert_rows_close(w[t].cpu().numpy(), ref_t[t], tables[t], 0.01, what="line between prepares t=%d" % t)
+
+
 def test_backward_is_deterministic():
     rng = np.random.default_rng(43)
     T, B, D, Rs = 2, 1500, 64, [20_000, 300]
