@@ -25,6 +25,15 @@ __device__ __forceinline__ int64_t cache_slot(const uint4 &entry, int bit, uint6
     return -1;
 }
 
+// The entry without the rows whose slot is num_hot or more: what is left are exactly the rows that cache_slot takes.
+__device__ __forceinline__ uint4 cache_clip(uint4 entry, uint64_t num_hot)
+{
+    uint64_t bits = ((uint64_t)entry.y << 32) | entry.x;
+    uint64_t end = (uint64_t)entry.z + (uint64_t)__popcll(bits);
+    for (; bits && end > num_hot; --end) bits &= ~(1ull << (63 - __clzll((long long)bits)));
+    return make_uint4((uint32_t)bits, (uint32_t)(bits >> 32), entry.z, entry.w);
+}
+
 // Slot of row r (0 <= r < num_rows) in the cache, or -1 if the row is not cached.
 __device__ __forceinline__ int64_t cache_probe(const CacheEntry *__restrict__ index, uint64_t r, uint64_t num_hot)
 {

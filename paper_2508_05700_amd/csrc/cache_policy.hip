@@ -474,7 +474,9 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_write_kernel(uint32_t *freq, int
         if (threadIdx.x < SEL_TILE / 64) {
             const int64_t e = tile0 / 64 + threadIdx.x;
             old_entry[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
-            if (e * 64 < num_rows) old_entry[threadIdx.x] = *reinterpret_cast<const uint4 *>(f.old_index + e);
+            // clipped, so that the rows counted as kept are the rows copied from the old cache
+            if (e * 64 < num_rows)
+                old_entry[threadIdx.x] = cache_clip(*reinterpret_cast<const uint4 *>(f.old_index + e), (uint64_t)f.old_num_hot);
         }
         if (threadIdx.x == 0) s_kept = 0u;
     }

@@ -1759,6 +1759,39 @@ def test_cache_refresh_equals_select_then_rebuild(R, num_hot, D, dtype):
         assert status.item() == 0
 
 
+@pytest.mark.parametrize("old_num_hot", [0, 1, 70, 649, 650])
+def test_cache_refresh_counts_as_kept_the_rows_it_copies_from_the_old_cache(old_num_hot):
+    # an index that names more rows than the old cache is said to hold: the rows past its end come from the table
+    rng = np.random.default_rng(77)
+    R, D, num_hot = 9000, 16, 700
+    table = H.dev((rng.standard_normal((R, D)) * 0.01).astype(np.float32))
+    ptr = int(table.data_ptr())
+    old_hot = np.sort(np.concatenate([np.arange(64, 180), rng.choice(np.arange(200, R), size=534, replace=False)])).astype(np.int64)
+    old_rows = torch.empty((old_hot.size, D), dtype=torch.float32, device=H.DEV)
+    old_idx = torch.empty(emb.emb_cache_index_bytes(R), dtype=torch.uint8, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    emb.emb_cache_build(ptr, R, D, "f32", H.dev(old_hot), old_rows, old_idx, status)
+    old_rows += 1.0                                                   # where a row came from shows in its value
+    ws = torch.empty(emb.emb_cache_select_workspace_bytes(R), dtype=torch.uint8, device=H.DEV)
+    freq = np.zeros(R, dtype=np.uint32)
+    freq[rng.choice(old_hot, size=400, replace=False)] = 3
+    freq[64:150] = 2
+    fd = _freq_dev(freq)
+    hot = torch.empty(num_hot, dtype=torch.int64, device=H.DEV)
+    rows = torch.empty((num_hot, D), dtype=torch.float32, device=H.DEV)
+    idx = torch.empty_like(old_idx)
+    moved = torch.zeros(2, dtype=torch.int64, device=H.DEV)
+    emb.emb_cache_refresh(fd, num_hot, 0, ws, ptr, D, "f32", old_rows if old_num_hot else None, old_idx, old_num_hot, hot,
+                          rows, idx, moved, None, status)
+    torch.cuda.synchronize()
+    chosen = hot.cpu().numpy()
+    kept = np.isin(chosen, old_hot[:old_num_hot])
+    want = table.cpu().numpy()[chosen]
+    want[kept] += np.float32(1.0)
+    assert np.array_equal(rows.cpu().numpy(), want)
+    assert moved.cpu().tolist() == [int(kept.sum()), int((~kept).sum())] and status.item() == 0
+
+
 def test_cache_policy_loop_matches_the_oracle_step_by_step():
     # a drifting Zipf stream of raw IDs: observe each batch, refresh every few batches; the hot set, the
     # counters, hits and misses and the pooled output follow the oracle's at every step
