@@ -1599,6 +1599,37 @@ def test_cache_observe_counts_like_the_oracle():
     assert status.item() == 0 and np.array_equal(_freq_host(fd), ref)
 
 
+@pytest.mark.parametrize("R", [(1 << 32) - 1, 1 << 32, (1 << 32) + 1])
+def test_cache_observe_of_tables_around_two_to_the_32_rows(R):
+    # up to 2^32 - 1 rows a workgroup merges its lookups under 32-bit row numbers, whose highest value means "free";
+    # beyond under 64-bit ones.  Popular rows at both ends of the table, rows out of range, and raw IDs.
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 17 GB of counters")
+    rng = np.random.default_rng(5050 + R % 7)
+    fd = torch.zeros(R, dtype=torch.int32, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    far = np.minimum(rng.zipf(1.2, size=40_000) - 1, R - 1).astype(np.int64)
+    rows = np.concatenate([far, R - 1 - far, rng.integers(0, R, size=40_000)]).astype(np.int64)
+    rng.shuffle(rows)
+    rows[:3] = [-1, R, (1 << 62) + 5]
+    rows[3:3000] = R - 1
+    raw = rng.integers(0, 1 << 64, size=30_000, dtype=np.uint64)
+    raw[:3000] = raw[0]
+    emb.emb_cache_observe(R, H.dev(rows), fd, status)
+    torch.cuda.synchronize()
+    assert status.item() == emb.STATUS_BAD_INDEX
+    status.zero_()
+    emb.emb_cache_observe_hashed(R, 991, H.dev(raw), fd, status)
+    torch.cuda.synchronize()
+    assert status.item() == 0
+    counted = np.concatenate([rows[3:], oracle.hash_ids(raw, 991, R)])
+    touched, place = np.unique(counted, return_inverse=True)
+    ref = np.zeros(touched.size, dtype=np.uint32)
+    assert oracle.cache_observe(ref, place.astype(np.int64)) == 0
+    assert np.array_equal(fd[H.dev(touched)].cpu().numpy().view(np.uint32), ref)
+    assert int(fd.sum(dtype=torch.int64)) == counted.size             # and no other counter
+
+
 def _select_case(freq, num_hot, shift):
     R = freq.size
     fd = _freq_dev(freq)
