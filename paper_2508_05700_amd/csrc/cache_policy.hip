@@ -42,6 +42,10 @@ constexpr uint32_t SEL_EXACT = SEL_BINS - 1;               // values below have 
 constexpr int SEL_REPLICAS = 8;                            // of the first histogram: fewer adds per word
 constexpr int SEL_HIST_BLOCKS = 256;                       // one workgroup per CU: 64 KB of loads in flight each
 constexpr int SEL_GROUPS = 64;                             // words that collect the kept rows of a refresh
+constexpr uint32_t SEL_TILE_CHUNKS = 4 * SEL_TILE;         // chunks that a tile's workgroup copies itself (sel_wide_copy_kernel)
+constexpr int SEL_WIDE_GRID = 256;                         // with two loads a lane 2 MB in flight
+constexpr int SEL_WIDE_UNROLL = 2;
+constexpr int SEL_WIDE_CHUNKS = 512;                       // a wavefront's share of rows: at most so many chunks, or one row
 // digits of the threshold where it is not below SEL_EXACT: bits 21.., 10..20, 0..9
 constexpr int SEL_SHIFT1 = 21, SEL_SHIFT2 = 10;
 
@@ -53,7 +57,8 @@ struct SelCtrl {
     uint64_t need1;      // after the first digit
     uint32_t prefix2, pad1;
     uint64_t need2;      // after the second
-    uint32_t thr, pad2;  // the threshold and the number of rows to take at it
+    uint32_t thr;        // the threshold and the number of rows to take at it
+    uint32_t wide;       // a tile has left its rows to sel_wide_copy_kernel
     uint64_t take;
 };
 static_assert(sizeof(SelCtrl) <= 256, "the control block has 256 bytes");
@@ -269,6 +274,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void sel_pick_kernel(const unsigned long
         ctrl->exact = bin < SEL_EXACT ? 1u : 0u;
         ctrl->thr0 = bin;
         ctrl->take0 = left;
+        ctrl->wide = 0u;
     }
 }
 
@@ -440,6 +446,7 @@ struct RefreshArgs {
     uint32_t chunk_magic;         // floor(2^32 / chunks) + 1: i / chunks for i < SEL_TILE * 1024 (0: one chunk)
     unsigned long long *moved;    // nullable
     unsigned long long *groups;   // [SEL_GROUPS], zero
+    uint32_t *wide;               // SelCtrl::wide
 };
 
 // Write the selected rows in ascending order and age the counters.  A row is selected if its counter is above
@@ -543,7 +550,11 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_write_kernel(uint32_t *freq, int
     }
     // ---- rows: consecutive lanes copy consecutive chunks of the tile's part of the cache
     const uint32_t chunks = (uint32_t)f.chunks;
-    const uint32_t items = selected * chunks;
+    uint32_t items = selected * chunks;
+    if (items > SEL_TILE_CHUNKS) {   // uniform; sel_wide_copy_kernel tells such tiles by the same test
+        items = 0u;
+        if (threadIdx.x == 0) *f.wide = 1u;
+    }
     constexpr int UNROLL = 4;
     for (uint32_t i0 = threadIdx.x; i0 < items; i0 += CP_BLOCK * UNROLL) {
         uint4 x[UNROLL];
@@ -585,6 +596,61 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_write_kernel(uint32_t *freq, int
                 }
             }
             if (blockIdx.x == 0) atomicAdd(&f.moved[1], (unsigned long long)num_hot);   // all rows, less the kept ones
+        }
+    }
+}
+
+// The rows of the tiles that hold more than SEL_TILE_CHUNKS chunks of the new cache.  Left to the tile's one
+// workgroup they are a serial chain of 1.5 us per 1024 chunks while the rest of the chip is idle: of 10 000 rows of
+// 4096 bytes side by side a refresh took 1590 us with all of them in the old cache and 2455 with none.  Copied from
+// the finished list, which is what this kernel does, it takes 65 and 771.  Tiles up to the line are the faster for
+// being copied in the pass (75 000 of 1.5e6 rows of 512 bytes, 6550 chunks a tile: 54 us, emb_cache_rebuild's copy
+// 68); at 32 768 chunks a tile the two are even (95 us in the pass, 89 here).
+// A wavefront takes a share of consecutive rows of the list: a lane each finds where a row comes from, then all
+// lanes copy the share's chunks.  unit: rows of a share (at most EMB_WAVE).  2 MB in flight are what the two places
+// that rows come from agree on: 4096-byte rows, 2, 4 and 8 MB: 771, 792 and 819 us over the link, 65, 57 and 56 from
+// the old cache.
+__global__ __launch_bounds__(CP_BLOCK) void sel_wide_copy_kernel(const SelCtrl *__restrict__ ctrl,
+                                                                 const unsigned long long *__restrict__ base, int64_t tiles,
+                                                                 int64_t num_rows, int64_t num_hot,
+                                                                 const int64_t *__restrict__ hot, int unit, RefreshArgs f)
+{
+    if (!ctrl->wide) return;   // uniform
+    const int lane = threadIdx.x & (EMB_WAVE - 1);
+    const int64_t wave = (int64_t)blockIdx.x * (CP_BLOCK / EMB_WAVE) + threadIdx.x / EMB_WAVE;
+    const int64_t step = (int64_t)gridDim.x * (CP_BLOCK / EMB_WAVE) * unit;
+    const uint32_t chunks = (uint32_t)f.chunks;
+    const uint32_t items = (uint32_t)unit * chunks;
+    for (int64_t k0 = wave * unit; k0 < num_hot; k0 += step) {   // the same for every lane
+        uint64_t src = 0ull;
+        if (lane < unit && k0 + lane < num_hot) {
+            const int64_t row = hot[k0 + lane];
+            if (row >= 0 && row < num_rows) {   // always true, as in sel_write_kernel
+                const int64_t tile = row / SEL_TILE;
+                const uint64_t end = tile + 1 < tiles ? base[tile + 1] : (uint64_t)num_hot;
+                if ((end - base[tile]) * chunks > SEL_TILE_CHUNKS) {
+                    const int64_t slot = cache_probe(f.old_index, (uint64_t)row, (uint64_t)f.old_num_hot);
+                    src = reinterpret_cast<uint64_t>(slot >= 0 ? f.old_rows + slot * (int64_t)chunks * 16
+                                                               : f.table + row * (int64_t)chunks * 16);
+                }
+            }
+        }
+        if (__ballot(src != 0ull) == 0ull) continue;
+        for (uint32_t i0 = 0; i0 < items; i0 += EMB_WAVE * SEL_WIDE_UNROLL) {
+            uint4 x[SEL_WIDE_UNROLL];
+            bool mine[SEL_WIDE_UNROLL];
+#pragma unroll
+            for (int u = 0; u < SEL_WIDE_UNROLL; ++u) {
+                const uint32_t i = i0 + u * EMB_WAVE + lane;
+                const uint32_t k = f.chunk_magic ? __umulhi(i, f.chunk_magic) : i;
+                const uint64_t p = (uint64_t)shfl_i64((int64_t)src, (int)(k < (uint32_t)unit ? k : 0u), EMB_WAVE);
+                mine[u] = i < items && p != 0ull;
+                if (mine[u]) x[u] = load_chunk(reinterpret_cast<const char *>(p) + (int64_t)(i - k * chunks) * 16);
+            }
+#pragma unroll
+            for (int u = 0; u < SEL_WIDE_UNROLL; ++u)
+                if (mine[u])
+                    *reinterpret_cast<uint4 *>(f.new_rows + (k0 * chunks + i0 + u * EMB_WAVE + lane) * 16) = x[u];
         }
     }
 }
@@ -693,8 +759,19 @@ int select_run(uint32_t *freq_dev, int64_t num_rows, int64_t num_hot, int32_t de
     if (refresh) {
         RefreshArgs f = *refresh;
         f.groups = reinterpret_cast<unsigned long long *>(ws + L.groups);
+        f.wide = &ctrl->wide;
         hipLaunchKernelGGL(sel_write_kernel<true>, dim3((unsigned)L.tiles), dim3(CP_BLOCK), 0, s, freq_dev, num_rows, ctrl,
                            base, ties, num_hot, (int)decay_shift, hot_rows_out_dev, f);
+        // only where the rows chosen from one tile can be so many
+        if ((num_hot < SEL_TILE ? num_hot : SEL_TILE) * f.chunks > (int64_t)SEL_TILE_CHUNKS) {
+            EMB_RETURN_IF_LAUNCH_FAILED();
+            int unit = SEL_WIDE_CHUNKS / f.chunks;
+            unit = unit < 1 ? 1 : (unit > EMB_WAVE ? EMB_WAVE : unit);
+            const int64_t per_block = (int64_t)unit * (CP_BLOCK / EMB_WAVE);
+            const int64_t blocks = (num_hot + per_block - 1) / per_block;
+            hipLaunchKernelGGL(sel_wide_copy_kernel, dim3((unsigned)(blocks < SEL_WIDE_GRID ? blocks : SEL_WIDE_GRID)),
+                               dim3(CP_BLOCK), 0, s, ctrl, base, L.tiles, num_rows, num_hot, hot_rows_out_dev, unit, f);
+        }
     } else {
         hipLaunchKernelGGL(sel_write_kernel<false>, dim3((unsigned)L.tiles), dim3(CP_BLOCK), 0, s, freq_dev, num_rows, ctrl,
                            base, ties, num_hot, (int)decay_shift, hot_rows_out_dev, RefreshArgs{});
@@ -754,7 +831,8 @@ extern "C" int emb_cache_refresh(uint32_t *freq_dev, int64_t num_rows, int64_t n
     f.chunks = (int32_t)(row_bytes / 16);   // rows of every storage type are whole 16-byte chunks
     f.chunk_magic = f.chunks == 1 ? 0u : (uint32_t)((UINT64_C(1) << 32) / (uint32_t)f.chunks) + 1u;
     f.moved = reinterpret_cast<unsigned long long *>(moved_dev);
-    f.groups = nullptr;
+    f.groups = nullptr;   // these two: select_run
+    f.wide = nullptr;
     rc = select_run(freq_dev, num_rows, num_hot, decay_shift, L, static_cast<char *>(workspace_dev), hot_rows_out_dev,
                     info_out_dev, emb_stream(stream), &f);
     if (rc != EMB_OK || num_hot > 0) return rc;

@@ -1823,6 +1823,84 @@ def test_cache_refresh_counts_as_kept_the_rows_it_copies_from_the_old_cache(old_
     assert moved.cpu().tolist() == [int(kept.sum()), int((~kept).sum())] and status.item() == 0
 
 
+# rows chosen from each tile of 4096 rows: a tile of more than 16384 chunks of 16 bytes leaves its copy to another kernel
+@pytest.mark.parametrize("D,dtype,per_tile,last", [
+    (32, "bf16", [4096, 0, 4000], 4001), (64, "f32", [1024, 5, 1025, 4096, 3996], 3996), (128, "int4", [3276, 3277, 77], 90),
+    (1024, "f32", [64, 65, 300, 1], 1), (4096, "f32", [17, 16], 4096)])
+def test_cache_refresh_of_tiles_with_many_chosen_rows(D, dtype, per_tile, last):
+    rng = np.random.default_rng(D + len(per_tile))
+    R = 4096 * (len(per_tile) - 1) + last
+    rowb = emb.emb_row_bytes(D, dtype)
+    table = torch.randint(0, 256, (R, rowb), dtype=torch.uint8, device=H.DEV)
+    torch_type = {"f32": torch.float32, "bf16": torch.bfloat16, "int4": torch.uint8}[dtype]
+    ptr = int(table.data_ptr())
+    hot = np.sort(np.concatenate([4096 * t + rng.choice(last if t == len(per_tile) - 1 else 4096, size=n, replace=False)
+                                  for t, n in enumerate(per_tile)])).astype(np.int64)
+    freq = np.zeros(R, dtype=np.uint32)
+    freq[hot] = rng.integers(2, 9, size=hot.size)
+    old_hot = np.sort(rng.choice(R, size=R // 2, replace=False)).astype(np.int64)
+    old_rows = torch.empty((old_hot.size, rowb), dtype=torch.uint8, device=H.DEV)
+    old_idx = torch.empty(emb.emb_cache_index_bytes(R), dtype=torch.uint8, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    emb.emb_cache_build(ptr, R, D, dtype, H.dev(old_hot), old_rows.view(torch_type), old_idx, status)
+    old_rows.bitwise_xor_(0xFF)                                       # where a row came from shows in its bytes
+    ws = torch.full((emb.emb_cache_select_workspace_bytes(R),), 0xA5, dtype=torch.uint8, device=H.DEV)
+    for old_num_hot in (old_hot.size, old_hot.size // 3):
+        fd = _freq_dev(freq)
+        got_hot = torch.full((hot.size,), -9, dtype=torch.int64, device=H.DEV)
+        rows = torch.zeros((hot.size, rowb), dtype=torch.uint8, device=H.DEV)
+        idx = torch.full_like(old_idx, 0x77)
+        moved = torch.zeros(2, dtype=torch.int64, device=H.DEV)
+        emb.emb_cache_refresh(fd, hot.size, 1, ws, ptr, D, dtype, old_rows.view(torch_type), old_idx, old_num_hot, got_hot,
+                              rows.view(torch_type), idx, moved, None, status)
+        torch.cuda.synchronize()
+        assert np.array_equal(got_hot.cpu().numpy(), hot)
+        kept = torch.from_numpy(np.isin(hot, old_hot[:old_num_hot])).to(H.DEV)
+        want = table[got_hot]
+        want[kept] ^= 0xFF
+        assert torch.equal(rows, want)
+        assert moved.cpu().tolist() == [int(kept.sum()), int((~kept).sum())] and status.item() == 0
+
+
+@pytest.mark.parametrize("known", [True, False])
+def test_cache_refresh_of_rows_side_by_side_is_no_slower_than_the_two_calls(known):
+    # the chosen rows of few tiles must not be left to the few workgroups of those tiles (which takes about twenty times
+    # as long as the two calls here); the bound of three allows for whatever else disturbs a short measurement
+    R, D, num_hot = 50_000, 1024, 8000
+    table = torch.zeros((R, D), dtype=torch.float32, device=H.DEV)
+    ptr = int(table.data_ptr())
+    freq = torch.zeros(R, dtype=torch.int32, device=H.DEV)
+    freq[:num_hot] = 7
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    old_hot = torch.arange(num_hot if known else 0, dtype=torch.int64, device=H.DEV)
+    old_rows = torch.empty((num_hot, D), dtype=torch.float32, device=H.DEV)
+    rows = torch.empty_like(old_rows)
+    old_idx = torch.empty(emb.emb_cache_index_bytes(R), dtype=torch.uint8, device=H.DEV)
+    idx = torch.empty_like(old_idx)
+    emb.emb_cache_build(ptr, R, D, "f32", old_hot, old_rows, old_idx, status)
+    ws = torch.empty(emb.emb_cache_select_workspace_bytes(R), dtype=torch.uint8, device=H.DEV)
+    hot = torch.empty(num_hot, dtype=torch.int64, device=H.DEV)
+
+    def two():
+        emb.emb_cache_select(freq, num_hot, 0, ws, hot, None)
+        emb.emb_cache_rebuild(ptr, R, D, "f32", old_rows, old_idx, old_hot.numel(), hot, rows, idx, None, status)
+
+    def one():
+        emb.emb_cache_refresh(freq, num_hot, 0, ws, ptr, D, "f32", old_rows, old_idx, old_hot.numel(), hot, rows, idx, None,
+                              None, status)
+
+    best = {two: float("inf"), one: float("inf")}
+    for _ in range(8):
+        for fn in best:
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            fn()
+            ev[1].record()
+            torch.cuda.synchronize()
+            best[fn] = min(best[fn], ev[0].elapsed_time(ev[1]))
+    assert best[one] < 3 * best[two], best
+
+
 def test_cache_policy_loop_matches_the_oracle_step_by_step():
     # a drifting Zipf stream of raw IDs: observe each batch, refresh every few batches; the hot set, the
     # counters, hits and misses and the pooled output follow the oracle's at every step
