@@ -180,7 +180,8 @@ __device__ __forceinline__ void sel_load4(const uint32_t *__restrict__ freq, int
 
 // Histogram of the counters with a bin for each value below SEL_EXACT.  Most counters are zero and most of
 // the others small: the values 0 to 3 are counted in registers (four 16-bit fields of one word, flushed
-// before they can overflow), the rest by LDS adds.  A workgroup adds its bins to one of SEL_REPLICAS copies.
+// before they can overflow), those of the last bin in another, the rest by LDS adds.  A workgroup adds its bins to
+// one of SEL_REPLICAS copies.
 __global__ __launch_bounds__(SEL_BLOCK) void sel_values_kernel(const uint32_t *__restrict__ freq, int64_t num_rows,
                                                                unsigned long long *__restrict__ hist)
 {
@@ -194,6 +195,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void sel_values_kernel(const uint32_t *_
     constexpr int FLUSH = 65535 / (4 * UNROLL);   // trips until a 16-bit field may be full
     int64_t q = (int64_t)blockIdx.x * SEL_BLOCK + threadIdx.x;
     const int64_t trips = (quads + UNROLL * stride - 1) / (UNROLL * stride);   // the same for every thread
+    uint32_t large = 0u;
     for (int64_t t0 = 0; t0 < trips; t0 += FLUSH) {
         unsigned long long small = 0ull;
         const int64_t t1 = t0 + FLUSH < trips ? t0 + FLUSH : trips;
@@ -210,7 +212,8 @@ __global__ __launch_bounds__(SEL_BLOCK) void sel_values_kernel(const uint32_t *_
                     const uint32_t x = v[u][c];
                     if (c >= valid[u]) continue;
                     if (x < 4u) small += 1ull << (16 * x);
-                    else atomicAdd(&lds[x < SEL_EXACT ? x : SEL_EXACT], 1u);
+                    else if (x < SEL_EXACT) atomicAdd(&lds[x], 1u);
+                    else ++large;
                 }
         }
 #pragma unroll
@@ -221,6 +224,9 @@ __global__ __launch_bounds__(SEL_BLOCK) void sel_values_kernel(const uint32_t *_
             if (lane == 0 && c) atomicAdd(&lds[f], c);
         }
     }
+#pragma unroll
+    for (int d = EMB_WAVE >> 1; d >= 1; d >>= 1) large += __shfl_xor(large, d, EMB_WAVE);
+    if (lane == 0 && large) atomicAdd(&lds[SEL_EXACT], large);
     __syncthreads();
     unsigned long long *mine = hist + (size_t)(blockIdx.x % SEL_REPLICAS) * SEL_BINS;
     for (int i = threadIdx.x; i < SEL_BINS; i += SEL_BLOCK) {
@@ -278,6 +284,22 @@ __global__ __launch_bounds__(SEL_BLOCK) void sel_pick_kernel(const unsigned long
     }
 }
 
+// Adds one to the bin of every lane that has one.  Counters of like size share their upper digits, and an LDS add of
+// 64 lanes to one word is served lane by lane: where the wavefront has one bin, one lane adds for all (2.5e8 counters
+// of 3000: the three digits 3130 us with an add per lane, 780 so).
+__device__ __forceinline__ void sel_add(uint32_t *lds, bool counted, uint32_t bin)
+{
+    const unsigned long long lanes = __ballot(counted);
+    if (lanes == 0ull) return;
+    const int first = __ffsll(lanes) - 1;
+    const uint32_t bin0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
+    if (__ballot(counted && bin == bin0) == lanes) {
+        if ((int)(threadIdx.x & (EMB_WAVE - 1)) == first) atomicAdd(&lds[bin0], (uint32_t)__popcll(lanes));
+    } else if (counted) {
+        atomicAdd(&lds[bin], 1u);
+    }
+}
+
 // Where the threshold is not below SEL_EXACT: histogram of digit DIGIT (1, 2, 3 from the top) over the
 // counters not below SEL_EXACT whose digits above it are those of the threshold.  Every workgroup picks the
 // digit before from the finished histogram; the first one leaves it for the next launch.
@@ -310,18 +332,23 @@ __global__ __launch_bounds__(SEL_BLOCK) void sel_digit_kernel(const uint32_t *__
     }
     __syncthreads();
     const int64_t quads = (num_rows + 3) / 4;
-    for (int64_t q = (int64_t)blockIdx.x * SEL_BLOCK + threadIdx.x; q < quads; q += (int64_t)gridDim.x * SEL_BLOCK) {
-        uint32_t v[4];
-        int valid;
-        sel_load4(freq, q, num_rows, v, valid);
+    const int64_t stride = (int64_t)gridDim.x * SEL_BLOCK;
+    constexpr int UNROLL = 4;
+    for (int64_t q0 = (int64_t)blockIdx.x * SEL_BLOCK; q0 < quads; q0 += UNROLL * stride) {   // the same for every thread
+        uint32_t v[UNROLL][4];
+        int valid[UNROLL];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const uint32_t x = v[c];
-            if (x < SEL_EXACT) continue;   // counters past the array read as zero
-            if (DIGIT == 1) atomicAdd(&lds[x >> SEL_SHIFT1], 1u);
-            if (DIGIT == 2 && (x >> SEL_SHIFT1) == prefix) atomicAdd(&lds[(x >> SEL_SHIFT2) & (SEL_BINS - 1)], 1u);
-            if (DIGIT == 3 && (x >> SEL_SHIFT2) == prefix) atomicAdd(&lds[x & ((1u << SEL_SHIFT2) - 1)], 1u);
-        }
+        for (int u = 0; u < UNROLL; ++u) sel_load4(freq, q0 + threadIdx.x + u * stride, num_rows, v[u], valid[u]);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t x = v[u][c];   // counters past the array read as zero
+                const bool large = x >= SEL_EXACT;
+                if (DIGIT == 1) sel_add(lds, large, x >> SEL_SHIFT1);
+                if (DIGIT == 2) sel_add(lds, large && (x >> SEL_SHIFT1) == prefix, (x >> SEL_SHIFT2) & (SEL_BINS - 1));
+                if (DIGIT == 3) sel_add(lds, large && (x >> SEL_SHIFT2) == prefix, x & ((1u << SEL_SHIFT2) - 1));
+            }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < SEL_BINS; i += SEL_BLOCK) {

@@ -1675,6 +1675,29 @@ def test_cache_select_is_the_exact_top_k(R):
             _select_case(freq, num_hot, shift)
 
 
+@pytest.mark.parametrize("low,high", [(3000, 3001), (1 << 30, (1 << 30) + 2)])
+def test_cache_select_of_large_counters_of_like_size_takes_no_longer_than_its_passes(low, high):
+    # counters of 2047 and more take three passes beyond the three of small ones.  Added up one by one, the digits that
+    # most of them share make it six times the time of small counters; the bound lies between that and two
+    R = 100_000_000
+    ws = torch.empty(emb.emb_cache_select_workspace_bytes(R), dtype=torch.uint8, device=H.DEV)
+    hot = torch.empty(R // 20, dtype=torch.int64, device=H.DEV)
+    best = []
+    for freq in (torch.zeros(R, dtype=torch.int32, device=H.DEV),
+                 torch.randint(low, high, (R,), dtype=torch.int32, device=H.DEV)):
+        times = []
+        for _ in range(8):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            emb.emb_cache_select(freq, R // 20, 0, ws, hot)
+            ev[1].record()
+            torch.cuda.synchronize()
+            times.append(ev[0].elapsed_time(ev[1]))
+        best.append(min(times))
+    assert best[1] < 4 * best[0], best
+    assert torch.equal(hot, torch.nonzero(freq == high - 1).flatten()[:R // 20])
+
+
 def test_cache_select_rejects_bad_arguments():
     R = 1000
     fd = torch.zeros(R, dtype=torch.int32, device=H.DEV)
