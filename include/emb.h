@@ -683,7 +683,8 @@ int emb_cache_rebuild(const void *table_dev, int64_t num_rows, int32_t D, int32_
 /* A whole refresh in one call: emb_cache_select, then emb_cache_rebuild with the
  * rows it chose.  Same arguments, results and errors as the two calls; the pass
  * that writes the chosen rows writes the new cache's index and copies its rows as
- * well. */
+ * well (a launch of its own copies those of parts of the table where very many
+ * neighbouring rows were chosen). */
 int emb_cache_refresh(uint32_t *freq_dev, int64_t num_rows, int64_t num_hot, int32_t decay_shift,
                       void *workspace_dev, size_t workspace_bytes, const void *table_dev, int32_t D,
                       int32_t dtype, const void *old_cache_rows_dev, const void *old_cache_index_dev,

@@ -505,11 +505,13 @@ int launch_update(const BwdArgs &a, const BwdLayout &L, const KeyT *keys, const 
     EMB_MARK(a, 4);
 
     const int64_t pthreads = L.qslots > L.slots ? L.qslots : L.slots;
-    // Beside update_kernel a workgroup of sixteen wavefronts waits for a whole free CU.  In a small step that wait is
-    // the step's own length (3 tables x 512 bags of 20: 110 us, with four wavefronts 91).  In a large one it keeps
-    // long_reduce_kernel away from the update until the update drains: 2.6e6 lookups, reduce 35 us and update 219,
-    // with four wavefronts 134 and 239 (traces of two cards; the step 413 and 415 us on one), because both then run
-    // at once for the reduce's whole length.
+    // Beside update_kernel a workgroup of sixteen wavefronts waits for a whole free CU, one of four starts at once.  In a
+    // large step the wait is worth having: it keeps long_reduce_kernel away from the update until the update drains
+    // (2.6e6 lookups: reduce 35 us and update 219, with four wavefronts 134 and 239 because both then run at once for
+    // the reduce's whole length, traces of two cards).  Up to some 1.3e6 lookups the two are within 1 % of each other,
+    // four wavefronts ahead from 9e5 on.  Steps in us, four / sixteen wavefronts, in turn on one card: 30 720 lookups
+    // 100.3 / 101.0 (spread 5 %), 148 687 bf16 120.3 / 120.4, 655 360 158.1 / 157.2, 983 040 196.6 / 197.2, 1.15e6
+    // 220.9 / 221.6, 1.31e6 234.3 / 236.2, 1.97e6 313.1 / 307.4, 2.62e6 403.4 / 394.9.
 #define EMB_PREPARE(BLOCK)                                                                                              \
     hipLaunchKernelGGL(long_prepare_kernel<BLOCK>, dim3((unsigned)((pthreads + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, ls, n, \
                        ctrl, queue, queue_end, (uint32_t)L.qslots, span_head, wave_heads, (uint32_t)L.slots, segs,     \

@@ -16,8 +16,9 @@
 // Then a pass counts the selected rows per tile, a scan places the tiles, and a
 // last pass writes the rows in ascending order, the order the cache index needs,
 // and ages the counters.  A refresh (emb_cache_refresh) lets that last pass write
-// the index and fetch the rows of the new cache as well.  Everything is integer
-// work: results are exact.
+// the index and fetch the rows of the new cache as well, all but those of tiles
+// with very many chosen rows (sel_wide_copy_kernel).  Everything is integer work:
+// results are exact.
 //
 // What bounds it: 80 MB of counters (2e7 rows) are read three times (16 us each
 // at the rate of a large copy; the second and third time from the memory-side

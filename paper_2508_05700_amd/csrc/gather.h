@@ -193,10 +193,13 @@ __device__ __forceinline__ void emb_two_level_bounds(const int64_t *__restrict__
 
 // Bounds of the workgroup's bags straight from the bag lengths, for batches of up to EMB_LENGTHS_DIRECT_BAGS
 // bags: every workgroup adds up the lengths before its first bag itself (at most 16 KB, from the L2), which
-// saves the launch that would make sums within tiles.  A launch that has to wait for the one before it costs
-// 4.5 us in a full queue and 2 us of host time; reading 4096 lengths costs a workgroup about 1 us, and the
-// total grows with the square of the number of bags.  first: the workgroup's first bag; bags: how many it has
-// (at most BLOCK / LPR); g: the calling thread's.  Every thread of the workgroup calls this.
+// saves the launch that would make sums within tiles (about 3 us of a call in a full queue).  The reads grow with
+// the square of the number of bags, and with the row width (up to 4 bags a workgroup).  Calls in us, lengths here /
+// sums within tiles, one fixed-length table of fp32 rows, bags of 1: 4096 bags 7.5 / 9.4 (D = 16), 7.6 / 10.6 (64),
+// 7.4 / 10.6 (256), 9.8 / 13.1 (1024); 8192 bags 7.4 / 9.5, 7.7 / 10.6, 10.1 / 11.1, 16.6 / 19.2; 16 384 bags 7.5 / 9.4,
+// 8.7 / 10.5, 22.6 / 14.8, 33.4 / 28.0.  The line is the last size at which the widest rows lose nothing of the gain.
+// first: the workgroup's first bag; bags: how many it has (at most BLOCK / LPR); g: the calling thread's.  Every thread
+// of the workgroup calls this.
 constexpr int64_t EMB_LENGTHS_DIRECT_BAGS = 4096;
 template <int BLOCK, int GROUPS>
 __device__ __forceinline__ void emb_bounds_from_lengths(const int32_t *__restrict__ lengths, int64_t first, int bags, int g,
