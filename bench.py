@@ -46,13 +46,13 @@ PMC_TRAFFIC = {
     "kib_per_launch": {     # workload -> kernel -> (FETCH_SIZE, WRITE_SIZE)
         "3": {"bag_forward_train_kernel": (177568.9, 68960.1), "update_kernel": (240525.8, 324005.4)},
         "3b": {"bag_forward_train_kernel": (94766.7, 83182.2), "update_kernel": (169998.0, 220262.5)},
-        "2": {"bag_forward_hashed_kernel": (176278.2, 33800.9), "bag_forward_kernel": (177913.7, 32768.0)},
-        "2u": {"bag_forward_hashed_kernel": (338181.9, 33793.6), "bag_forward_kernel": (338144.8, 32768.0)},
+        "2": {"bag_forward_kernel<HASHED>": (176278.2, 33800.9), "bag_forward_kernel": (177913.7, 32768.0)},
+        "2u": {"bag_forward_kernel<HASHED>": (338181.9, 33793.6), "bag_forward_kernel": (338144.8, 32768.0)},
         "2un": {"bag_forward_kernel": (346124.6, 32768.0)},
         "2q4": {"bag_forward_quant_kernel": (122247.6, 33832.7)},
         "2uq4": {"bag_forward_quant_kernel": (232535.4, 33926.1)},
         "2uq4r": {"bag_forward_quant_kernel": (190417.8, 33872.1)},
-        "4": {"bag_forward_hashed_kernel": (52665.0, 8704.2)},
+        "4": {"bag_forward_kernel<HASHED>": (52665.0, 8704.2)},
     },
 }
 
@@ -636,20 +636,15 @@ def cache_policy_study(args, w, seed, ptr, store, n_hot, static_hot, dbs, offset
         torch.cuda.synchronize()
 
     def refresh():
-        ev = [emb.Event(timing=True) for _ in range(3)]
+        ev = [emb.Event(timing=True) for _ in range(2)]
         cache.moved.zero_()
         ev[0].record()
-        emb.emb_cache_select(cache.freq, cache.capacity, cache.decay_shift, cache.workspace, cache.hot, cache.info)
+        cache.refresh()
         ev[1].record()
-        new = 1 - cache.active
-        emb.emb_cache_rebuild(ptr, w.R, w.D, store, cache.rows[cache.active], cache.index[cache.active], cache.num_hot,
-                              cache.hot[:cache.capacity], cache.rows[new], cache.index[new], cache.moved, status)
-        ev[2].record()
-        cache.active, cache.num_hot = new, cache.capacity
         torch.cuda.synchronize()
         kept, fetched = [int(x) for x in cache.moved.cpu().tolist()]
         thr, tied = [int(x) for x in cache.info.cpu().tolist()]
-        return {"select_ms": round(ev[0].elapsed_time(ev[1]), 3), "rebuild_ms": round(ev[1].elapsed_time(ev[2]), 3),
+        return {"refresh_ms": round(ev[0].elapsed_time(ev[1]), 3),
                 "rows_kept_in_hbm": kept, "rows_fetched_from_table": fetched, "threshold_count": thr,
                 "rows_at_threshold": tied}
 
@@ -698,9 +693,9 @@ def cache_policy_study(args, w, seed, ptr, store, n_hot, static_hot, dbs, offset
         st.update(refresh())
         st["hit_rate"], st["ms_per_step"] = measure(dbs, fwd_dynamic)
         result["stages"].append(st)
-        log("cache policy: %.0e lookups watched (%.0f s): %.2f %% hits, step %.3f ms; refresh = select %.2f ms + "
-            "rebuild %.2f ms (%d rows kept in HBM, %d fetched)" % (
-                watched, time.time() - t0, 100 * st["hit_rate"], st["ms_per_step"], st["select_ms"], st["rebuild_ms"],
+        log("cache policy: %.0e lookups watched (%.0f s): %.2f %% hits, step %.3f ms; refresh %.2f ms "
+            "(%d rows kept in HBM, %d fetched)" % (
+                watched, time.time() - t0, 100 * st["hit_rate"], st["ms_per_step"], st["refresh_ms"],
                 st["rows_kept_in_hbm"], st["rows_fetched_from_table"]))
     # popularity moves: the same law over other IDs (another seed gives another rank -> ID map)
     seed2 = seed + 1
@@ -1079,7 +1074,8 @@ def main() -> int:
         return e
 
     if fused:
-        fwd_name, fwd_pmc = "bag_forward_hashed_kernel (hash + gather-pool)", "bag_forward_hashed_kernel"
+        # counters are kept apart by the template's form: raw IDs hashed in the kernel, or row numbers
+        fwd_name, fwd_pmc = "bag_forward_kernel<HASHED> (hash + gather-pool)", "bag_forward_kernel<HASHED>"
         if w.quant:
             fwd_name = "bag_forward_quant_kernel (hash + gather-dequantise-pool, %s rows of %d B)" % (w.quant, rowb)
             fwd_pmc = "bag_forward_quant_kernel"
