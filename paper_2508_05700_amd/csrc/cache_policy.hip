@@ -43,7 +43,8 @@ constexpr uint32_t SEL_EXACT = SEL_BINS - 1;               // values below have 
 constexpr int SEL_REPLICAS = 8;                            // of the first histogram: fewer adds per word
 constexpr int SEL_HIST_BLOCKS = 256;                       // one workgroup per CU: 64 KB of loads in flight each
 constexpr int SEL_GROUPS = 64;                             // words that collect the kept rows of a refresh
-constexpr uint32_t SEL_TILE_CHUNKS = 4 * SEL_TILE;         // chunks that a tile's workgroup copies itself (sel_wide_copy_kernel)
+constexpr int64_t SEL_TILE_CHUNKS = 4 * SEL_TILE;          // chunks that a tile's workgroup copies itself, or, where that is
+constexpr int64_t SEL_TILE_SHARE = 256;                    // more, this part of all chunks (sel_wide_copy_kernel)
 constexpr int SEL_WIDE_GRID = 256;                         // with two loads a lane 2 MB in flight
 constexpr int SEL_WIDE_UNROLL = 2;
 constexpr int SEL_WIDE_CHUNKS = 512;                       // a wavefront's share of rows: at most so many chunks, or one row
@@ -474,6 +475,7 @@ struct RefreshArgs {
     uint32_t chunk_magic;         // floor(2^32 / chunks) + 1: i / chunks for i < SEL_TILE * 1024 (0: one chunk)
     unsigned long long *moved;    // nullable
     unsigned long long *groups;   // [SEL_GROUPS], zero
+    uint32_t tile_chunks;         // a tile with more chunks than this leaves them to sel_wide_copy_kernel
     uint32_t *wide;               // SelCtrl::wide
 };
 
@@ -579,7 +581,7 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_write_kernel(uint32_t *freq, int
     // ---- rows: consecutive lanes copy consecutive chunks of the tile's part of the cache
     const uint32_t chunks = (uint32_t)f.chunks;
     uint32_t items = selected * chunks;
-    if (items > SEL_TILE_CHUNKS) {   // uniform; sel_wide_copy_kernel tells such tiles by the same test
+    if (items > f.tile_chunks) {   // uniform; sel_wide_copy_kernel tells such tiles by the same test
         items = 0u;
         if (threadIdx.x == 0) *f.wide = 1u;
     }
@@ -628,12 +630,15 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_write_kernel(uint32_t *freq, int
     }
 }
 
-// The rows of the tiles that hold more than SEL_TILE_CHUNKS chunks of the new cache.  Left to the tile's one
-// workgroup they are a serial chain of 1.5 us per 1024 chunks while the rest of the chip is idle: of 10 000 rows of
-// 4096 bytes side by side a refresh took 1590 us with all of them in the old cache and 2455 with none.  Copied from
-// the finished list, which is what this kernel does, it takes 65 and 771.  Tiles up to the line are the faster for
-// being copied in the pass (75 000 of 1.5e6 rows of 512 bytes, 6550 chunks a tile: 54 us, emb_cache_rebuild's copy
-// 68); at 32 768 chunks a tile the two are even (95 us in the pass, 89 here).
+// The rows of the tiles that hold more than tile_chunks chunks of the new cache.  Left to the tile's one workgroup they
+// are a serial chain of 1.5 us per 1024 chunks while the rest of the chip is idle: of 10 000 rows of 4096 bytes side by
+// side a refresh took 1590 us with all of them in the old cache and 2455 with none.  Copied from the finished list,
+// which is what this kernel does, it takes 61 and 776.  Tiles up to the line are the faster for being copied in the
+// pass: 75 000 of 1.5e6 rows of 512 bytes, 6550 chunks a tile, 54 us, emb_cache_rebuild's copy 68; at 32 768 chunks a
+// tile the two are even (95 us in the pass, 89 here).  And where no tile holds more than one part in SEL_TILE_SHARE of
+// the cache, the chain of the fullest is no longer than the whole chip needs for all of it, and copying in the pass
+// lets rows from the old cache pass beside those from the link: 1.25e7 rows of 256 bytes, 1.1e7 of them kept and most
+// side by side, 7.8 ms in the pass, 9.1 with this kernel for every tile of more than 16 384 chunks.
 // A wavefront takes a share of consecutive rows of the list: a lane each finds where a row comes from, then all
 // lanes copy the share's chunks.  unit: rows of a share (at most EMB_WAVE).  2 MB in flight are what the two places
 // that rows come from agree on: 4096-byte rows, 2, 4 and 8 MB: 771, 792 and 819 us over the link, 65, 57 and 56 from
@@ -656,7 +661,7 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_wide_copy_kernel(const SelCtrl *
             if (row >= 0 && row < num_rows) {   // always true, as in sel_write_kernel
                 const int64_t tile = row / SEL_TILE;
                 const uint64_t end = tile + 1 < tiles ? base[tile + 1] : (uint64_t)num_hot;
-                if ((end - base[tile]) * chunks > SEL_TILE_CHUNKS) {
+                if ((end - base[tile]) * chunks > f.tile_chunks) {
                     const int64_t slot = cache_probe(f.old_index, (uint64_t)row, (uint64_t)f.old_num_hot);
                     src = reinterpret_cast<uint64_t>(slot >= 0 ? f.old_rows + slot * (int64_t)chunks * 16
                                                                : f.table + row * (int64_t)chunks * 16);
@@ -791,7 +796,7 @@ int select_run(uint32_t *freq_dev, int64_t num_rows, int64_t num_hot, int32_t de
         hipLaunchKernelGGL(sel_write_kernel<true>, dim3((unsigned)L.tiles), dim3(CP_BLOCK), 0, s, freq_dev, num_rows, ctrl,
                            base, ties, num_hot, (int)decay_shift, hot_rows_out_dev, f);
         // only where the rows chosen from one tile can be so many
-        if ((num_hot < SEL_TILE ? num_hot : SEL_TILE) * f.chunks > (int64_t)SEL_TILE_CHUNKS) {
+        if ((num_hot < SEL_TILE ? num_hot : SEL_TILE) * f.chunks > (int64_t)f.tile_chunks) {
             EMB_RETURN_IF_LAUNCH_FAILED();
             int unit = SEL_WIDE_CHUNKS / f.chunks;
             unit = unit < 1 ? 1 : (unit > EMB_WAVE ? EMB_WAVE : unit);
@@ -859,6 +864,9 @@ extern "C" int emb_cache_refresh(uint32_t *freq_dev, int64_t num_rows, int64_t n
     f.chunks = (int32_t)(row_bytes / 16);   // rows of every storage type are whole 16-byte chunks
     f.chunk_magic = f.chunks == 1 ? 0u : (uint32_t)((UINT64_C(1) << 32) / (uint32_t)f.chunks) + 1u;
     f.moved = reinterpret_cast<unsigned long long *>(moved_dev);
+    const int64_t share = num_hot * f.chunks / SEL_TILE_SHARE;
+    const int64_t limit = share < SEL_TILE_CHUNKS ? SEL_TILE_CHUNKS : share;
+    f.tile_chunks = (uint32_t)(limit < 0xFFFFFFFFll ? limit : 0xFFFFFFFFll);   // (no tile holds 2^32)
     f.groups = nullptr;   // these two: select_run
     f.wide = nullptr;
     rc = select_run(freq_dev, num_rows, num_hot, decay_shift, L, static_cast<char *>(workspace_dev), hot_rows_out_dev,

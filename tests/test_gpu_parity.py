@@ -1846,10 +1846,12 @@ def test_cache_refresh_counts_as_kept_the_rows_it_copies_from_the_old_cache(old_
     assert moved.cpu().tolist() == [int(kept.sum()), int((~kept).sum())] and status.item() == 0
 
 
-# rows chosen from each tile of 4096 rows: a tile of more than 16384 chunks of 16 bytes leaves its copy to another kernel
+# rows chosen from each tile of 4096 rows: a tile of more than 16384 chunks of 16 bytes, and more than one in 256 of all
+# chunks (17 408 in the last case), leaves its copy to another kernel
 @pytest.mark.parametrize("D,dtype,per_tile,last", [
     (32, "bf16", [4096, 0, 4000], 4001), (64, "f32", [1024, 5, 1025, 4096, 3996], 3996), (128, "int4", [3276, 3277, 77], 90),
-    (1024, "f32", [64, 65, 300, 1], 1), (4096, "f32", [17, 16], 4096)])
+    (1024, "f32", [64, 65, 300, 1], 1), (4096, "f32", [17, 16], 4096),
+    (4096, "f32", [4096, 17, 18, 221], 4096)])
 def test_cache_refresh_of_tiles_with_many_chosen_rows(D, dtype, per_tile, last):
     rng = np.random.default_rng(D + len(per_tile))
     R = 4096 * (len(per_tile) - 1) + last
