@@ -34,25 +34,25 @@ def log(*a):
 # dispatch, averaged over the dispatches of a run of this script), for the kernel sources whose digest
 # is recorded with them: once a source file under csrc/ changes, `traffic` is reported as null until
 # the counters are taken again.  The scale factors come from kernels of known traffic in the same
-# runs: the 512 MiB device copy of --pmc-calibration reads 524288 KiB and FETCH_SIZE shows 262172
+# runs: the 512 MiB device copy of --pmc-calibration reads 524288 KiB and FETCH_SIZE shows 262166
 # (factor 2.0: the counter prices this part's 128-byte read requests as 64 bytes); the copy's and the
 # table fill's writes (524288 and 2500000 KiB) are counted exactly (factor 1.0).  Read requests of 64
 # bytes or less are counted at their true size, so for kernels that issue those (4-byte accumulators,
 # 48-byte quantised rows) the scaled figure is an upper bound.
 PMC_TRAFFIC = {
-    "sources": "b73ec1126545090a",
+    "sources": "375ae14ba9031948",
     "fetch_scale": 2.0,
     "write_scale": 1.0,
     "kib_per_launch": {     # workload -> kernel -> (FETCH_SIZE, WRITE_SIZE)
-        "3": {"bag_forward_train_kernel": (177568.9, 68960.1), "update_kernel": (240525.8, 324005.4)},
-        "3b": {"bag_forward_train_kernel": (94766.7, 83182.2), "update_kernel": (169998.0, 220262.5)},
-        "2": {"bag_forward_kernel<HASHED>": (176278.2, 33800.9), "bag_forward_kernel": (177913.7, 32768.0)},
-        "2u": {"bag_forward_kernel<HASHED>": (338181.9, 33793.6), "bag_forward_kernel": (338144.8, 32768.0)},
-        "2un": {"bag_forward_kernel": (346124.6, 32768.0)},
-        "2q4": {"bag_forward_quant_kernel": (122247.6, 33832.7)},
-        "2uq4": {"bag_forward_quant_kernel": (232535.4, 33926.1)},
-        "2uq4r": {"bag_forward_quant_kernel": (190417.8, 33872.1)},
-        "4": {"bag_forward_kernel<HASHED>": (52665.0, 8704.2)},
+        "3": {"bag_forward_train_kernel": (173366.8, 69652.5), "update_kernel": (240501.5, 324005.7)},
+        "3b": {"bag_forward_train_kernel": (90648.0, 73751.6), "update_kernel": (170014.5, 220230.0)},
+        "2": {"bag_forward_kernel<HASHED>": (172049.2, 33886.4), "bag_forward_kernel": (172211.5, 32768.0)},
+        "2u": {"bag_forward_kernel<HASHED>": (338210.1, 33800.3), "bag_forward_kernel": (338158.8, 32768.0)},
+        "2un": {"bag_forward_kernel": (339660.0, 32768.0)},
+        "2q4": {"bag_forward_quant_kernel": (112740.8, 33824.5)},
+        "2uq4": {"bag_forward_quant_kernel": (225084.2, 33896.1)},
+        "2uq4r": {"bag_forward_quant_kernel": (182139.6, 33859.2)},
+        "4": {"bag_forward_kernel<HASHED>": (52441.7, 8704.3)},
     },
 }
 
