@@ -634,7 +634,7 @@ __global__ __launch_bounds__(CP_BLOCK) void sel_write_kernel(uint32_t *freq, int
 // are a serial chain of 1.5 us per 1024 chunks while the rest of the chip is idle: of 10 000 rows of 4096 bytes side by
 // side a refresh took 1590 us with all of them in the old cache and 2455 with none.  Copied from the finished list,
 // which is what this kernel does, it takes 61 and 776.  Tiles up to the line are the faster for being copied in the
-// pass: 75 000 of 1.5e6 rows of 512 bytes, 6550 chunks a tile, 54 us, emb_cache_rebuild's copy 68; at 32 768 chunks a
+// pass: 75 000 of 1.5e6 rows of 512 bytes, 6550 chunks a tile, 54 us, emb_cache_rebuild's copy 62; at 32 768 chunks a
 // tile the two are even (95 us in the pass, 89 here).  And where no tile holds more than one part in SEL_TILE_SHARE of
 // the cache, the chain of the fullest is no longer than the whole chip needs for all of it, and copying in the pass
 // lets rows from the old cache pass beside those from the link: 1.25e7 rows of 256 bytes, 1.1e7 of them kept and most

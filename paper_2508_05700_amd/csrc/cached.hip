@@ -66,14 +66,16 @@ __global__ __launch_bounds__(CB_BLOCK) void cache_mark_kernel(const int64_t *__r
     if (prev < 0 || (prev >> 6) != entry) e->before = (uint32_t)k;
 }
 
-// One thread per 16-byte chunk copies the hot rows into the cache, COPY_UNROLL
-// chunks at a time.  With an older cache at hand (a refresh), a row that it holds
-// is taken from there, in HBM, and only newly admitted rows are read from the
-// table.  moved (nullable): [0] += rows taken from the older cache, [1] += rows
-// read from the table, summed over the workgroup first: adds to one word are
-// served one at a time, about 24 ns each, so a launch has COPY_GRID workgroups.
-constexpr int COPY_BLOCK = 512;
-constexpr int COPY_UNROLL = 4;
+// One thread per 16-byte chunk copies the hot rows into the cache.  With an older
+// cache at hand (a refresh), a row that it holds is taken from there, in HBM, and
+// only newly admitted rows are read from the table.  moved (nullable): [0] += rows
+// taken from the older cache, [1] += rows read from the table, summed over the
+// workgroup first: adds to one word are served one at a time, about 24 ns each, so
+// a launch has COPY_GRID workgroups.  They fill the chip with one chunk a lane in
+// flight, 8 MB: the link is slower with more (50 000 rows of 256 bytes, alone 257 us,
+// with four chunks a lane on half the lanes, 16 MB, 270; 5000 of 4096: 399 and 415),
+// and rows of the old cache are no slower (50 000 of 4096 bytes 85 and 102 us).
+constexpr int COPY_BLOCK = 1024;
 constexpr int COPY_GRID = 512;
 __global__ __launch_bounds__(COPY_BLOCK) void cache_copy_kernel(const char *__restrict__ table,
                                                                 const char *__restrict__ old_rows,
@@ -85,41 +87,19 @@ __global__ __launch_bounds__(COPY_BLOCK) void cache_copy_kernel(const char *__re
     const int64_t total = num_hot * chunks_per_row;
     const int64_t stride = (int64_t)gridDim.x * COPY_BLOCK;
     uint32_t kept = 0u, fetched = 0u;
-    for (int64_t i0 = (int64_t)blockIdx.x * COPY_BLOCK + threadIdx.x; i0 < total; i0 += stride * COPY_UNROLL) {
-        int64_t row[COPY_UNROLL], chunk[COPY_UNROLL];
-        uint4 entry[COPY_UNROLL], v[COPY_UNROLL];
-#pragma unroll
-        for (int u = 0; u < COPY_UNROLL; ++u) {
-            const int64_t i = i0 + u * stride;
-            row[u] = -1;
-            chunk[u] = 0;
-            if (i < total) {
-                // (below 2^32 the quotient takes a 32-bit division)
-                const int64_t k = total <= 0xFFFFFFFFll ? (int64_t)((uint32_t)i / (uint32_t)chunks_per_row) : i / chunks_per_row;
-                chunk[u] = i - k * chunks_per_row;
-                row[u] = hot[k];
-                if (row[u] < 0 || row[u] >= num_rows) row[u] = -1;
-            }
+    for (int64_t i = (int64_t)blockIdx.x * COPY_BLOCK + threadIdx.x; i < total; i += stride) {
+        // (below 2^32 the quotient takes a 32-bit division)
+        const int64_t k = total <= 0xFFFFFFFFll ? (int64_t)((uint32_t)i / (uint32_t)chunks_per_row) : i / chunks_per_row;
+        const int64_t chunk = i - k * chunks_per_row;
+        const int64_t row = hot[k];
+        if (row < 0 || row >= num_rows) continue;
+        const int64_t slot = old_index ? cache_probe(old_index, (uint64_t)row, (uint64_t)old_num_hot) : -1;
+        const char *src = slot >= 0 ? old_rows + slot * chunks_per_row * 16 : table + row * chunks_per_row * 16;
+        *reinterpret_cast<uint4 *>(cache_rows + i * 16) = load_chunk(src + chunk * 16);
+        if (chunk == 0) {
+            kept += slot >= 0 ? 1u : 0u;
+            fetched += slot >= 0 ? 0u : 1u;
         }
-#pragma unroll
-        for (int u = 0; u < COPY_UNROLL; ++u) {
-            entry[u] = make_uint4(0u, 0u, 0u, 0u);
-            if (old_index && row[u] >= 0) entry[u] = load_chunk(reinterpret_cast<const char *>(old_index + (row[u] >> 6)));
-        }
-#pragma unroll
-        for (int u = 0; u < COPY_UNROLL; ++u) {
-            if (row[u] < 0) continue;
-            const int64_t slot = cache_slot(entry[u], (int)(row[u] & 63), (uint64_t)old_num_hot);
-            const char *src = slot >= 0 ? old_rows + slot * chunks_per_row * 16 : table + row[u] * chunks_per_row * 16;
-            v[u] = load_chunk(src + chunk[u] * 16);
-            if (chunk[u] == 0) {
-                kept += slot >= 0 ? 1u : 0u;
-                fetched += slot >= 0 ? 0u : 1u;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < COPY_UNROLL; ++u)
-            if (row[u] >= 0) *reinterpret_cast<uint4 *>(cache_rows + (i0 + u * stride) * 16) = v[u];
     }
     cache_add_hit_miss(kept, fetched, moved);
 }
