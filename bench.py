@@ -40,19 +40,19 @@ def log(*a):
 # bytes or less are counted at their true size, so for kernels that issue those (4-byte accumulators,
 # 48-byte quantised rows) the scaled figure is an upper bound.
 PMC_TRAFFIC = {
-    "sources": "375ae14ba9031948",
+    "sources": "b8cac524dc38a0fd",
     "fetch_scale": 2.0,
     "write_scale": 1.0,
     "kib_per_launch": {     # workload -> kernel -> (FETCH_SIZE, WRITE_SIZE)
-        "3": {"bag_forward_train_kernel": (173366.8, 69652.5), "update_kernel": (240501.5, 324005.7)},
-        "3b": {"bag_forward_train_kernel": (90648.0, 73751.6), "update_kernel": (170014.5, 220230.0)},
-        "2": {"bag_forward_kernel<HASHED>": (172049.2, 33886.4), "bag_forward_kernel": (172211.5, 32768.0)},
-        "2u": {"bag_forward_kernel<HASHED>": (338210.1, 33800.3), "bag_forward_kernel": (338158.8, 32768.0)},
-        "2un": {"bag_forward_kernel": (339660.0, 32768.0)},
-        "2q4": {"bag_forward_quant_kernel": (112740.8, 33824.5)},
-        "2uq4": {"bag_forward_quant_kernel": (225084.2, 33896.1)},
-        "2uq4r": {"bag_forward_quant_kernel": (182139.6, 33859.2)},
-        "4": {"bag_forward_kernel<HASHED>": (52441.7, 8704.3)},
+        "3": {"bag_forward_train_kernel": (173359.5, 69728.3), "update_kernel": (240548.3, 324004.8)},
+        "3b": {"bag_forward_train_kernel": (90614.2, 73776.4), "update_kernel": (169951.8, 220247.8)},
+        "2": {"bag_forward_kernel<HASHED>": (172061.2, 33884.1), "bag_forward_kernel": (172172.9, 32768.0)},
+        "2u": {"bag_forward_kernel<HASHED>": (338208.6, 33805.0), "bag_forward_kernel": (338159.4, 32768.0)},
+        "2un": {"bag_forward_kernel": (339591.9, 32768.0)},
+        "2q4": {"bag_forward_quant_kernel": (112761.6, 33824.0)},
+        "2uq4": {"bag_forward_quant_kernel": (225121.7, 33896.7)},
+        "2uq4r": {"bag_forward_quant_kernel": (182149.3, 33861.7)},
+        "4": {"bag_forward_kernel<HASHED>": (52444.9, 8704.2)},
     },
 }
 
