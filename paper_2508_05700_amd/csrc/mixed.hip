@@ -8,12 +8,20 @@
 // A workgroup serves bags of one table; emb_table_shapes_init numbers the
 // workgroups (first_block) so that a table whose rows need fewer lanes gets
 // fewer of them.  The gather loop is gather_pool_bag (gather.h).
+//
+// Every die works on one stretch of those numbers (its L2 then holds few tables' hot rows), and the stretches
+// are cut so that the dies have the same amount of work (DieShares).
 #include "emb_internal.h"
 #include "gather.h"
 
 namespace {
 
 constexpr int MX_BLOCK = 256;
+
+// Die d serves workgroups first[d] .. first[d + 1] - 1 of the numbering.
+struct DieShares {
+    uint32_t first[EMB_XCDS + 1];
+};
 
 struct PlainSource {
     const char *weights;
@@ -47,13 +55,15 @@ __device__ __forceinline__ void mixed_bags(const emb_table &tb, const emb_table_
 
 __global__ __launch_bounds__(MX_BLOCK) void bag_forward_mixed_kernel(const emb_table *__restrict__ tables,
                                                                      const emb_table_shape *__restrict__ shapes,
-                                                                     int32_t T, uint32_t total_blocks, int64_t B,
+                                                                     int32_t T, DieShares dies, int64_t B,
                                                                      int64_t nnz, const int64_t *__restrict__ rows,
                                                                      const int64_t *__restrict__ offsets, int32_t mode,
                                                                      float *__restrict__ out, uint32_t *status)
 {
-    const uint32_t lb = emb_xcd_block(blockIdx.x, gridDim.x);
-    if (lb >= total_blocks) return;          // the grid is rounded up to whole dies
+    // workgroups are dealt to the dies round-robin by number (emb_xcd_block)
+    const uint32_t die = blockIdx.x % EMB_XCDS;
+    const uint32_t lb = dies.first[die] + blockIdx.x / EMB_XCDS;
+    if (lb >= dies.first[die + 1]) return;   // the grid has room for the die with the most workgroups
     // the table with first_block[t] <= lb < first_block[t + 1] (uniform over the workgroup)
     int lo = 0, hi = T;
     while (hi - lo > 1) {
@@ -91,6 +101,47 @@ int mixed_lanes(int32_t D, int32_t dtype, int *lanes)
     while (l * 16 < bytes) l <<= 1;
     *lanes = l;
     return EMB_OK;
+}
+
+// A lookup costs its row's bytes and as much again as MX_ROW_COST 16-byte chunks for its index, address and request,
+// whatever the width: a die serves some 10e9 rows of 64 bytes a second and 4e9 of 256.  Six tables each of 64-byte fp32
+// and bf16 rows, eight of 256 and four of 512 bytes, 3.9e6 lookups, offsets, hashing and lookup together: equal numbers of
+// workgroups (which is a cost of 0: equal bytes) 189 us, 2 162, 4 148, 8 138, 16 147, 64 (equal lookups) 169; nine
+// tables of 32, 128 and 512 bytes, 1.4e6 lookups: 70, 53, 46, 46, 44, 50.
+constexpr int MX_ROW_COST = 8;
+inline uint64_t mixed_block_cost(const emb_table_shape &sh)
+{
+    return (uint64_t)(MX_BLOCK / sh.lanes) * (uint64_t)(sh.D * emb_elem_size(sh.dtype) / 16 + MX_ROW_COST);
+}
+
+inline uint64_t mixed_blocks(const emb_table_shape *shapes, int32_t T, int32_t t, uint32_t total_blocks)
+{
+    return (t + 1 < T ? shapes[t + 1].first_block : total_blocks) - shapes[t].first_block;
+}
+
+// Cuts the numbered workgroups into EMB_XCDS stretches of equal cost.  Returns the largest number of workgroups in one.
+uint32_t mixed_die_shares(const emb_table_shape *shapes, int32_t T, int64_t B, uint32_t total_blocks, DieShares &dies)
+{
+    uint64_t total = 0;
+    for (int32_t t = 0; t < T; ++t) {
+        total += mixed_blocks(shapes, T, t, total_blocks) * mixed_block_cost(shapes[t]);
+    }
+    uint64_t before = 0;   // cost of the tables before t
+    uint32_t d = 1, most = 0;
+    dies.first[0] = 0;
+    for (int32_t t = 0; t < T; ++t) {
+        const uint64_t blocks = mixed_blocks(shapes, T, t, total_blocks), per = mixed_block_cost(shapes[t]);
+        // the cuts that fall into this table: the first workgroup that starts at or after d eighths of the cost
+        for (; d < EMB_XCDS && total * d <= (before + blocks * per) * EMB_XCDS; ++d) {
+            const uint64_t at = (total * d + EMB_XCDS - 1) / EMB_XCDS;
+            dies.first[d] = shapes[t].first_block + (uint32_t)((at > before ? at - before : 0) + per - 1) / per;
+        }
+        before += blocks * per;
+    }
+    for (; d <= EMB_XCDS; ++d) dies.first[d] = total_blocks;
+    for (d = 0; d < EMB_XCDS; ++d)
+        if (dies.first[d + 1] - dies.first[d] > most) most = dies.first[d + 1] - dies.first[d];
+    return most;
 }
 
 }  // namespace
@@ -143,9 +194,11 @@ extern "C" int emb_bag_forward_mixed(const emb_table *tables_host, const emb_tab
     }
     if (!offsets_dev || !out_dev || (nnz > 0 && !rows_dev)) return EMB_ERR_INVALID_ARG;
     if (!emb_aligned(out_dev, 16)) return EMB_ERR_INVALID_ARG;
-    const int64_t grid = emb_round_up_xcds((int64_t)first);
+    DieShares dies;
+    const int64_t grid = (int64_t)mixed_die_shares(shapes_host, T, B, (uint32_t)first, dies) * EMB_XCDS;
+    if (grid > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(bag_forward_mixed_kernel, dim3((unsigned)grid), dim3(MX_BLOCK), 0, emb_stream(stream), tables_dev,
-                       shapes_dev, T, (uint32_t)first, B, nnz, rows_dev, offsets_dev, mode, out_dev, status_dev);
+                       shapes_dev, T, dies, B, nnz, rows_dev, offsets_dev, mode, out_dev, status_dev);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }

@@ -245,6 +245,36 @@ def test_forward_mixed_widths_and_types_matches_oracle(layout, mode):
     assert int(status.item()) == st_ref == emb.STATUS_BAD_INDEX
 
 
+@pytest.mark.parametrize("B,widths", [
+    (1, [16]),                                  # one workgroup: seven dies without any
+    (1, [256, 4, 64]),                          # fewer workgroups than dies
+    (700, [4, 4, 4, 4, 4, 4, 4, 256]),          # almost all of the cost in the last table: several cuts inside it
+    (700, [256, 4, 4, 4, 4, 4, 4, 4]),          # ... in the first
+    (64, [64] * 16),                            # cuts that fall between tables
+    (8193, [8, 128, 8]),
+])
+def test_forward_mixed_every_bag_once_wherever_the_dies_are_cut(B, widths):
+    # the lookup of each table alone goes through the same loop: the same bits
+    rng = np.random.default_rng(1650 + B + len(widths))
+    T, R = len(widths), 500
+    tables = [H.dev(rng.standard_normal((R, D)).astype(np.float32)) for D in widths]
+    off, _ = oracle.lengths_to_offsets(rng.integers(0, 9, size=T * B).astype(np.int32))
+    rows = rng.integers(0, R, size=int(off[-1])).astype(np.int64)
+    mt = emb.MixedTables(tables, B, "table_major", device=torch.device(H.DEV))
+    out = torch.full((mt.out_floats,), float("nan"), dtype=torch.float32, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    emb.emb_bag_forward_mixed(mt, H.dev(rows), H.dev(off), "mean", out, status)
+    torch.cuda.synchronize()
+    assert status.item() == 0
+    got, col = out.cpu().numpy(), 0
+    for t, D in enumerate(widths):
+        ts = emb.TableSet([tables[t]], D, "f32", device=torch.device(H.DEV))
+        seg = off[t * B:(t + 1) * B + 1]
+        ref, st = H.gpu_forward(ts, rows[seg[0]:seg[-1]], seg - seg[0], B, "mean")
+        assert st == 0 and np.array_equal(got[col * B:(col + D) * B], ref.reshape(-1)), t
+        col += D
+
+
 @pytest.mark.parametrize("D,dtype", [(64, "f32"), (16, "bf16"), (1024, "f32")])
 def test_forward_streaming_hint_changes_no_bit(D, dtype):
     rng = np.random.default_rng(1700 + D)
