@@ -231,7 +231,8 @@ int emb_event_elapsed_ms(void *start, void *stop, float *ms_out);
  * the key build, the sort, the optional list of distinct rows, the short-run
  * update and the long-run path, for callers that time the stages.
  * side (host, nullable): see emb_side_stream; NULL runs everything on
- * `stream`.  Results do not depend on it. */
+ * `stream`, as a batch of few lookups (2^18 at most) does in any case.
+ * Results do not depend on it. */
 int emb_bag_backward_rowwise_adagrad(const emb_table *tables_host, const emb_table *tables_dev,
                                      int32_t T, int32_t D, int32_t dtype,
                                      const int64_t *rows_dev, const int64_t *offsets_dev,
@@ -402,7 +403,8 @@ int emb_bag_forward_train(const emb_table *tables_host, const emb_table *tables_
  * offsets, row numbers, status bits and the backward's records are
  * bit-identical to the two calls; two launches fewer (the sums within tiles
  * of 4096 lengths are one launch, the tiles' prefix sums are taken by the
- * backward's set-up kernel, and the lookup adds the two).  A negative length
+ * backward's set-up kernel, and the lookup adds the two; with few lookups the
+ * lookup does the work of both set-up launches).  A negative length
  * counts as 0 and sets EMB_STATUS_BAD_OFFSETS; nnz must be the sum of the
  * lengths (a different nnz sets EMB_STATUS_BAD_OFFSETS and aborts the backward
  * as malformed offsets do).  offsets_out_dev must not overlap lengths_dev.
@@ -416,7 +418,7 @@ int emb_bag_forward_train_lengths(const emb_table *tables_host, const emb_table 
                                   uint32_t *status_dev, void *stream);
 /* emb_bag_forward_train_lengths for a loop whose previous backward deferred
  * its join (emb_side_stream, defer_join): `after` (nullable) is that
- * backward's side stream; `stream` waits for its join_event after the two
+ * backward's side stream; `stream` waits for its join_event after the
  * set-up launches and before the lookup.  workspace_dev and
  * num_unique_out_dev must not be the ones that backward used. */
 int emb_bag_forward_train_lengths_after(const emb_table *tables_host, const emb_table *tables_dev,

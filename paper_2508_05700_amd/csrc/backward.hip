@@ -15,6 +15,8 @@
 //            order) and Adagrad is applied once to its row              (update.h)
 //   runs     only when the caller asks for the list of distinct rows: head
 //            flags, scan and compaction into unique keys and counts
+// Small steps (small_step, bwd_common.h), whose launches would each be shorter than the way from one to the next, take
+// fewer of them: tile_merge_sort.h and update_spans.h.  The sorted records and the sums are the same bit for bit.
 // The payload carried through the sort is the bag number: lookups of one row
 // are then ordered by bag, which is ascending lookup order except between
 // duplicates inside one bag, whose gradient terms are identical.  Every sum is
@@ -23,7 +25,9 @@
 #include "gather.h"
 #include "radix_sort.h"
 #include "scan.h"
+#include "tile_merge_sort.h"
 #include "update.h"
+#include "update_spans.h"
 #include "u64mod.h"
 
 namespace {
@@ -123,12 +127,13 @@ inline BwdLayout bwd_layout(int32_t T, int64_t B, int64_t nnz, int64_t total_row
 // tile_prefix != NULL: `offsets` holds sums within tiles of EMB_OFFSETS_TILE lengths (emb_offsets_tile_sums);
 // the kernel first writes the exclusive prefix sums of the tile totals there (one entry per tile of the
 // T_all * B lengths, whatever T says) and reads every offset through emb_offset_at.
+// table_start != NULL: receives the tables' first records and, after the last, nnz (T + 1 entries).
 __global__ __launch_bounds__(1024) void bwd_init_kernel(BwdCtrl *ctrl, const int64_t *__restrict__ offsets, int32_t T,
                                                          int64_t B, int64_t nnz, uint32_t *__restrict__ first_tile,
                                                          SortTile *__restrict__ desc, uint32_t tiles,
                                                          int64_t *num_unique_out, uint32_t *status,
                                                          int64_t *__restrict__ tile_prefix = nullptr,
-                                                         int64_t n_lengths = 0)
+                                                         int64_t n_lengths = 0, int64_t *__restrict__ table_start = nullptr)
 {
     __shared__ uint32_t wave_sums[1024 / EMB_WAVE];
     __shared__ int64_t wave_sums64[1024 / EMB_WAVE];
@@ -160,6 +165,10 @@ __global__ __launch_bounds__(1024) void bwd_init_kernel(BwdCtrl *ctrl, const int
             const bool ok = s >= 0 && s <= e && e <= nnz && (t > 0 || s == 0) && (t < T - 1 || e == nnz);
             if (ok) c = (uint32_t)((e - s + SORT_TILE - 1) / SORT_TILE);
             else bad = 1;
+            if (table_start) {
+                table_start[t] = s;
+                if (t == T - 1) table_start[T] = e;
+            }
         }
         uint32_t total;
         const uint32_t inc = block_inclusive_scan<uint32_t, 1024>(c, wave_sums, total);
@@ -435,7 +444,9 @@ struct BwdArgs {
     const int32_t *lengths = nullptr;    // ... from these (NULL when there are no bags)
     int64_t *offsets_out = nullptr;      // ... and written here
     int64_t B = 0, nnz = 0, total_rows = 0, max_rows = 0;
-    int passes = 1;   // of the sort: enough for the bits of max_rows, the value that marks an invalid row
+    int key_bits = 1; // of max_rows, the value that marks an invalid row
+    int passes = 1;   // of the sort: enough for key_bits
+    bool small = false;   // small_step
     const float *dout = nullptr;
     float lr = 0.f, eps = 0.f;
     char *ws = nullptr;
@@ -455,7 +466,52 @@ struct BwdArgs {
         return EMB_OK;
     }
 };
+// What a small step keeps where a larger one has its tile descriptors and its spans' first run starts.
+inline int64_t *table_start_of(const BwdArgs &a, const BwdLayout &L) { return reinterpret_cast<int64_t *>(a.ws + L.tile_desc); }
+inline uint32_t *span_flags_of(const BwdArgs &a, const BwdLayout &L) { return reinterpret_cast<uint32_t *>(a.ws + L.span_head); }
+inline bool small_step_merges(const BwdArgs &a) { return a.nnz > MERGE_TILE; }   // else no table has more than one tile
 #define EMB_MARK(a, i) do { if ((a).mark(i) != EMB_OK) return EMB_ERR_HIP; } while (0)
+
+// How often a scatter of the sort polls one word of another workgroup before it gives the sort up
+// (sort_lookback_walk, radix_sort.h); emb_debug_sort_poll_limit changes it.  update_spans_kernel polls as often
+// before it sums another wavefront's chunk itself.
+static constexpr uint32_t SORT_POLL_LIMIT_DEFAULT = 1u << 20;
+static constexpr int SORT_SCAN_BLOCKS = RADIX / SCAN_DIGITS / (SCAN_BLOCK_THREADS / EMB_WAVE);   // workgroups of the scan, per pass
+static constexpr int SORT_EXCHANGE_MAX_TILES = 64;   // per table, on average: above it every pass counts and scans
+static uint32_t sort_poll_limit = SORT_POLL_LIMIT_DEFAULT;
+
+extern "C" void emb_debug_sort_poll_limit(int64_t polls)
+{
+    sort_poll_limit = polls < 0 ? SORT_POLL_LIMIT_DEFAULT : (polls > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)polls);
+}
+
+template <int LPR, int CPL, int EU, bool BF16>
+int launch_update_spans(const BwdArgs &a, const BwdLayout &L, const uint32_t *keys, const uint32_t *pay, int chunks)
+{
+    const uint32_t n = (uint32_t)a.nnz;
+    BagDiv bdiv;
+    bdiv.B = (uint32_t)a.B;
+    bdiv.magic = 0xFFFFFFFFu / (uint32_t)a.B;
+    // Some 2048 wavefronts at least, as far as spans of 8 records give them: a wavefront costs its start and its staging
+    // however few records it has, and each round of runs (64 / LPR at a time) the way to its rows and back.  us for spans
+    // of 4 / 8 / 16 / 32 records, 256-byte rows unless said: 60 records 4.6 / 4.3 / 4.5 / 5.8, 3 000 8.4 / 7.7 / 9.4 / 10.5,
+    // 30 720 15 / 12.8 / 12.1 / 13.1 (768-byte rows 30 / 28 / 30 / 34), 66 000 of 64 bytes 15 / 11.3 / 9.1 / 9.2, 148 674 of
+    // 96 bytes 64 / 41 / 30 / 26, 220 000 61 / 41 / 33 / 30.
+    uint32_t span = 8;
+    while (span < (uint32_t)SPAN_MAX && n > span * 2048u) span *= 2;
+    const uint32_t block_records = UPD_BLOCK / EMB_WAVE * span;
+    const uint32_t span_blocks = (n + block_records - 1) / block_records;
+    const uint32_t count_blocks = (n + SPAN_COUNT_RECORDS - 1) / SPAN_COUNT_RECORDS;
+    hipLaunchKernelGGL((update_spans_kernel<LPR, CPL, EU, BF16>), dim3(span_blocks + count_blocks), dim3(UPD_BLOCK), 0, a.stream,
+                       a.tables_dev, a.T, keys, pay, n, (uint32_t)a.total_rows, reinterpret_cast<const float *>(a.ws + L.bag_scale),
+                       a.dout, chunks, a.D, 1.0f / (float)a.D, a.lr, a.eps, bdiv, span, count_blocks, span_flags_of(a, L),
+                       reinterpret_cast<float *>(a.ws + L.partials), sort_poll_limit, reinterpret_cast<BwdCtrl *>(a.ws + L.ctrl),
+                       a.num_unique_out);
+    EMB_RETURN_IF_LAUNCH_FAILED();
+    EMB_MARK(a, 4);
+    EMB_MARK(a, 5);
+    return EMB_OK;
+}
 
 template <typename KeyT, int LPR, int CPL, int EU, bool BF16>
 int launch_update(const BwdArgs &a, const BwdLayout &L, const KeyT *keys, const uint32_t *pay, int chunks)
@@ -549,18 +605,6 @@ int launch_update(const BwdArgs &a, const BwdLayout &L, const KeyT *keys, const 
     return EMB_OK;
 }
 
-// How often a scatter of the sort polls one word of another workgroup before it gives the sort up
-// (sort_lookback_walk, radix_sort.h); emb_debug_sort_poll_limit changes it.
-static constexpr uint32_t SORT_POLL_LIMIT_DEFAULT = 1u << 20;
-static constexpr int SORT_SCAN_BLOCKS = RADIX / SCAN_DIGITS / (SCAN_BLOCK_THREADS / EMB_WAVE);   // workgroups of the scan, per pass
-static constexpr int SORT_EXCHANGE_MAX_TILES = 64;   // per table, on average: above it every pass counts and scans
-static uint32_t sort_poll_limit = SORT_POLL_LIMIT_DEFAULT;
-
-extern "C" void emb_debug_sort_poll_limit(int64_t polls)
-{
-    sort_poll_limit = polls < 0 ? SORT_POLL_LIMIT_DEFAULT : (polls > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)polls);
-}
-
 // Keys, sort and the optional list of distinct rows: everything that needs the indices only.
 // prepared: the control block, the tile descriptors and the records are in the workspace already
 // (emb_bag_forward_train put them there), so only the passes and the optional list run.
@@ -590,7 +634,8 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     EMB_MARK(a, 0);
     if (!prepared) {
         hipLaunchKernelGGL(bwd_init_kernel, dim3(1), dim3(1024), 0, s, ctrl, a.offsets, a.nnz > 0 ? a.T : 0, a.B, a.nnz,
-                           first_tile, tile_desc, a.nnz > 0 ? tiles : 0u, a.num_unique_out, a.status);
+                           first_tile, tile_desc, a.nnz > 0 && !a.small ? tiles : 0u, a.num_unique_out, a.status, nullptr, 0,
+                           a.small ? table_start_of(a, L) : nullptr);
         EMB_RETURN_IF_LAUNCH_FAILED();
     }
     if (a.nnz == 0) {
@@ -609,7 +654,8 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
 
     KeyT *kin = keys_a, *kout = keys_b;
     uint32_t *pin = pay_a, *pout = pay_b;
-    // Two ways through the passes (radix_sort.h).  Tables of up to SORT_EXCHANGE_MAX_TILES tiles of records
+    // A small step sorts its tiles and merges them (tile_merge_sort.h); otherwise there are two ways through the passes
+    // (radix_sort.h).  Tables of up to SORT_EXCHANGE_MAX_TILES tiles of records
     // each (all the host can know is the average): the digits of all passes are counted by one launch
     // and scanned by one, and the scatters of the later passes exchange their counts.  Larger tables: a
     // counting launch and a scan per pass, because a scatter's walk back over its table's earlier tiles
@@ -619,8 +665,40 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     // first counting launch
     const bool want_list = a.unique_keys_out || a.unique_counts_out;
     unsigned long long *list_flags = want_list ? tile_heads : nullptr;
-    const bool exchange = a.nnz <= (int64_t)SORT_EXCHANGE_MAX_TILES * SORT_TILE * (a.T > 0 ? a.T : 1);
+    const int passes = a.small ? 0 : a.passes;
+    const bool exchange = !a.small && a.nnz <= (int64_t)SORT_EXCHANGE_MAX_TILES * SORT_TILE * (a.T > 0 ? a.T : 1);
     const uint32_t poll_limit = sort_poll_limit;
+    if constexpr (sizeof(KeyT) == 4) {
+        if (a.small) {
+            const int passes_in_lds = (a.key_bits + MERGE_BITS_MAX - 1) / MERGE_BITS_MAX;
+            const int bits = (a.key_bits + passes_in_lds - 1) / passes_in_lds;
+            const int64_t *table_start = table_start_of(a, L);
+            const bool merges = small_step_merges(a);
+#define EMB_TILE_SORT(BITS, LAST)                                                                                          \
+    hipLaunchKernelGGL((tile_sort_kernel<BITS, LAST>), dim3((unsigned)(n / MERGE_TILE + a.T)), dim3(MERGE_BLOCK), 0, s, keys_a, pay_a, keys_b, pay_b,   \
+                       table_start, a.T, passes_in_lds, a.tables_dev, local_sentinel, sentinel, list_flags, flat_tiles,    \
+                       span_flags_of(a, L), (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK), ctrl)
+#define EMB_TILE_SORT_BITS(BITS)              \
+    if (merges) EMB_TILE_SORT(BITS, false);   \
+    else EMB_TILE_SORT(BITS, true);           \
+    break
+            switch (bits) {
+                case 10: EMB_TILE_SORT_BITS(10);
+                case 9: EMB_TILE_SORT_BITS(9);
+                case 8: EMB_TILE_SORT_BITS(8);
+                default: EMB_TILE_SORT_BITS(MERGE_BITS_MIN);
+            }
+#undef EMB_TILE_SORT_BITS
+#undef EMB_TILE_SORT
+            EMB_RETURN_IF_LAUNCH_FAILED();
+            if (merges) {
+                hipLaunchKernelGGL(tile_merge_kernel, dim3((unsigned)(n / PLACE_BLOCK + a.T)), dim3(PLACE_BLOCK), 0, s, keys_b, pay_b, keys_a, pay_a,
+                                   table_start, a.T, a.tables_dev, local_sentinel, sentinel, ctrl);
+                EMB_RETURN_IF_LAUNCH_FAILED();
+            }
+            if (!merges) kin = keys_b;
+        }
+    }
     if (exchange) {
         for (int p0 = 0; p0 < a.passes; p0 += 4) {
             unsigned long long *fl = p0 == 0 ? sort_flags : nullptr;   // the first launch clears the scatters' words
@@ -641,12 +719,12 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
                            ctrl);
         EMB_RETURN_IF_LAUNCH_FAILED();
     }
-    for (int p = 0; p < a.passes; ++p) {
+    for (int p = 0; p < passes; ++p) {
         const int shift = p * RADIX_BITS;
         uint32_t *hp = hist + (size_t)p * RADIX * (tiles + 1);
         const bool lookback = exchange && p > 0;
         unsigned long long *fl = lookback ? sort_flags + (size_t)(p - 1) * tiles * RADIX : nullptr;
-        const bool last = p == a.passes - 1;
+        const bool last = p == passes - 1;
         if (!exchange) {
             hipLaunchKernelGGL((sort_hist_kernel<KeyT, 1>), dim3(tiles), dim3(SORT_BLOCK), 0, s, kin, tile_desc, p, hist,
                                tiles, (unsigned long long *)nullptr, 0, p == 0 ? list_flags : nullptr, flat_tiles, ctrl);
@@ -696,7 +774,7 @@ template <typename KeyT>
 int run_update(const BwdArgs &a, const BwdLayout &L)
 {
     // an odd number of passes leaves the sorted records in the second pair of arrays
-    const bool in_b = (a.passes & 1) != 0;
+    const bool in_b = a.small ? !small_step_merges(a) : (a.passes & 1) != 0;
     const KeyT *kin = reinterpret_cast<const KeyT *>(a.ws + (in_b ? L.keys_b : L.keys_a));
     const uint32_t *pin = reinterpret_cast<const uint32_t *>(a.ws + (in_b ? L.pay_b : L.pay_a));
     EMB_MARK(a, 3);
@@ -708,6 +786,11 @@ int run_update(const BwdArgs &a, const BwdLayout &L)
     const int chunks = a.D * emb_elem_size(a.dtype) / 16;
     const bool bf16 = a.dtype == EMB_BF16;
 #define EMB_UPD(LL, C, EU)                                                                   \
+    if constexpr (sizeof(KeyT) == 4) {                                                       \
+        if (a.small)                                                                         \
+            return bf16 ? launch_update_spans<LL, C, EU, true>(a, L, kin, pin, chunks)       \
+                        : launch_update_spans<LL, C, EU, false>(a, L, kin, pin, chunks);     \
+    }                                                                                        \
     return bf16 ? launch_update<KeyT, LL, C, EU, true>(a, L, kin, pin, chunks)               \
                 : launch_update<KeyT, LL, C, EU, false>(a, L, kin, pin, chunks)
     switch (L.lpr * 100 + L.cpl) {
@@ -766,13 +849,18 @@ struct TrainSource {
 
 constexpr int TRAIN_BLOCK = 256;
 
-template <int LPR, int CPL, int UNROLL, bool BF16, typename KeyT>
+// MAKE_OFFSETS (a small step from lengths): no launch stands before this one but the sums within tiles, and not even that
+// for up to EMB_LENGTHS_DIRECT_BAGS bags.  The kernel makes the bounds itself, from `lengths` or from the sums in `offsets`
+// as bag_forward_kernel does, and whoever has a table's first or the batch's last bag writes what the set-up kernel
+// would have: table_start, the control block (the bags partition [0, nnz) iff the last one ends there).
+template <int LPR, int CPL, int UNROLL, bool BF16, typename KeyT, bool MAKE_OFFSETS>
 __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
     const emb_table *__restrict__ tables, int32_t T, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ raw, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
     float *__restrict__ out, int64_t *__restrict__ rows_out, KeyT *__restrict__ keys, uint32_t *__restrict__ pay,
     float *__restrict__ bag_scale, BwdCtrl *ctrl, uint32_t *status, const int64_t *__restrict__ tile_prefix,
-    int64_t *__restrict__ offsets_out)
+    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths, int64_t *__restrict__ table_start,
+    int64_t *num_unique_out)
 {
     // tile_prefix != NULL: `offsets` are sums within tiles (emb_offset_at) and the final offsets go to offsets_out
     constexpr int GROUPS = TRAIN_BLOCK / LPR;
@@ -782,10 +870,43 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
     const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
     const int t = tail ? T - 1 : (int)t_raw;
     const int l = threadIdx.x % LPR;
-    const int64_t b = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS + threadIdx.x / LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
     const bool live = b < B;
     const int64_t bag = (int64_t)t * B + b;
     const emb_table tb = tables[t];
+    TrainSource<KeyT> src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
+                          (int64_t)chunks_per_row * 16, rows_out, keys, pay, (uint32_t)bag};
+    float *const out_row = out + bag * ((int64_t)chunks_per_row * F);
+    if constexpr (MAKE_OFFSETS) {
+        __shared__ int64_t prefixes[TRAIN_BLOCK + 1];
+        __shared__ int64_t wave_sums[2 * TRAIN_BLOCK / EMB_WAVE];
+        int64_t s, e;
+        if (lengths) {   // uniform
+            const int64_t left = B - b0;
+            emb_bounds_from_lengths<TRAIN_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < GROUPS ? (int)left : GROUPS,
+                                                         threadIdx.x / LPR, prefixes, wave_sums, status, s, e);
+        } else {
+            emb_two_level_bounds<TRAIN_BLOCK>(offsets, (int64_t)T * B, live, bag, prefixes, wave_sums, s, e);
+        }
+        if (live && l == 0) {
+            bag_scale[bag] = (mode == EMB_POOL_MEAN && e > s) ? 1.0f / (float)(e - s) : 1.0f;
+            offsets_out[bag + 1] = e;
+            if (bag == 0) offsets_out[0] = 0;
+            if (b == 0) table_start[t] = s;
+            if (bag == (int64_t)T * B - 1) {
+                table_start[T] = e;
+                ctrl->abort = e != nnz ? 1u : 0u;
+                ctrl->num_runs = 0;
+                ctrl->num_unique = 0;
+                ctrl->task_and_multi_count = 0ull;
+                if (e != nnz) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
+                if (num_unique_out) *num_unique_out = 0;
+            }
+        }
+        gather_pool_range<LPR, CPL, UNROLL, BF16>(src, live, s, e, l, nnz, raw, chunks_per_row, mode, out_row, status);
+        return;
+    }
     if (live && l == 0) {
         // what bwd_keys_kernel does per bag: the scale of its gradient, or the abort of the backward
         int64_t s, e;
@@ -797,10 +918,14 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
             if (bag == 0) offsets_out[0] = 0;
         }
     }
-    TrainSource<KeyT> src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
-                          (int64_t)chunks_per_row * 16, rows_out, keys, pay, (uint32_t)bag};
-    gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode,
-                                            out + bag * ((int64_t)chunks_per_row * F), status, tile_prefix);
+    gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
+                                            tile_prefix);
+}
+
+// A small step from lengths whose lookup makes the bags' bounds itself (at most as many tiles of sums as a workgroup scans).
+inline bool train_makes_offsets(const BwdArgs &a)
+{
+    return a.small && a.from_lengths && (int64_t)a.T * a.B <= (int64_t)TRAIN_BLOCK * EMB_OFFSETS_TILE;
 }
 
 template <typename KeyT, int LPR, int CPL, int UNROLL>
@@ -815,19 +940,28 @@ int launch_train(bool bf16, const BwdArgs &a, const BwdLayout &L, const int64_t 
     KeyT *keys = reinterpret_cast<KeyT *>(a.ws + L.keys_a);
     uint32_t *pay = reinterpret_cast<uint32_t *>(a.ws + L.pay_a);
     float *bag_scale = reinterpret_cast<float *>(a.ws + L.bag_scale);
-    // made from lengths: the offsets are the sums within tiles in the workspace plus the tiles' prefix sums
+    // made from lengths: the offsets are the sums within tiles in the workspace plus the tiles' prefix sums (bwd_init_kernel's,
+    // or the kernel's own)
+    const bool make = train_makes_offsets(a);
     const int64_t *offsets = a.from_lengths ? reinterpret_cast<const int64_t *>(a.ws + L.local_offsets) : a.offsets;
-    const int64_t *tile_prefix = a.from_lengths ? reinterpret_cast<const int64_t *>(a.ws + L.tile_prefix) : nullptr;
-    if (bf16)
-        hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, true, KeyT>), dim3((unsigned)blocks),
-                           dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw,
-                           offsets, chunks, a.mode, out, rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix,
-                           a.offsets_out);
-    else
-        hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, false, KeyT>), dim3((unsigned)blocks),
-                           dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw,
-                           offsets, chunks, a.mode, out, rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix,
-                           a.offsets_out);
+    const int64_t *tile_prefix = a.from_lengths && !make ? reinterpret_cast<const int64_t *>(a.ws + L.tile_prefix) : nullptr;
+    const int32_t *lengths = make && (int64_t)a.T * a.B <= EMB_LENGTHS_DIRECT_BAGS ? a.lengths : nullptr;
+#define EMB_TRAIN(BF, MAKE)                                                                                              \
+    hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, BF, KeyT, MAKE>), dim3((unsigned)blocks),             \
+                       dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets, \
+                       chunks, a.mode, out, rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out,  \
+                       lengths, table_start_of(a, L), a.num_unique_out)
+    if constexpr (sizeof(KeyT) == 4) {
+        if (make) {
+            if (bf16) EMB_TRAIN(true, true);
+            else EMB_TRAIN(false, true);
+            EMB_RETURN_IF_LAUNCH_FAILED();
+            return EMB_OK;
+        }
+    }
+    if (bf16) EMB_TRAIN(true, false);
+    else EMB_TRAIN(false, false);
+#undef EMB_TRAIN
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
@@ -838,7 +972,14 @@ int run_train_forward(const BwdArgs &a, const BwdLayout &L, const int64_t *raw, 
     BwdCtrl *ctrl = reinterpret_cast<BwdCtrl *>(a.ws + L.ctrl);
     uint32_t *first_tile = reinterpret_cast<uint32_t *>(a.ws + L.first_tile);
     SortTile *tile_desc = reinterpret_cast<SortTile *>(a.ws + L.tile_desc);
-    if (a.from_lengths) {
+    if (train_makes_offsets(a)) {
+        const int64_t n_lengths = (int64_t)a.T * a.B;
+        if (n_lengths > EMB_LENGTHS_DIRECT_BAGS) {
+            const int rc = emb_offsets_tile_sums(a.lengths, n_lengths, reinterpret_cast<int64_t *>(a.ws + L.local_offsets), a.status,
+                                                 a.stream);
+            if (rc != EMB_OK) return rc;
+        }
+    } else if (a.from_lengths) {
         // bag offsets on the way: sums within tiles by one launch; the tiles' prefix sums by the
         // single workgroup of bwd_init_kernel; the lookup adds the two (and writes the offsets out)
         const int64_t n_lengths = (int64_t)a.T * a.B;
@@ -848,15 +989,16 @@ int run_train_forward(const BwdArgs &a, const BwdLayout &L, const int64_t *raw, 
         const int rc = emb_offsets_tile_sums(a.lengths, n_lengths, local, a.status, a.stream);
         if (rc != EMB_OK) return rc;
         hipLaunchKernelGGL(bwd_init_kernel, dim3(1), dim3(1024), 0, a.stream, ctrl, local, a.nnz > 0 ? a.T : 0, a.B, a.nnz,
-                           first_tile, tile_desc, a.nnz > 0 ? (uint32_t)L.tiles : 0u, a.num_unique_out, a.status,
-                           tile_prefix, n_lengths);
+                           first_tile, tile_desc, a.nnz > 0 && !a.small ? (uint32_t)L.tiles : 0u, a.num_unique_out, a.status,
+                           tile_prefix, n_lengths, a.small ? table_start_of(a, L) : nullptr);
     } else {
         hipLaunchKernelGGL(bwd_init_kernel, dim3(1), dim3(1024), 0, a.stream, ctrl, a.offsets, a.nnz > 0 ? a.T : 0, a.B,
-                           a.nnz, first_tile, tile_desc, a.nnz > 0 ? (uint32_t)L.tiles : 0u, a.num_unique_out, a.status);
+                           a.nnz, first_tile, tile_desc, a.nnz > 0 && !a.small ? (uint32_t)L.tiles : 0u, a.num_unique_out,
+                           a.status, nullptr, 0, a.small ? table_start_of(a, L) : nullptr);
     }
     EMB_RETURN_IF_LAUNCH_FAILED();
     // Work of an earlier backward that still runs on its side stream changes table rows: the lookup
-    // waits for it; the two launches above read neither tables nor that backward's workspace.
+    // waits for it; the launches above read neither tables nor that backward's workspace.
     if (a.after && hipStreamWaitEvent(a.stream, reinterpret_cast<hipEvent_t>(a.after->join_event), 0) != hipSuccess)
         return EMB_ERR_HIP;
     if (a.T == 0 || a.B == 0) return EMB_OK;
@@ -916,7 +1058,9 @@ int bwd_plan(const emb_table *tables_host, const emb_table *tables_dev, int32_t 
     a.tables_dev = tables_dev;
     a.T = T; a.D = D; a.dtype = dtype;
     a.B = B; a.nnz = nnz; a.total_rows = total_rows; a.max_rows = max_rows;
+    a.key_bits = bits < 1 ? 1 : bits;
     a.passes = passes;
+    a.small = small_step(T, nnz, L.key_bytes);
     a.ws = reinterpret_cast<char *>(workspace_dev);
     a.stream = emb_stream(stream);
     return EMB_OK;

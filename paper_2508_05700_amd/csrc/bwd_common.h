@@ -31,6 +31,20 @@ constexpr int PREP_BLOCK_LARGE = 1024;            // the same for more than PREP
 constexpr int64_t PREP_SMALL_MAX = 1 << 20;
 constexpr int UPD_LDS_TABLES = 512; // table directories up to this size are staged in LDS
 
+// Small steps (32-bit keys, at most UPD_LDS_TABLES tables) are sorted by tile_merge_sort.h and updated by update_spans.h,
+// on the caller's stream alone; larger ones by radix_sort.h and update.h.  What ends them is the merge, whose work is
+// the number of records times the records of a table, of which the host knows the average.  Whole steps of 256-byte rows
+// in us, small / large, in turn on one card: one table 60 000 records 54 / 100, 120 000 83 / 108, 240 000 160 / 119;
+// four tables 120 000 57 / 107, 240 000 87 / 118, 480 000 177 / 139; sixteen 128 000 53 / 105, 256 000 74 / 118,
+// 512 000 126 / 145, 1 024 000 255 / 200.  Up to SMALL_STEP_MAX a batch that has all its records in one of its tables
+// loses 40 % at most; sixteen even tables would still gain at twice as many.
+constexpr int64_t SMALL_STEP_MAX = 1 << 18;
+constexpr int64_t SMALL_STEP_MERGE_MAX = (int64_t)1 << 35;   // records times average records of a table
+static inline bool small_step(int32_t T, int64_t nnz, int key_bytes)
+{
+    return key_bytes == 4 && nnz > 0 && nnz <= SMALL_STEP_MAX && T <= UPD_LDS_TABLES && nnz * nnz / T <= SMALL_STEP_MERGE_MAX;
+}
+
 struct LongSeg {
     uint32_t lo, hi;       // records [lo, hi) of the sorted arrays
     uint32_t chunk_base;   // first chunk-sum slot (runs of several chunks)

@@ -33,51 +33,48 @@ struct SortTile {
 static_assert(sizeof(SortTile) == 32, "tile descriptors are read as two 16-byte loads");
 
 // Stable rank of every record of a wavefront's share of a tile among the records
-// of the same digit, and the wavefront's digit counts.  A wavefront walks its
-// share 64 records at a time in ascending order; lanes holding the same digit
-// are matched with one ballot per digit bit (every lane collects the lanes whose
-// bit differs from its own: what is left are its peers), the lowest of them bumps
-// the wavefront's private LDS counter, so there are no LDS atomics and no
-// same-address serialisation when many records share a digit (the hot rows of
-// a skewed batch, or the table bits of the key).
-template <typename KeyT, bool WANT_RANK>
-__device__ __forceinline__ void wave_rank_digits(const KeyT (&key)[SORT_ITEMS], uint32_t wbase, uint32_t n, int shift,
-                                                 uint32_t *cnt /*LDS [RADIX], this wavefront's, zeroed*/,
-                                                 uint32_t (&rank)[SORT_ITEMS])
+// of the same digit (BITS bits from `shift` on), and the wavefront's digit counts.
+// A wavefront has ITEMS steps of 64 consecutive records each.  In a step, lanes
+// holding the same digit are matched with one ballot per digit bit (every lane
+// collects the lanes whose bit differs from its own: what is left are its peers);
+// the lowest of them adds their number to the wavefront's private LDS counter and
+// gets its value before, so no two lanes of an instruction add to one counter,
+// whatever the records (the hot rows of a skewed batch).  A wavefront's LDS
+// operations are carried out in order, so the adds of all steps go out one behind
+// the other and are waited for once: with a load and a store in the place of each
+// add, every step waited for the one before it (tiles of 4096 records of 18 bits
+// in LDS, two passes: 15.2 us then, FIXME now).
+template <typename KeyT, int BITS, int ITEMS>
+__device__ __forceinline__ void wave_rank_digits(const KeyT (&key)[ITEMS], uint32_t wbase, uint32_t n, int shift,
+                                                 uint32_t *cnt /*LDS [1 << BITS], this wavefront's, zeroed*/,
+                                                 uint32_t (&rank)[ITEMS])
 {
     const int lane = threadIdx.x & (EMB_WAVE - 1);
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t prev[ITEMS];
+    int leader[ITEMS];
 #pragma unroll
-    for (int k = 0; k < SORT_ITEMS; ++k) {
-        const uint32_t i = wbase + k * EMB_WAVE + lane;
-        const bool live = i < n;
-        rank[k] = 0;
-        const uint64_t lv = __ballot(live);
-        if (lv == 0) continue;            // uniform: the share ends before this step
-        const uint32_t digit = (uint32_t)(key[k] >> shift) & (RADIX - 1);
+    for (int k = 0; k < ITEMS; ++k) {
+        const bool live = wbase + k * EMB_WAVE + lane < n;
+        const uint32_t digit = (uint32_t)(key[k] >> shift) & ((1u << BITS) - 1);
         // (kept as two 32-bit halves: a lane's own bit, spread over a word, serves both)
         uint32_t differ_lo = 0, differ_hi = 0;
 #pragma unroll
-        for (int bit = 0; bit < RADIX_BITS; ++bit) {
+        for (int bit = 0; bit < BITS; ++bit) {
             const uint32_t set = digit & (1u << bit);
             const uint64_t with = __ballot(set != 0);
             const uint32_t mine = set ? 0xFFFFFFFFu : 0u;   // all ones if my bit is set
             differ_lo |= (uint32_t)with ^ mine;
             differ_hi |= (uint32_t)(with >> 32) ^ mine;
         }
-        const uint64_t peers = lv & ~(((uint64_t)differ_hi << 32) | differ_lo);   // dead lanes match nobody
-        const uint32_t before = __popcll(peers & lt_mask);
-        uint32_t prev = 0;
-        if (live && before == 0) {  // lowest lane of each digit group updates the wavefront's counter
-            prev = cnt[digit];
-            cnt[digit] = prev + (uint32_t)__popcll(peers);
-        }
-        if (WANT_RANK) {
-            const int leader = live ? (__ffsll((unsigned long long)peers) - 1) : lane;
-            prev = __shfl(prev, leader, EMB_WAVE);
-            rank[k] = prev + before;
-        }
+        const uint64_t peers = __ballot(live) & ~(((uint64_t)differ_hi << 32) | differ_lo);   // dead lanes match nobody
+        rank[k] = __popcll(peers & lt_mask);
+        leader[k] = live ? (__ffsll((unsigned long long)peers) - 1) : lane;
+        prev[k] = 0;
+        if (live && rank[k] == 0) prev[k] = atomicAdd(&cnt[digit], (uint32_t)__popcll(peers));
     }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) rank[k] += (uint32_t)__shfl((int)prev[k], leader[k], EMB_WAVE);
 }
 
 // hist is [passes][tiles + 1][RADIX]: entry (p, t, d) holds the count of digit d of pass p in
@@ -363,7 +360,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_scatter_kernel(const KeyT *__
         key[k] = i < end ? keys_in[i] : (KeyT)0;
         pay[k] = i < end ? pay_in[i] : 0u;
     }
-    wave_rank_digits<KeyT, true>(key, wbase, end, shift, cnt[wave], rank);
+    wave_rank_digits<KeyT, RADIX_BITS, SORT_ITEMS>(key, wbase, end, shift, cnt[wave], rank);
     __syncthreads();
 
     // thread d: digit d's count in the tile, its start inside the tile and the number of the

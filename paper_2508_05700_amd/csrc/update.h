@@ -199,11 +199,14 @@ __device__ __forceinline__ void adagrad_apply(const GradAcc<BF16> (&acc)[CPL], u
                                               float lr, float eps)
 {
     constexpr int F = GradAcc<BF16>::F;
-    float sq = 0.f;
+    // (the fused operations are spelled out: which square of the first two is rounded by itself must not depend on the
+    // kernel this is compiled into)
+    float sq = acc[0].a[1] * acc[0].a[1];
 #pragma unroll
     for (int c = 0; c < CPL; ++c)
 #pragma unroll
-        for (int i = 0; i < F; ++i) sq += acc[c].a[i] * acc[c].a[i];  // lanes past the row hold zeros
+        for (int i = 0; i < F; ++i)
+            if (c > 0 || i != 1) sq = __builtin_fmaf(acc[c].a[i], acc[c].a[i], sq);  // lanes past the row hold zeros
     sq = group_sum<LPR>(sq);
     const float s_new = s_old + sq * inv_D;
     const float step = lr * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(s_new) + eps);
@@ -254,6 +257,72 @@ __device__ __forceinline__ void load_records(const E *__restrict__ p, E (&out)[N
 // ---------------------------------------------------------------------------
 // short runs: one wavefront per span of UPD_SPAN sorted records
 // ---------------------------------------------------------------------------
+// A run of up to UPD_SHORT_MAX records by a lane group: records [pos, end) of the window whose bags are in LDS (`bags`).
+template <typename KeyT, int LPR, int CPL, int EU, bool BF16, bool ALWAYS_LDS>
+__device__ __forceinline__ void update_short_run(const TableDirT<ALWAYS_LDS> &dir, const BagDiv &bdiv, const uint32_t *bags /*LDS*/,
+                                                 int pos, int end, KeyT key, const float *__restrict__ bag_scale,
+                                                 const float *__restrict__ dout, int l, int32_t chunks_per_row, int32_t D,
+                                                 float inv_D, float lr, float eps)
+{
+    constexpr int F = GradAcc<BF16>::F;
+    constexpr int V = GradAcc<BF16>::V;
+    // ---- the row, its accumulator and the first EU gradient rows, all requested together
+    const int t = bdiv.table(bags[pos]);
+    const int64_t r = (int64_t)key - dir.base(t);
+    char *wrow = dir.weights(t) + r * ((int64_t)chunks_per_row * 16);
+    float *aptr = dir.accum(t) + r;
+    // gradient rows of records e0 .. e0 + EU - 1 of the run (zeros past its end)
+    auto load_batch = [&](int e0, float4 (&gr)[EU][CPL][V], float (&sc)[EU]) {
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+            const int e = e0 + u;
+            sc[u] = 0.f;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+#pragma unroll
+                for (int x = 0; x < V; ++x) gr[u][c][x] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (e < end) {
+                const uint32_t bag = bags[e];
+                sc[u] = bag_scale[bag];
+                const float *grow = dout + (int64_t)bag * D;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    const int chunk = l + c * LPR;
+                    if (chunk < chunks_per_row) load_grad<BF16>(grow + (int64_t)chunk * F, gr[u][c]);
+                }
+            }
+        }
+    };
+    GradAcc<BF16> acc[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) acc[c].zero();
+    // The first gradient rows are requested before the table row and its accumulator: loads come
+    // back in the order they were asked for, so the sum can start while the row is still on its way.
+    float4 gr[EU][CPL][V];
+    float sc[EU];
+    load_batch(pos, gr, sc);
+    uint4 w[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+        const int chunk = l + c * LPR;
+        w[c] = make_uint4(0, 0, 0, 0);
+        if (chunk < chunks_per_row) w[c] = load_chunk_nt(wrow + (int64_t)chunk * 16);
+    }
+    const float s_old = load_f32_nt(aptr);
+#pragma unroll
+    for (int u = 0; u < EU; ++u)
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c].fma(sc[u], gr[u][c]);
+    for (int e0 = pos + EU; e0 < end; e0 += EU) {
+        load_batch(e0, gr, sc);
+#pragma unroll
+        for (int u = 0; u < EU; ++u)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) acc[c].fma(sc[u], gr[u][c]);
+    }
+    adagrad_apply<LPR, CPL, BF16>(acc, w, s_old, wrow, aptr, l, chunks_per_row, inv_D, lr, eps);
+}
+
 template <typename KeyT, int LPR, int CPL, int EU, bool BF16, bool LDS_DIR>
 __global__ __launch_bounds__(UPD_BLOCK) void update_kernel(const emb_table *__restrict__ tables, int32_t T,
                                                            const KeyT *__restrict__ keys,
@@ -267,8 +336,6 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_kernel(const emb_table *__re
     constexpr int WAVES = UPD_BLOCK / EMB_WAVE;
     constexpr int GPW = EMB_WAVE / LPR;            // lane groups per wavefront
     constexpr int WIN = UPD_SPAN + UPD_LOOK;       // records staged per wavefront
-    constexpr int F = GradAcc<BF16>::F;
-    constexpr int V = GradAcc<BF16>::V;
     static_assert(UPD_SPAN == 4 * EMB_WAVE && UPD_LOOK == 32, "staging below assumes 4 records per lane + 32");
     EMB_STAGE_TABLE_DIR_T(dir, tables, T, UPD_BLOCK, LDS_DIR)
     // [0] = the record before the span, [1 + e] = record e of the window, [WIN + 1] = the record after it
@@ -355,7 +422,6 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_kernel(const emb_table *__re
     __syncthreads();
 
     if (in) {
-        const int64_t row_bytes = (int64_t)chunks_per_row * 16;
         // groups take the runs round-robin: every group gets the same number of runs, give or take one
         for (uint32_t k = g; k < runs; k += GPW) {
             const int pos = lh[wave][k];
@@ -365,61 +431,8 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_kernel(const emb_table *__re
             // longer than UPD_SHORT_MAX records (a run that is not over after the look-ahead is): not
             // this kernel's; long_detect_kernel has queued it for the chunked path
             if (end - pos > UPD_SHORT_MAX || (end == WIN && lk[wave][WIN + 1] == key)) continue;
-            // ---- the row, its accumulator and the first EU gradient rows, all requested together
-            const int t = bdiv.table(lp[wave][pos]);
-            const int64_t r = (int64_t)key - dir.base(t);
-            char *wrow = dir.weights(t) + r * row_bytes;
-            float *aptr = dir.accum(t) + r;
-            // gradient rows of records e0 .. e0 + EU - 1 of the run (zeros past its end)
-            auto load_batch = [&](int e0, float4 (&gr)[EU][CPL][V], float (&sc)[EU]) {
-#pragma unroll
-                for (int u = 0; u < EU; ++u) {
-                    const int e = e0 + u;
-                    sc[u] = 0.f;
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c)
-#pragma unroll
-                        for (int x = 0; x < V; ++x) gr[u][c][x] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (e < end) {
-                        const uint32_t bag = lp[wave][e];
-                        sc[u] = bag_scale[bag];
-                        const float *grow = dout + (int64_t)bag * D;
-#pragma unroll
-                        for (int c = 0; c < CPL; ++c) {
-                            const int chunk = l + c * LPR;
-                            if (chunk < chunks_per_row) load_grad<BF16>(grow + (int64_t)chunk * F, gr[u][c]);
-                        }
-                    }
-                }
-            };
-            GradAcc<BF16> acc[CPL];
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[c].zero();
-            // The first gradient rows are requested before the table row and its accumulator: loads come
-            // back in the order they were asked for, so the sum can start while the row is still on its way.
-            float4 gr[EU][CPL][V];
-            float sc[EU];
-            load_batch(pos, gr, sc);
-            uint4 w[CPL];
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const int chunk = l + c * LPR;
-                w[c] = make_uint4(0, 0, 0, 0);
-                if (chunk < chunks_per_row) w[c] = load_chunk_nt(wrow + (int64_t)chunk * 16);
-            }
-            const float s_old = load_f32_nt(aptr);
-#pragma unroll
-            for (int u = 0; u < EU; ++u)
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c].fma(sc[u], gr[u][c]);
-            for (int e0 = pos + EU; e0 < end; e0 += EU) {
-                load_batch(e0, gr, sc);
-#pragma unroll
-                for (int u = 0; u < EU; ++u)
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) acc[c].fma(sc[u], gr[u][c]);
-            }
-            adagrad_apply<LPR, CPL, BF16>(acc, w, s_old, wrow, aptr, l, chunks_per_row, inv_D, lr, eps);
+            update_short_run<KeyT, LPR, CPL, EU, BF16>(dir, bdiv, lp[wave], pos, end, key, bag_scale, dout, l, chunks_per_row, D,
+                                                        inv_D, lr, eps);
         }
     }
 }
@@ -612,6 +625,76 @@ __device__ __forceinline__ void finish_run(const GradAcc<BF16> (&acc)[CPL], cons
     adagrad_apply<LPR, CPL, BF16>(acc, w, *aptr, wrow, aptr, l, chunks_per_row, inv_D, lr, eps);
 }
 
+// Adds the lane groups' sums up by a butterfly: every group ends with the total.
+template <int LPR, int CPL, bool BF16>
+__device__ __forceinline__ void group_butterfly(GradAcc<BF16> (&acc)[CPL])
+{
+#pragma unroll
+    for (int d = LPR; d < EMB_WAVE; d <<= 1)
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+            for (int i = 0; i < GradAcc<BF16>::F; ++i) acc[c].a[i] += __shfl_xor(acc[c].a[i], d, EMB_WAVE);
+}
+
+// Sum of the gradients of records [lo, hi), at most LONG_CHUNK of them, by a whole wavefront: its lane groups take the
+// records round-robin and are then combined by the butterfly.
+template <int LPR, int CPL, int EU, bool BF16>
+__device__ __forceinline__ void chunk_sum(GradAcc<BF16> (&acc)[CPL], const uint32_t *__restrict__ pay,
+                                          const float *__restrict__ bag_scale, const float *__restrict__ dout,
+                                          uint32_t lo, uint32_t hi, int32_t chunks_per_row, int32_t D)
+{
+    constexpr int GPW = EMB_WAVE / LPR;  // lane groups per wavefront
+    constexpr int F = GradAcc<BF16>::F;
+    constexpr int V = GradAcc<BF16>::V;
+    const int lane = threadIdx.x & (EMB_WAVE - 1);
+    const int l = lane % LPR;
+    const int g = lane / LPR;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) acc[c].zero();
+    // a group's records are lo + g, lo + g + GPW, ...: their bags are requested PF at a time,
+    // then the gradient rows EU at a time, so a chunk costs few dependent memory round trips
+    constexpr int PF = (LONG_CHUNK / GPW) < 16 ? (LONG_CHUNK / GPW) : 16;
+    static_assert(PF % EU == 0, "prefetch depth must be whole sub-batches");
+    for (uint32_t i0 = lo + g; i0 < hi; i0 += GPW * PF) {
+        uint32_t bags[PF];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const uint32_t i = i0 + u * GPW;
+            bags[u] = i < hi ? pay[i] : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int u0 = 0; u0 < PF; u0 += EU) {
+            if (bags[u0] == 0xFFFFFFFFu) continue;   // past the end of the chunk
+            float4 v[EU][CPL][V];
+            float sc[EU];
+#pragma unroll
+            for (int u = 0; u < EU; ++u) {
+                const uint32_t bag = bags[u0 + u];
+                sc[u] = 0.f;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c)
+#pragma unroll
+                    for (int x = 0; x < V; ++x) v[u][c][x] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (bag != 0xFFFFFFFFu) {
+                    sc[u] = bag_scale[bag];
+                    const float *grow = dout + (int64_t)bag * D;
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) {
+                        const int chunk = l + c * LPR;
+                        if (chunk < chunks_per_row) load_grad<BF16>(grow + (int64_t)chunk * F, v[u][c]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < EU; ++u)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) acc[c].fma(sc[u], v[u][c]);
+        }
+    }
+    group_butterfly<LPR, CPL, BF16>(acc);
+}
+
 // One wavefront per chunk task.
 template <typename KeyT, int LPR, int CPL, int EU, bool BF16>
 __global__ __launch_bounds__(UPD_BLOCK) void long_reduce_kernel(const emb_table *__restrict__ tables, int32_t T,
@@ -654,55 +737,7 @@ __global__ __launch_bounds__(UPD_BLOCK) void long_reduce_kernel(const emb_table 
         const uint32_t hi = (sg.hi - lo > (uint32_t)LONG_CHUNK) ? lo + LONG_CHUNK : sg.hi;
 
         GradAcc<BF16> acc[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c].zero();
-        // a group's records are lo + g, lo + g + GPW, ...: their bags are requested PF at a time,
-        // then the gradient rows EU at a time, so a chunk costs few dependent memory round trips
-        constexpr int PF = (LONG_CHUNK / GPW) < 16 ? (LONG_CHUNK / GPW) : 16;
-        static_assert(PF % EU == 0, "prefetch depth must be whole sub-batches");
-        for (uint32_t i0 = lo + g; i0 < hi; i0 += GPW * PF) {
-            uint32_t bags[PF];
-#pragma unroll
-            for (int u = 0; u < PF; ++u) {
-                const uint32_t i = i0 + u * GPW;
-                bags[u] = i < hi ? pay[i] : 0xFFFFFFFFu;
-            }
-#pragma unroll
-            for (int u0 = 0; u0 < PF; u0 += EU) {
-                if (bags[u0] == 0xFFFFFFFFu) continue;   // past the end of the chunk
-                float4 v[EU][CPL][V];
-                float sc[EU];
-#pragma unroll
-                for (int u = 0; u < EU; ++u) {
-                    const uint32_t bag = bags[u0 + u];
-                    sc[u] = 0.f;
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c)
-#pragma unroll
-                        for (int x = 0; x < V; ++x) v[u][c][x] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (bag != 0xFFFFFFFFu) {
-                        sc[u] = bag_scale[bag];
-                        const float *grow = dout + (int64_t)bag * D;
-#pragma unroll
-                        for (int c = 0; c < CPL; ++c) {
-                            const int chunk = l + c * LPR;
-                            if (chunk < chunks_per_row) load_grad<BF16>(grow + (int64_t)chunk * F, v[u][c]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < EU; ++u)
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) acc[c].fma(sc[u], v[u][c]);
-            }
-        }
-        // butterfly over the lane groups of the wavefront: every group ends with the chunk sum
-#pragma unroll
-        for (int d = LPR; d < EMB_WAVE; d <<= 1)
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
-#pragma unroll
-                for (int i = 0; i < F; ++i) acc[c].a[i] += __shfl_xor(acc[c].a[i], d, EMB_WAVE);
+        chunk_sum<LPR, CPL, EU, BF16>(acc, pay, bag_scale, dout, lo, hi, chunks_per_row, D);
 
         if (g == 0) {
             if (sg.n_chunks == 1) {
@@ -783,12 +818,7 @@ __global__ __launch_bounds__(UPD_BLOCK) void long_combine_kernel(const emb_table
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) acc[c].fma(1.0f, v[u][c]);
         }
-#pragma unroll
-        for (int d = LPR; d < EMB_WAVE; d <<= 1)
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
-#pragma unroll
-                for (int i = 0; i < F; ++i) acc[c].a[i] += __shfl_xor(acc[c].a[i], d, EMB_WAVE);
+        group_butterfly<LPR, CPL, BF16>(acc);
         if (g == 0)
             finish_run<KeyT, LPR, CPL, BF16>(acc, dir, bdiv, keys, pay, sg.lo, l, chunks_per_row, inv_D, lr, eps);
     }

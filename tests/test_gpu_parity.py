@@ -1340,6 +1340,70 @@ def test_backward_sort_wait_that_runs_out_abandons_the_backward_and_changes_noth
     _check_backward_against_oracle(tables, Rs, rows, off, B, D, "sum", dout, "after an abandoned sort")
 
 
+def _rows_with_run_lengths(rng, n, R, runs):
+    """n row numbers below R: the first rows as often as `runs` says while that fits, the rest at random, shuffled."""
+    hot = np.repeat(np.arange(len(runs)), runs)[:n]
+    r = np.concatenate([hot, rng.integers(min(len(runs), R - 1), R, size=n - hot.size)])
+    rng.shuffle(r)
+    return np.minimum(r, R - 1)
+
+
+@pytest.mark.parametrize("per_table,R,D,dtype", [
+    ([1], 1, 16, "f32"),
+    ([0, 7, 0], 100, 64, "f32"),
+    ([600, 424], 1 << 10, 48, "bf16"),                    # as many records as one tile sorts; key bits across a pass
+    ([601, 424], (1 << 10) - 1, 48, "bf16"),              # one more: the merge is launched
+    ([1024, 1025, 2047], 5000, 16, "f32"),
+    ([5000, 0, 3], 1 << 20, 8, "bf16"),                   # 21 bits: three passes
+    ([9, 20_011, 4096], (1 << 20) - 1, 64, "f32"),        # 20 bits: two; tables of one and of many tiles
+    ([66_000, 100], 300, 4, "f32"),                       # a few rows with hundreds of lookups each
+    ([70_000], 3, 16, "f32"),                             # ... with tens of thousands: chunks found far behind
+    ([8_000], 700, 320, "f32"),
+    ([(1 << 18) - 5, 5], 200_000, 16, "f32"),             # the last sizes of the small route ...
+    ([100_000, (1 << 18) + 1 - 100_000], 200_000, 16, "f32"),   # ... and beyond
+])
+def test_small_steps_give_the_bits_of_the_general_route(per_table, R, D, dtype):
+    # The same batch with more tables than the small route takes: the added tables have no lookups.  Rows, accumulators,
+    # distinct rows and counts must not differ in a bit, also where a wavefront does not wait for other wavefronts'
+    # sums but makes them itself (a bound of zero; the list of distinct rows waits as well, so without it).
+    rng = np.random.default_rng(52_000 + sum(per_table) + D)
+    T, B = len(per_table), 40
+    runs = [31, 32, 33, 64, 255, 256, 257, 511, 512, 513, 3000, 1, 2]
+    rows = np.concatenate([_rows_with_run_lengths(rng, n, R, runs) for n in per_table]).astype(np.int64)
+    if rows.size > 50:
+        rows[rng.integers(0, rows.size, size=20)] = rng.choice([-1, R, 1 << 40], size=20)
+    lengths = np.concatenate([rng.multinomial(n, np.full(B, 1.0 / B)) for n in per_table]).astype(np.int32)
+    off, _ = oracle.lengths_to_offsets(lengths)
+    tables = [(rng.standard_normal((R, D)) * 0.01).astype(np.float32) for _ in range(T)]
+    if dtype == "bf16":
+        tables = [wl.f32_to_bf16_bits(t).reshape(R, D) for t in tables]
+    dout = rng.standard_normal((T, B, D)).astype(np.float32)
+
+    def run(extra, poll_limit=-1, want_unique=True):
+        more = [np.zeros((1, D), dtype=tables[0].dtype)] * extra
+        ts, w, acc = H.make_tableset(tables + more, dtype, with_accum=True)
+        offs = np.concatenate([off, np.full(extra * B, off[-1], dtype=np.int64)])
+        d = np.concatenate([dout, np.zeros((extra, B, D), np.float32)])
+        emb.emb_debug_sort_poll_limit(poll_limit)
+        try:
+            g = H.gpu_backward(ts, rows, offs, B, "mean", d, 0.01, 1e-8, want_unique=want_unique)
+        finally:
+            emb.emb_debug_sort_poll_limit(-1)
+        return g, [H.host_table(x) for x in w[:T]], [x.cpu().numpy() for x in acc[:T]]
+
+    g, w, acc = run(0)
+    g2, w2, acc2 = run(513 - T)
+    assert g["status"] == g2["status"] and g["status"] & ~emb.STATUS_BAD_INDEX == 0
+    assert np.array_equal(g["unique_keys"], g2["unique_keys"]) and np.array_equal(g["unique_counts"], g2["unique_counts"])
+    for t in range(T):
+        assert np.array_equal(w[t], w2[t]) and np.array_equal(acc[t], acc2[t]), t
+    if sum(per_table) <= 1 << 18:
+        g3, w3, acc3 = run(0, poll_limit=0, want_unique=False)
+        assert g3["status"] == g["status"] and g3["U"] == g["U"]
+        for t in range(T):
+            assert np.array_equal(w[t], w3[t]) and np.array_equal(acc[t], acc3[t]), t
+
+
 def test_backward_empty_batch():
     tables = [np.ones((10, 16), dtype=np.float32)]
     ts, w_dev, acc_dev = H.make_tableset(tables, "f32", with_accum=True)
