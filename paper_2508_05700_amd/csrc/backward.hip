@@ -36,7 +36,7 @@ namespace {
 // workspace
 // ---------------------------------------------------------------------------
 struct BwdLayout {
-    size_t ctrl, keys_a, keys_b, pay_a, pay_b, bag_scale, first_tile, tile_desc, hist, sort_flags, tile_heads, seg_start, seg_real,
+    size_t ctrl, keys_a, keys_b, pay_a, pay_b, bag_scale, first_tile, tile_desc, hist, sort_flags, tile_heads,
         local_offsets, tile_prefix,
         queue, queue_end, span_head, wave_heads, segs, multi_list, chunk_tasks, partials, total;
     int key_bytes;
@@ -98,8 +98,6 @@ inline BwdLayout bwd_layout(int32_t T, int64_t B, int64_t nnz, int64_t total_row
     L.hist = off;        off += align256((size_t)max_passes * (L.tiles + 1) * RADIX * 4);
     L.sort_flags = off;  off += align256((size_t)(max_passes - 1) * L.tiles * RADIX * 8);
     L.tile_heads = off;  off += align256((size_t)L.flat_tiles * 8);    // one exchange word per tile (runs_list_kernel)
-    L.seg_start = off;   off += align256((n + 1) * 4);
-    L.seg_real = off;    off += align256(n * 4);
     L.queue = off;       off += align256((size_t)L.qslots * 4);
     L.queue_end = off;   off += align256((size_t)L.qslots * 4);
     L.span_head = off;   off += align256((size_t)L.slots * 4);
@@ -257,28 +255,23 @@ __global__ __launch_bounds__(256) void bwd_keys_kernel(const emb_table *__restri
 // ---------------------------------------------------------------------------
 // Invalid rows leave sentinel records at the end of their table's range, i.e.
 // between the runs of two tables.  Every change of key starts a run; runs of the
-// sentinel are numbered with the others (their start ends the run before them)
-// but are not rows: seg_real maps a run to its place in the list of distinct rows.
-// One launch numbers the runs.  A tile (SORT_TILE records of the sorted array, whatever table they belong
-// to) counts its run starts and row starts, and learns how many lie in the tiles before it from those tiles
+// sentinel end the run before them, but are not rows.
+// One launch lists the rows.  A tile (SORT_TILE records of the sorted array, whatever table they belong
+// to) counts the rows that start in it, and learns how many lie in the tiles before it from those tiles
 // themselves: the exchange of the sort's scatters (radix_sort.h: a count, then a prefix, in one flagged word;
-// bounded waits for tiles with smaller numbers only).  Here a tile has one word that holds both numbers
-// (31 bits each: there are fewer than 2^31 records), and the tile's first wavefront walks back
+// bounded waits for tiles with smaller numbers only).  Here a tile has one word, and its first wavefront walks back
 // RUNS_WINDOWS * 64 tiles per round trip to memory: lane l requests the words of tiles t - l, t - 64 - l, ...
-// together, then the windows are added up nearest first until one holds a tile that knows its prefix.
-// flags: [tiles], cleared by the sort's first counting launch.
+// together, then the windows are added up nearest first until one holds a tile that knows its prefix.  How often a row
+// occurs is the way to the next run start: in the tile, or, for the tile's last run, looked for after it by the whole
+// workgroup, SORT_BLOCK records at a time (a second launch over all runs cost 6 us, and 1.5 us between the two).
+// flags: [tiles], cleared by the sort's first launch.
 constexpr int RUNS_WINDOWS = 4;
-__device__ __forceinline__ unsigned long long runs_pack(uint32_t runs, uint32_t rows)
-{
-    return ((unsigned long long)runs << 31) | rows;
-}
-__device__ __forceinline__ bool runs_lookback(unsigned long long *flags, uint32_t me, uint32_t count_runs,
-                                              uint32_t count_rows, uint32_t poll_limit, uint32_t &before_runs,
-                                              uint32_t &before_rows)
+__device__ __forceinline__ bool runs_lookback(unsigned long long *flags, uint32_t me, uint32_t count, uint32_t poll_limit,
+                                              uint32_t &before)
 {
     const int lane = threadIdx.x & (EMB_WAVE - 1);
-    if (lane == 0) sort_flag_store(flags + me, SORT_FLAG_COUNT | runs_pack(count_runs, count_rows));
-    uint32_t sum_runs = 0, sum_rows = 0;
+    if (lane == 0) sort_flag_store(flags + me, SORT_FLAG_COUNT | count);
+    uint32_t sum = 0;
     bool done = false, ok = true;   // the same in all lanes
     for (int64_t t = (int64_t)me - 1; !done; t -= RUNS_WINDOWS * EMB_WAVE) {
         unsigned long long x[RUNS_WINDOWS];
@@ -311,32 +304,23 @@ __device__ __forceinline__ bool runs_lookback(unsigned long long *flags, uint32_
                 done = true;
                 break;
             }
-            uint32_t r = lane <= stop ? (uint32_t)((v >> 31) & 0x7FFFFFFFu) : 0u;
-            uint32_t q = lane <= stop ? (uint32_t)(v & 0x7FFFFFFFu) : 0u;
+            uint32_t q = lane <= stop ? (uint32_t)v : 0u;
 #pragma unroll
-            for (int d = EMB_WAVE >> 1; d >= 1; d >>= 1) {
-                r += (uint32_t)__shfl_xor((int)r, d, EMB_WAVE);
-                q += (uint32_t)__shfl_xor((int)q, d, EMB_WAVE);
-            }
-            sum_runs += r;
-            sum_rows += q;
+            for (int d = EMB_WAVE >> 1; d >= 1; d >>= 1) q += (uint32_t)__shfl_xor((int)q, d, EMB_WAVE);
+            sum += q;
             if (prefix) done = true;
         }
     }
-    if (lane == 0)
-        sort_flag_store(flags + me, ok ? (SORT_FLAG_PREFIX | runs_pack(sum_runs + count_runs, sum_rows + count_rows))
-                                       : SORT_FLAG_FAILED);
-    before_runs = sum_runs;
-    before_rows = sum_rows;
+    if (lane == 0) sort_flag_store(flags + me, ok ? (SORT_FLAG_PREFIX | (uint32_t)(sum + count)) : SORT_FLAG_FAILED);
+    before = sum;
     return ok;
 }
 
 template <typename KeyT>
 __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__restrict__ keys, uint32_t n, KeyT sentinel,
                                                                unsigned long long *__restrict__ flags, uint32_t tiles,
-                                                               uint32_t *__restrict__ seg_start,
-                                                               uint32_t *__restrict__ seg_real,
-                                                               int64_t *__restrict__ unique_keys_out, BwdCtrl *ctrl,
+                                                               int64_t *__restrict__ unique_keys_out,
+                                                               int32_t *__restrict__ unique_counts_out, BwdCtrl *ctrl,
                                                                int64_t *num_unique_out, uint32_t poll_limit,
                                                                uint32_t *status)
 {
@@ -344,13 +328,14 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
         if (threadIdx.x == 0) sort_flag_store(flags + blockIdx.x, SORT_FLAG_FAILED);
         return;
     }
-    __shared__ unsigned long long wave_sums[SORT_WAVES];
-    __shared__ unsigned long long tile_before;   // runs in the high half, rows in the low half
-    __shared__ uint32_t lookback_failed;
-    // the tile's runs in order: where each starts, and its place among the rows (NO_ROW: the marker's run)
-    __shared__ uint32_t run_pos[SORT_TILE];
-    __shared__ uint32_t run_row[SORT_TILE];
-    constexpr uint32_t NO_ROW = 0xFFFFFFFFu;
+    __shared__ uint32_t wave_sums[SORT_WAVES];
+    __shared__ uint32_t rows_before, lookback_failed, after;
+    // the tile's runs in order: where each starts (and, after them, where the last one ends), and its place among the
+    // tile's rows (NO_ROW: the marker's run)
+    __shared__ uint32_t run_pos[SORT_TILE + 1];
+    __shared__ uint16_t run_row[SORT_TILE];
+    constexpr uint32_t NO_ROW = 0xFFFFu;
+    static_assert(SORT_TILE < 0xFFFF, "runs and rows of a tile are counted in 16 bits each");
     // a thread looks at SORT_ITEMS consecutive records (the arrays carry SORT_PAD records of slack; what
     // lies past n is not looked at) and at the record before them
     const uint32_t base = blockIdx.x * SORT_TILE + threadIdx.x * SORT_ITEMS;
@@ -360,38 +345,39 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
         load_records<KeyT, SORT_ITEMS>(keys + base, k);
         if (base > 0) prev = keys[base - 1];
     }
-    unsigned long long f[SORT_ITEMS], c = 0;
+    uint32_t f[SORT_ITEMS], c = 0;
 #pragma unroll
     for (int e = 0; e < SORT_ITEMS; ++e) {
         const uint32_t i = base + e;
-        f[e] = 0ull;
+        f[e] = 0u;
         if (i < n && (i == 0 || k[e] != (e == 0 ? prev : k[e - 1])))
-            f[e] = (1ull << 32) | (k[e] != sentinel ? 1ull : 0ull);   // high half: runs, low half: rows
+            f[e] = (1u << 16) | (k[e] != sentinel ? 1u : 0u);   // high half: runs, low half: rows
         c += f[e];
     }
-    unsigned long long total;
-    const unsigned long long inc = block_inclusive_scan<unsigned long long, SORT_BLOCK>(c, wave_sums, total);
+    uint32_t total;
+    const uint32_t inc = block_inclusive_scan<uint32_t, SORT_BLOCK>(c, wave_sums, total);
+    const uint32_t tile_runs = total >> 16, tile_rows = total & 0xFFFFu;
     // the tile's runs go to LDS in order while the first wavefront asks the earlier tiles
     {
-        unsigned long long at = inc - c;
-        uint32_t v = (uint32_t)(at >> 32), u = (uint32_t)at;
+        const uint32_t at = inc - c;
+        uint32_t v = at >> 16, u = at & 0xFFFFu;
 #pragma unroll
         for (int e = 0; e < SORT_ITEMS; ++e) {
             if (f[e]) {
-                const bool real = (f[e] & 1ull) != 0;
+                const bool real = (f[e] & 1u) != 0;
                 run_pos[v] = base + e;
-                run_row[v] = real ? u : NO_ROW;
+                run_row[v] = (uint16_t)(real ? u : NO_ROW);
                 u += real ? 1u : 0u;
                 ++v;
             }
         }
     }
+    if (threadIdx.x == 0) after = n;
     if (threadIdx.x < EMB_WAVE) {
-        uint32_t runs_before = 0, rows_before = 0;
-        const bool ok = runs_lookback(flags, blockIdx.x, (uint32_t)(total >> 32), (uint32_t)total, poll_limit,
-                                      runs_before, rows_before);
+        uint32_t before = 0;
+        const bool ok = runs_lookback(flags, blockIdx.x, tile_rows, poll_limit, before);
         if (threadIdx.x == 0) {
-            tile_before = ((unsigned long long)runs_before << 32) | rows_before;
+            rows_before = before;
             lookback_failed = ok ? 0u : 1u;
         }
     }
@@ -403,34 +389,28 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
         }
         return;
     }
-    const uint32_t v0 = (uint32_t)(tile_before >> 32), u0 = (uint32_t)tile_before;
-    const uint32_t tile_runs = (uint32_t)(total >> 32);
+    // the end of the tile's last run: the first record after the tile that has another key
+    if (unique_counts_out && tile_runs > 0) {   // uniform
+        const KeyT last = keys[run_pos[tile_runs - 1]];
+        for (uint32_t i0 = (blockIdx.x + 1) * SORT_TILE; i0 < n; i0 += SORT_BLOCK) {   // uniform
+            const uint32_t i = i0 + threadIdx.x;
+            if (i < n && keys[i] != last) atomicMin(&after, i);
+            __syncthreads();
+            if (after < i0 + SORT_BLOCK) break;   // (a smaller one than the first found here is not found later)
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) run_pos[tile_runs] = after;
+        __syncthreads();
+    }
+    const uint32_t u0 = rows_before;
     for (uint32_t i = threadIdx.x; i < tile_runs; i += SORT_BLOCK) {   // consecutive lanes, consecutive entries
         const uint32_t pos = run_pos[i], row = run_row[i];
-        seg_start[v0 + i] = pos;
-        seg_real[v0 + i] = row == NO_ROW ? NO_ROW : u0 + row;
-        if (row != NO_ROW && unique_keys_out) unique_keys_out[u0 + row] = (int64_t)keys[pos];
+        if (row == NO_ROW) continue;
+        if (unique_keys_out) unique_keys_out[u0 + row] = (int64_t)keys[pos];
+        if (unique_counts_out) unique_counts_out[u0 + row] = (int32_t)(run_pos[i + 1] - pos);
     }
-    if (blockIdx.x == tiles - 1 && threadIdx.x == 0) {   // the last tile knows the totals
-        const unsigned long long all = tile_before + total;
-        const uint32_t runs = (uint32_t)(all >> 32);
-        ctrl->num_runs = runs;
-        seg_start[runs] = n;   // the last run ends with the records
-        if (num_unique_out) *num_unique_out = (int64_t)(uint32_t)all;
-    }
-}
-
-__global__ __launch_bounds__(256) void runs_counts_kernel(const uint32_t *__restrict__ seg_start,
-                                                          const uint32_t *__restrict__ seg_real,
-                                                          int32_t *__restrict__ unique_counts_out,
-                                                          const BwdCtrl *ctrl)
-{
-    if (ctrl->abort) return;
-    const uint32_t runs = ctrl->num_runs;
-    for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < runs; v += gridDim.x * 256) {
-        const uint32_t u = seg_real[v];
-        if (u != 0xFFFFFFFFu) unique_counts_out[u] = (int32_t)(seg_start[v + 1] - seg_start[v]);
-    }
+    // the last tile knows the total
+    if (blockIdx.x == tiles - 1 && threadIdx.x == 0 && num_unique_out) *num_unique_out = (int64_t)(u0 + tile_rows);
 }
 
 // ---------------------------------------------------------------------------
@@ -622,8 +602,6 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     uint32_t *hist = reinterpret_cast<uint32_t *>(a.ws + L.hist);
     unsigned long long *sort_flags = reinterpret_cast<unsigned long long *>(a.ws + L.sort_flags);
     unsigned long long *tile_heads = reinterpret_cast<unsigned long long *>(a.ws + L.tile_heads);
-    uint32_t *seg_start = reinterpret_cast<uint32_t *>(a.ws + L.seg_start);
-    uint32_t *seg_real = reinterpret_cast<uint32_t *>(a.ws + L.seg_real);
     const KeyT sentinel = (KeyT)a.total_rows;       // after the sort
     const KeyT local_sentinel = (KeyT)a.max_rows;   // during it
     const uint32_t n = (uint32_t)a.nnz;
@@ -754,15 +732,8 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     if (want_list) {
         // (the update counts the distinct rows again on its own: ctrl->num_unique is not touched here)
         hipLaunchKernelGGL(runs_list_kernel<KeyT>, dim3(flat_tiles), dim3(SORT_BLOCK), 0, s, kin, n, sentinel, tile_heads,
-                           flat_tiles, seg_start, seg_real, a.unique_keys_out, ctrl, a.num_unique_out, poll_limit,
-                           a.status);
+                           flat_tiles, a.unique_keys_out, a.unique_counts_out, ctrl, a.num_unique_out, poll_limit, a.status);
         EMB_RETURN_IF_LAUNCH_FAILED();
-        if (a.unique_counts_out) {
-            const unsigned cgrid = (unsigned)(flat_tiles < 1024 ? flat_tiles : 1024);
-            hipLaunchKernelGGL(runs_counts_kernel, dim3(cgrid), dim3(256), 0, s, seg_start, seg_real,
-                               a.unique_counts_out, ctrl);
-            EMB_RETURN_IF_LAUNCH_FAILED();
-        }
     }
 
     EMB_MARK(a, 3);
@@ -897,7 +868,6 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
             if (bag == (int64_t)T * B - 1) {
                 table_start[T] = e;
                 ctrl->abort = e != nnz ? 1u : 0u;
-                ctrl->num_runs = 0;
                 ctrl->num_unique = 0;
                 ctrl->task_and_multi_count = 0ull;
                 if (e != nnz) emb_flag(status, EMB_STATUS_BAD_OFFSETS);

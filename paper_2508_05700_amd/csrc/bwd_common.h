@@ -4,8 +4,7 @@
 
 struct BwdCtrl {
     uint32_t abort;        // offsets are not a partition of [0, nnz): do nothing
-    uint32_t num_runs;     // runs of equal keys, those of the sentinel included (distinct-row list only)
-    uint32_t reserved0;
+    uint32_t reserved[2];
     uint32_t num_unique;   // U
     unsigned long long task_and_multi_count;  // low half: chunk tasks; high half: queued runs of several chunks
     uint32_t pad[58];

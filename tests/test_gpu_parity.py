@@ -1404,6 +1404,22 @@ def test_small_steps_give_the_bits_of_the_general_route(per_table, R, D, dtype):
             assert np.array_equal(w[t], w3[t]) and np.array_equal(acc[t], acc3[t]), t
 
 
+@pytest.mark.parametrize("counts,bad", [
+    ([4096], 0), ([4095, 1], 0), ([4097], 0), ([1, 4095, 4096], 0), ([8192, 3], 0), ([5, 12_283, 4096, 1, 1], 0),
+    ([4096], 4096), ([4090], 5000), ([1, 20_000], 3), ([], 9000),
+])
+def test_distinct_rows_whose_lookups_end_around_a_tile_of_the_list(counts, bad):
+    # a tile of the list is 4096 sorted records; `bad` invalid lookups follow the rows
+    T, B, D, R = 1, 7, 4, 10
+    rows = np.concatenate([np.repeat(np.arange(len(counts)), counts), np.full(bad, -1)]).astype(np.int64)
+    np.random.default_rng(77 + rows.size).shuffle(rows)
+    off = np.linspace(0, rows.size, T * B + 1).astype(np.int64)
+    ts, _, _ = H.make_tableset([np.zeros((R, D), np.float32)], "f32", with_accum=True)
+    g = H.gpu_backward(ts, rows, off, B, "sum", np.ones((T, B, D), np.float32), 0.01, 1e-8)
+    assert g["status"] == (emb.STATUS_BAD_INDEX if bad else 0)
+    assert g["unique_keys"].tolist() == list(range(len(counts))) and g["unique_counts"].tolist() == counts
+
+
 def test_backward_empty_batch():
     tables = [np.ones((10, 16), dtype=np.float32)]
     ts, w_dev, acc_dev = H.make_tableset(tables, "f32", with_accum=True)
