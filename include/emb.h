@@ -231,7 +231,7 @@ int emb_event_elapsed_ms(void *start, void *stop, float *ms_out);
  * the key build, the sort, the optional list of distinct rows, the short-run
  * update and the long-run path, for callers that time the stages.
  * side (host, nullable): see emb_side_stream; NULL runs everything on
- * `stream`, as a batch of few lookups (2^18 at most) does in any case.
+ * `stream`, as a batch of few lookups (2^20 at most) does in any case.
  * Results do not depend on it. */
 int emb_bag_backward_rowwise_adagrad(const emb_table *tables_host, const emb_table *tables_dev,
                                      int32_t T, int32_t D, int32_t dtype,

@@ -15,8 +15,8 @@
 //            order) and Adagrad is applied once to its row              (update.h)
 //   runs     only when the caller asks for the list of distinct rows: head
 //            flags, scan and compaction into unique keys and counts
-// Small steps (small_step, bwd_common.h), whose launches would each be shorter than the way from one to the next, take
-// fewer of them: tile_merge_sort.h and update_spans.h.  The sorted records and the sums are the same bit for bit.
+// Small steps (small_step and spans_step, bwd_common.h), whose launches would each be shorter than the way from one to
+// the next, take fewer of them: tile_merge_sort.h and update_spans.h.  The sorted records and the sums are the same bit for bit.
 // The payload carried through the sort is the bag number: lookups of one row
 // are then ordered by bag, which is ascending lookup order except between
 // duplicates inside one bag, whose gradient terms are identical.  Every sum is
@@ -427,6 +427,7 @@ struct BwdArgs {
     int key_bits = 1; // of max_rows, the value that marks an invalid row
     int passes = 1;   // of the sort: enough for key_bits
     bool small = false;   // small_step
+    bool spans = false;   // spans_step: the update is update_spans_kernel's
     const float *dout = nullptr;
     float lr = 0.f, eps = 0.f;
     char *ws = nullptr;
@@ -446,7 +447,7 @@ struct BwdArgs {
         return EMB_OK;
     }
 };
-// What a small step keeps where a larger one has its tile descriptors and its spans' first run starts.
+// What a small step keeps where others have the sort's tile descriptors and the first run starts of update.h's spans.
 inline int64_t *table_start_of(const BwdArgs &a, const BwdLayout &L) { return reinterpret_cast<int64_t *>(a.ws + L.tile_desc); }
 inline uint32_t *span_flags_of(const BwdArgs &a, const BwdLayout &L) { return reinterpret_cast<uint32_t *>(a.ws + L.span_head); }
 inline bool small_step_merges(const BwdArgs &a) { return a.nnz > MERGE_TILE; }   // else no table has more than one tile
@@ -541,20 +542,12 @@ int launch_update(const BwdArgs &a, const BwdLayout &L, const KeyT *keys, const 
     EMB_MARK(a, 4);
 
     const int64_t pthreads = L.qslots > L.slots ? L.qslots : L.slots;
-    // Beside update_kernel a workgroup of sixteen wavefronts waits for a whole free CU, one of four starts at once.  In a
-    // large step the wait is worth having: it keeps long_reduce_kernel away from the update until the update drains
-    // (2.6e6 lookups: reduce 35 us and update 219, with four wavefronts 134 and 239 because both then run at once for
-    // the reduce's whole length, traces of two cards).  Up to some 1.3e6 lookups the two are within 1 % of each other,
-    // four wavefronts ahead from 9e5 on.  Steps in us, four / sixteen wavefronts, in turn on one card: 30 720 lookups
-    // 100.3 / 101.0 (spread 5 %), 148 687 bf16 120.3 / 120.4, 655 360 158.1 / 157.2, 983 040 196.6 / 197.2, 1.15e6
-    // 220.9 / 221.6, 1.31e6 234.3 / 236.2, 1.97e6 313.1 / 307.4, 2.62e6 403.4 / 394.9.
-#define EMB_PREPARE(BLOCK)                                                                                              \
-    hipLaunchKernelGGL(long_prepare_kernel<BLOCK>, dim3((unsigned)((pthreads + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, ls, n, \
-                       ctrl, queue, queue_end, (uint32_t)L.qslots, span_head, wave_heads, (uint32_t)L.slots, segs,     \
-                       multi_list, chunk_tasks, (uint32_t)L.chunk_cap)
-    if (a.nnz <= PREP_SMALL_MAX) EMB_PREPARE(PREP_BLOCK);
-    else EMB_PREPARE(PREP_BLOCK_LARGE);
-#undef EMB_PREPARE
+    // A workgroup of sixteen wavefronts waits beside update_kernel until a CU is free, which is worth having: it keeps
+    // long_reduce_kernel away from the update until the update drains (2.6e6 lookups: reduce 35 us and update 219, with
+    // workgroups of four wavefronts 134 and 239 because both then run at once for the reduce's whole length).
+    hipLaunchKernelGGL(long_prepare_kernel, dim3((unsigned)((pthreads + PREP_BLOCK - 1) / PREP_BLOCK)), dim3(PREP_BLOCK), 0, ls, n,
+                       ctrl, queue, queue_end, (uint32_t)L.qslots, span_head, wave_heads, (uint32_t)L.slots, segs, multi_list,
+                       chunk_tasks, (uint32_t)L.chunk_cap);
     EMB_RETURN_IF_LAUNCH_FAILED();
 
     // one wavefront per task; enough workgroups to fill the chip, tasks beyond that are strided over
@@ -643,6 +636,8 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     // first counting launch
     const bool want_list = a.unique_keys_out || a.unique_counts_out;
     unsigned long long *list_flags = want_list ? tile_heads : nullptr;
+    uint32_t *span_flags = a.spans ? span_flags_of(a, L) : nullptr;   // those of update_spans_kernel are cleared with them
+    const uint32_t n_span_flags = (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK);
     const int passes = a.small ? 0 : a.passes;
     const bool exchange = !a.small && a.nnz <= (int64_t)SORT_EXCHANGE_MAX_TILES * SORT_TILE * (a.T > 0 ? a.T : 1);
     const uint32_t poll_limit = sort_poll_limit;
@@ -655,7 +650,7 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
 #define EMB_TILE_SORT(BITS, LAST)                                                                                          \
     hipLaunchKernelGGL((tile_sort_kernel<BITS, LAST>), dim3((unsigned)(n / MERGE_TILE + a.T)), dim3(MERGE_BLOCK), 0, s, keys_a, pay_a, keys_b, pay_b,   \
                        table_start, a.T, passes_in_lds, a.tables_dev, local_sentinel, sentinel, list_flags, flat_tiles,    \
-                       span_flags_of(a, L), (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK), ctrl)
+                       span_flags, n_span_flags, ctrl)
 #define EMB_TILE_SORT_BITS(BITS)              \
     if (merges) EMB_TILE_SORT(BITS, false);   \
     else EMB_TILE_SORT(BITS, true);           \
@@ -683,7 +678,8 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
             const int np = a.passes - p0 < 4 ? a.passes - p0 : 4;
 #define EMB_SORT_HIST(NP)                                                                                          \
     hipLaunchKernelGGL((sort_hist_kernel<KeyT, NP>), dim3(tiles), dim3(SORT_BLOCK), 0, s, kin, tile_desc, p0, hist, \
-                       tiles, fl, a.passes - 1, p0 == 0 ? list_flags : nullptr, flat_tiles, ctrl)
+                       tiles, fl, a.passes - 1, p0 == 0 ? list_flags : nullptr, flat_tiles, \
+                       p0 == 0 ? span_flags : nullptr, n_span_flags, ctrl)
             switch (np) {
                 case 1: EMB_SORT_HIST(1); break;
                 case 2: EMB_SORT_HIST(2); break;
@@ -705,7 +701,8 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
         const bool last = p == passes - 1;
         if (!exchange) {
             hipLaunchKernelGGL((sort_hist_kernel<KeyT, 1>), dim3(tiles), dim3(SORT_BLOCK), 0, s, kin, tile_desc, p, hist,
-                               tiles, (unsigned long long *)nullptr, 0, p == 0 ? list_flags : nullptr, flat_tiles, ctrl);
+                               tiles, (unsigned long long *)nullptr, 0, p == 0 ? list_flags : nullptr, flat_tiles,
+                               p == 0 ? span_flags : nullptr, n_span_flags, ctrl);
             EMB_RETURN_IF_LAUNCH_FAILED();
             hipLaunchKernelGGL(sort_scan_kernel, dim3(SORT_SCAN_BLOCKS), dim3(SCAN_BLOCK_THREADS), 0, s, hp, tiles, ctrl);
             EMB_RETURN_IF_LAUNCH_FAILED();
@@ -758,7 +755,7 @@ int run_update(const BwdArgs &a, const BwdLayout &L)
     const bool bf16 = a.dtype == EMB_BF16;
 #define EMB_UPD(LL, C, EU)                                                                   \
     if constexpr (sizeof(KeyT) == 4) {                                                       \
-        if (a.small)                                                                         \
+        if (a.spans)                                                                         \
             return bf16 ? launch_update_spans<LL, C, EU, true>(a, L, kin, pin, chunks)       \
                         : launch_update_spans<LL, C, EU, false>(a, L, kin, pin, chunks);     \
     }                                                                                        \
@@ -1031,6 +1028,7 @@ int bwd_plan(const emb_table *tables_host, const emb_table *tables_dev, int32_t 
     a.key_bits = bits < 1 ? 1 : bits;
     a.passes = passes;
     a.small = small_step(T, nnz, L.key_bytes);
+    a.spans = spans_step(T, nnz, L.key_bytes);
     a.ws = reinterpret_cast<char *>(workspace_dev);
     a.stream = emb_stream(stream);
     return EMB_OK;

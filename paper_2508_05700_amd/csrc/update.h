@@ -526,9 +526,8 @@ __global__ __launch_bounds__(256) void long_detect_kernel(const KeyT *__restrict
 // (queue_end), else at the first run start of the spans after it, which the
 // wavefront looks up together, 64 spans per round trip.
 // The kernel is launched beside update_kernel, whose workgroups of two wavefronts take every place that comes
-// free; launch_update says which size of workgroup (BLOCK) it has when.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void long_prepare_kernel(uint32_t n, BwdCtrl *ctrl,
+// free; launch_update says what the size of its workgroups does there.
+__global__ __launch_bounds__(PREP_BLOCK) void long_prepare_kernel(uint32_t n, BwdCtrl *ctrl,
                                                            const uint32_t *__restrict__ queue,
                                                            const uint32_t *__restrict__ queue_end, uint32_t slots,
                                                            const uint32_t *__restrict__ span_head,
@@ -538,14 +537,14 @@ __global__ __launch_bounds__(BLOCK) void long_prepare_kernel(uint32_t n, BwdCtrl
                                                            uint2 *__restrict__ chunk_tasks, uint32_t chunk_cap)
 {
     if (ctrl->abort) return;
-    __shared__ uint32_t wave_sums[BLOCK / EMB_WAVE];
-    const uint32_t s = blockIdx.x * BLOCK + threadIdx.x;
+    __shared__ uint32_t wave_sums[PREP_BLOCK / EMB_WAVE];
+    const uint32_t s = blockIdx.x * PREP_BLOCK + threadIdx.x;
     const int lane = threadIdx.x & (EMB_WAVE - 1);
 
     // distinct rows: sum of the run counts
     {
         uint32_t h = s < n_spans ? wave_heads[s] : 0u, total;
-        block_inclusive_scan<uint32_t, BLOCK>(h, wave_sums, total);
+        block_inclusive_scan<uint32_t, PREP_BLOCK>(h, wave_sums, total);
         if (threadIdx.x == 0 && total) atomicAdd(&ctrl->num_unique, total);
     }
 
@@ -577,9 +576,9 @@ __global__ __launch_bounds__(BLOCK) void long_prepare_kernel(uint32_t n, BwdCtrl
     // counter (tasks in the low half, runs of several chunks in the high half): same-address
     // device atomics are slow, and there are hundreds of workgroups
     uint32_t total_chunks, total_multi;
-    const uint32_t inc_c = block_inclusive_scan<uint32_t, BLOCK>(chunks, wave_sums, total_chunks);
+    const uint32_t inc_c = block_inclusive_scan<uint32_t, PREP_BLOCK>(chunks, wave_sums, total_chunks);
     const uint32_t multi = chunks > 1 ? 1u : 0u;
-    const uint32_t inc_m = block_inclusive_scan<uint32_t, BLOCK>(multi, wave_sums, total_multi);
+    const uint32_t inc_m = block_inclusive_scan<uint32_t, PREP_BLOCK>(multi, wave_sums, total_multi);
     __shared__ unsigned long long s_base;
     if (threadIdx.x == 0) {
         s_base = 0;

@@ -1,4 +1,4 @@
-// Segment reduce and row-wise Adagrad of a small step (small_step, bwd_common.h) in one launch.
+// Segment reduce and row-wise Adagrad of a step of few records (spans_step, bwd_common.h) in one launch.
 //
 // What bounds the arrangement of update.h at these sizes is latency: a wavefront that owns 256 sorted records
 // deals some 32 dependent rounds (gradients, row, update) to its lane groups, 32 us for 30 720 records on a
