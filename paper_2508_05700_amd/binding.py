@@ -9,6 +9,7 @@ PyTorch is used for device memory and streams.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import List, Optional, Sequence
 
@@ -273,8 +274,91 @@ def _check(fn: str, rc: int) -> None:
 
 
 _U64 = (torch.int64, torch.uint64)
+_U32 = (torch.int32, torch.uint32)
 _TABLE_TORCH = {"f32": torch.float32, "bf16": torch.bfloat16, "int8": torch.uint8, "int4": torch.uint8,
                 "int4r64": torch.uint8}
+
+
+# ---------------------------------------------------------------------------
+# calls whose work on the device is a few microseconds: their tensors are checked and their arguments passed by
+# csrc/calls.cpp where that module is built, through ctypes otherwise.  Per entry point the arguments that are tensors:
+# place, name and dtype.  (6.2 us of host time for the smallest lookup through ctypes, 4.1 with the module; 2.9 of both is the launch.)
+# ---------------------------------------------------------------------------
+_i32, _i64, _f32, _u8 = torch.int32, torch.int64, torch.float32, torch.uint8
+_TENSORS = {
+    "emb_bag_forward_lengths": {5: ("rows", _i64), 6: ("lengths", _i32), 10: ("out", _f32), 11: ("offsets_out", _i64),
+                                12: ("scratch", _u8), 14: ("status", _i32)},
+    "emb_bag_forward_hashed_lengths": {5: ("raw", _U64), 6: ("lengths", _i32), 10: ("out", _f32), 11: ("offsets_out", _i64),
+                                       12: ("rows_out", _i64), 13: ("scratch", _u8), 15: ("status", _i32)},
+    "emb_bag_forward_train_lengths_after": {5: ("raw", _U64), 6: ("lengths", _i32), 10: ("out", _f32),
+                                            11: ("offsets_out", _i64), 12: ("rows_out", _i64), 13: ("workspace", _u8),
+                                            15: ("num_unique", _i64), 16: ("status", _i32)},
+    "emb_bag_backward_sort_prepared": {7: ("workspace", _u8), 9: ("unique_keys", _i64), 10: ("unique_counts", _i32),
+                                       11: ("num_unique", _i64), 12: ("status", _i32)},
+    "emb_bag_backward_update": {7: ("dout", _f32), 10: ("workspace", _u8), 12: ("num_unique", _i64)},
+    "emb_bag_backward_rowwise_adagrad": {5: ("rows", _i64), 6: ("offsets", _i64), 10: ("dout", _f32), 13: ("workspace", _u8),
+                                         15: ("unique_keys", _i64), 16: ("unique_counts", _i32), 17: ("num_unique", _i64),
+                                         18: ("status", _i32)},
+    "emb_lengths_to_offsets": {0: ("lengths", _i32), 2: ("offsets", _i64), 3: ("status", _i32)},
+    "emb_hash_ids_tables": {3: ("raw", _U64), 4: ("offsets", _i64), 7: ("rows", _i64), 8: ("status", _i32)},
+    "emb_bag_forward_mixed": {5: ("rows", _i64), 6: ("offsets", _i64), 10: ("out", _f32), 12: ("status", _i32)},
+    "emb_bag_forward_cached_hashed_lengths": {5: ("cache_index", _u8), 8: ("raw", _U64), 9: ("lengths", _i32),
+                                              13: ("out", _f32), 14: ("offsets_out", _i64), 15: ("scratch", _u8),
+                                              17: ("hit_miss", _U64), 18: ("status", _i32)},
+    "emb_bag_forward_cached_tables_hashed_lengths": {5: ("raw", _U64), 6: ("lengths", _i32), 10: ("out", _f32),
+                                                     11: ("offsets_out", _i64), 12: ("scratch", _u8), 14: ("hit_miss", _U64),
+                                                     15: ("status", _i32)},
+    "emb_cache_observe_hashed": {2: ("raw", _U64), 4: ("freq", _U32), 5: ("status", _i32)},
+    "emb_cache_refresh": {0: ("freq", _U32), 4: ("workspace", _u8), 10: ("old_cache_index", _u8), 12: ("hot_rows_out", _i64),
+                          14: ("cache_index", _u8), 15: ("moved", _U64), 16: ("info_out", _U64), 17: ("status", _i32)},
+}
+_calls_module = None     # False: there is none
+_entries = {}
+
+
+def _load_calls():
+    """The module of csrc/calls.cpp, or False where it is neither built nor can be, or was made for another torch."""
+    import importlib.machinery
+    import importlib.util
+    try:
+        if _build.calls_is_stale():
+            _build.build_calls(verbose=False)
+        spec = importlib.util.spec_from_file_location(
+            __package__ + "._calls", _build.CALLS, loader=importlib.machinery.ExtensionFileLoader(__package__ + "._calls", _build.CALLS))
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        return module
+    except (OSError, ImportError, RuntimeError):
+        return False
+
+
+def _ctypes_entry(name: str):
+    fn, kinds = getattr(lib(), name), _TENSORS[name]
+
+    def call(*args):
+        return fn(*[_ptr(a, kinds[i][1], kinds[i][0]) if i in kinds else a for i, a in enumerate(args)])
+    return call
+
+
+def _native_entry(name: str):
+    global _calls_module
+    if _calls_module is None:
+        _calls_module = _load_calls()
+    if not _calls_module:
+        return None
+    for k, (known, n) in enumerate(_calls_module.names()):
+        if known == name:
+            address = C.cast(getattr(lib(), name), C.c_void_p).value
+            _calls_module.bind(k, address, tuple(_TENSORS[name].get(i) for i in range(n)), _ptr)
+            return functools.partial(_calls_module.call, k)
+    return None
+
+
+def _entry(name: str):
+    f = _entries.get(name)
+    if f is None:
+        f = _entries[name] = _native_entry(name) or _ctypes_entry(name)
+    return f
 
 
 class TableSet(_HostDescriptors):
@@ -342,18 +426,16 @@ def emb_hash_ids_tables(tables: TableSet, raw: torch.Tensor, offsets: torch.Tens
     nnz = raw.numel()
     if rows.numel() != nnz or offsets.numel() != tables.T * B + 1:
         raise TypeError("shape mismatch")
-    _check("emb_hash_ids_tables", lib().emb_hash_ids_tables(
-        tables.host_ptr, tables.dev_ptr, tables.T, _ptr(raw, _U64, "raw"), _ptr(offsets, torch.int64, "offsets"),
-        int(B), nnz, _ptr(rows, torch.int64, "rows"), _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_hash_ids_tables", _entry("emb_hash_ids_tables")(
+        tables.host_ptr, tables.dev_ptr, tables.T, raw, offsets, int(B), nnz, rows, status, _stream()))
 
 
 def emb_lengths_to_offsets(lengths: torch.Tensor, offsets: torch.Tensor, status: Optional[torch.Tensor] = None) -> None:
     n = lengths.numel()
     if offsets.numel() != n + 1:
         raise TypeError("offsets must have lengths.numel() + 1 elements")
-    _check("emb_lengths_to_offsets", lib().emb_lengths_to_offsets(
-        _ptr(lengths, torch.int32, "lengths") if n else None, n, _ptr(offsets, torch.int64, "offsets"),
-        _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_lengths_to_offsets", _entry("emb_lengths_to_offsets")(
+        lengths if n else None, n, offsets, status, _stream()))
 
 
 def emb_bag_forward(tables: TableSet, rows: torch.Tensor, offsets: torch.Tensor, B: int, mode: str,
@@ -406,12 +488,10 @@ def emb_bag_forward_hashed_lengths(tables: TableSet, raw: torch.Tensor, lengths:
         raise TypeError("shape mismatch")
     if rows_out is not None and rows_out.numel() != nnz:
         raise TypeError("rows_out must have as many elements as raw")
-    _check("emb_bag_forward_hashed_lengths", lib().emb_bag_forward_hashed_lengths(
-        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], _ptr(raw, _U64, "raw"),
-        _ptr(lengths, torch.int32, "lengths") if n else None, int(B), nnz,
-        POOL[mode] | (ROWS_STREAMING if streaming else 0), _ptr(out, torch.float32, "out"),
-        _ptr(offsets_out, torch.int64, "offsets_out"), _ptr(rows_out, torch.int64, "rows_out"),
-        _ptr(scratch, torch.uint8, "scratch"), scratch.numel(), _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_bag_forward_hashed_lengths", _entry("emb_bag_forward_hashed_lengths")(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], raw, lengths if n else None,
+        int(B), nnz, POOL[mode] | (ROWS_STREAMING if streaming else 0), out, offsets_out, rows_out, scratch,
+        scratch.numel(), status, _stream()))
 
 
 def emb_bag_forward_lengths(tables: TableSet, rows: torch.Tensor, lengths: torch.Tensor, B: int, mode: str,
@@ -422,12 +502,10 @@ def emb_bag_forward_lengths(tables: TableSet, rows: torch.Tensor, lengths: torch
     n = tables.T * B
     if lengths.numel() != n or offsets_out.numel() != n + 1 or out.numel() != n * tables.D:
         raise TypeError("shape mismatch")
-    _check("emb_bag_forward_lengths", lib().emb_bag_forward_lengths(
-        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], _ptr(rows, torch.int64, "rows"),
-        _ptr(lengths, torch.int32, "lengths") if n else None, int(B), rows.numel(),
-        POOL[mode] | (ROWS_STREAMING if streaming else 0), _ptr(out, torch.float32, "out"),
-        _ptr(offsets_out, torch.int64, "offsets_out"), _ptr(scratch, torch.uint8, "scratch"), scratch.numel(),
-        _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_bag_forward_lengths", _entry("emb_bag_forward_lengths")(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], rows, lengths if n else None,
+        int(B), rows.numel(), POOL[mode] | (ROWS_STREAMING if streaming else 0), out, offsets_out, scratch,
+        scratch.numel(), status, _stream()))
 
 
 class MixedTables(_HostDescriptors):
@@ -472,10 +550,9 @@ def emb_bag_forward_mixed(mt: MixedTables, rows: torch.Tensor, offsets: torch.Te
                           status: Optional[torch.Tensor] = None) -> None:
     if offsets.numel() != mt.T * mt.B + 1 or out.numel() < mt.out_floats:
         raise TypeError("shape mismatch")
-    _check("emb_bag_forward_mixed", lib().emb_bag_forward_mixed(
-        mt.tables.host_ptr, mt.tables.dev_ptr, mt._host_address(), mt.dev.data_ptr(), mt.T,
-        _ptr(rows, torch.int64, "rows"), _ptr(offsets, torch.int64, "offsets"), mt.B, rows.numel(), POOL[mode],
-        _ptr(out, torch.float32, "out"), out.numel(), _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_bag_forward_mixed", _entry("emb_bag_forward_mixed")(
+        mt.tables.host_ptr, mt.tables.dev_ptr, mt._host_address(), mt.dev.data_ptr(), mt.T, rows, offsets, mt.B,
+        rows.numel(), POOL[mode], out, out.numel(), status, _stream()))
 
 
 def emb_row_bytes(D: int, dtype: str) -> int:
@@ -571,6 +648,11 @@ def _lookup_events(events):
     return (C.c_void_p * 2)(*[None if e is None else int(e.cuda_event) for e in events])
 
 
+def _address(array) -> Optional[int]:
+    """Address of a ctypes array that the caller holds during the call."""
+    return None if array is None else C.addressof(array)
+
+
 def _stage_events(stage_events):
     if stage_events is None:
         return None
@@ -648,12 +730,10 @@ def emb_bag_forward_train_lengths_after(tables: TableSet, raw: torch.Tensor, len
         raise TypeError("shape mismatch")
     if rows_out is not None and rows_out.numel() != nnz:
         raise TypeError("rows_out must have as many elements as raw")
-    _check("emb_bag_forward_train_lengths_after", lib().emb_bag_forward_train_lengths_after(
-        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], _ptr(raw, _U64, "raw"),
-        _ptr(lengths, torch.int32, "lengths") if n else None, int(B), nnz, POOL[mode], _ptr(out, torch.float32, "out"),
-        _ptr(offsets_out, torch.int64, "offsets_out"), _ptr(rows_out, torch.int64, "rows_out"),
-        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _ptr(num_unique, torch.int64, "num_unique"),
-        _ptr(status, torch.int32, "status"), C.addressof(after.c) if after is not None else None, _stream()))
+    _check("emb_bag_forward_train_lengths_after", _entry("emb_bag_forward_train_lengths_after")(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], raw, lengths if n else None,
+        int(B), nnz, POOL[mode], out, offsets_out, rows_out, workspace, workspace.numel(), num_unique, status,
+        C.addressof(after.c) if after is not None else None, _stream()))
 
 
 def emb_bag_backward_sort_prepared(tables: TableSet, B: int, nnz: int, workspace: torch.Tensor,
@@ -665,12 +745,10 @@ def emb_bag_backward_sort_prepared(tables: TableSet, B: int, nnz: int, workspace
     for t, name in ((unique_keys, "unique_keys"), (unique_counts, "unique_counts")):
         if t is not None and t.numel() < nnz:
             raise TypeError(name + " must hold at least nnz elements")
-    _check("emb_bag_backward_sort_prepared", lib().emb_bag_backward_sort_prepared(
-        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], int(B), int(nnz),
-        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
-        _ptr(unique_keys, torch.int64, "unique_keys"), _ptr(unique_counts, torch.int32, "unique_counts"),
-        _ptr(num_unique, torch.int64, "num_unique"), _ptr(status, torch.int32, "status"),
-        _stage_events(stage_events), _stream()))
+    events = _stage_events(stage_events)
+    _check("emb_bag_backward_sort_prepared", _entry("emb_bag_backward_sort_prepared")(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], int(B), int(nnz), workspace,
+        workspace.numel(), unique_keys, unique_counts, num_unique, status, _address(events), _stream()))
 
 
 def emb_bag_backward_update(tables: TableSet, B: int, nnz: int, dout: torch.Tensor, lr: float, eps: float,
@@ -680,11 +758,11 @@ def emb_bag_backward_update(tables: TableSet, B: int, nnz: int, dout: torch.Tens
     """Second half of the backward, from the records emb_bag_backward_sort left in ``workspace``."""
     if dout.numel() != tables.T * B * tables.D:
         raise TypeError("shape mismatch")
-    _check("emb_bag_backward_update", lib().emb_bag_backward_update(
-        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], int(B), int(nnz),
-        _ptr(dout, torch.float32, "dout"), C.c_float(lr), C.c_float(eps),
-        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _ptr(num_unique, torch.int64, "num_unique"),
-        _stage_events(stage_events), None if side is None else C.addressof(side.c), _stream()))
+    events = _stage_events(stage_events)
+    _check("emb_bag_backward_update", _entry("emb_bag_backward_update")(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], int(B), int(nnz), dout,
+        C.c_float(lr).value, C.c_float(eps).value, workspace, workspace.numel(), num_unique, _address(events),
+        None if side is None else C.addressof(side.c), _stream()))
 
 
 def emb_bag_backward_rowwise_adagrad(tables: TableSet, rows: torch.Tensor, offsets: torch.Tensor, B: int, mode: str,
@@ -705,14 +783,12 @@ def emb_bag_backward_rowwise_adagrad(tables: TableSet, rows: torch.Tensor, offse
     for t, name in ((unique_keys, "unique_keys"), (unique_counts, "unique_counts")):
         if t is not None and t.numel() < nnz:
             raise TypeError(name + " must hold at least nnz elements")
-    _check("emb_bag_backward_rowwise_adagrad", lib().emb_bag_backward_rowwise_adagrad(
-        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype],
-        _ptr(rows, torch.int64, "rows"), _ptr(offsets, torch.int64, "offsets"), int(B), nnz, POOL[mode],
-        _ptr(dout, torch.float32, "dout"), C.c_float(lr), C.c_float(eps),
-        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
-        _ptr(unique_keys, torch.int64, "unique_keys"), _ptr(unique_counts, torch.int32, "unique_counts"),
-        _ptr(num_unique, torch.int64, "num_unique"), _ptr(status, torch.int32, "status"),
-        _stage_events(stage_events), None if side is None else C.addressof(side.c), _stream()))
+    events = _stage_events(stage_events)
+    _check("emb_bag_backward_rowwise_adagrad", _entry("emb_bag_backward_rowwise_adagrad")(
+        tables.host_ptr, tables.dev_ptr, tables.T, tables.D, DTYPE[tables.dtype], rows, offsets, int(B), nnz,
+        POOL[mode], dout, C.c_float(lr).value, C.c_float(eps).value, workspace, workspace.numel(), unique_keys,
+        unique_counts, num_unique, status, _address(events), None if side is None else C.addressof(side.c),
+        _stream()))
 
 
 def emb_cache_index_bytes(num_rows: int) -> int:
@@ -768,13 +844,12 @@ def emb_bag_forward_cached_hashed_lengths(table_ptr: int, num_rows: int, D: int,
     ``scratch`` holds ``emb_offsets_scratch_bytes(B)`` bytes."""
     if lengths.numel() != B or offsets_out.numel() != B + 1 or out.numel() != B * D:
         raise TypeError("shape mismatch")
-    _check("emb_bag_forward_cached_hashed_lengths", lib().emb_bag_forward_cached_hashed_lengths(
-        int(table_ptr), int(num_rows), int(D), DTYPE[dtype], _ptr(cache_rows, _TABLE_TORCH[dtype], "cache_rows"),
-        _ptr(cache_index, torch.uint8, "cache_index"), int(num_hot), C.c_uint64(int(salt) % (1 << 64)),
-        _ptr(raw, _U64, "raw"), _ptr(lengths, torch.int32, "lengths") if B else None, int(B), raw.numel(), POOL[mode],
-        _ptr(out, torch.float32, "out"), _ptr(offsets_out, torch.int64, "offsets_out"),
-        _ptr(scratch, torch.uint8, "scratch"), scratch.numel(), _ptr(hit_miss, _U64, "hit_miss"),
-        _ptr(status, torch.int32, "status"), _lookup_events(lookup_events), _stream()))
+    events = _lookup_events(lookup_events)
+    _check("emb_bag_forward_cached_hashed_lengths", _entry("emb_bag_forward_cached_hashed_lengths")(
+        int(table_ptr), int(num_rows), int(D), DTYPE[dtype], _ptr(cache_rows, _TABLE_TORCH[dtype],
+        "cache_rows"), cache_index, int(num_hot), int(salt) % (1 << 64), raw, lengths if B else None, int(B),
+        raw.numel(), POOL[mode], out, offsets_out, scratch, scratch.numel(), hit_miss, status, _address(events),
+        _stream()))
 
 
 def emb_cache_stage_misses(table_ptr: int, num_rows: int, D: int, dtype: str, cache_index: torch.Tensor, num_hot: int,
@@ -813,7 +888,6 @@ def emb_bag_forward_staged(table_ptr: int, num_rows: int, D: int, dtype: str, ca
         _stream()))
 
 
-_U32 = (torch.int32, torch.uint32)
 
 
 def emb_cache_observe(num_rows: int, rows: torch.Tensor, freq: torch.Tensor,
@@ -829,9 +903,8 @@ def emb_cache_observe_hashed(num_rows: int, salt: int, raw: torch.Tensor, freq: 
                              status: Optional[torch.Tensor] = None) -> None:
     if freq.numel() != num_rows:
         raise TypeError("freq must hold one counter per table row")
-    _check("emb_cache_observe_hashed", lib().emb_cache_observe_hashed(
-        int(num_rows), C.c_uint64(int(salt) % (1 << 64)), _ptr(raw, _U64, "raw"), raw.numel(),
-        _ptr(freq, _U32, "freq"), _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_cache_observe_hashed", _entry("emb_cache_observe_hashed")(
+        int(num_rows), int(salt) % (1 << 64), raw, raw.numel(), freq, status, _stream()))
 
 
 def emb_cache_select_workspace_bytes(num_rows: int) -> int:
@@ -882,13 +955,11 @@ def emb_cache_refresh(freq: torch.Tensor, num_hot: int, decay_shift: int, worksp
     """``emb_cache_select`` followed by ``emb_cache_rebuild`` with the rows it chose, in one call."""
     if hot_rows_out.numel() < num_hot:
         raise TypeError("hot_rows_out too small")
-    _check("emb_cache_refresh", lib().emb_cache_refresh(
-        _ptr(freq, _U32, "freq"), freq.numel(), int(num_hot), int(decay_shift), _ptr(workspace, torch.uint8, "workspace"),
-        workspace.numel(), int(table_ptr), int(D), DTYPE[dtype], _ptr(old_cache_rows, _TABLE_TORCH[dtype], "old_cache_rows"),
-        _ptr(old_cache_index, torch.uint8, "old_cache_index"), int(old_num_hot),
-        _ptr(hot_rows_out, torch.int64, "hot_rows_out"), _ptr(cache_rows, _TABLE_TORCH[dtype], "cache_rows"),
-        _ptr(cache_index, torch.uint8, "cache_index"), _ptr(moved, _U64, "moved"), _ptr(info_out, _U64, "info_out"),
-        _ptr(status, torch.int32, "status"), _stream()))
+    _check("emb_cache_refresh", _entry("emb_cache_refresh")(
+        freq, freq.numel(), int(num_hot), int(decay_shift), workspace, workspace.numel(), int(table_ptr),
+        int(D), DTYPE[dtype], _ptr(old_cache_rows, _TABLE_TORCH[dtype], "old_cache_rows"), old_cache_index,
+        int(old_num_hot), hot_rows_out, _ptr(cache_rows, _TABLE_TORCH[dtype], "cache_rows"), cache_index, moved,
+        info_out, status, _stream()))
 
 
 def emb_version_record_bytes(T: int) -> int:
@@ -1008,12 +1079,11 @@ def emb_bag_forward_cached_tables_hashed_lengths(ct: CachedTables, raw: torch.Te
     n = ct.T * B
     if lengths.numel() != n or offsets_out.numel() != n + 1 or out.numel() != n * ct.D:
         raise TypeError("shape mismatch")
-    _check("emb_bag_forward_cached_tables_hashed_lengths", lib().emb_bag_forward_cached_tables_hashed_lengths(
-        ct._host_address(), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], _ptr(raw, _U64, "raw"),
-        _ptr(lengths, torch.int32, "lengths") if n else None, int(B), raw.numel(), POOL[mode],
-        _ptr(out, torch.float32, "out"), _ptr(offsets_out, torch.int64, "offsets_out"),
-        _ptr(scratch, torch.uint8, "scratch"), scratch.numel(), _ptr(hit_miss, _U64, "hit_miss"),
-        _ptr(status, torch.int32, "status"), _lookup_events(lookup_events), _stream()))
+    events = _lookup_events(lookup_events)
+    _check("emb_bag_forward_cached_tables_hashed_lengths", _entry("emb_bag_forward_cached_tables_hashed_lengths")(
+        ct._host_address(), ct.dev.data_ptr(), ct.T, ct.D, DTYPE[ct.dtype], raw, lengths if n else None, int(B),
+        raw.numel(), POOL[mode], out, offsets_out, scratch, scratch.numel(), hit_miss, status, _address(events),
+        _stream()))
 
 
 def emb_checksum(data, sum_out: torch.Tensor, nbytes: Optional[int] = None) -> None:

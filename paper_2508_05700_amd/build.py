@@ -1,7 +1,8 @@
-"""Builds the HIP library (``libemb_hip.so``) for gfx950 with hipcc.
+"""Builds the HIP library (``libemb_hip.so``) for gfx950 with hipcc, and with g++ the CPython module
+(``_calls.so``) that marshals the shortest calls.
 
-The library is plain C ABI (``include/emb.h``); there is no torch extension and
-no Python C module, so one ``hipcc -shared`` line is the whole build.
+The library is plain C ABI (``include/emb.h``): one ``hipcc -shared`` line.  The module knows torch tensors and is of
+use to ``binding.py`` only, which does without it where it is missing.
 """
 from __future__ import annotations
 
@@ -15,6 +16,10 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libemb_hip.so")
 
+CALLS = os.path.join(PKG, "_calls.so")
+CALLS_SRC = os.path.join(CSRC, "calls.cpp")
+
+CXX = os.environ.get("CXX", "g++")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -35,6 +40,24 @@ def is_stale() -> bool:
     return os.path.getmtime(LIB) < max(os.path.getmtime(d) for d in deps)
 
 
+def calls_is_stale() -> bool:
+    deps = (CALLS_SRC, os.path.join(ROOT, "include", "emb.h"))
+    return not os.path.exists(CALLS) or os.path.getmtime(CALLS) < max(os.path.getmtime(d) for d in deps)
+
+
+def build_calls(verbose: bool = True) -> str:
+    """Compile ``csrc/calls.cpp`` against the torch that is installed."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    _run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+          "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
+          "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+          CALLS_SRC, "-o", CALLS, "-L", os.path.join(t, "lib"), "-ltorch_python", "-lc10"], verbose)
+    return CALLS
+
+
 def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -44,11 +67,11 @@ def _run(cmd, verbose):
     if log.strip() and verbose:
         print(log, flush=True)
     if p.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + log)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + log)
 
 
 def build(verbose: bool = True, jobs: int = 6) -> str:
-    """Compile every ``csrc/*.hip`` for gfx950 (in parallel) and link ``libemb_hip.so``."""
+    """Compile every ``csrc/*.hip`` for gfx950 (in parallel) and link ``libemb_hip.so``; then ``_calls.so``."""
     from concurrent.futures import ThreadPoolExecutor
 
     objdir = os.path.join(PKG, "_build")
@@ -64,6 +87,7 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(cmds)))) as ex:
         list(ex.map(lambda c: _run(c, verbose), cmds))
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+    build_calls(verbose)
     return LIB
 
 

@@ -9,6 +9,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2508_05700_amd import binding as b
 
@@ -557,3 +558,31 @@ def test_copied_descriptors_are_read_where_the_copy_holds_them(cls, duplicate):
     two = duplicate(one)
     assert two._host_address() == two.host.ctypes.data
     assert one._host_address() == one.host.ctypes.data
+
+
+@pytest.mark.parametrize("name", sorted(b._TENSORS))
+def test_native_marshalling_agrees_with_ctypes(name):
+    # the module of csrc/calls.cpp and the ctypes route of the same entry point: number of arguments, statuses, refusals
+    native, by_ctypes = b._native_entry(name), b._ctypes_entry(name)
+    assert native is not None, "csrc/calls.cpp is not built"
+    argtypes = getattr(b.lib(), name).argtypes
+    args = [None if t is C.c_void_p else 0.0 if t is C.c_float else 0 if t in (C.c_uint64, C.c_size_t) else -1 for t in argtypes]
+    assert native(*args) == by_ctypes(*args) < 0                      # negative sizes
+    zero = [0 if a == -1 else a for a in args]
+    assert native(*zero) == by_ctypes(*zero)                          # nothing to do, or null pointers
+    for place, (what, dtype) in b._TENSORS[name].items():
+        assert argtypes[place] is C.c_void_p
+        accepted = dtype[0] if isinstance(dtype, tuple) else dtype
+        for bad in (torch.zeros(4, dtype=accepted), torch.zeros(4, dtype=torch.float64), torch.nn.Parameter(torch.zeros(4))):
+            with_bad = args[:place] + [bad] + args[place + 1:]
+            messages = []
+            for f in (native, by_ctypes):
+                with pytest.raises(TypeError) as e:
+                    f(*with_bad)
+                messages.append(str(e.value))
+            assert messages[0] == messages[1] and what in messages[0]
+    for wrong in (args[:-1], args + [0]):
+        with pytest.raises(TypeError):
+            native(*wrong)
+    with pytest.raises(TypeError):
+        native(*[1.5 if t in (C.c_int32, C.c_int64) else a for t, a in zip(argtypes, args)])
