@@ -137,17 +137,26 @@ struct CachedSource {
 constexpr int CF_BLOCK = 256;
 
 // Bounds of bag `bag` for the cached lookups.  offsets_out == NULL: `offsets` are the final offsets.
-// Otherwise (the calls that take bag lengths) `offsets` holds the sums within tiles of lengths, the bounds
-// come from emb_two_level_bounds and the final offsets are written to offsets_out.  Every thread of the
-// workgroup calls this; the choice is uniform over the launch.
-template <int BLOCK>
-__device__ __forceinline__ void cached_bag_bounds(const int64_t *__restrict__ offsets, int64_t *__restrict__ offsets_out,
-                                                  int64_t n_bags, bool live, int64_t bag, int l, int64_t *tile_prefix,
-                                                  int64_t *wave_sums, int64_t &s, int64_t &e)
+// Otherwise (the calls that take bag lengths) the final offsets are written to offsets_out, and the bounds come
+// straight from `lengths` if that is given (emb_bounds_from_lengths: up to EMB_LENGTHS_DIRECT_BAGS bags), else from
+// `offsets`, the sums within tiles of lengths (emb_two_level_bounds).  Every thread of the workgroup calls this; the
+// choice is uniform over the launch.  n_bags: of all tables; first, in_table: the workgroup's first bag, and the bags
+// of its table from there on.
+constexpr int CB_LDS_BOUNDS = CF_BLOCK + 1, CB_LDS_SUMS = 2 * CF_BLOCK / EMB_WAVE;   // int64 words of LDS
+template <int LPR>
+__device__ __forceinline__ void cached_bag_bounds(const int64_t *__restrict__ offsets, const int32_t *__restrict__ lengths,
+                                                  int64_t *__restrict__ offsets_out, int64_t n_bags, int64_t first,
+                                                  int64_t in_table, bool live, int64_t bag, int l, int64_t *bounds,
+                                                  int64_t *wave_sums, uint32_t *status, int64_t &s, int64_t &e)
 {
+    constexpr int GROUPS = CF_BLOCK / LPR;
     s = e = 0;
     if (offsets_out) {
-        emb_two_level_bounds<BLOCK>(offsets, n_bags, live, bag, tile_prefix, wave_sums, s, e);
+        if (lengths)
+            emb_bounds_from_lengths<CF_BLOCK, GROUPS>(lengths, first, in_table < GROUPS ? (int)in_table : GROUPS,
+                                                      threadIdx.x / LPR, bounds, wave_sums, status, s, e);
+        else
+            emb_two_level_bounds<CF_BLOCK>(offsets, n_bags, live, bag, bounds, wave_sums, s, e);
         if (live && l == 0) {
             offsets_out[bag + 1] = e;
             if (bag == 0) offsets_out[0] = 0;
@@ -157,6 +166,7 @@ __device__ __forceinline__ void cached_bag_bounds(const int64_t *__restrict__ of
         e = offsets[bag + 1];
     }
 }
+static_assert(CF_BLOCK == Q_BLOCK, "the cached lookups over plain and quantised rows scan the same number of tiles");
 
 template <int LPR, int CPL, int UNROLL, bool BF16>
 __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_kernel(const char *__restrict__ table,
@@ -169,10 +179,10 @@ __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_kernel(const char
                                                                       float *__restrict__ out,
                                                                       unsigned long long *hit_miss, uint32_t *status,
                                                                       bool hashed, uint64_t salt, uint64_t magic,
-                                                                      int64_t *__restrict__ offsets_out)
+                                                                      int64_t *__restrict__ offsets_out,
+                                                                      const int32_t *__restrict__ lengths)
 {
-    __shared__ int64_t tile_prefix[CF_BLOCK];
-    __shared__ int64_t wave_sums[CF_BLOCK / EMB_WAVE];
+    __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
     constexpr int GROUPS = CF_BLOCK / LPR;
     const int l = threadIdx.x % LPR;
     const int64_t b = (int64_t)blockIdx.x * GROUPS + threadIdx.x / LPR;
@@ -180,7 +190,8 @@ __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_kernel(const char
                      status, 0u,         0u,    hashed,             salt,              magic};
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     int64_t s, e;
-    cached_bag_bounds<CF_BLOCK>(offsets, offsets_out, B, b < B, b, l, tile_prefix, wave_sums, s, e);
+    const int64_t b0 = (int64_t)blockIdx.x * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, B, b0, B - b0, b < B, b, l, bounds, wave_sums, status, s, e);
     gather_pool_range<LPR, CPL, UNROLL, BF16>(src, b < B, s, e, l, nnz, rows, chunks_per_row, mode,
                                               out + b * ((int64_t)chunks_per_row * F), status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
@@ -190,18 +201,18 @@ template <int LPR, int CPL, int UNROLL>
 int launch_cached(bool bf16, hipStream_t s, const char *table, const char *cache_rows, const CacheEntry *index,
                   int64_t num_rows, int64_t num_hot, int64_t B, int64_t nnz, const int64_t *rows,
                   const int64_t *offsets, int32_t chunks, int32_t mode, float *out, unsigned long long *hit_miss,
-                  uint32_t *status, bool hashed, uint64_t salt, uint64_t magic, int64_t *offsets_out)
+                  uint32_t *status, bool hashed, uint64_t salt, uint64_t magic, int64_t *offsets_out, const int32_t *lengths)
 {
     constexpr int GROUPS = CF_BLOCK / LPR;
     dim3 grid((unsigned)((B + GROUPS - 1) / GROUPS));
     if (bf16)
         hipLaunchKernelGGL((bag_forward_cached_kernel<LPR, CPL, UNROLL, true>), grid, dim3(CF_BLOCK), 0, s, table,
                            cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, chunks, mode, out, hit_miss, status,
-                           hashed, salt, magic, offsets_out);
+                           hashed, salt, magic, offsets_out, lengths);
     else
         hipLaunchKernelGGL((bag_forward_cached_kernel<LPR, CPL, UNROLL, false>), grid, dim3(CF_BLOCK), 0, s, table,
                            cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, chunks, mode, out, hit_miss, status,
-                           hashed, salt, magic, offsets_out);
+                           hashed, salt, magic, offsets_out, lengths);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
@@ -217,17 +228,18 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_cached_quant_kernel(const
                                                                            float *__restrict__ out,
                                                                            unsigned long long *hit_miss, uint32_t *status,
                                                                            bool hashed, uint64_t salt, uint64_t magic,
-                                                                           int64_t *__restrict__ offsets_out)
+                                                                           int64_t *__restrict__ offsets_out,
+                                                                           const int32_t *__restrict__ lengths)
 {
-    __shared__ int64_t tile_prefix[Q_BLOCK];
-    __shared__ int64_t wave_sums[Q_BLOCK / EMB_WAVE];
+    __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
     constexpr int GROUPS = Q_BLOCK / LPR;
     const int l = threadIdx.x % LPR;
     const int64_t b = (int64_t)blockIdx.x * GROUPS + threadIdx.x / LPR;
     CachedSource src{table, cache_rows, index, (uint64_t)num_rows, (uint64_t)num_hot, row_bytes, status, 0u, 0u,
                      hashed, salt, magic};
     int64_t s, e;
-    cached_bag_bounds<Q_BLOCK>(offsets, offsets_out, B, b < B, b, l, tile_prefix, wave_sums, s, e);
+    const int64_t b0 = (int64_t)blockIdx.x * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, B, b0, B - b0, b < B, b, l, bounds, wave_sums, status, s, e);
     gather_dequant_pool_range<LPR, BITS, UNROLL>(src, b < B, b, s, e, l, nnz, rows, D, mode, out, status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
@@ -237,14 +249,14 @@ int dispatch_cached_quant(int lpr, hipStream_t s, const char *table, const char 
                           int64_t num_rows, int64_t num_hot, int64_t B, int64_t nnz, const int64_t *rows,
                           const int64_t *offsets, int32_t D, int64_t row_bytes, int32_t mode, float *out,
                           unsigned long long *hit_miss, uint32_t *status, bool hashed, uint64_t salt, uint64_t magic,
-                          int64_t *offsets_out)
+                          int64_t *offsets_out, const int32_t *lengths)
 {
 #define EMB_CQ(L)                                                                                                   \
     do {                                                                                                            \
         constexpr int GROUPS = Q_BLOCK / L;                                                                         \
         hipLaunchKernelGGL((bag_forward_cached_quant_kernel<L, BITS, 8>), dim3((unsigned)((B + GROUPS - 1) / GROUPS)), \
                            dim3(Q_BLOCK), 0, s, table, cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, D, \
-                           row_bytes, mode, out, hit_miss, status, hashed, salt, magic, offsets_out);               \
+                           row_bytes, mode, out, hit_miss, status, hashed, salt, magic, offsets_out, lengths);      \
         EMB_RETURN_IF_LAUNCH_FAILED();                                                                              \
         return EMB_OK;                                                                                              \
     } while (0)
@@ -286,10 +298,9 @@ __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_tables_kernel(
     const emb_cached_table *__restrict__ tables, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ ids, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
     float *__restrict__ out, unsigned long long *hit_miss, uint32_t *status, bool hashed, int32_t T,
-    int64_t *__restrict__ offsets_out)
+    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths)
 {
-    __shared__ int64_t tile_prefix[CF_BLOCK];
-    __shared__ int64_t wave_sums[CF_BLOCK / EMB_WAVE];
+    __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
     constexpr int GROUPS = CF_BLOCK / LPR;
     const uint32_t t = blockIdx.x / blocks_per_table;   // the grid is exactly T * blocks_per_table
     const int l = threadIdx.x % LPR;
@@ -299,7 +310,9 @@ __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_tables_kernel(
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     const int64_t bag = (int64_t)t * B + b;
     int64_t s, e;
-    cached_bag_bounds<CF_BLOCK>(offsets, offsets_out, (int64_t)T * B, b < B, bag, l, tile_prefix, wave_sums, s, e);
+    const int64_t b0 = (int64_t)(blockIdx.x % blocks_per_table) * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, (int64_t)T * B, (int64_t)t * B + b0, B - b0, b < B, bag, l, bounds, wave_sums,
+                           status, s, e);
     gather_pool_range<LPR, CPL, UNROLL, BF16>(src, b < B, s, e, l, nnz, ids, chunks_per_row, mode,
                                               out + bag * ((int64_t)chunks_per_row * F), status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
@@ -310,10 +323,9 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_cached_tables_quant_kerne
     const emb_cached_table *__restrict__ tables, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ ids, const int64_t *__restrict__ offsets, int32_t D, int64_t row_bytes, int32_t mode,
     float *__restrict__ out, unsigned long long *hit_miss, uint32_t *status, bool hashed, int32_t T,
-    int64_t *__restrict__ offsets_out)
+    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths)
 {
-    __shared__ int64_t tile_prefix[Q_BLOCK];
-    __shared__ int64_t wave_sums[Q_BLOCK / EMB_WAVE];
+    __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
     constexpr int GROUPS = Q_BLOCK / LPR;
     const uint32_t t = blockIdx.x / blocks_per_table;
     const int l = threadIdx.x % LPR;
@@ -322,7 +334,9 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_cached_tables_quant_kerne
     CachedSource src = cached_source_of(tb, row_bytes, status, hashed);
     const int64_t bag = (int64_t)t * B + b;
     int64_t s, e;
-    cached_bag_bounds<Q_BLOCK>(offsets, offsets_out, (int64_t)T * B, b < B, bag, l, tile_prefix, wave_sums, s, e);
+    const int64_t b0 = (int64_t)(blockIdx.x % blocks_per_table) * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, (int64_t)T * B, (int64_t)t * B + b0, B - b0, b < B, bag, l, bounds, wave_sums,
+                           status, s, e);
     gather_dequant_pool_range<LPR, BITS, UNROLL>(src, b < B, bag, s, e, l, nnz, ids, D, mode, out, status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
@@ -340,6 +354,7 @@ struct CachedTablesArgs {
     bool hashed;
     hipStream_t s;
     int64_t *offsets_out;   // NULL: `offsets` are final; else they are sums within tiles and the offsets go here
+    const int32_t *lengths; // not NULL: the bounds come from these, not from `offsets`
 };
 
 template <int LPR, int CPL, int UNROLL>
@@ -353,11 +368,11 @@ int launch_cached_tables(const CachedTablesArgs &a, bool bf16)
     if (bf16)
         hipLaunchKernelGGL((bag_forward_cached_tables_kernel<LPR, CPL, UNROLL, true>), grid, dim3(CF_BLOCK), 0, a.s,
                            a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, chunks, a.mode, a.out, a.hit_miss,
-                           a.status, a.hashed, a.T, a.offsets_out);
+                           a.status, a.hashed, a.T, a.offsets_out, a.lengths);
     else
         hipLaunchKernelGGL((bag_forward_cached_tables_kernel<LPR, CPL, UNROLL, false>), grid, dim3(CF_BLOCK), 0, a.s,
                            a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, chunks, a.mode, a.out, a.hit_miss,
-                           a.status, a.hashed, a.T, a.offsets_out);
+                           a.status, a.hashed, a.T, a.offsets_out, a.lengths);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
@@ -370,7 +385,7 @@ int launch_cached_tables_quant(const CachedTablesArgs &a)
     if (per_table * a.T > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((bag_forward_cached_tables_quant_kernel<LPR, BITS, 8>), dim3((unsigned)(per_table * a.T)),
                        dim3(Q_BLOCK), 0, a.s, a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, a.D,
-                       a.row_bytes, a.mode, a.out, a.hit_miss, a.status, a.hashed, a.T, a.offsets_out);
+                       a.row_bytes, a.mode, a.out, a.hit_miss, a.status, a.hashed, a.T, a.offsets_out, a.lengths);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
@@ -492,7 +507,7 @@ static int cached_entry(const void *table_dev, int64_t num_rows, int32_t D, int3
                         const void *cache_index_dev, int64_t num_hot, const int64_t *rows_dev,
                         const int64_t *offsets_dev, int64_t B, int64_t nnz, int32_t mode, float *out_dev,
                         uint64_t *hit_miss_dev, uint32_t *status_dev, void *stream, bool hashed, uint64_t salt,
-                        int64_t *offsets_out_dev = nullptr)
+                        int64_t *offsets_out_dev = nullptr, const int32_t *lengths_dev = nullptr)
 {
     const uint64_t magic = num_rows > 0 ? emb_mod_magic((uint64_t)num_rows) : 0;
     if (B < 0 || nnz < 0 || num_rows <= 0 || num_hot < 0) return EMB_ERR_INVALID_ARG;
@@ -501,7 +516,7 @@ static int cached_entry(const void *table_dev, int64_t num_rows, int32_t D, int3
     if (rc != EMB_OK) return rc;
     if (B == 0) return EMB_OK;
     if (!table_dev || !cache_index_dev || (num_hot > 0 && !cache_rows_dev)) return EMB_ERR_INVALID_ARG;
-    if (!offsets_dev || !out_dev || (nnz > 0 && !rows_dev)) return EMB_ERR_INVALID_ARG;
+    if ((!offsets_dev && !lengths_dev) || !out_dev || (nnz > 0 && !rows_dev)) return EMB_ERR_INVALID_ARG;
     if (!emb_aligned(table_dev, 16) || !emb_aligned(cache_index_dev, 16) || !emb_aligned(cache_rows_dev, 16) ||
         !emb_aligned(out_dev, 16))
         return EMB_ERR_INVALID_ARG;
@@ -516,9 +531,9 @@ static int cached_entry(const void *table_dev, int64_t num_rows, int32_t D, int3
         unsigned long long *hm = reinterpret_cast<unsigned long long *>(hit_miss_dev);
         if (emb_quant_bits(dtype) == 8)
             return dispatch_cached_quant<8>(ql, s, tp, cp, ip, num_rows, num_hot, B, nnz, rows_dev, offsets_dev, D, rb,
-                                            mode, out_dev, hm, status_dev, hashed, salt, magic, offsets_out_dev);
+                                            mode, out_dev, hm, status_dev, hashed, salt, magic, offsets_out_dev, lengths_dev);
         return dispatch_cached_quant<4>(ql, s, tp, cp, ip, num_rows, num_hot, B, nnz, rows_dev, offsets_dev, D, rb, mode,
-                                        out_dev, hm, status_dev, hashed, salt, magic, offsets_out_dev);
+                                        out_dev, hm, status_dev, hashed, salt, magic, offsets_out_dev, lengths_dev);
     }
     const int chunks = D * emb_elem_size(dtype) / 16;
     int lpr, cpl;
@@ -530,7 +545,7 @@ static int cached_entry(const void *table_dev, int64_t num_rows, int32_t D, int3
                                   reinterpret_cast<const CacheEntry *>(cache_index_dev), num_rows, num_hot, B, nnz, \
                                   rows_dev, offsets_dev, chunks, mode, out_dev,                                  \
                                   reinterpret_cast<unsigned long long *>(hit_miss_dev), status_dev, hashed, salt, magic, \
-                                  offsets_out_dev)
+                                  offsets_out_dev, lengths_dev)
     if (cpl == 1) {
         switch (lpr) {
             case 1: EMB_CF(1, 1, 8);
@@ -574,7 +589,8 @@ extern "C" int emb_bag_forward_cached_hashed(const void *table_dev, int64_t num_
 
 // The calls that take bag lengths: argument checks they share, then the sums within tiles into the scratch
 // array (with no bags at all, the single offset 0 straight to the caller).  Returns > 0 when nothing is left
-// to do.  `local` receives where the lookup finds the sums.
+// to do.  `local` receives where the lookup finds the sums, NULL if it makes do with the lengths: a launch less (16 bags
+// of 20 rows 10.8 -> 8.7 us, 512 17.3 -> 14.9, 4096 INT4 bags of 5 23.2 -> 19.6, four tables of 1000 bags of 2 13.6 -> 9.6).
 static int lengths_front(const int32_t *lengths_dev, int64_t n, int64_t *offsets_out_dev, void *scratch_dev,
                          size_t scratch_bytes, uint32_t *status_dev, void *stream, const int64_t **local)
 {
@@ -582,14 +598,16 @@ static int lengths_front(const int32_t *lengths_dev, int64_t n, int64_t *offsets
     if (n > (int64_t)CF_BLOCK * EMB_OFFSETS_TILE) return EMB_ERR_UNSUPPORTED;   // more tiles than a workgroup scans
     if (n > 0 && (!lengths_dev || !scratch_dev || !emb_aligned(scratch_dev, 16) || scratch_bytes < ((size_t)n + 1) * 8))
         return EMB_ERR_INVALID_ARG;
+    if (n > 0 && n <= EMB_LENGTHS_DIRECT_BAGS) {
+        *local = nullptr;
+        return EMB_OK;
+    }
     int64_t *dst = n == 0 ? offsets_out_dev : reinterpret_cast<int64_t *>(scratch_dev);
     *local = dst;
     const int rc = emb_offsets_tile_sums(lengths_dev, n, dst, status_dev, emb_stream(stream));
     if (rc != EMB_OK) return rc;
     return n == 0 ? 1 : EMB_OK;
 }
-static_assert(CF_BLOCK == Q_BLOCK, "the cached lookups over plain and quantised rows scan the same number of tiles");
-
 // For callers that time the lookup kernel of a call that launches two: events[i] (hipEvent_t; the array and
 // each entry nullable) is recorded on the call's stream.
 static bool lookup_event(void *const *events, int i, void *stream)
@@ -622,7 +640,7 @@ extern "C" int emb_bag_forward_cached_hashed_lengths(const void *table_dev, int6
     if (!lookup_event(lookup_events, 0, stream)) return EMB_ERR_HIP;
     rc = cached_entry(table_dev, num_rows, D, dtype, cache_rows_dev, cache_index_dev, num_hot,
                       reinterpret_cast<const int64_t *>(raw_dev), local, B, nnz, mode, out_dev, hit_miss_dev, status_dev,
-                      stream, true, salt, offsets_out_dev);
+                      stream, true, salt, offsets_out_dev, local ? nullptr : lengths_dev);
     if (rc != EMB_OK) return rc;
     return lookup_event(lookup_events, 1, stream) ? EMB_OK : EMB_ERR_HIP;
 }
@@ -678,7 +696,8 @@ extern "C" int emb_bag_forward_cached_tables_hashed_lengths(const emb_cached_tab
     if (rc != EMB_OK) return rc > 0 ? EMB_OK : rc;
     if (!lookup_event(lookup_events, 0, stream)) return EMB_ERR_HIP;
     rc = emb_forward_cached_unchecked_tables(tables_dev, T, D, dtype, reinterpret_cast<const int64_t *>(raw_dev), local, B,
-                                             nnz, mode, out_dev, hit_miss_dev, status_dev, stream, true, offsets_out_dev);
+                                             nnz, mode, out_dev, hit_miss_dev, status_dev, stream, true, offsets_out_dev,
+                                             local ? nullptr : lengths_dev);
     if (rc != EMB_OK) return rc;
     return lookup_event(lookup_events, 1, stream) ? EMB_OK : EMB_ERR_HIP;
 }
@@ -688,7 +707,7 @@ extern "C" int emb_bag_forward_cached_tables_hashed_lengths(const emb_cached_tab
 int emb_forward_cached_unchecked_tables(const emb_cached_table *td, int32_t T, int32_t D, int32_t dtype,
                                         const int64_t *ids_dev, const int64_t *offsets_dev, int64_t B, int64_t nnz,
                                         int32_t mode, float *out_dev, uint64_t *hit_miss_dev, uint32_t *status_dev,
-                                        void *stream, bool hashed, int64_t *offsets_out_dev)
+                                        void *stream, bool hashed, int64_t *offsets_out_dev, const int32_t *lengths_dev)
 {
     if (T < 0 || B < 0 || nnz < 0) return EMB_ERR_INVALID_ARG;
     if (mode != EMB_POOL_SUM && mode != EMB_POOL_MEAN) return EMB_ERR_INVALID_ARG;
@@ -696,13 +715,13 @@ int emb_forward_cached_unchecked_tables(const emb_cached_table *td, int32_t T, i
     if (rc != EMB_OK) return rc;
     if (T == 0 || B == 0) return EMB_OK;
     if (!td) return EMB_ERR_INVALID_ARG;
-    if (!offsets_dev || !out_dev || (nnz > 0 && !ids_dev)) return EMB_ERR_INVALID_ARG;
+    if ((!offsets_dev && !lengths_dev) || !out_dev || (nnz > 0 && !ids_dev)) return EMB_ERR_INVALID_ARG;
     if (!emb_aligned(out_dev, 16)) return EMB_ERR_INVALID_ARG;
     if (B > (int64_t)0x7FFFFFFF || T > 65535) return EMB_ERR_UNSUPPORTED;
 
     CachedTablesArgs a{td,      T,      B,         nnz,  ids_dev, offsets_dev, D, mode, emb_row_bytes(D, dtype),
                        out_dev, reinterpret_cast<unsigned long long *>(hit_miss_dev), status_dev, hashed, emb_stream(stream),
-                       offsets_out_dev};
+                       offsets_out_dev, lengths_dev};
     if (emb_is_quant(dtype))
         return emb_quant_bits(dtype) == 8 ? dispatch_cached_tables_quant<8>(emb_quant_lanes(D), a)
                                           : dispatch_cached_tables_quant<4>(emb_quant_lanes(D), a);

@@ -99,11 +99,13 @@ static inline int emb_check_cached_tables(const emb_cached_table *th, const emb_
 
 // emb_bag_forward_cached_tables / _hashed over descriptors that exist in device memory only and were
 // validated earlier (the latched copy of a hosted version record; versioned.hip).  With offsets_out_dev,
-// offsets_dev holds sums within tiles (emb_offsets_tile_sums) and the lookup writes the offsets there.
+// offsets_dev holds sums within tiles (emb_offsets_tile_sums), or lengths_dev the bag lengths, and the lookup writes
+// the offsets there.
 int emb_forward_cached_unchecked_tables(const emb_cached_table *tables_dev, int32_t T, int32_t D, int32_t dtype,
                                         const int64_t *ids_dev, const int64_t *offsets_dev, int64_t B, int64_t nnz,
                                         int32_t mode, float *out_dev, uint64_t *hit_miss_dev, uint32_t *status_dev,
-                                        void *stream, bool hashed, int64_t *offsets_out_dev = nullptr);
+                                        void *stream, bool hashed, int64_t *offsets_out_dev = nullptr,
+                                        const int32_t *lengths_dev = nullptr);
 
 // Argument checks of everything that builds a cache (cached.hip); old_index_dev == NULL: no older cache.
 int emb_check_cache_build(const void *table_dev, int64_t num_rows, int32_t D, int32_t dtype, const void *old_rows_dev,

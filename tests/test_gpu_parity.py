@@ -2426,6 +2426,13 @@ def test_cached_forward_from_lengths_equals_offsets_then_cached_forward(dtype, D
         assert torch.equal(got, want) and torch.equal(hm1, hm2) and int(hm1.sum()) == raw.size
 
 
+@pytest.mark.parametrize("T,B", [(1, 1), (1, 4096), (1, 4097), (3, 1365), (4, 1024), (2, 2049), (5, 3)])
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("int4", 128), ("bf16", 8), ("f32", 260), ("int8", 16)])
+def test_cached_forward_from_few_lengths_equals_offsets_then_cached_forward(dtype, D, T, B):
+    # up to 4096 bags the lookup makes their bounds from the lengths alone
+    test_cached_forward_from_lengths_equals_offsets_then_cached_forward(dtype, D, T, B)
+
+
 def test_cached_forward_from_lengths_argument_limits():
     D, R, K = 16, 100, 10
     tab = torch.zeros((R, D), dtype=torch.float32, device=H.DEV)
