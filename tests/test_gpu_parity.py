@@ -68,6 +68,25 @@ def test_offsets_bit_exact(n):
     assert status.item() == 0 and np.array_equal(out.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 8194, 12_287, 12_288, 12_290, 12_291, 4096 * 1023 + 1022, 4096 * 1023 + 1023,
+                               4096 * 1024 + 1023, 4096 * 1024 + 1024, 4096 * 1025])
+@pytest.mark.parametrize("negative", [False, True])
+def test_offsets_around_the_tiles_that_leave_their_sums_to_later_ones(n, negative):
+    # 4096 lengths a tile; what is left is a tile if it has at least as many lengths as there are tiles before it; up to
+    # 1024 tiles in one or two launches
+    rng = np.random.default_rng(8000 + n)
+    lengths = rng.integers(0, 1 << 20, size=n).astype(np.int32)
+    if negative:
+        lengths[[0, 4095, n - 1]] = [-1, -(1 << 31), -7]
+    off = torch.full((n + 1,), -1, dtype=torch.int64, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    emb.emb_lengths_to_offsets(H.dev(lengths), off, status)
+    torch.cuda.synchronize()
+    ref, _ = oracle.lengths_to_offsets(lengths)
+    assert np.array_equal(off.cpu().numpy(), ref)
+    assert status.item() == (emb.STATUS_BAD_OFFSETS if negative else 0)
+
+
 def test_offsets_large_values_and_negative_lengths():
     L = np.full(10_000, 2_000_000_000, dtype=np.int32)      # sums far beyond 32 bits
     L[[5, 4096, 9999]] = [-1, -2_000_000_000, -7]
