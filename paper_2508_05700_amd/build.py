@@ -54,7 +54,8 @@ def build_calls(verbose: bool = True) -> str:
     _run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
           "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
-          CALLS_SRC, "-o", CALLS, "-L", os.path.join(t, "lib"), "-ltorch_python", "-lc10"], verbose)
+          CALLS_SRC, "-o", CALLS + ".%d" % os.getpid(), "-L", os.path.join(t, "lib"), "-ltorch_python", "-lc10"], verbose)
+    os.replace(CALLS + ".%d" % os.getpid(), CALLS)   # other processes see all of it or none
     return CALLS
 
 

@@ -53,14 +53,14 @@ bool pointer_of(PyObject *o, const ArgSpec &s, void *&out)
         return false;
     }
     if (THPVariable_CheckExact(o)) {
-        const at::Tensor &t = THPVariable_Unpack(o);
-        if (t.is_cuda() && ((s.mask >> (int)t.scalar_type()) & 1ull) && t.is_contiguous()) {
-            try {
+        try {   // (a sparse tensor refuses the question for its layout, one without storage that for its address)
+            const at::Tensor &t = THPVariable_Unpack(o);
+            if (t.is_cuda() && ((s.mask >> (int)t.scalar_type()) & 1ull) && t.is_contiguous()) {
                 out = t.data_ptr();
                 return true;
-            } catch (...) {
-                // a tensor without storage: the slow way says so
             }
+        } catch (...) {
+            // the slow way says so
         }
     }
     PyObject *r = PyObject_CallFunctionObjArgs(slow_pointer, o, s.dtype, s.name, nullptr);

@@ -1441,6 +1441,12 @@ def test_distinct_rows_whose_lookups_end_around_a_tile_of_the_list(counts, bad):
     assert g["unique_keys"].tolist() == list(range(len(counts))) and g["unique_counts"].tolist() == counts
 
 
+def test_a_sparse_tensor_is_an_error():
+    lengths = torch.ones(8, dtype=torch.int32, device=H.DEV).to_sparse()
+    with pytest.raises((TypeError, RuntimeError)):
+        emb.emb_lengths_to_offsets(lengths, torch.zeros(9, dtype=torch.int64, device=H.DEV))
+
+
 def test_backward_empty_batch():
     tables = [np.ones((10, 16), dtype=np.float32)]
     ts, w_dev, acc_dev = H.make_tableset(tables, "f32", with_accum=True)
