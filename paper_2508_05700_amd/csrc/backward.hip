@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void bwd_keys_kernel(const emb_table *__restri
 // RUNS_WINDOWS * 64 tiles per round trip to memory: lane l requests the words of tiles t - l, t - 64 - l, ...
 // together, then the windows are added up nearest first until one holds a tile that knows its prefix.  How often a row
 // occurs is the way to the next run start: in the tile, or, for the tile's last run, looked for after it by the whole
-// workgroup, SORT_BLOCK records at a time (a second launch over all runs cost 6 us, and 1.5 us between the two).
+// workgroup (a second launch over all runs cost 6 us, and 1.5 us between the two).
 // flags: [tiles], cleared by the sort's first launch.
 constexpr int RUNS_WINDOWS = 4;
 __device__ __forceinline__ bool runs_lookback(unsigned long long *flags, uint32_t me, uint32_t count, uint32_t poll_limit,
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
         return;
     }
     __shared__ uint32_t wave_sums[SORT_WAVES];
-    __shared__ uint32_t rows_before, lookback_failed, after;
+    __shared__ uint32_t rows_before, lookback_failed;
     // the tile's runs in order: where each starts (and, after them, where the last one ends), and its place among the
     // tile's rows (NO_ROW: the marker's run)
     __shared__ uint32_t run_pos[SORT_TILE + 1];
@@ -372,7 +372,6 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
             }
         }
     }
-    if (threadIdx.x == 0) after = n;
     if (threadIdx.x < EMB_WAVE) {
         uint32_t before = 0;
         const bool ok = runs_lookback(flags, blockIdx.x, tile_rows, poll_limit, before);
@@ -389,17 +388,23 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
         }
         return;
     }
-    // the end of the tile's last run: the first record after the tile that has another key
+    // The end of the tile's last run: the first record after the tile that has another key.  The records of a run are
+    // consecutive, so the threads that see its key are the first ones: a step of single records, which is enough but
+    // for few tiles, then strides of SORT_BLOCK^2 and SORT_BLOCK records and single ones again (a row with
+    // a fifth of 2.6e6 lookups: the list adds 12 us to the step).
     if (unique_counts_out && tile_runs > 0) {   // uniform
         const KeyT last = keys[run_pos[tile_runs - 1]];
-        for (uint32_t i0 = (blockIdx.x + 1) * SORT_TILE; i0 < n; i0 += SORT_BLOCK) {   // uniform
-            const uint32_t i = i0 + threadIdx.x;
-            if (i < n && keys[i] != last) atomicMin(&after, i);
-            __syncthreads();
-            if (after < i0 + SORT_BLOCK) break;   // (a smaller one than the first found here is not found later)
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) run_pos[tile_runs] = after;
+        uint32_t end = (blockIdx.x + 1) * SORT_TILE < n ? (blockIdx.x + 1) * SORT_TILE : n;   // the records before it are of the run
+        auto step = [&](uint32_t stride) {      // every thread gets the number of threads whose stride is all of the run
+            const uint32_t i = end + (threadIdx.x + 1) * stride - 1;   // < 2^31 + 2^27
+            const uint32_t same = (uint32_t)__syncthreads_count(i < n && keys[i] == last);
+            end += same * stride;
+            return same;
+        };
+        if (step(1) == (uint32_t)SORT_BLOCK)
+            for (uint32_t stride = SORT_BLOCK * SORT_BLOCK; stride >= 1; stride /= SORT_BLOCK)
+                while (step(stride) == (uint32_t)SORT_BLOCK) { }
+        if (threadIdx.x == 0) run_pos[tile_runs] = end;
         __syncthreads();
     }
     const uint32_t u0 = rows_before;

@@ -1441,6 +1441,13 @@ def test_distinct_rows_whose_lookups_end_around_a_tile_of_the_list(counts, bad):
     assert g["unique_keys"].tolist() == list(range(len(counts))) and g["unique_counts"].tolist() == counts
 
 
+@pytest.mark.parametrize("counts", [[4096 + 512], [4096 + 513, 1], [1, 300_000, 5], [3, 4096 + (1 << 18), 1], [700_001, 20_000]])
+def test_distinct_rows_with_lookups_over_many_tiles_of_the_list(counts):
+    # the end of such a row's records is looked for in steps of 512, 512^2 and single records
+    test_distinct_rows_whose_lookups_end_around_a_tile_of_the_list(counts, 0)
+    test_distinct_rows_whose_lookups_end_around_a_tile_of_the_list(counts, 9)
+
+
 def test_a_sparse_tensor_is_an_error():
     lengths = torch.ones(8, dtype=torch.int32, device=H.DEV).to_sparse()
     with pytest.raises((TypeError, RuntimeError)):
