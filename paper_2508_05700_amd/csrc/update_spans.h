@@ -134,7 +134,10 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_spans_kernel(
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) mine += wave_heads[w];
             const unsigned long long all = atomicAdd(&ctrl->task_and_multi_count, mine) + mine;
-            if ((uint32_t)(all >> 32) == count_blocks && num_unique_out) *num_unique_out = (int64_t)(uint32_t)all;
+            if ((uint32_t)(all >> 32) == count_blocks) {   // the last one; the next update of these records counts from nothing
+                ctrl->task_and_multi_count = 0ull;
+                if (num_unique_out) *num_unique_out = (int64_t)(uint32_t)all;
+            }
         }
         return;
     }

@@ -1448,6 +1448,22 @@ def test_distinct_rows_with_lookups_over_many_tiles_of_the_list(counts):
     test_distinct_rows_whose_lookups_end_around_a_tile_of_the_list(counts, 9)
 
 
+@pytest.mark.parametrize("n", [5, 3000, 300_000])
+def test_update_counts_the_distinct_rows_each_time_it_runs(n):
+    # two updates of one sort's records, rows with few lookups each
+    T, B, D, R = 1, 16, 16, n
+    rows = np.random.default_rng(n).integers(0, R, size=n).astype(np.int64)
+    off = np.linspace(0, n, B + 1).astype(np.int64)
+    ts, _, _ = H.make_tableset([np.zeros((R, D), np.float32)], "f32", with_accum=True)
+    ws = torch.empty(emb.emb_bag_backward_workspace_bytes(T, B, n, R, D, "f32"), dtype=torch.uint8, device=H.DEV)
+    nu = torch.zeros(1, dtype=torch.int64, device=H.DEV)
+    emb.emb_bag_backward_sort(ts, H.dev(rows), H.dev(off), B, "sum", ws)
+    for _ in range(3):
+        nu.fill_(-1)
+        emb.emb_bag_backward_update(ts, B, n, torch.ones(T * B * D, device=H.DEV), 0.01, 1e-8, ws, nu)
+        assert int(nu.item()) == np.unique(rows).size
+
+
 def test_a_sparse_tensor_is_an_error():
     lengths = torch.ones(8, dtype=torch.int32, device=H.DEV).to_sparse()
     with pytest.raises((TypeError, RuntimeError)):
