@@ -11,6 +11,7 @@
 //
 // Every die works on one stretch of those numbers (its L2 then holds few tables' hot rows), and the stretches
 // are cut so that the dies have the same amount of work (DieShares).
+#include "die_shares.h"
 #include "emb_internal.h"
 #include "gather.h"
 
@@ -114,36 +115,6 @@ inline uint64_t mixed_block_cost(const emb_table_shape &sh)
     return (uint64_t)(MX_BLOCK / sh.lanes) * (uint64_t)(sh.D * emb_elem_size(sh.dtype) / 16 + MX_ROW_COST);
 }
 
-inline uint64_t mixed_blocks(const emb_table_shape *shapes, int32_t T, int32_t t, uint32_t total_blocks)
-{
-    return (t + 1 < T ? shapes[t + 1].first_block : total_blocks) - shapes[t].first_block;
-}
-
-// Cuts the numbered workgroups into EMB_XCDS stretches of equal cost.  Returns the largest number of workgroups in one.
-uint32_t mixed_die_shares(const emb_table_shape *shapes, int32_t T, int64_t B, uint32_t total_blocks, DieShares &dies)
-{
-    uint64_t total = 0;
-    for (int32_t t = 0; t < T; ++t) {
-        total += mixed_blocks(shapes, T, t, total_blocks) * mixed_block_cost(shapes[t]);
-    }
-    uint64_t before = 0;   // cost of the tables before t
-    uint32_t d = 1, most = 0;
-    dies.first[0] = 0;
-    for (int32_t t = 0; t < T; ++t) {
-        const uint64_t blocks = mixed_blocks(shapes, T, t, total_blocks), per = mixed_block_cost(shapes[t]);
-        // the cuts that fall into this table: the first workgroup that starts at or after d eighths of the cost
-        for (; d < EMB_XCDS && total * d <= (before + blocks * per) * EMB_XCDS; ++d) {
-            const uint64_t at = (total * d + EMB_XCDS - 1) / EMB_XCDS;
-            dies.first[d] = shapes[t].first_block + (uint32_t)((at > before ? at - before : 0) + per - 1) / per;
-        }
-        before += blocks * per;
-    }
-    for (; d <= EMB_XCDS; ++d) dies.first[d] = total_blocks;
-    for (d = 0; d < EMB_XCDS; ++d)
-        if (dies.first[d + 1] - dies.first[d] > most) most = dies.first[d + 1] - dies.first[d];
-    return most;
-}
-
 }  // namespace
 
 extern "C" int emb_table_shapes_init(emb_table_shape *shapes_host, int32_t T, int64_t B)
@@ -195,7 +166,11 @@ extern "C" int emb_bag_forward_mixed(const emb_table *tables_host, const emb_tab
     if (!offsets_dev || !out_dev || (nnz > 0 && !rows_dev)) return EMB_ERR_INVALID_ARG;
     if (!emb_aligned(out_dev, 16)) return EMB_ERR_INVALID_ARG;
     DieShares dies;
-    const int64_t grid = (int64_t)mixed_die_shares(shapes_host, T, B, (uint32_t)first, dies) * EMB_XCDS;
+    // (a launch has fewer than 2^32 threads)
+    const int64_t grid = (int64_t)EMB_XCDS *
+                         emb_die_shares<EMB_XCDS>(T, [&](int32_t t) { return t < T ? shapes_host[t].first_block : (uint32_t)first; },
+                                                  [&](int32_t t) { return mixed_block_cost(shapes_host[t]); },
+                                                  0xFFFFFFFFu / MX_BLOCK / EMB_XCDS, dies.first);
     if (grid > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(bag_forward_mixed_kernel, dim3((unsigned)grid), dim3(MX_BLOCK), 0, emb_stream(stream), tables_dev,
                        shapes_dev, T, dies, B, nnz, rows_dev, offsets_dev, mode, out_dev, status_dev);

@@ -549,6 +549,14 @@ def test_exact_remainder_on_the_host(tmp_path):
     assert out.returncode == 0 and out.stdout.startswith("OK"), out.stdout
 
 
+def test_die_shares_on_the_host(tmp_path):
+    exe = str(tmp_path / "die_shares_check")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2508_05700_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host", "die_shares_check.cpp"), "-o", exe])
+    out = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
+    assert out.returncode == 0 and out.stdout.startswith("OK"), out.stdout
+
+
 @pytest.mark.parametrize("cls", [b.TableSet, b.MixedTables, b.CachedTables])
 @pytest.mark.parametrize("duplicate", [copy.copy, copy.deepcopy, lambda o: pickle.loads(pickle.dumps(o))])
 def test_copied_descriptors_are_read_where_the_copy_holds_them(cls, duplicate):
