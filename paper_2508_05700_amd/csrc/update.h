@@ -711,7 +711,6 @@ __global__ __launch_bounds__(UPD_BLOCK) void long_reduce_kernel(const emb_table 
     if (ctrl->abort) return;
     EMB_STAGE_TABLE_DIR(dir, tables, T, UPD_BLOCK)
     __syncthreads();
-    constexpr int GPW = EMB_WAVE / LPR;  // lane groups per wavefront
     constexpr int F = GradAcc<BF16>::F;
     constexpr int V = GradAcc<BF16>::V;
     const int lane = threadIdx.x & (EMB_WAVE - 1);
