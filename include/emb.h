@@ -258,7 +258,10 @@ int emb_bag_backward_rowwise_adagrad(const emb_table *tables_host, const emb_tab
  * Both take the arguments of emb_bag_backward_rowwise_adagrad with the same
  * meaning; T, D, dtype, B, nnz, the tables and the workspace must be the same
  * in both calls, and the update must be ordered after the sort (same stream,
- * or an event).  The sort records stage events 0..3, the update 3..5.
+ * or an event).  The records stay as they are: a further update from the same
+ * sort, ordered after the one before it, is one more step over the same
+ * lookups, with the gradient and learning rate it is given.
+ * The sort records stage events 0..3, the update 3..5.
  * emb_bag_backward_rowwise_adagrad is exactly the two calls in a row. */
 int emb_bag_backward_sort(const emb_table *tables_host, const emb_table *tables_dev, int32_t T,
                           int32_t D, int32_t dtype, const int64_t *rows_dev,

@@ -14,6 +14,10 @@
 // spans before its own, i.e. to wavefronts that were started earlier (as the waits of radix_sort.h).  The wait is
 // bounded, and needs no second outcome: a wavefront that gives up sums the missing chunks itself, in the same order.
 //
+// A launch leaves every flag as it found it, zero, so that the records can serve another update.  A flag has one writer and
+// one reader; whoever comes second clears it.  That is the reader, unless it gave up before the sum was there: it leaves
+// SPAN_GIVEN_UP then, and the writer, which finds that in the place of zero, clears it.
+//
 // A chunk sum goes to memory with stores that are visible to the whole device once complete (relaxed atomics of
 // device scope are not held back by the die's L2); the flag follows when they are.  No fence: a fence of device
 // scope writes back every dirty line of the L2.
@@ -23,6 +27,7 @@
 
 constexpr int SPAN_MAX = EMB_WAVE - UPD_LOOK;      // sorted records per wavefront at most: with the look-ahead one a lane
 constexpr uint32_t SPAN_COUNT_RECORDS = 2048;      // records whose distinct rows a counting workgroup counts
+constexpr uint32_t SPAN_SUMMED = 1, SPAN_GIVEN_UP = 2;   // a chunk's flag: its sum is in memory; its reader will not look at it
 
 __device__ __forceinline__ void span_store(float *p, float v)
 {
@@ -31,6 +36,12 @@ __device__ __forceinline__ void span_store(float *p, float v)
 __device__ __forceinline__ float span_load(const float *p)
 {
     return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// What the writer of a flag (mine: SPAN_SUMMED) and a reader that gives up (mine: SPAN_GIVEN_UP) do with it.
+__device__ __forceinline__ void span_flag_put(uint32_t *flag, uint32_t mine)
+{
+    const uint32_t found = __hip_atomic_exchange(flag, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (found != 0u) __hip_atomic_store(flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // the other has been here
 }
 
 // First record of the run that record i0 belongs to, by the whole wavefront.  `key` is its key; records of other runs
@@ -256,7 +267,7 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_spans_kernel(
                 }
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the sum is in memory before the flag is
-            if (lane == 0) __hip_atomic_store(flags + slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) span_flag_put(flags + slot, SPAN_SUMMED);
             continue;
         }
         if (n_before > 0) {
@@ -275,6 +286,11 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_spans_kernel(
                 ready = __ballot(!have) == 0;
             }
             asm volatile("" ::: "memory");
+            for (uint32_t c = lane; c < n_before; c += EMB_WAVE) {
+                uint32_t *flag = flags + (lo + c * LONG_CHUNK) / LONG_CHUNK;
+                if (ready) __hip_atomic_store(flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else span_flag_put(flag, SPAN_GIVEN_UP);
+            }
             GradAcc<BF16> acc[CPL];
 #pragma unroll
             for (int c = 0; c < CPL; ++c) acc[c].zero();

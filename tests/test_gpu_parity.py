@@ -1464,6 +1464,51 @@ def test_update_counts_the_distinct_rows_each_time_it_runs(n):
         assert int(nu.item()) == np.unique(rows).size
 
 
+@pytest.mark.parametrize("n,D,dtype", [
+    (5_000, 64, "f32"), (5_000, 8, "bf16"), (30_000, 48, "bf16"), (150_000, 16, "f32"), (400_000, 64, "f32"),
+])
+def test_several_updates_from_one_sort_equal_updates_from_a_sort_each(n, D, dtype):
+    _check_several_updates(n, D, dtype, 0)
+
+
+def _check_several_updates(n, D, dtype, extra_tables):
+    # Another gradient each time, over rows with one to 3000 lookups: a chunk sum of one update must not serve the next.
+    # The second update gives up every wait between wavefronts at once (and must leave nothing behind that the third
+    # one takes for a sum).  Bit for bit, with the number of distinct rows.
+    rng = np.random.default_rng(61_000 + n + D)
+    B, R = 40, 3_000
+    T = 1 + extra_tables       # the added ones have no lookups
+    rows = H.dev(_rows_with_run_lengths(rng, n, R, [257, 300, 511, 512, 513, 769, 33, 32, 3000]).astype(np.int64))
+    lengths = rng.multinomial(n, np.full(B, 1.0 / B))
+    off = H.dev(np.concatenate([[0], np.cumsum(lengths), np.full(extra_tables * B, n)]).astype(np.int64))
+    first = (rng.standard_normal((R, D)) * 0.01).astype(np.float32)
+    if dtype == "bf16":
+        first = wl.f32_to_bf16_bits(first).reshape(R, D)
+    tables = [first] + [np.zeros((1, D), first.dtype)] * extra_tables
+    douts = [torch.from_numpy(rng.standard_normal((T, B, D)).astype(np.float32)).to(H.DEV) for _ in range(4)]
+
+    def run(sort_each):
+        ts, w, acc = H.make_tableset(tables, dtype, with_accum=True)
+        ws = torch.empty(emb.emb_bag_backward_workspace_bytes(T, B, n, ts.total_rows, D, dtype), dtype=torch.uint8, device=H.DEV)
+        nu = torch.zeros(1, dtype=torch.int64, device=H.DEV)
+        seen = []
+        for k, d in enumerate(douts):
+            if k == 0 or sort_each:
+                emb.emb_bag_backward_sort(ts, rows, off, B, "mean", ws)
+            nu.fill_(-1)
+            emb.emb_debug_sort_poll_limit(0 if k == 1 and not sort_each else -1)
+            try:
+                emb.emb_bag_backward_update(ts, B, n, d, 0.01, 1e-8, ws, nu)
+            finally:
+                emb.emb_debug_sort_poll_limit(-1)
+            seen.append((w[0].clone(), acc[0].clone(), int(nu.item())))
+        return seen
+
+    for k, (one, each) in enumerate(zip(run(False), run(True))):
+        assert one[2] == each[2] == torch.unique(rows).numel(), k
+        assert torch.equal(one[0], each[0]) and torch.equal(one[1], each[1]), k
+
+
 def test_a_sparse_tensor_is_an_error():
     lengths = torch.ones(8, dtype=torch.int32, device=H.DEV).to_sparse()
     with pytest.raises((TypeError, RuntimeError)):
@@ -2709,3 +2754,38 @@ def test_a_captured_training_step_replays_like_eager_calls(side, from_lengths):
         check(bi, "replay %d" % i)
         junk = torch.randn(1 << 20, device=dev).sum().item()          # eager work between the replays
         assert np.isfinite(junk)
+
+
+@pytest.mark.parametrize("defer", [True, False])
+def test_a_captured_update_of_few_lookups_can_be_joined(defer):
+    # such an update leaves nothing on the side stream; the wait for it is captured all the same
+    rng = np.random.default_rng(9100)
+    T, B, D, R, n = 2, 50, 16, 400, 3000
+    rows = H.dev(rng.integers(0, R, size=n).astype(np.int64))
+    off = H.dev(np.linspace(0, n, T * B + 1).astype(np.int64))
+    dout = torch.from_numpy(rng.standard_normal((T, B, D)).astype(np.float32)).to(H.DEV)
+    tables = [(rng.standard_normal((R, D)) * 0.01).astype(np.float32) for _ in range(T)]
+    nbytes = emb.emb_bag_backward_workspace_bytes(T, B, n, T * R, D, "f32")
+
+    def program():
+        ts, w, acc = H.make_tableset(tables, "f32", with_accum=True)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=H.DEV)
+        side = emb.SideStream(torch.device(H.DEV))
+        side.defer_join = defer
+
+        def step():
+            emb.emb_bag_backward_sort(ts, rows, off, B, "sum", ws)
+            emb.emb_bag_backward_update(ts, B, n, dout, 0.01, 1e-8, ws, None, None, side)
+            side.join()
+        return step, w, acc, (ts, ws, side)
+
+    eager, w, acc, keep = program()
+    captured, w2, acc2, keep2 = program()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(device=H.DEV)):
+        captured()
+    for i in range(3):
+        eager()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(w + acc, w2 + acc2)), i
