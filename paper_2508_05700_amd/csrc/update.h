@@ -453,16 +453,21 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_kernel(const emb_table *__re
 // run start inside the span (queue_end, NO_RECORD if there is none), and the
 // span's first run start (span_head), so that the end of a run that leaves its span
 // is found by looking at the spans after it and not by searching the keys.
+// First of all it clears what long_prepare_kernel counts in: the records may have served an update before.
 constexpr uint32_t NO_RECORD = 0xFFFFFFFFu;
 
 template <typename KeyT>
 __global__ __launch_bounds__(256) void long_detect_kernel(const KeyT *__restrict__ keys, uint32_t n, KeyT sentinel,
-                                                          const BwdCtrl *ctrl, uint32_t *__restrict__ queue,
+                                                          BwdCtrl *ctrl, uint32_t *__restrict__ queue,
                                                           uint32_t *__restrict__ queue_end,
                                                           uint32_t *__restrict__ span_head,
                                                           uint32_t *__restrict__ wave_heads, uint32_t slots)
 {
     if (ctrl->abort) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctrl->num_unique = 0;
+        ctrl->task_and_multi_count = 0ull;
+    }
     static_assert(UPD_SPAN == 4 * EMB_WAVE, "four records per lane");
     static_assert(UPD_SHORT_MAX % 4 == 0 && UPD_SHORT_MAX + 4 <= SORT_PAD, "far records are read four at a time");
     const int lane = threadIdx.x & (EMB_WAVE - 1);

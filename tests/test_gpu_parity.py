@@ -1471,6 +1471,12 @@ def test_several_updates_from_one_sort_equal_updates_from_a_sort_each(n, D, dtyp
     _check_several_updates(n, D, dtype, 0)
 
 
+@pytest.mark.parametrize("n,D,dtype,extra_tables", [(5_000, 48, "bf16", 512), (30_000, 64, "f32", 600), ((1 << 20) + 5_000, 4, "f32", 0)])
+def test_several_updates_from_one_sort_with_many_tables_or_lookups(n, D, dtype, extra_tables):
+    # more tables or lookups than the update in one launch takes: rows with many lookups are counted and cut in launches of their own
+    _check_several_updates(n, D, dtype, extra_tables)
+
+
 def _check_several_updates(n, D, dtype, extra_tables):
     # Another gradient each time, over rows with one to 3000 lookups: a chunk sum of one update must not serve the next.
     # The second update gives up every wait between wavefronts at once (and must leave nothing behind that the third
