@@ -161,13 +161,17 @@ size_t emb_bag_backward_workspace_bytes(int32_t T, int64_t B, int64_t nnz, int64
  * stream that `stream` does not wait for.
  * defer_join != 0 (set by the caller; a struct filled by hand is zeroed
  * first): emb_bag_backward_update / emb_bag_backward_rowwise_adagrad record
- * join_event on the side stream but do not make `stream` wait for it.  A wait
+ * join_event after the work on the side stream but do not make `stream` wait
+ * for it; the rest of their work is on `stream`.  (A batch of few lookups has
+ * nothing on the side stream: see emb_bag_backward_rowwise_adagrad.  Then
+ * join_event is recorded on `stream`, after the whole update.)  A wait
  * that a stream reaches before the awaited work has ended costs it some
  * 10 us after that work's end; one that it reaches later costs almost
  * nothing.  So a training loop defers the wait until work that does not
  * depend on the update has been enqueued behind it: the next step's
  * emb_bag_forward_train_lengths_after waits just before its lookup reads the
- * tables, after its two set-up launches.  Until some stream has waited
+ * tables, after the launches that set it up (two; with few lookups one or
+ * none).  Until some stream has waited
  * (that call, or emb_side_stream_join) and the work ordered after the wait,
  * the caller must not read or write the tables and accumulators, nor reuse
  * the backward's workspace and num_unique_out_dev: a loop that defers

@@ -494,6 +494,10 @@ int launch_update_spans(const BwdArgs &a, const BwdLayout &L, const uint32_t *ke
                        reinterpret_cast<float *>(a.ws + L.partials), sort_poll_limit, reinterpret_cast<BwdCtrl *>(a.ws + L.ctrl),
                        a.num_unique_out);
     EMB_RETURN_IF_LAUNCH_FAILED();
+    // nothing is left on the side stream, but whoever waits for its join_event waits for this update
+    if (a.side && a.side->defer_join &&
+        hipEventRecord(reinterpret_cast<hipEvent_t>(a.side->join_event), a.stream) != hipSuccess)
+        return EMB_ERR_HIP;
     EMB_MARK(a, 4);
     EMB_MARK(a, 5);
     return EMB_OK;

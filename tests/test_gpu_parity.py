@@ -2762,6 +2762,33 @@ def test_a_captured_training_step_replays_like_eager_calls(side, from_lengths):
         assert np.isfinite(junk)
 
 
+def test_a_deferred_update_of_few_lookups_is_waited_for_by_another_stream():
+    # the update stands behind some milliseconds of other work; a copy on another stream that waits for it by the side
+    # stream's event sees the rows as they are after it
+    rng = np.random.default_rng(9050)
+    T, B, D, R, n = 1, 50, 16, 400, 3000
+    ts, w, _ = H.make_tableset([np.zeros((R, D), np.float32)], "f32", with_accum=True)
+    rows = H.dev(rng.integers(0, R, size=n).astype(np.int64))
+    off = H.dev(np.linspace(0, n, T * B + 1).astype(np.int64))
+    dout = torch.ones(T * B * D, device=H.DEV)
+    ws = torch.empty(emb.emb_bag_backward_workspace_bytes(T, B, n, R, D, "f32"), dtype=torch.uint8, device=H.DEV)
+    emb.emb_bag_backward_sort(ts, rows, off, B, "sum", ws)
+    side = emb.SideStream(torch.device(H.DEV))
+    side.defer_join = True
+    busy = torch.randn((4096, 4096), device=H.DEV)
+    seen = torch.empty_like(w[0])
+    other = torch.cuda.Stream(device=H.DEV)
+    torch.cuda.synchronize()
+    for _ in range(8):
+        busy = torch.mm(busy, busy).tanh()
+    emb.emb_bag_backward_update(ts, B, n, dout, 0.01, 1e-8, ws, None, None, side)
+    with torch.cuda.stream(other):
+        side.join()
+        seen.copy_(w[0])
+    torch.cuda.synchronize()
+    assert bool((w[0] != 0).any()) and torch.equal(seen, w[0])
+
+
 @pytest.mark.parametrize("defer", [True, False])
 def test_a_captured_update_of_few_lookups_can_be_joined(defer):
     # such an update leaves nothing on the side stream; the wait for it is captured all the same
