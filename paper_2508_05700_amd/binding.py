@@ -317,14 +317,16 @@ _entries = {}
 
 
 def _load_calls():
-    """The module of csrc/calls.cpp, or False where it is neither built nor can be, or was made for another torch."""
+    """The module of csrc/calls.cpp for this torch, or False where it is neither built nor can be."""
     import importlib.machinery
     import importlib.util
     try:
         if _build.calls_is_stale():
+            if not _build.calls_can_be_built():
+                return False
             _build.build_calls(verbose=False)
-        spec = importlib.util.spec_from_file_location(
-            __package__ + "._calls", _build.CALLS, loader=importlib.machinery.ExtensionFileLoader(__package__ + "._calls", _build.CALLS))
+        loader = importlib.machinery.ExtensionFileLoader(__package__ + "._calls", _build.calls_path())
+        spec = importlib.util.spec_from_file_location(loader.name, loader.path, loader=loader)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
         return module

@@ -1,8 +1,9 @@
 """Builds the HIP library (``libemb_hip.so``) for gfx950 with hipcc, and with g++ the CPython module
-(``_calls.so``) that marshals the shortest calls.
+(``_calls.*.so``) that marshals the shortest calls.
 
-The library is plain C ABI (``include/emb.h``): one ``hipcc -shared`` line.  The module knows torch tensors and is of
-use to ``binding.py`` only, which does without it where it is missing.
+The library is plain C ABI (``include/emb.h``): one ``hipcc -shared`` line.  The module knows torch tensors (it is
+compiled against the layout of those of one torch, which its file's name says) and is of use to ``binding.py`` only,
+which does without it where it is missing.
 """
 from __future__ import annotations
 
@@ -16,7 +17,6 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libemb_hip.so")
 
-CALLS = os.path.join(PKG, "_calls.so")
 CALLS_SRC = os.path.join(CSRC, "calls.cpp")
 
 CXX = os.environ.get("CXX", "g++")
@@ -40,9 +40,33 @@ def is_stale() -> bool:
     return os.path.getmtime(LIB) < max(os.path.getmtime(d) for d in deps)
 
 
-def calls_is_stale() -> bool:
+def calls_path() -> str:
+    """The module for this interpreter and this torch: those of others have other names."""
+    import re
+    import sysconfig
+
+    import torch
+    return os.path.join(PKG, "_calls.%s-torch-%s.so" % (sysconfig.get_config_var("SOABI"),
+                                                        re.sub(r"[^A-Za-z0-9.+]", "_", torch.__version__)))
+
+
+def _calls_failed_path() -> str:
+    """Empty file left by an attempt to compile the module that failed."""
+    return os.path.join(PKG, "_build", os.path.basename(calls_path()) + ".failed")
+
+
+def _older_than_calls_sources(path: str) -> bool:
     deps = (CALLS_SRC, os.path.join(ROOT, "include", "emb.h"))
-    return not os.path.exists(CALLS) or os.path.getmtime(CALLS) < max(os.path.getmtime(d) for d in deps)
+    return not os.path.exists(path) or os.path.getmtime(path) < max(os.path.getmtime(d) for d in deps)
+
+
+def calls_is_stale() -> bool:
+    return _older_than_calls_sources(calls_path())
+
+
+def calls_can_be_built() -> bool:
+    """False where the file cannot be written, and after a failed attempt until the sources change."""
+    return os.access(PKG, os.W_OK) and _older_than_calls_sources(_calls_failed_path())
 
 
 def build_calls(verbose: bool = True) -> str:
@@ -50,13 +74,22 @@ def build_calls(verbose: bool = True) -> str:
     import sysconfig
 
     import torch
-    t = os.path.dirname(torch.__file__)
-    _run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
-          "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
-          "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
-          CALLS_SRC, "-o", CALLS + ".%d" % os.getpid(), "-L", os.path.join(t, "lib"), "-ltorch_python", "-lc10"], verbose)
-    os.replace(CALLS + ".%d" % os.getpid(), CALLS)   # other processes see all of it or none
-    return CALLS
+    t, out, failed = os.path.dirname(torch.__file__), calls_path(), _calls_failed_path()
+    part = out + ".%d" % os.getpid()
+    try:
+        _run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+              "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(t, "include"),
+              "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+              CALLS_SRC, "-o", part, "-L", os.path.join(t, "lib"), "-ltorch_python", "-lc10"], verbose)
+    except (OSError, RuntimeError):
+        os.makedirs(os.path.dirname(failed), exist_ok=True)
+        with open(failed, "w"):
+            pass
+        raise
+    os.replace(part, out)   # other processes see all of it or none
+    if os.path.exists(failed):
+        os.remove(failed)
+    return out
 
 
 def _run(cmd, verbose):
@@ -72,7 +105,8 @@ def _run(cmd, verbose):
 
 
 def build(verbose: bool = True, jobs: int = 6) -> str:
-    """Compile every ``csrc/*.hip`` for gfx950 (in parallel) and link ``libemb_hip.so``; then ``_calls.so``."""
+    """Compile every ``csrc/*.hip`` for gfx950 (in parallel) and link ``libemb_hip.so``; then the module of ``csrc/calls.cpp``,
+    whose failure is reported and no error."""
     from concurrent.futures import ThreadPoolExecutor
 
     objdir = os.path.join(PKG, "_build")
@@ -88,7 +122,10 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(cmds)))) as ex:
         list(ex.map(lambda c: _run(c, verbose), cmds))
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
-    build_calls(verbose)
+    try:
+        build_calls(verbose)
+    except (OSError, RuntimeError) as e:
+        print("no module of csrc/calls.cpp, calls go through ctypes: %s" % e, file=sys.stderr, flush=True)
     return LIB
 
 

@@ -594,3 +594,35 @@ def test_native_marshalling_agrees_with_ctypes(name):
             native(*wrong)
     with pytest.raises(TypeError):
         native(*[1.5 if t in (C.c_int32, C.c_int64) else a for t, a in zip(argtypes, args)])
+
+
+def test_native_marshalling_is_looked_for_under_the_name_of_this_torch_and_interpreter(monkeypatch):
+    import sysconfig
+    from paper_2508_05700_amd import build
+    here = build.calls_path()
+    assert os.path.exists(here) and sysconfig.get_config_var("SOABI") in here and torch.__version__ in here
+    monkeypatch.setattr(torch, "__version__", "99.0/other build")
+    assert build.calls_path() != here and os.path.dirname(build.calls_path()) == os.path.dirname(here)
+    assert build.calls_is_stale()                               # one made for another torch is not taken for it
+    monkeypatch.undo()
+    monkeypatch.setattr(sysconfig, "get_config_var", lambda name: "cpython-399-other")
+    assert build.calls_path() != here and build.calls_is_stale()
+
+
+def test_native_marshalling_that_cannot_be_compiled_is_no_error_and_tried_once(monkeypatch, tmp_path):
+    from paper_2508_05700_amd import build
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setattr(build, "CXX", str(tmp_path / "no_such_compiler"))
+    tried = []
+    run = build._run
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose: tried.append(cmd) or run(cmd, verbose))
+    assert b._load_calls() is False and len(tried) == 1
+    assert b._load_calls() is False and len(tried) == 1         # nor by the next process, until the sources change
+    monkeypatch.setattr(build, "sources", lambda: [])           # the library's own commands succeed
+    monkeypatch.setattr(build, "HIPCC", "true")
+    assert build.build(verbose=False) == build.LIB
+    os.utime(build._calls_failed_path(), (0, 0))                # older than the sources
+    assert build.calls_can_be_built()
+    monkeypatch.setattr(build.os, "access", lambda path, mode: False)
+    tried.clear()
+    assert b._load_calls() is False and not tried               # a folder that cannot be written
