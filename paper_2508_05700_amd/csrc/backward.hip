@@ -646,7 +646,7 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     const bool want_list = a.unique_keys_out || a.unique_counts_out;
     unsigned long long *list_flags = want_list ? tile_heads : nullptr;
     uint32_t *span_flags = a.spans ? span_flags_of(a, L) : nullptr;   // those of update_spans_kernel are cleared with them
-    const uint32_t n_span_flags = (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK);
+    const uint32_t n_span_flags = a.spans ? (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK) : 0u;
     const int passes = a.small ? 0 : a.passes;
     const bool exchange = !a.small && a.nnz <= (int64_t)SORT_EXCHANGE_MAX_TILES * SORT_TILE * (a.T > 0 ? a.T : 1);
     const uint32_t poll_limit = sort_poll_limit;
@@ -1037,7 +1037,7 @@ int bwd_plan(const emb_table *tables_host, const emb_table *tables_dev, int32_t 
     a.key_bits = bits < 1 ? 1 : bits;
     a.passes = passes;
     a.small = small_step(T, nnz, L.key_bytes);
-    a.spans = spans_step(T, nnz, L.key_bytes);
+    a.spans = spans_step(T, nnz, L.key_bytes, D, dtype == EMB_BF16);
     a.ws = reinterpret_cast<char *>(workspace_dev);
     a.stream = emb_stream(stream);
     return EMB_OK;

@@ -28,8 +28,8 @@ constexpr int LONG_CHUNK = 256;     // records of a queued run summed by one wav
 constexpr int PREP_BLOCK = 1024;     // workgroup of the kernel that turns queued runs into tasks
 constexpr int UPD_LDS_TABLES = 512; // table directories up to this size are staged in LDS
 
-// Small steps (32-bit keys, at most UPD_LDS_TABLES tables) are sorted by tile_merge_sort.h and updated by update_spans.h,
-// on the caller's stream alone; larger ones by radix_sort.h and update.h.  What ends the first is the merge, whose work
+// Small steps (32-bit keys, at most UPD_LDS_TABLES tables) are sorted by tile_merge_sort.h (small_step) and updated by
+// update_spans.h, on the caller's stream alone (spans_step); larger ones by radix_sort.h and update.h.  What ends the first is the merge, whose work
 // is the number of records times the records of a table, of which the host knows the average.  Whole steps of 256-byte
 // rows in us, with both / neither, in turn on one card: one table 60 000 records 54 / 100, 120 000 83 / 108, 240 000
 // 160 / 119; four tables 120 000 57 / 107, 240 000 87 / 118, 480 000 177 / 139; sixteen 128 000 53 / 105, 256 000 74 / 118,
@@ -42,13 +42,22 @@ static inline bool small_step(int32_t T, int64_t nnz, int key_bytes)
     return key_bytes == 4 && nnz > 0 && nnz <= SMALL_STEP_MAX && T <= UPD_LDS_TABLES && nnz * nnz / T <= SMALL_STEP_MERGE_MAX;
 }
 // What ends the second is the start and the staging of a wavefront per 32 records, which the fork to a second stream and
-// the join cost less than in the end.  Sorted the same way, in us, update_spans.h / update.h: one table 343 000 records of
-// 224 bytes 117 / 140, 480 000 of 64 80 / 106, of 256 127 / 147, 960 000 179 / 200; four 480 000 122 / 139, 960 000
-// 185 / 189; sixteen 512 000 130 / 145, 1 024 000 197 / 200, 2 049 000 339 / 315, 2 623 000 439 / 410.
-constexpr int64_t SPANS_STEP_MAX = 1 << 20;
-static inline bool spans_step(int32_t T, int64_t nnz, int key_bytes)
+// the join cost less than in the end, and sooner for bf16 rows, whose accumulators leave two wavefronts on a SIMD where
+// update.h has four.  Updates alone of the same sorted records in us, update_spans.h / update.h:
+//   fp32, one table of 128-byte rows that hardly repeat, 1 040 000 records 70 / 54; of 256 bytes 850 000 57 / 56,
+//   1 040 000 73 / 61; three tables with popular heads 850 000 70 / 75, 1 040 000 82 / 85; sixteen 850 000 88 / 92;
+//   bf16, one table of 128-byte rows that hardly repeat 500 000 45 / 55, 700 000 68 / 56; three of 256 bytes with popular
+//   heads 500 000 70 / 71, 700 000 91 / 86; sixteen 500 000 81 / 82, 700 000 106 / 101, of 384 bytes 850 000 181 / 156.
+// Wider rows gain up to the same lines (fp32 of 4 KB 300 000 336 / 415, of 16 KB 1245 / 1348; bf16 of 8 KB 1014 / 1115), except
+// bf16 rows beyond 8 KB: the sums of a chunk of 16 KB do not fit the registers (410 spilled a lane), and a row with many lookups is one
+// after the other of those.  Rows of 16 KB with popular heads, 10 000 records 695 / 1026, 12 000 815 / 1021, 16 000
+// 1078 / 1005, 60 000 1738 / 989; of 9 KB 16 000 979 / 836.
+constexpr int64_t SPANS_STEP_MAX = 3 << 18, SPANS_STEP_MAX_BF16 = 1 << 19, SPANS_STEP_MAX_BF16_WIDEST = 3 << 12;
+constexpr int32_t SPANS_BF16_WIDEST = 4096;   // values of a row; wider ones have 16 chunks a lane
+static inline bool spans_step(int32_t T, int64_t nnz, int key_bytes, int32_t D, bool bf16)
 {
-    return key_bytes == 4 && nnz > 0 && nnz <= SPANS_STEP_MAX && T <= UPD_LDS_TABLES;
+    const int64_t most = !bf16 ? SPANS_STEP_MAX : D <= SPANS_BF16_WIDEST ? SPANS_STEP_MAX_BF16 : SPANS_STEP_MAX_BF16_WIDEST;
+    return key_bytes == 4 && nnz > 0 && nnz <= most && T <= UPD_LDS_TABLES;
 }
 
 struct LongSeg {

@@ -1381,7 +1381,19 @@ def _rows_with_run_lengths(rng, n, R, runs):
     ([(1 << 18) - 5, 5], 200_000, 16, "f32"),             # the last sizes of the small route ...
     ([100_000, (1 << 18) + 1 - 100_000], 200_000, 16, "f32"),   # ... and beyond: the update's launch after the general sort
     ([200_000], 3000, 48, "bf16"),                        # too many in one table for the merge
-    ([(1 << 20) - 9, 9], 20_000, 4, "f32"),               # the last size of the one update launch
+    ([(1 << 20) - 9, 9], 20_000, 4, "f32"),               # beyond the one update launch
+    ([(3 << 18) - 9, 9], 20_000, 4, "f32"),               # its last size with fp32 rows ...
+    ([(3 << 18) - 9, 10], 20_000, 4, "f32"),              # ... one more
+    ([9, (1 << 19) - 9], 20_000, 8, "bf16"),              # with bf16 rows
+    ([10, (1 << 19) - 9], 20_000, 8, "bf16"),
+    ([3 << 12], 60, 4104, "bf16"),                        # with bf16 rows beyond 8 KB
+    ([(3 << 12) + 1], 60, 4104, "bf16"),
+    ([1_300, 5_000], 60, 1024, "f32"),                    # every number of chunks of a row that a lane of a wavefront holds, runs
+    ([5_000], 60, 1032, "f32"),                           # of several chunks of records among them
+    ([5_000], 60, 4096, "f32"),
+    ([5_000], 60, 2048, "bf16"),
+    ([5_000], 60, 4096, "bf16"),
+    ([5_000], 60, 8192, "bf16"),
 ])
 def test_small_steps_give_the_bits_of_the_general_route(per_table, R, D, dtype):
     # The same batch with more tables than the small route takes: the added tables have no lookups.  Rows, accumulators,
