@@ -29,18 +29,25 @@ constexpr int PREP_BLOCK = 1024;     // workgroup of the kernel that turns queue
 constexpr int UPD_LDS_TABLES = 512; // table directories up to this size are staged in LDS
 
 // Small steps (32-bit keys, at most UPD_LDS_TABLES tables) are sorted by tile_merge_sort.h (small_step) and updated by
-// update_spans.h, on the caller's stream alone (spans_step); larger ones by radix_sort.h and update.h.  What ends the first is the merge, whose work
-// is the number of records times the records of a table, of which the host knows the average.  Whole steps of 256-byte
-// rows in us, with both / neither, in turn on one card: one table 60 000 records 54 / 100, 120 000 83 / 108, 240 000
-// 160 / 119; four tables 120 000 57 / 107, 240 000 87 / 118, 480 000 177 / 139; sixteen 128 000 53 / 105, 256 000 74 / 118,
-// 512 000 126 / 145, 1 024 000 255 / 200.  Up to SMALL_STEP_MAX a batch that has all its records in one of its tables
-// loses 40 % at most; sixteen even tables would still gain at twice as many.
-constexpr int64_t SMALL_STEP_MAX = 1 << 18;
-constexpr int64_t SMALL_STEP_MERGE_MAX = (int64_t)1 << 35;   // records times average records of a table
+// update_spans.h, on the caller's stream alone (spans_step); larger ones by radix_sort.h and update.h.  What ends the first
+// is the merge, whose work is the number of records times the records of a table, of which the host knows the average:
+// SMALL_STEP_MERGE_MAX is where even tables lose.  But a batch may have all its records in one of its tables:
+// SMALL_STEP_MAX is where such a batch takes as long as it does without either route.  Whole steps of 256-byte rows with
+// popular heads in us, merged / sorted by radix_sort.h / that in its earlier form (wave_rank_digits) and update.h, in turn on
+// one card:
+//   even tables: one 92 000 records 68 / 71 / 105, 110 000 75 / 73 / 106, 150 000 111 / 81 / 113; two 130 000 68 / 76 / 106,
+//   150 000 83 / 79 / 112; four 160 000 73 / 83 / 114, 262 000 94 / 94 / 121; seven 150 000 65 / 81 / 114; sixteen 160 000
+//   65 / 87 / 122, 262 000 81 / 100 / 127;
+//   all records in one of two 150 000 115 / 82 / 115, of seven 131 / 98 / 131, of twenty-four 140 / 107 / 141, of sixteen
+//   185 000 160 / 113 / 147, 262 000 211 / 134 / 162; four fifths in one of sixteen 160 000 113 / 103 / 140, 262 000
+//   186 / 127 / 160.
+constexpr int64_t SMALL_STEP_MAX = 150'000;
+constexpr int64_t SMALL_STEP_MERGE_MAX = (int64_t)9 << 30;   // records times average records of a table
 static inline bool small_step(int32_t T, int64_t nnz, int key_bytes)
 {
     return key_bytes == 4 && nnz > 0 && nnz <= SMALL_STEP_MAX && T <= UPD_LDS_TABLES && nnz * nnz / T <= SMALL_STEP_MERGE_MAX;
 }
+
 // What ends the second is the start and the staging of a wavefront per 32 records, which the fork to a second stream and
 // the join cost less than in the end, and sooner for bf16 rows, whose accumulators leave two wavefronts on a SIMD where
 // update.h has four.  Updates alone of the same sorted records in us, update_spans.h / update.h:
@@ -49,8 +56,8 @@ static inline bool small_step(int32_t T, int64_t nnz, int key_bytes)
 //   bf16, one table of 128-byte rows that hardly repeat 500 000 45 / 55, 700 000 68 / 56; three of 256 bytes with popular
 //   heads 500 000 70 / 71, 700 000 91 / 86; sixteen 500 000 81 / 82, 700 000 106 / 101, of 384 bytes 850 000 181 / 156.
 // Wider rows gain up to the same lines (fp32 of 4 KB 300 000 336 / 415, of 16 KB 1245 / 1348; bf16 of 8 KB 1014 / 1115), except
-// bf16 rows beyond 8 KB: the sums of a chunk of 16 KB do not fit the registers (410 spilled a lane), and a row with many lookups is one
-// after the other of those.  Rows of 16 KB with popular heads, 10 000 records 695 / 1026, 12 000 815 / 1021, 16 000
+// bf16 rows beyond 8 KB: the sums of a chunk of 16 KB do not fit the registers (410 spilled a lane), and a row with many
+// lookups is many such chunks.  Rows of 16 KB with popular heads, 10 000 records 695 / 1026, 12 000 815 / 1021, 16 000
 // 1078 / 1005, 60 000 1738 / 989; of 9 KB 16 000 979 / 836.
 constexpr int64_t SPANS_STEP_MAX = 3 << 18, SPANS_STEP_MAX_BF16 = 1 << 19, SPANS_STEP_MAX_BF16_WIDEST = 3 << 12;
 constexpr int32_t SPANS_BF16_WIDEST = 4096;   // values of a row; wider ones have 16 chunks a lane

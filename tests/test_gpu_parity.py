@@ -1378,9 +1378,13 @@ def _rows_with_run_lengths(rng, n, R, runs):
     ([66_000, 100], 300, 4, "f32"),                       # a few rows with hundreds of lookups each
     ([70_000], 3, 16, "f32"),                             # ... with tens of thousands: chunks found far behind
     ([8_000], 700, 320, "f32"),
-    ([(1 << 18) - 5, 5], 200_000, 16, "f32"),             # the last sizes of the small route ...
-    ([100_000, (1 << 18) + 1 - 100_000], 200_000, 16, "f32"),   # ... and beyond: the update's launch after the general sort
+    ([(1 << 18) - 5, 5], 200_000, 16, "f32"),             # beyond the small route: the update's launch after the general sort
+    ([100_000, (1 << 18) + 1 - 100_000], 200_000, 16, "f32"),
     ([200_000], 3000, 48, "bf16"),                        # too many in one table for the merge
+    ([3 << 15], 3000, 16, "f32"),                         # the last size of one table that is merged, one more
+    ([(3 << 15) + 1], 3000, 16, "f32"),
+    ([149_990, 5, 5], 200_000, 16, "f32"),                # the last size of several, nearly all of it in one; one more
+    ([75_000, 75_000, 1], 200_000, 16, "f32"),
     ([(1 << 20) - 9, 9], 20_000, 4, "f32"),               # beyond the one update launch
     ([(3 << 18) - 9, 9], 20_000, 4, "f32"),               # its last size with fp32 rows ...
     ([(3 << 18) - 9, 10], 20_000, 4, "f32"),              # ... one more
@@ -1430,7 +1434,7 @@ def test_small_steps_give_the_bits_of_the_general_route(per_table, R, D, dtype):
     assert np.array_equal(g["unique_keys"], g2["unique_keys"]) and np.array_equal(g["unique_counts"], g2["unique_counts"])
     for t in range(T):
         assert np.array_equal(w[t], w2[t]) and np.array_equal(acc[t], acc2[t]), t
-    if sum(per_table) <= 1 << 17:   # (the general sort waits as well)
+    if sum(per_table) <= 3 << 15:   # (the general sort waits as well)
         g3, w3, acc3 = run(0, poll_limit=0, want_unique=False)
         assert g3["status"] == g["status"] and g3["U"] == g["U"]
         for t in range(T):
