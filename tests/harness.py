@@ -103,6 +103,19 @@ def make_tableset(tables_np: List[np.ndarray], dtype: str, with_accum: bool = Fa
     return emb.TableSet(w, tables_np[0].shape[1], dtype, accum=acc, salts=salts, device=torch.device(DEV)), w, acc
 
 
+MANY_TABLES = 512   # added to a batch's tables: more than the routes for few lookups take, so it goes the general way
+
+
+def add_empty_tables(extra: int, tables: List[np.ndarray], off: np.ndarray, dout: np.ndarray):
+    """(tables, offsets, gradient) with `extra` tables of one row behind the others, without lookups."""
+    if not extra:
+        return tables, off, dout
+    B, D = dout.shape[1:]
+    return (tables + [np.zeros((1, D), dtype=tables[0].dtype)] * extra,
+            np.concatenate([off, np.full(extra * B, off[-1], dtype=np.int64)]),
+            np.concatenate([dout, np.zeros((extra, B, D), dtype=np.float32)]))
+
+
 def gpu_forward(ts, rows_np, off_np, B, mode):
     out = torch.full((ts.T, B, ts.D), float("nan"), dtype=torch.float32, device=DEV)
     status = torch.zeros(1, dtype=torch.int32, device=DEV)

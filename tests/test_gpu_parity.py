@@ -712,7 +712,8 @@ def _check_backward_against_oracle(tables, Rs, rows, off, B, D, mode, dout, what
         assert int((acc_dev[t] != 0).sum().item()) == int((ref_a[t] != 0).sum())      # nothing else was touched
 
 
-def test_backward_sort_tables_of_very_different_key_widths():
+@pytest.mark.parametrize("extra", [0, H.MANY_TABLES])
+def test_backward_sort_tables_of_very_different_key_widths(extra):
     # Tables whose keys need different numbers of sort passes in one batch (the passes cover the widest):
     # table 0 (22-bit keys): one row with 30 000 lookups and one with 9 000 (runs that leave their span by
     #   dozens of spans; their ends are found from the noted run starts), the rest spread out;
@@ -720,6 +721,7 @@ def test_backward_sort_tables_of_very_different_key_widths():
     #   sorts last inside the table);
     # table 2 (27-bit keys, four passes): rows spread over the whole table, a hot row, and the last row;
     # table 3: no lookups; table 4: a single lookup.
+    # extra: more tables than the route for few lookups takes; without them it is merged (three passes of nine bits in LDS).
     rng = np.random.default_rng(777)
     D, B = 4, 64
     Rs = [3_000_000, 200, 70_000_000, 50, 1000]
@@ -747,7 +749,8 @@ def test_backward_sort_tables_of_very_different_key_widths():
     rows = np.concatenate(parts).astype(np.int64)
     tables = [(rng.standard_normal((R, D)) * 0.01).astype(np.float32) for R in Rs]
     dout = rng.standard_normal((T, B, D)).astype(np.float32)
-    _check_backward_against_oracle(tables, Rs, rows, off, B, D, "sum", dout, "buckets", emb.STATUS_BAD_INDEX)
+    tables, off, dout = H.add_empty_tables(extra, tables, off, dout)
+    _check_backward_against_oracle(tables, Rs + [1] * extra, rows, off, B, D, "sum", dout, "buckets", emb.STATUS_BAD_INDEX)
 
 
 def test_backward_sort_one_table_of_many_tiles():
@@ -801,7 +804,8 @@ def test_backward_sort_more_than_a_thousand_tiles(T):
     _check_backward_against_oracle(tables, [R] * T, rows, off, B, D, "sum", dout, "more than a thousand tiles")
 
 
-def test_backward_split_calls_on_two_streams_equal_the_single_call():
+@pytest.mark.parametrize("extra", [0, H.MANY_TABLES])
+def test_backward_split_calls_on_two_streams_equal_the_single_call(extra):
     # emb_bag_backward_sort on a second stream (while other work runs on the first), then
     # emb_bag_backward_update: bit-identical tables, accumulators and row lists.
     rng = np.random.default_rng(4343)
@@ -810,6 +814,8 @@ def test_backward_split_calls_on_two_streams_equal_the_single_call():
     rows = rows.copy()
     rows[[3, 40_000]] = [1 << 40, -1]                        # invalid rows travel through the split too
     dout = rng.standard_normal((T, B, D)).astype(np.float32)
+    tables, off, dout = H.add_empty_tables(extra, tables, off, dout)
+    T += extra
     nnz = rows.size
     ts1, w1, a1 = H.make_tableset(tables, "f32", with_accum=True)
     g1 = H.gpu_backward(ts1, rows, off, B, "mean", dout, 0.01, 1e-8, side=False)
@@ -1204,13 +1210,14 @@ def test_many_tables_take_the_paths_without_lds_staging():
         H.assert_rows_close(w[t].cpu().numpy(), ref_t[t], tables[t], 0.01, what="many tables rows t=%d" % t)
 
 
-@pytest.mark.parametrize("extra", [0, 1])
+@pytest.mark.parametrize("nnz", [3 << 18, (3 << 18) + 1, 1 << 20, (1 << 20) + 1])
 @pytest.mark.parametrize("side", [True, False])
-def test_backward_at_the_line_between_the_two_ways_to_prepare_long_runs(extra, side):
-    # up to 2^20 records the queued runs are prepared by workgroups of four wavefronts, beyond by sixteen; the
-    # gradients are small whole numbers, so the sums of the runs (3500 records in table 1) are exact in any order
-    rng = np.random.default_rng(46 + extra)
-    T, B, D, Rs, nnz = 2, 1024, 16, [50_000, 150], (1 << 20) + extra
+def test_backward_at_the_line_between_the_two_ways_to_sum_long_runs(nnz, side):
+    # up to 3 * 2^18 records the runs of many records are summed by the launch that sums the short ones, beyond by launches
+    # of their own; the gradients are small whole numbers, so the sums of the runs (2600 and more records in table 1)
+    # are exact in any order
+    rng = np.random.default_rng(46 + nnz)
+    T, B, D, Rs = 2, 1024, 16, [50_000, 150]
     half = [nnz // 2, nnz - nnz // 2]
     lengths = np.concatenate([rng.multinomial(n, np.full(B, 1.0 / B)) for n in half]).astype(np.int32)
     off, _ = oracle.lengths_to_offsets(lengths)
@@ -1271,12 +1278,14 @@ def test_backward_bad_indices_skipped_and_bad_offsets_abort():
             assert np.all(acc_dev[t].cpu().numpy() == 0)
 
 
-def test_training_steps_with_the_join_deferred_into_the_next_lookup_equal_steps_that_join_at_once():
+@pytest.mark.parametrize("extra", [H.MANY_TABLES, 0])
+def test_training_steps_with_the_join_deferred_into_the_next_lookup_equal_steps_that_join_at_once(extra):
     # Five training steps over the same tables (hot IDs in every batch, so the long-run path on the side
     # stream has work and its rows are read again by the next step's lookup).  Route A joins the side
     # stream at the end of every backward; route B defers the join into the next step's lookup call and
     # alternates between two workspaces.  Pooled outputs of every step, final tables and accumulators bit
-    # for bit; route A's final tables against the oracle run over the same five steps.
+    # for bit; route A's final tables against the oracle run over the same five steps.  (Without the added tables, which
+    # have no lookups, the steps are updated in one launch and leave nothing on the side stream.)
     rng = np.random.default_rng(4477)
     T, B, D = 3, 1200, 16
     Rs = [30_000, 17, 50_001]
@@ -1292,11 +1301,11 @@ def test_training_steps_with_the_join_deferred_into_the_next_lookup_equal_steps_
         steps.append((lengths, off, raw, dout))
 
     def run(defer):
-        w = [H.dev(t) for t in tables]
-        acc = [torch.zeros(R, dtype=torch.float32, device=H.DEV) for R in Rs]
-        ts = emb.TableSet(w, D, "f32", accum=acc, salts=salts, device=torch.device(H.DEV))
+        w = [H.dev(t) for t in tables] + [torch.zeros((1, D), device=H.DEV) for _ in range(extra)]
+        acc = [torch.zeros(t.shape[0], dtype=torch.float32, device=H.DEV) for t in w]
+        ts = emb.TableSet(w, D, "f32", accum=acc, salts=salts + [0] * extra, device=torch.device(H.DEV))
         max_nnz = max(s[2].size for s in steps)
-        nbytes = emb.emb_bag_backward_workspace_bytes(T, B, max_nnz, ts.total_rows, D, "f32")
+        nbytes = emb.emb_bag_backward_workspace_bytes(T + extra, B, max_nnz, ts.total_rows, D, "f32")
         wss = [torch.empty(nbytes, dtype=torch.uint8, device=H.DEV) for _ in range(2 if defer else 1)]
         nus = [torch.zeros(1, dtype=torch.int64, device=H.DEV) for _ in wss]
         side = emb.SideStream(torch.device(H.DEV))
@@ -1305,8 +1314,10 @@ def test_training_steps_with_the_join_deferred_into_the_next_lookup_equal_steps_
         outs, offs = [], []
         for k, (lengths, off, raw, dout) in enumerate(steps):
             ws, nu = wss[k % len(wss)], nus[k % len(wss)]
-            out = torch.full((T, B, D), float("nan"), dtype=torch.float32, device=H.DEV)
-            offs_out = torch.full((T * B + 1,), -1, dtype=torch.int64, device=H.DEV)
+            lengths = np.concatenate([lengths, np.zeros(extra * B, np.int32)])
+            dout = np.concatenate([dout, np.zeros((extra, B, D), np.float32)])
+            out = torch.full((T + extra, B, D), float("nan"), dtype=torch.float32, device=H.DEV)
+            offs_out = torch.full(((T + extra) * B + 1,), -1, dtype=torch.int64, device=H.DEV)
             emb.emb_bag_forward_train_lengths_after(ts, H.dev(raw), H.dev(lengths), B, "sum", out, offs_out, ws,
                                                     side if defer else None, None, nu, st)
             emb.emb_bag_backward_sort_prepared(ts, B, raw.size, ws, None, None, nu, st)
@@ -1323,7 +1334,7 @@ def test_training_steps_with_the_join_deferred_into_the_next_lookup_equal_steps_
     outs_b, offs_b, w_b, acc_b = run(True)
     for k in range(len(steps)):
         assert torch.equal(outs_a[k], outs_b[k]) and torch.equal(offs_a[k], offs_b[k]), k
-        assert np.array_equal(offs_a[k].cpu().numpy(), steps[k][1])
+        assert np.array_equal(offs_a[k].cpu().numpy()[:T * B + 1], steps[k][1])
     for t in range(T):
         assert torch.equal(w_a[t], w_b[t]) and torch.equal(acc_a[t], acc_b[t]), t
     ref_t, ref_a = [t.copy() for t in tables], [np.zeros(R, np.float32) for R in Rs]
@@ -1338,25 +1349,28 @@ def test_training_steps_with_the_join_deferred_into_the_next_lookup_equal_steps_
         assert np.array_equal(np.flatnonzero((w_a[t].cpu().numpy() != tables[t]).any(axis=1)), changed)
 
 
-def test_backward_sort_wait_that_runs_out_abandons_the_backward_and_changes_nothing():
-    # From the second pass on, the workgroups of a sort pass wait for each other's digit counts; the waits are
-    # bounded.  With the bound at zero every wait fails at once (forced from the host; every kernel still runs
+@pytest.mark.parametrize("extra,want_unique", [(H.MANY_TABLES, False), (H.MANY_TABLES, True), (0, True)])
+def test_backward_sort_wait_that_runs_out_abandons_the_backward_and_changes_nothing(extra, want_unique):
+    # From the second pass on, the workgroups of a sort pass wait for each other's digit counts, those of the list of
+    # distinct rows for each other's numbers of rows; the waits are bounded.  (Without the added tables the batch is merged,
+    # and the list alone waits; without the list the passes alone do.)  With the bound at zero every wait fails at once (forced from the host; every kernel still runs
     # to its end): the status word says so, no row and no accumulator changes, and the same call with the
     # default bound afterwards gives the oracle's result.
     rng = np.random.default_rng(4471)
     T, B, D, Rs = 2, 700, 16, [70_000, 300]          # 14 000 lookups per table: several sort tiles, three passes
     tables, lengths, off, rows = H.random_case(rng, T, B, D, Rs, 20, scale=0.01)
     dout = rng.standard_normal((T, B, D)).astype(np.float32)
+    tables, off, dout = H.add_empty_tables(extra, tables, off, dout)
     ts, w_dev, acc_dev = H.make_tableset(tables, "f32", with_accum=True)
     emb.emb_debug_sort_poll_limit(0)
     try:
-        g = H.gpu_backward(ts, rows, off, B, "sum", dout, 0.01, 1e-8)
+        g = H.gpu_backward(ts, rows, off, B, "sum", dout, 0.01, 1e-8, want_unique=want_unique)
     finally:
         emb.emb_debug_sort_poll_limit(-1)
     assert g["status"] == emb.STATUS_SORT_ABANDONED
-    for t in range(T):
+    for t in range(T + extra):
         assert np.array_equal(w_dev[t].cpu().numpy(), tables[t]) and np.all(acc_dev[t].cpu().numpy() == 0)
-    _check_backward_against_oracle(tables, Rs, rows, off, B, D, "sum", dout, "after an abandoned sort")
+    _check_backward_against_oracle(tables, Rs + [1] * extra, rows, off, B, D, "sum", dout, "after an abandoned sort")
 
 
 def _rows_with_run_lengths(rng, n, R, runs):
@@ -1417,10 +1431,8 @@ def test_small_steps_give_the_bits_of_the_general_route(per_table, R, D, dtype):
     dout = rng.standard_normal((T, B, D)).astype(np.float32)
 
     def run(extra, poll_limit=-1, want_unique=True):
-        more = [np.zeros((1, D), dtype=tables[0].dtype)] * extra
-        ts, w, acc = H.make_tableset(tables + more, dtype, with_accum=True)
-        offs = np.concatenate([off, np.full(extra * B, off[-1], dtype=np.int64)])
-        d = np.concatenate([dout, np.zeros((extra, B, D), np.float32)])
+        more, offs, d = H.add_empty_tables(extra, tables, off, dout)
+        ts, w, acc = H.make_tableset(more, dtype, with_accum=True)
         emb.emb_debug_sort_poll_limit(poll_limit)
         try:
             g = H.gpu_backward(ts, rows, offs, B, "mean", d, 0.01, 1e-8, want_unique=want_unique)
@@ -1429,7 +1441,7 @@ def test_small_steps_give_the_bits_of_the_general_route(per_table, R, D, dtype):
         return g, [H.host_table(x) for x in w[:T]], [x.cpu().numpy() for x in acc[:T]]
 
     g, w, acc = run(0)
-    g2, w2, acc2 = run(513 - T)
+    g2, w2, acc2 = run(H.MANY_TABLES)
     assert g["status"] == g2["status"] and g["status"] & ~emb.STATUS_BAD_INDEX == 0
     assert np.array_equal(g["unique_keys"], g2["unique_keys"]) and np.array_equal(g["unique_counts"], g2["unique_counts"])
     for t in range(T):
@@ -2692,26 +2704,28 @@ def _graph_inputs(rng, T, B, max_len, Rs):
     return lengths, raw
 
 
-@pytest.mark.parametrize("side,from_lengths", [(False, False), (True, False), (True, True)])
-def test_a_captured_training_step_replays_like_eager_calls(side, from_lengths):
+@pytest.mark.parametrize("side,from_lengths,extra", [(False, False, 0), (True, False, 0), (True, True, 0), (False, False, H.MANY_TABLES),
+                                                     (True, False, H.MANY_TABLES), (True, True, H.MANY_TABLES)])
+def test_a_captured_training_step_replays_like_eager_calls(side, from_lengths, extra):
     # offsets + training lookup + sort + update captured once into a graph, then replayed on new inputs
     # written into the same buffers (the number of lookups is part of the captured arguments, so every batch
     # here has the same total); each replay is compared with the oracle, with eager work and
-    # synchronisations between the replays.
+    # synchronisations between the replays.  extra: tables without lookups, enough of them that the step goes the general way
+    # (several launches of the sort and the update, a fork to the side stream and back).
     rng = np.random.default_rng(9000 + side + 2 * from_lengths)
-    T, B, D = 3, 400, 64
-    Rs = [5000, 300, 20_000]
+    T, B, D = 3 + extra, 400, 64
+    Rs = [5000, 300, 20_000] + [1] * extra
     tables = [(rng.standard_normal((R, D)) * 0.01).astype(np.float32) for R in Rs]
     ref_tables = [t.copy() for t in tables]
     ref_acc = [np.zeros(R, np.float32) for R in Rs]
-    ts, w_dev, acc_dev = H.make_tableset(ref_tables, "f32", accum_np=ref_acc, salts=[3, 4, 5])
+    ts, w_dev, acc_dev = H.make_tableset(ref_tables, "f32", accum_np=ref_acc, salts=[3 + t for t in range(T)])
     nnz = 9000
 
     def batch():
-        cuts = np.sort(rng.integers(0, nnz + 1, size=T * B - 1))
-        lengths = np.diff(np.concatenate([[0], cuts, [nnz]])).astype(np.int32)
+        cuts = np.sort(rng.integers(0, nnz + 1, size=3 * B - 1))
+        lengths = np.concatenate([np.diff(np.concatenate([[0], cuts, [nnz]])), np.zeros(extra * B)]).astype(np.int32)
         raw = np.minimum(rng.zipf(1.3, size=nnz), 1 << 30).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
-        dout = rng.standard_normal((T, B, D)).astype(np.float32)
+        dout = np.concatenate([rng.standard_normal((3, B, D)), np.zeros((extra, B, D))]).astype(np.float32)
         return lengths, raw, dout
 
     dev = torch.device(H.DEV)
