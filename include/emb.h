@@ -235,8 +235,10 @@ int emb_event_elapsed_ms(void *start, void *stop, float *ms_out);
  * the key build, the sort, the optional list of distinct rows, the short-run
  * update and the long-run path, for callers that time the stages.
  * side (host, nullable): see emb_side_stream; NULL runs everything on
- * `stream`, as a batch of few lookups (2^20 at most) does in any case.
- * Results do not depend on it. */
+ * `stream`.  A batch of few lookups runs on `stream` alone in any case: up
+ * to 3 * 2^18 lookups of fp32 rows, 2^19 of bf16 rows, 12 288 of bf16 rows of
+ * more than 4096 values, over at most 512 tables that together have fewer than
+ * 2^32 - 1 rows.  Results do not depend on it. */
 int emb_bag_backward_rowwise_adagrad(const emb_table *tables_host, const emb_table *tables_dev,
                                      int32_t T, int32_t D, int32_t dtype,
                                      const int64_t *rows_dev, const int64_t *offsets_dev,
@@ -443,17 +445,26 @@ int emb_bag_backward_sort_prepared(const emb_table *tables_host, const emb_table
                                    int64_t *num_unique_out_dev, uint32_t *status_dev,
                                    void *const *stage_events, void *stream);
 
-/* Diagnostics of the backward's sort (the radix sort named with the update in
- * Section 3.1's fine-tuning step is this build's choice; the paper gives no
- * algorithm).  From the second pass on, the workgroups of a sort pass tell
- * each other their digit counts through words in the workspace; a workgroup
- * waits for words of workgroups that were started before it, polling each at
- * most `polls` times (default 2^20, some seconds).  When a wait runs out the
- * sort is abandoned: EMB_STATUS_SORT_ABANDONED is set, every later kernel of
- * the backward returns at once and no table row changes.  That is not
- * expected to happen; this call exists to test the path: polls == 0 makes
- * every wait fail at once, polls < 0 restores the default.  Host-only, takes
- * effect for calls enqueued afterwards, process-wide. */
+/* Diagnostics of the backward's waits between workgroups (the radix sort named with
+ * the update in Section 3.1's fine-tuning step is this build's choice; the
+ * paper gives no algorithm).  A workgroup waits for words in the workspace that
+ * workgroups started before it write, polling each at most `polls` times (default
+ * 2^20, some seconds), in three places:
+ *   - the sort's passes from the second on tell each other their digit counts
+ *     (a batch of up to 150 000 lookups over tables of like size is merged
+ *     instead, without a wait);
+ *   - the list of distinct rows, if asked for, is numbered across workgroups;
+ *   - the update of a batch of few lookups (see
+ *     emb_bag_backward_rowwise_adagrad) hands on the sums of a row with more
+ *     than 256 lookups.
+ * When one of the first two runs out the sort is abandoned:
+ * EMB_STATUS_SORT_ABANDONED is set, every later kernel of the backward returns
+ * at once and no table row changes.  When the third runs out the waiting
+ * workgroup makes the sums itself, in the same order: the update completes with the same
+ * results.  Neither is expected to happen; this call exists to test the
+ * paths: polls == 0 makes every wait fail at once, polls < 0 restores the
+ * default.  Host-only, takes effect for calls enqueued afterwards,
+ * process-wide. */
 void emb_debug_sort_poll_limit(int64_t polls);
 
 /* ---- host-resident table with an HBM hot-row cache (Section 3.3) --------- */

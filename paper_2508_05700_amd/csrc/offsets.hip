@@ -6,7 +6,7 @@
 //      entry per sum, where nothing else has been written yet,
 //   2. every tile adds up the sums it finds in its part, and then overwrites that part with the offsets.
 // One tile (n < 8192) needs the second only.  These launches are shorter than the way from one to the next: 196 608
-// lengths take 10.5 us with the three below, 7.8 with these; 1e6 17.6 and 11, 4e6 40 and 30.  More tiles than that, three:
+// lengths take 10.5 us with the three below, 7.8 with these; 1e6 17.6 and 10.4, 4e6 40 and 29.  More tiles than that, three:
 //   1. every tile of 4096 lengths writes its local inclusive sums to
 //      offsets[i+1] (so the last entry of a tile holds the tile total),
 //   2. one block turns the tile totals into global inclusive sums,
@@ -176,7 +176,7 @@ extern "C" int emb_lengths_to_offsets(const int32_t *lengths_dev, int64_t n, int
     if (tiles > 0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     hipStream_t s = emb_stream(stream);
     // whole tiles; what is left is a tile of its own if it has an entry for each tile before it, else the last one's
-    // (and up to 8191 lengths are one tile and one launch: 4097 lengths 9.0 us with three, 5.4 with one, 8000 9.1 and 7.0)
+    // (and up to 8191 lengths are one tile and one launch: 4097 lengths 9.0 us with three, 4.7 with one, 8000 9.1 and 6.2)
     int64_t parts = n < SCAN_TILE ? 1 : n / SCAN_TILE;
     if (parts > 1 && n - parts * SCAN_TILE >= parts) ++parts;
     if (parts <= DIRECT_TILES) {
