@@ -1499,7 +1499,8 @@ def test_several_updates_from_one_sort_equal_updates_from_a_sort_each(n, D, dtyp
     _check_several_updates(n, D, dtype, 0)
 
 
-@pytest.mark.parametrize("n,D,dtype,extra_tables", [(5_000, 48, "bf16", 512), (30_000, 64, "f32", 600), ((1 << 20) + 5_000, 4, "f32", 0)])
+@pytest.mark.parametrize("n,D,dtype,extra_tables", [(5_000, 48, "bf16", 512), (30_000, 64, "f32", 600), ((1 << 20) + 5_000, 4, "f32", 0),
+                                                    (13_000, 4104, "bf16", 0)])   # (the last: merged, but not updated in one launch)
 def test_several_updates_from_one_sort_with_many_tables_or_lookups(n, D, dtype, extra_tables):
     # more tables or lookups than the update in one launch takes: rows with many lookups are counted and cut in launches of their own
     _check_several_updates(n, D, dtype, extra_tables)
