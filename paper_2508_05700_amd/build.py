@@ -7,6 +7,7 @@ which does without it where it is missing.
 """
 from __future__ import annotations
 
+import contextlib
 import glob
 import os
 import subprocess
@@ -87,7 +88,7 @@ def build_calls(verbose: bool = True) -> str:
             pass
         raise
     os.replace(part, out)   # other processes see all of it or none
-    if os.path.exists(failed):
+    with contextlib.suppress(FileNotFoundError):
         os.remove(failed)
     return out
 
