@@ -228,8 +228,7 @@ __device__ __forceinline__ void emb_bounds_from_lengths(const int32_t *__restric
         mine = 0;
     }
     if (bad) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
-#pragma unroll
-    for (int d = EMB_WAVE >> 1; d >= 1; d >>= 1) before += shfl_i64(before, lane ^ d, EMB_WAVE);
+    before = wave_inclusive_scan(before);   // (the last lane has the sum)
     int64_t inc = mine;
     if (wave * EMB_WAVE < GROUPS) inc = wave_inclusive_scan(mine);   // uniform over the wavefront
     if (lane == EMB_WAVE - 1) {
