@@ -33,48 +33,69 @@ struct SortTile {
 static_assert(sizeof(SortTile) == 32, "tile descriptors are read as two 16-byte loads");
 
 // Stable rank of every record of a wavefront's share of a tile among the records
-// of the same digit (BITS bits from `shift` on), and the wavefront's digit counts.
+// of the same digit (`bits` bits from `shift` on), and the wavefront's digit counts.
 // A wavefront has ITEMS steps of 64 consecutive records each.  In a step, lanes
 // holding the same digit are matched with one ballot per digit bit (every lane
-// collects the lanes whose bit differs from its own: what is left are its peers);
-// the lowest of them adds their number to the wavefront's private LDS counter and
-// gets its value before, so no two lanes of an instruction add to one counter,
-// whatever the records (the hot rows of a skewed batch).  A wavefront's LDS
-// operations are carried out in order, so the adds of all steps go out one behind
-// the other and are waited for once: with a load and a store in the place of each
-// add, every step waited for the one before it (tiles of 4096 records of 18 bits
-// in LDS, 18-bit keys: 15.2 us for two passes then, 13.2 now).
+// collects the lanes whose bit differs from its own: what is left are its peers).
+// Every lane then reads its digit's count of the steps before in the wavefront's private
+// LDS counters, and the lowest of the peers adds their number to it, so no two lanes of an
+// instruction add to one counter, whatever the records (the hot rows of a skewed batch).  A
+// wavefront's LDS operations are carried out in order, so the reads and adds of all steps go out
+// one behind the other and are waited for once.
+// What bounds it is the issue of its vector instructions, four cycles each on one SIMD: four a record and bit (a
+// sign-extended bit, its ballot, two three-operand operations on the halves of the mask), a dozen more a record.  With the
+// ballot taken of an int, the rank counted by and + popcount and the count handed round by a shuffle from the lowest peer
+// it was twice as many: three scatters of 2.6e6 records 17.5 + 21.4 + 20.3 us, 16.3 + 19.1 + 17.6 now; two passes of nine bits
+// over tiles of 1024 records 7.6 us a launch, 6.6 now.
+// BITS: of a digit, 0: `bits`, known at run time only (uniform).
 template <typename KeyT, int BITS, int ITEMS>
-__device__ __forceinline__ void wave_rank_digits(const KeyT (&key)[ITEMS], uint32_t wbase, uint32_t n, int shift,
-                                                 uint32_t *cnt /*LDS [1 << BITS], this wavefront's, zeroed*/,
+__device__ __forceinline__ void wave_rank_digits(const KeyT (&key)[ITEMS], uint32_t wbase, uint32_t n, int shift, int bits,
+                                                 uint32_t *cnt /*LDS [1 << bits], this wavefront's, zeroed*/,
                                                  uint32_t (&rank)[ITEMS])
 {
     const int lane = threadIdx.x & (EMB_WAVE - 1);
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint32_t prev[ITEMS];
-    int leader[ITEMS];
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t mask = (1u << (BITS ? BITS : bits)) - 1;
+    // the lanes whose bit differs from mine (kept as two halves: a lane's own bit, spread over a word, serves both)
+    auto match = [&](uint32_t digit, int bit, uint32_t &differ_lo, uint32_t &differ_hi) {
+        uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int32_t)digit, (uint32_t)bit, 1u);   // all ones if my bit is set
+        asm("" : "+v"(mine));   // (the ballot is of this, not of a bit shifted out a second time)
+        const uint64_t with = __builtin_amdgcn_ballot_w64(mine != 0);
+        constexpr uint32_t OR_XOR = 0xDE;   // second | (first ^ third)
+        differ_lo = __builtin_amdgcn_bitop3_b32((uint32_t)with, differ_lo, mine, OR_XOR);
+        differ_hi = __builtin_amdgcn_bitop3_b32((uint32_t)(with >> 32), differ_hi, mine, OR_XOR);
+    };
+    uint32_t before[ITEMS];
+    auto count = [&](int k, uint32_t differ_lo, uint32_t differ_hi) {
+        const uint32_t digit = (uint32_t)(key[k] >> shift) & mask;
         const bool live = wbase + k * EMB_WAVE + lane < n;
-        const uint32_t digit = (uint32_t)(key[k] >> shift) & ((1u << BITS) - 1);
-        // (kept as two 32-bit halves: a lane's own bit, spread over a word, serves both)
-        uint32_t differ_lo = 0, differ_hi = 0;
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(live);   // dead lanes match nobody
+        const uint32_t peers_lo = (uint32_t)lanes & ~differ_lo, peers_hi = (uint32_t)(lanes >> 32) & ~differ_hi;
+        rank[k] = __builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));   // of the lanes below mine
+        before[k] = __hip_atomic_load(&cnt[digit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (live && rank[k] == 0)
+            (void)__hip_atomic_fetch_add(&cnt[digit], (uint32_t)(__popc(peers_lo) + __popc(peers_hi)), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    if constexpr (BITS > 0) {   // record by record: few registers
 #pragma unroll
-        for (int bit = 0; bit < BITS; ++bit) {
-            const uint32_t set = digit & (1u << bit);
-            const uint64_t with = __ballot(set != 0);
-            const uint32_t mine = set ? 0xFFFFFFFFu : 0u;   // all ones if my bit is set
-            differ_lo |= (uint32_t)with ^ mine;
-            differ_hi |= (uint32_t)(with >> 32) ^ mine;
+        for (int k = 0; k < ITEMS; ++k) {
+            uint32_t differ_lo = 0, differ_hi = 0;
+#pragma unroll
+            for (int bit = 0; bit < BITS; ++bit) match((uint32_t)(key[k] >> shift), bit, differ_lo, differ_hi);
+            count(k, differ_lo, differ_hi);
         }
-        const uint64_t peers = __ballot(live) & ~(((uint64_t)differ_hi << 32) | differ_lo);   // dead lanes match nobody
-        rank[k] = __popcll(peers & lt_mask);
-        leader[k] = live ? (__ffsll((unsigned long long)peers) - 1) : lane;
-        prev[k] = 0;
-        if (live && rank[k] == 0) prev[k] = atomicAdd(&cnt[digit], (uint32_t)__popcll(peers));
+    } else {
+        uint32_t differ_lo[ITEMS], differ_hi[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) differ_lo[k] = differ_hi[k] = 0;
+        for (int bit = 0; bit < bits; ++bit)
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) match((uint32_t)(key[k] >> shift), bit, differ_lo[k], differ_hi[k]);
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) count(k, differ_lo[k], differ_hi[k]);
     }
 #pragma unroll
-    for (int k = 0; k < ITEMS; ++k) rank[k] += (uint32_t)__shfl((int)prev[k], leader[k], EMB_WAVE);
+    for (int k = 0; k < ITEMS; ++k) rank[k] += before[k];
 }
 
 // hist is [passes][tiles + 1][RADIX]: entry (p, t, d) holds the count of digit d of pass p in
@@ -363,7 +384,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_scatter_kernel(const KeyT *__
         key[k] = i < end ? keys_in[i] : (KeyT)0;
         pay[k] = i < end ? pay_in[i] : 0u;
     }
-    wave_rank_digits<KeyT, RADIX_BITS, SORT_ITEMS>(key, wbase, end, shift, cnt[wave], rank);
+    wave_rank_digits<KeyT, RADIX_BITS, SORT_ITEMS>(key, wbase, end, shift, RADIX_BITS, cnt[wave], rank);
     __syncthreads();
 
     // thread d: digit d's count in the tile, its start inside the tile and the number of the

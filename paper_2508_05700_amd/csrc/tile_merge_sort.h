@@ -111,7 +111,7 @@ __global__ __launch_bounds__(MERGE_BLOCK) void tile_sort_kernel(const uint32_t *
         const int shift = p * BITS;
         for (uint32_t i = lane; i < DIGITS; i += EMB_WAVE) cnt[wave][i] = 0;
         __builtin_amdgcn_wave_barrier();   // (the wavefront's own counters: no other touches them before the next barrier)
-        wave_rank_digits<uint32_t, BITS, MERGE_ITEMS>(key, wbase, count, shift, cnt[wave], rank);
+        wave_rank_digits<uint32_t, BITS, MERGE_ITEMS>(key, wbase, count, shift, BITS, cnt[wave], rank);
         __syncthreads();
         // thread d: PER consecutive digits; their starts inside the tile, and the wavefronts' within them
         {
