@@ -386,9 +386,9 @@ int emb_quantize_rows(const float *src_dev, int64_t num_rows, int32_t D, int32_t
  * the ranking model, so every lookup is followed by its backward):
  * emb_bag_forward_hashed that also begins the backward of the same batch.
  * While it has the row number and the bag of every lookup in hand it validates
- * the offsets and writes the backward's (row, bag) records and per-bag
- * gradient scales into workspace_dev, so that the backward needs no pass over
- * the indices:
+ * the offsets and writes the backward's (row, bag) records (with few lookups:
+ * sorted already in parts) and per-bag gradient scales into workspace_dev, so
+ * that the backward needs no pass over the indices:
  *     emb_bag_forward_train            (this call; reads the tables)
  *     ... the model computes dout ...
  *     emb_bag_backward_sort_prepared   (emb_bag_backward_sort without rows_dev)

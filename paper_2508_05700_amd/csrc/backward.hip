@@ -455,6 +455,7 @@ struct BwdArgs {
 // What a small step keeps where others have the sort's tile descriptors and the first run starts of update.h's spans.
 inline int64_t *table_start_of(const BwdArgs &a, const BwdLayout &L) { return reinterpret_cast<int64_t *>(a.ws + L.tile_desc); }
 inline uint32_t *span_flags_of(const BwdArgs &a, const BwdLayout &L) { return reinterpret_cast<uint32_t *>(a.ws + L.span_head); }
+inline uint32_t n_span_flags(const BwdArgs &a) { return a.spans ? (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK) : 0u; }
 inline bool small_step_merges(const BwdArgs &a) { return a.nnz > MERGE_TILE; }   // else no table has more than one tile
 #define EMB_MARK(a, i) do { if ((a).mark(i) != EMB_OK) return EMB_ERR_HIP; } while (0)
 
@@ -587,6 +588,23 @@ int launch_update(const BwdArgs &a, const BwdLayout &L, const KeyT *keys, const 
     return EMB_OK;
 }
 
+// The tiles of a small step: at least one per MERGE_TILE records, and the first pair of arrays to the second.
+inline int64_t tile_sort_blocks(const BwdArgs &a) { return a.nnz / MERGE_TILE + a.T; }
+inline TileSortArgs tile_sort_args(const BwdArgs &a, const BwdLayout &L)
+{
+    TileSortArgs t;
+    t.keys_out = reinterpret_cast<uint32_t *>(a.ws + L.keys_b);
+    t.pay_out = reinterpret_cast<uint32_t *>(a.ws + L.pay_b);
+    t.passes = (a.key_bits + MERGE_BITS_MAX - 1) / MERGE_BITS_MAX;
+    t.bits = (a.key_bits + t.passes - 1) / t.passes;
+    t.last = !small_step_merges(a);
+    t.local_sentinel = (uint32_t)a.max_rows;
+    t.global_sentinel = (uint32_t)a.total_rows;
+    t.span_flags = span_flags_of(a, L);
+    t.n_flags = n_span_flags(a);
+    return t;
+}
+
 // Keys, sort and the optional list of distinct rows: everything that needs the indices only.
 // prepared: the control block, the tile descriptors and the records are in the workspace already
 // (emb_bag_forward_train put them there), so only the passes and the optional list run.
@@ -646,36 +664,32 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
     const bool want_list = a.unique_keys_out || a.unique_counts_out;
     unsigned long long *list_flags = want_list ? tile_heads : nullptr;
     uint32_t *span_flags = a.spans ? span_flags_of(a, L) : nullptr;   // those of update_spans_kernel are cleared with them
-    const uint32_t n_span_flags = a.spans ? (uint32_t)((a.nnz + LONG_CHUNK - 1) / LONG_CHUNK) : 0u;
+    const uint32_t span_flag_count = n_span_flags(a);
     const int passes = a.small ? 0 : a.passes;
     const bool exchange = !a.small && a.nnz <= (int64_t)SORT_EXCHANGE_MAX_TILES * SORT_TILE * (a.T > 0 ? a.T : 1);
     const uint32_t poll_limit = sort_poll_limit;
     if constexpr (sizeof(KeyT) == 4) {
         if (a.small) {
-            const int passes_in_lds = (a.key_bits + MERGE_BITS_MAX - 1) / MERGE_BITS_MAX;
-            const int bits = (a.key_bits + passes_in_lds - 1) / passes_in_lds;
             const int64_t *table_start = table_start_of(a, L);
             const bool merges = small_step_merges(a);
-#define EMB_TILE_SORT(BITS, LAST)                                                                                          \
-    hipLaunchKernelGGL((tile_sort_kernel<BITS, LAST>), dim3((unsigned)(n / MERGE_TILE + a.T)), dim3(MERGE_BLOCK), 0, s, keys_a, pay_a, keys_b, pay_b,   \
-                       table_start, a.T, passes_in_lds, a.tables_dev, local_sentinel, sentinel, list_flags, flat_tiles,    \
-                       span_flags, n_span_flags, ctrl)
-#define EMB_TILE_SORT_BITS(BITS)              \
-    if (merges) EMB_TILE_SORT(BITS, false);   \
-    else EMB_TILE_SORT(BITS, true);           \
-    break
-            switch (bits) {
-                case 10: EMB_TILE_SORT_BITS(10);
-                case 9: EMB_TILE_SORT_BITS(9);
-                case 8: EMB_TILE_SORT_BITS(8);
-                default: EMB_TILE_SORT_BITS(MERGE_BITS_MIN);
-            }
-#undef EMB_TILE_SORT_BITS
+            if (!prepared) {   // (the training lookup has sorted the tiles)
+                const TileSortArgs t = tile_sort_args(a, L);
+#define EMB_TILE_SORT(BITS)                                                                                            \
+    hipLaunchKernelGGL(tile_sort_kernel<BITS>, dim3((unsigned)tile_sort_blocks(a)), dim3(MERGE_BLOCK), 0, s, keys_a, pay_a, \
+                       table_start, a.T, a.tables_dev, t, ctrl)
+                switch (t.bits) {
+                    case 10: EMB_TILE_SORT(10); break;
+                    case 9: EMB_TILE_SORT(9); break;
+                    case 8: EMB_TILE_SORT(8); break;
+                    case 7: EMB_TILE_SORT(7); break;
+                    default: EMB_TILE_SORT(0); break;
+                }
 #undef EMB_TILE_SORT
-            EMB_RETURN_IF_LAUNCH_FAILED();
+                EMB_RETURN_IF_LAUNCH_FAILED();
+            }
             if (merges) {
                 hipLaunchKernelGGL(tile_merge_kernel, dim3((unsigned)(n / PLACE_BLOCK + a.T)), dim3(PLACE_BLOCK), 0, s, keys_b, pay_b, keys_a, pay_a,
-                                   table_start, a.T, a.tables_dev, local_sentinel, sentinel, ctrl);
+                                   table_start, a.T, a.tables_dev, local_sentinel, sentinel, list_flags, flat_tiles, ctrl);
                 EMB_RETURN_IF_LAUNCH_FAILED();
             }
             if (!merges) kin = keys_b;
@@ -688,7 +702,7 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
 #define EMB_SORT_HIST(NP)                                                                                          \
     hipLaunchKernelGGL((sort_hist_kernel<KeyT, NP>), dim3(tiles), dim3(SORT_BLOCK), 0, s, kin, tile_desc, p0, hist, \
                        tiles, fl, a.passes - 1, p0 == 0 ? list_flags : nullptr, flat_tiles, \
-                       p0 == 0 ? span_flags : nullptr, n_span_flags, ctrl)
+                       p0 == 0 ? span_flags : nullptr, span_flag_count, ctrl)
             switch (np) {
                 case 1: EMB_SORT_HIST(1); break;
                 case 2: EMB_SORT_HIST(2); break;
@@ -711,7 +725,7 @@ int run_sort(const BwdArgs &a, const BwdLayout &L, bool prepared = false)
         if (!exchange) {
             hipLaunchKernelGGL((sort_hist_kernel<KeyT, 1>), dim3(tiles), dim3(SORT_BLOCK), 0, s, kin, tile_desc, p, hist,
                                tiles, (unsigned long long *)nullptr, 0, p == 0 ? list_flags : nullptr, flat_tiles,
-                               p == 0 ? span_flags : nullptr, n_span_flags, ctrl);
+                               p == 0 ? span_flags : nullptr, span_flag_count, ctrl);
             EMB_RETURN_IF_LAUNCH_FAILED();
             hipLaunchKernelGGL(sort_scan_kernel, dim3(SORT_SCAN_BLOCKS), dim3(SCAN_BLOCK_THREADS), 0, s, hp, tiles, ctrl);
             EMB_RETURN_IF_LAUNCH_FAILED();
@@ -826,18 +840,29 @@ struct TrainSource {
 
 constexpr int TRAIN_BLOCK = 256;
 
-// MAKE_OFFSETS (a small step from lengths): no launch stands before this one but the sums within tiles, and not even that
-// for up to EMB_LENGTHS_DIRECT_BAGS bags.  The kernel makes the bounds itself, from `lengths` or from the sums in `offsets`
-// as bag_forward_kernel does, and whoever has a table's first or the batch's last bag writes what the set-up kernel
-// would have: table_start, the control block (the bags partition [0, nnz) iff the last one ends there).
-template <int LPR, int CPL, int UNROLL, bool BF16, typename KeyT, bool MAKE_OFFSETS>
+// What bwd_keys_kernel does per bag: the scale of its gradient, or the abort of the backward (the lookup flags the status
+// word).  Also writes the bag's offset out (offsets_out nullable).
+__device__ __forceinline__ void train_bag_scale(const int64_t *__restrict__ offsets, const int64_t *__restrict__ tile_prefix,
+                                                int64_t bag, int64_t nnz, int32_t mode, float *__restrict__ bag_scale,
+                                                BwdCtrl *ctrl, int64_t *__restrict__ offsets_out)
+{
+    int64_t s, e;
+    emb_bag_bounds(offsets, tile_prefix, bag, s, e);
+    if (s < 0 || e < s || e > nnz) atomicOr(&ctrl->abort, 1u);
+    else bag_scale[bag] = (mode == EMB_POOL_MEAN && e > s) ? 1.0f / (float)(e - s) : 1.0f;
+    if (offsets_out) {
+        offsets_out[bag + 1] = e;
+        if (bag == 0) offsets_out[0] = 0;
+    }
+}
+
+template <int LPR, int CPL, int UNROLL, bool BF16, typename KeyT>
 __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
     const emb_table *__restrict__ tables, int32_t T, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ raw, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
     float *__restrict__ out, int64_t *__restrict__ rows_out, KeyT *__restrict__ keys, uint32_t *__restrict__ pay,
     float *__restrict__ bag_scale, BwdCtrl *ctrl, uint32_t *status, const int64_t *__restrict__ tile_prefix,
-    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths, int64_t *__restrict__ table_start,
-    int64_t *num_unique_out)
+    int64_t *__restrict__ offsets_out)
 {
     // tile_prefix != NULL: `offsets` are sums within tiles (emb_offset_at) and the final offsets go to offsets_out
     constexpr int GROUPS = TRAIN_BLOCK / LPR;
@@ -854,6 +879,48 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
     const emb_table tb = tables[t];
     TrainSource<KeyT> src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
                           (int64_t)chunks_per_row * 16, rows_out, keys, pay, (uint32_t)bag};
+    float *const out_row = out + bag * ((int64_t)chunks_per_row * F);
+    if (live && l == 0) train_bag_scale(offsets, tile_prefix, bag, nnz, mode, bag_scale, ctrl, offsets_out);
+    gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
+                                            tile_prefix);
+}
+
+// The lookup of a small step, and beside it, in the first `tile_blocks` workgroups, the sort of its tiles from the raw IDs
+// (tile_sort_raw): each is a few dependent trips to memory on a part of the chip, and neither needs the other.  As two
+// launches, the lookup writing the records for the other, 30 720 lookups of 256-byte rows took 7.6 + 6.6 us and 148 700 of
+// 96 bytes 9.3 + 7.3; this one takes 12.0 and 13.8.  Of a tile's workgroup 1.7 us are the offsets, 0.5 its place, 2.8 the
+// IDs, their bags and rows, 4.2 two passes of the sort.
+// MAKE_OFFSETS (from lengths): no launch stands before this one but the sums within tiles, and not even that
+// for up to EMB_LENGTHS_DIRECT_BAGS bags.  The kernel makes the bounds itself, from `lengths` or from the sums in `offsets`
+// as bag_forward_kernel does, and whoever has a table's first or the batch's last bag writes what the set-up kernel
+// would have: table_start, the control block (the bags partition [0, nnz) iff the last one ends there).
+template <int LPR, int CPL, int UNROLL, bool BF16, bool MAKE_OFFSETS>
+__global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_small_kernel(
+    const emb_table *__restrict__ tables, int32_t T, int64_t B, uint32_t blocks_per_table, int64_t nnz,
+    const int64_t *__restrict__ raw, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
+    float *__restrict__ out, int64_t *__restrict__ rows_out, float *__restrict__ bag_scale, BwdCtrl *ctrl, uint32_t *status,
+    const int64_t *__restrict__ tile_prefix, int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths,
+    int64_t *__restrict__ table_start, int64_t *num_unique_out, uint32_t tile_blocks, TileSortArgs sort)
+{
+    static_assert(TRAIN_BLOCK == MERGE_BLOCK, "both kinds of workgroups are of one launch");
+    if (blockIdx.x < tile_blocks) {   // uniform
+        tile_sort_raw<MAKE_OFFSETS>(sort, blockIdx.x, tables, T, B, nnz, raw, lengths, offsets, tile_prefix, table_start, ctrl);
+        return;
+    }
+    constexpr int GROUPS = TRAIN_BLOCK / LPR;
+    constexpr int F = ChunkAcc<BF16>::FLOATS;
+    const uint32_t lb = emb_xcd_block(blockIdx.x - tile_blocks, gridDim.x - tile_blocks);   // (both are multiples of EMB_XCDS)
+    const uint32_t t_raw = lb / blocks_per_table;
+    const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
+    const int t = tail ? T - 1 : (int)t_raw;
+    const int l = threadIdx.x % LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
+    const bool live = b < B;
+    const int64_t bag = (int64_t)t * B + b;
+    const emb_table tb = tables[t];
+    HashedTableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
+                          (int64_t)chunks_per_row * 16, rows_out};
     float *const out_row = out + bag * ((int64_t)chunks_per_row * F);
     if constexpr (MAKE_OFFSETS) {
         __shared__ int64_t prefixes[TRAIN_BLOCK + 1];
@@ -881,21 +948,11 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
             }
         }
         gather_pool_range<LPR, CPL, UNROLL, BF16>(src, live, s, e, l, nnz, raw, chunks_per_row, mode, out_row, status);
-        return;
+    } else {
+        if (live && l == 0) train_bag_scale(offsets, tile_prefix, bag, nnz, mode, bag_scale, ctrl, offsets_out);
+        gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
+                                                tile_prefix);
     }
-    if (live && l == 0) {
-        // what bwd_keys_kernel does per bag: the scale of its gradient, or the abort of the backward
-        int64_t s, e;
-        emb_bag_bounds(offsets, tile_prefix, bag, s, e);
-        if (s < 0 || e < s || e > nnz) atomicOr(&ctrl->abort, 1u);   // the lookup below flags the status word
-        else bag_scale[bag] = (mode == EMB_POOL_MEAN && e > s) ? 1.0f / (float)(e - s) : 1.0f;
-        if (offsets_out) {
-            offsets_out[bag + 1] = e;
-            if (bag == 0) offsets_out[0] = 0;
-        }
-    }
-    gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
-                                            tile_prefix);
 }
 
 // A small step from lengths whose lookup makes the bags' bounds itself (at most as many tiles of sums as a workgroup scans).
@@ -921,22 +978,34 @@ int launch_train(bool bf16, const BwdArgs &a, const BwdLayout &L, const int64_t 
     const bool make = train_makes_offsets(a);
     const int64_t *offsets = a.from_lengths ? reinterpret_cast<const int64_t *>(a.ws + L.local_offsets) : a.offsets;
     const int64_t *tile_prefix = a.from_lengths && !make ? reinterpret_cast<const int64_t *>(a.ws + L.tile_prefix) : nullptr;
-    const int32_t *lengths = make && (int64_t)a.T * a.B <= EMB_LENGTHS_DIRECT_BAGS ? a.lengths : nullptr;
-#define EMB_TRAIN(BF, MAKE)                                                                                              \
-    hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, BF, KeyT, MAKE>), dim3((unsigned)blocks),             \
-                       dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets, \
-                       chunks, a.mode, out, rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out,  \
-                       lengths, table_start_of(a, L), a.num_unique_out)
     if constexpr (sizeof(KeyT) == 4) {
-        if (make) {
-            if (bf16) EMB_TRAIN(true, true);
-            else EMB_TRAIN(false, true);
+        if (a.small) {
+            const int32_t *lengths = make && (int64_t)a.T * a.B <= EMB_LENGTHS_DIRECT_BAGS ? a.lengths : nullptr;
+            const int64_t tile_blocks = emb_round_up_xcds(tile_sort_blocks(a));   // (not above nnz and T together: both small)
+#define EMB_TRAIN_SMALL(BF, MAKE)                                                                                            \
+    hipLaunchKernelGGL((bag_forward_train_small_kernel<LPR, CPL, UNROLL, BF, MAKE>), dim3((unsigned)(tile_blocks + blocks)), \
+                       dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets,     \
+                       chunks, a.mode, out, rows_out, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out, lengths,        \
+                       table_start_of(a, L), a.num_unique_out, (uint32_t)tile_blocks, tile_sort_args(a, L))
+            if (blocks + tile_blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
+            if (make) {
+                if (bf16) EMB_TRAIN_SMALL(true, true);
+                else EMB_TRAIN_SMALL(false, true);
+            } else {
+                if (bf16) EMB_TRAIN_SMALL(true, false);
+                else EMB_TRAIN_SMALL(false, false);
+            }
+#undef EMB_TRAIN_SMALL
             EMB_RETURN_IF_LAUNCH_FAILED();
             return EMB_OK;
         }
     }
-    if (bf16) EMB_TRAIN(true, false);
-    else EMB_TRAIN(false, false);
+#define EMB_TRAIN(BF)                                                                                                        \
+    hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, BF, KeyT>), dim3((unsigned)blocks), dim3(TRAIN_BLOCK), 0, \
+                       a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets, chunks, a.mode, out,      \
+                       rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out)
+    if (bf16) EMB_TRAIN(true);
+    else EMB_TRAIN(false);
 #undef EMB_TRAIN
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;

@@ -33,22 +33,6 @@ struct TableSource {
     }
 };
 
-// The entries are raw IDs: the row is splitmix64(raw XOR salt) mod num_rows (Section 2.2), computed
-// by the lane that fetched the ID, so hashing costs no pass of its own.  The row numbers can be
-// written out for the backward.
-struct HashedTableSource {
-    const char *weights;
-    uint64_t num_rows, salt, magic;
-    int64_t row_bytes;
-    int64_t *rows_out;   // nullable
-    __device__ __forceinline__ uint64_t resolve(int64_t raw, int64_t j) const
-    {
-        const uint64_t r = emb_fast_mod(emb_splitmix64((uint64_t)raw ^ salt), num_rows, magic);
-        if (rows_out) rows_out[j] = (int64_t)r;
-        return reinterpret_cast<uint64_t>(weights + (int64_t)r * row_bytes);
-    }
-};
-
 // HASHED: `rows` holds raw IDs (HashedTableSource).
 // MAKE_OFFSETS (the calls that take bag lengths): the kernel finds the bags' bounds itself and writes the final
 // offsets to offsets_out.  lengths != NULL: from the lengths (emb_bounds_from_lengths); else `offsets` holds the

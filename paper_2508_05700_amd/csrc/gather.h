@@ -5,6 +5,7 @@
 
 #include "emb_internal.h"
 #include "scan.h"
+#include "u64mod.h"
 
 // Per-lane accumulator for one 16-byte chunk of a row.
 template <bool BF16>
@@ -311,6 +312,22 @@ __device__ __forceinline__ void gather_rows(ChunkAcc<BF16> (&acc)[CPL], const ui
 #pragma unroll
         for (int c = 0; c < CPL; ++c) acc[c].add(v[i][c]);
 }
+
+// A Source whose entries are raw IDs: the row is splitmix64(raw XOR salt) mod num_rows (Section 2.2), computed
+// by the lane that fetched the ID, so hashing costs no pass of its own.  The row numbers can be
+// written out for the backward.
+struct HashedTableSource {
+    const char *weights;
+    uint64_t num_rows, salt, magic;
+    int64_t row_bytes;
+    int64_t *rows_out;   // nullable
+    __device__ __forceinline__ uint64_t resolve(int64_t raw, int64_t j) const
+    {
+        const uint64_t r = emb_fast_mod(emb_splitmix64((uint64_t)raw ^ salt), num_rows, magic);
+        if (rows_out) rows_out[j] = (int64_t)r;
+        return reinterpret_cast<uint64_t>(weights + (int64_t)r * row_bytes);
+    }
+};
 
 // Does `left` entries' worth of a batch of UNROLL at its full length, a half or a quarter: do_rows(n) with n a
 // compile-time constant.  The longest of the wavefront's bags decides (uniform).

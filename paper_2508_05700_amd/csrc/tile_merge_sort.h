@@ -14,14 +14,16 @@
 // record ranges (table_start), so the launches before it need not describe them.
 #pragma once
 #include "bwd_common.h"
+#include "gather.h"
 #include "radix_sort.h"
 #include "scan.h"
+#include "u64mod.h"
 
 constexpr int MERGE_ITEMS = 4;                         // records of a thread of the tile sort
 constexpr int MERGE_BLOCK = 256;
 constexpr int MERGE_WAVES = MERGE_BLOCK / EMB_WAVE;
 constexpr int MERGE_TILE = MERGE_BLOCK * MERGE_ITEMS;
-constexpr int MERGE_BITS_MIN = 7, MERGE_BITS_MAX = 10; // of a pass: tables of 2^20 rows take two passes, 2^30 three
+constexpr int MERGE_BITS_MAX = 10;                     // of a pass: tables of 2^20 rows take two passes, 2^30 three
 constexpr int PLACE_BLOCK = 512;                       // records (and threads) of a workgroup of the merge
 constexpr int PLACE_TILES = 4;                         // tiles a thread bisects side by side
 
@@ -32,24 +34,19 @@ struct MergePart {
 };
 
 // Part `b` of the tables' records cut into SIZE records each, table after table; false: there is none.  Every thread of
-// the workgroup calls this.  table_start: [T + 1], a partition of [0, nnz) in order unless ctrl->abort is set.
-template <int SIZE, int BLOCK>
-__device__ __forceinline__ bool merge_part_of(const int64_t *__restrict__ table_start, int32_t T, uint32_t b, const BwdCtrl *ctrl,
-                                              MergePart &part)
+// the workgroup calls this.  range(t, s, e): table t has records [s, e), a partition of [0, nnz) in order.
+template <int SIZE, int BLOCK, typename Range>
+__device__ __forceinline__ bool merge_part_in(int32_t T, uint32_t b, const Range &range, MergePart &part)
 {
     __shared__ uint32_t wave_sums[BLOCK / EMB_WAVE];
     __shared__ MergePart found;
     __shared__ uint32_t is_there;
-    const uint32_t abort = ctrl->abort;   // (asked for together with the ranges)
     if (threadIdx.x == 0) is_there = 0;
     uint32_t before = 0;
     for (int32_t t0 = 0; t0 < T; t0 += BLOCK) {
         const int32_t t = t0 + (int32_t)threadIdx.x;
         uint32_t s = 0, e = 0;
-        if (t < T) {
-            s = (uint32_t)table_start[t];
-            e = (uint32_t)table_start[t + 1];
-        }
+        if (t < T) range(t, s, e);
         const uint32_t parts = (e - s + SIZE - 1) / SIZE;
         uint32_t total;
         const uint32_t inc = before + block_inclusive_scan<uint32_t, BLOCK>(parts, wave_sums, total);   // (has barriers)
@@ -64,54 +61,71 @@ __device__ __forceinline__ bool merge_part_of(const int64_t *__restrict__ table_
     }
     __syncthreads();
     part = found;
-    return !abort && is_there;   // uniform
+    return is_there;   // uniform
 }
 
-// Sorts every tile by its key, stably: `passes` passes of BITS bits inside LDS.  LAST: there is nothing to merge (no
-// table has more than one tile), the keys are written as positions in the concatenation of the tables, as the last
-// pass of radix_sort.h does.
-// Also clears what the launches after it count in: the words of the list of distinct rows (list_flags, [list_tiles],
-// optional) and the flags of update_spans_kernel ([n_flags]).
-template <int BITS, bool LAST>
-__global__ __launch_bounds__(MERGE_BLOCK) void tile_sort_kernel(const uint32_t *__restrict__ keys_in,
-                                                                const uint32_t *__restrict__ pay_in,
-                                                                uint32_t *__restrict__ keys_out,
-                                                                uint32_t *__restrict__ pay_out,
-                                                                const int64_t *__restrict__ table_start, int32_t T,
-                                                                int passes, const emb_table *__restrict__ tables,
-                                                                uint32_t local_sentinel, uint32_t global_sentinel,
-                                                                unsigned long long *__restrict__ list_flags,
-                                                                uint32_t list_tiles, uint32_t *__restrict__ span_flags,
-                                                                uint32_t n_flags, const BwdCtrl *ctrl)
+// The same from table_start ([T + 1], a partition unless ctrl->abort is set); there is no part of an aborted backward.
+template <int SIZE, int BLOCK>
+__device__ __forceinline__ bool merge_part_of(const int64_t *__restrict__ table_start, int32_t T, uint32_t b, const BwdCtrl *ctrl,
+                                              MergePart &part)
 {
-    constexpr uint32_t DIGITS = 1u << BITS;
+    const uint32_t abort = ctrl->abort;   // (asked for together with the ranges)
+    const bool there = merge_part_in<SIZE, BLOCK>(T, b, [&](int32_t t, uint32_t &s, uint32_t &e) {
+        s = (uint32_t)table_start[t];
+        e = (uint32_t)table_start[t + 1];
+    }, part);
+    return !abort && there;
+}
+
+constexpr uint32_t MERGE_DIGITS = 1u << MERGE_BITS_MAX;
+struct TileSortLds {
+    uint32_t cnt[MERGE_WAVES][MERGE_DIGITS];   // per-wavefront digit counts, then offsets inside the tile
+    uint32_t sk[MERGE_TILE], sp[MERGE_TILE];
+    uint32_t wave_sums[MERGE_WAVES];
+};
+
+// How the tiles of a small step are sorted and where they go.
+struct TileSortArgs {
+    uint32_t *keys_out, *pay_out;
+    int passes, bits;                 // passes of `bits` (at most MERGE_BITS_MAX) bits each
+    bool last;                        // there is nothing to merge: no table has more than one tile
+    uint32_t local_sentinel, global_sentinel;
+    uint32_t *span_flags;             // [n_flags] flags of update_spans_kernel, cleared here: a tile has more threads than flags
+    uint32_t n_flags;
+};
+
+// Sorts a tile by its key, stably: `passes` passes of `bits` bits inside LDS.  load(i, count, key, pay): the records
+// i of the tile, those below count.  With nothing to merge the keys are written as positions in the concatenation of the tables, as the last pass of
+// radix_sort.h does.  BITS: a.bits where that is known to the compiler, else 0.
+template <int BITS, typename Load>
+__device__ __forceinline__ void tile_sort(const TileSortArgs &a, const MergePart &tile, uint32_t row_base, TileSortLds &lds,
+                                          const Load &load)
+{
+    constexpr uint32_t DIGITS = BITS ? 1u << BITS : MERGE_DIGITS;   // (with fewer bits than that the others count nothing)
     constexpr int PER = DIGITS > (uint32_t)MERGE_BLOCK ? DIGITS / MERGE_BLOCK : 1;   // digits a thread looks after
-    __shared__ uint32_t cnt[MERGE_WAVES][DIGITS];   // per-wavefront digit counts, then offsets inside the tile
-    __shared__ uint32_t sk[MERGE_TILE], sp[MERGE_TILE];
-    __shared__ uint32_t wave_sums[MERGE_WAVES];
-    const uint32_t gid = blockIdx.x * MERGE_BLOCK + threadIdx.x;   // a grid has at least one workgroup per MERGE_TILE records
-    if (list_flags && gid < list_tiles) list_flags[gid] = 0ull;
-    if (gid < n_flags) span_flags[gid] = 0u;
-    MergePart tile;
-    if (!merge_part_of<MERGE_TILE, MERGE_BLOCK>(table_start, T, blockIdx.x, ctrl, tile)) return;
+    const int bits = BITS ? BITS : a.bits;
     const uint32_t start = tile.seg_start + tile.index * MERGE_TILE;
     const uint32_t left = tile.seg_count - tile.index * MERGE_TILE;
     const uint32_t count = left < (uint32_t)MERGE_TILE ? left : MERGE_TILE;
     const int lane = threadIdx.x & (EMB_WAVE - 1);
     const int wave = threadIdx.x / EMB_WAVE;
     const uint32_t wbase = wave * (MERGE_ITEMS * EMB_WAVE);
-    uint32_t key[MERGE_ITEMS], pay[MERGE_ITEMS], rank[MERGE_ITEMS];
+    const uint32_t digit_mask = (1u << bits) - 1;
+    uint32_t at[MERGE_ITEMS], key[MERGE_ITEMS], pay[MERGE_ITEMS], rank[MERGE_ITEMS];
 #pragma unroll
     for (int k = 0; k < MERGE_ITEMS; ++k) {
-        const uint32_t i = wbase + k * EMB_WAVE + lane;
-        key[k] = i < count ? keys_in[start + i] : 0u;
-        pay[k] = i < count ? pay_in[start + i] : 0u;
+        at[k] = wbase + k * EMB_WAVE + lane;
+        key[k] = pay[k] = 0u;
     }
-    for (int p = 0; p < passes; ++p) {
-        const int shift = p * BITS;
-        for (uint32_t i = lane; i < DIGITS; i += EMB_WAVE) cnt[wave][i] = 0;
-        __builtin_amdgcn_wave_barrier();   // (the wavefront's own counters: no other touches them before the next barrier)
-        wave_rank_digits<uint32_t, BITS, MERGE_ITEMS>(key, wbase, count, shift, BITS, cnt[wave], rank);
+    load(at, count, key, pay);
+    __syncthreads();   // (it may have read what is counted in from here on)
+    for (int p = 0; p < a.passes; ++p) {
+        const int shift = p * bits;
+        // (the wavefront's own counters: no other touches them before the next barrier)
+        for (uint32_t i = lane; i < DIGITS / 4; i += EMB_WAVE)
+            reinterpret_cast<uint4 *>(lds.cnt[wave])[i] = make_uint4(0u, 0u, 0u, 0u);
+        __builtin_amdgcn_wave_barrier();
+        wave_rank_digits<uint32_t, BITS, MERGE_ITEMS>(key, wbase, count, shift, bits, lds.cnt[wave], rank);
         __syncthreads();
         // thread d: PER consecutive digits; their starts inside the tile, and the wavefronts' within them
         {
@@ -119,30 +133,35 @@ __global__ __launch_bounds__(MERGE_BLOCK) void tile_sort_kernel(const uint32_t *
             const uint32_t d0 = threadIdx.x * PER;
             const bool owner = d0 < DIGITS;
 #pragma unroll
+            for (int w = 0; w < MERGE_WAVES; ++w)
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    c[j][w] = owner ? lds.cnt[w][d0 + j] : 0u;
+                    total += c[j][w];
+                }
+            uint32_t run = block_inclusive_scan<uint32_t, MERGE_BLOCK>(total, lds.wave_sums, all) - total;
+#pragma unroll
             for (int j = 0; j < PER; ++j)
 #pragma unroll
                 for (int w = 0; w < MERGE_WAVES; ++w) {
-                    c[j][w] = owner ? cnt[w][d0 + j] : 0u;
-                    total += c[j][w];
+                    const uint32_t n = c[j][w];
+                    c[j][w] = run;
+                    run += n;
                 }
-            uint32_t run = block_inclusive_scan<uint32_t, MERGE_BLOCK>(total, wave_sums, all) - total;
             if (owner) {
 #pragma unroll
-                for (int j = 0; j < PER; ++j)
+                for (int w = 0; w < MERGE_WAVES; ++w)
 #pragma unroll
-                    for (int w = 0; w < MERGE_WAVES; ++w) {
-                        cnt[w][d0 + j] = run;
-                        run += c[j][w];
-                    }
+                    for (int j = 0; j < PER; ++j) lds.cnt[w][d0 + j] = c[j][w];
             }
         }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < MERGE_ITEMS; ++k) {
             if (wbase + k * EMB_WAVE + lane < count) {
-                const uint32_t at = cnt[wave][(key[k] >> shift) & (DIGITS - 1)] + rank[k];
-                sk[at] = key[k];
-                sp[at] = pay[k];
+                const uint32_t to = lds.cnt[wave][(key[k] >> shift) & digit_mask] + rank[k];
+                lds.sk[to] = key[k];
+                lds.sp[to] = pay[k];
             }
         }
         __syncthreads();
@@ -150,21 +169,196 @@ __global__ __launch_bounds__(MERGE_BLOCK) void tile_sort_kernel(const uint32_t *
         for (int k = 0; k < MERGE_ITEMS; ++k) {   // the records of the next pass, or of the way out
             const uint32_t i = wbase + k * EMB_WAVE + lane;
             if (i < count) {
-                key[k] = sk[i];
-                pay[k] = sp[i];
+                key[k] = lds.sk[i];
+                pay[k] = lds.sp[i];
             }
         }
     }
-    uint32_t row_base = 0;
-    if (LAST) row_base = (uint32_t)tables[tile.table].row_base;
 #pragma unroll
     for (int k = 0; k < MERGE_ITEMS; ++k) {
         const uint32_t i = wbase + k * EMB_WAVE + lane;
         if (i < count) {
-            keys_out[start + i] = LAST ? (key[k] == local_sentinel ? global_sentinel : key[k] + row_base) : key[k];
-            pay_out[start + i] = pay[k];
+            a.keys_out[start + i] = a.last ? (key[k] == a.local_sentinel ? a.global_sentinel : key[k] + row_base) : key[k];
+            a.pay_out[start + i] = pay[k];
         }
     }
+}
+
+// The records are in memory (emb_bag_backward_sort's).
+template <int BITS>
+__global__ __launch_bounds__(MERGE_BLOCK) void tile_sort_kernel(const uint32_t *__restrict__ keys_in,
+                                                                const uint32_t *__restrict__ pay_in,
+                                                                const int64_t *__restrict__ table_start, int32_t T,
+                                                                const emb_table *__restrict__ tables, TileSortArgs a,
+                                                                const BwdCtrl *ctrl)
+{
+    __shared__ TileSortLds lds;
+    const uint32_t gid = blockIdx.x * MERGE_BLOCK + threadIdx.x;
+    if (gid < a.n_flags) a.span_flags[gid] = 0u;
+    MergePart tile;
+    if (!merge_part_of<MERGE_TILE, MERGE_BLOCK>(table_start, T, blockIdx.x, ctrl, tile)) return;
+    const uint32_t start = tile.seg_start + tile.index * MERGE_TILE;
+    tile_sort<BITS>(a, tile, a.last ? (uint32_t)tables[tile.table].row_base : 0u, lds,
+              [&](const uint32_t (&i)[MERGE_ITEMS], uint32_t count, uint32_t (&key)[MERGE_ITEMS], uint32_t (&pay)[MERGE_ITEMS]) {
+#pragma unroll
+                  for (int k = 0; k < MERGE_ITEMS; ++k) {
+                      if (i[k] < count) {
+                          key[k] = keys_in[start + i[k]];
+                          pay[k] = pay_in[start + i[k]];
+                      }
+                  }
+              });
+}
+
+// ---------------------------------------------------------------------------
+// tiles straight from raw IDs, for the launch that does the lookup beside it
+// ---------------------------------------------------------------------------
+// The tile's workgroup needs the tables' record ranges and the bag of every record before any launch has written them: both
+// come from the bag offsets, which it makes itself in one of three forms.  Bags of the tile are found by bisection, first
+// in LDS.
+constexpr int TILE_SAMPLES = MERGE_BLOCK;
+static_assert((EMB_LENGTHS_DIRECT_BAGS + 1) * 4 <= sizeof(TileSortLds) && (2 * TILE_SAMPLES + 1) * 4 <= sizeof(TileSortLds),
+              "the offsets stand where the sort counts afterwards");
+
+// Offsets of up to EMB_LENGTHS_DIRECT_BAGS bags from their lengths, all of them, to LDS ([n + 1]); a negative length counts
+// as 0.  False (uniform): they do not add up to nnz.
+__device__ __forceinline__ bool tile_offsets_from_lengths(const int32_t *__restrict__ lengths, uint32_t n, int64_t nnz,
+                                                          uint32_t *off /*LDS*/, int64_t *wave_sums /*LDS*/)
+{
+    constexpr int PER = EMB_LENGTHS_DIRECT_BAGS / MERGE_BLOCK;
+    static_assert(PER * MERGE_BLOCK == EMB_LENGTHS_DIRECT_BAGS && PER % 4 == 0, "a thread's lengths are 16-byte accesses of LDS");
+    int32_t v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const uint32_t i = u * MERGE_BLOCK + threadIdx.x;
+        v[u] = i < n ? lengths[i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) off[u * MERGE_BLOCK + threadIdx.x] = v[u] < 0 ? 0u : (uint32_t)v[u];
+    __syncthreads();
+    uint4 *const own = reinterpret_cast<uint4 *>(off + threadIdx.x * PER);
+    uint4 x[PER / 4];
+    int64_t mine = 0, total;
+#pragma unroll
+    for (int u = 0; u < PER / 4; ++u) {
+        x[u] = own[u];
+        mine += (int64_t)x[u].x + x[u].y + x[u].z + x[u].w;
+    }
+    const int64_t before = block_inclusive_scan<int64_t, MERGE_BLOCK>(mine, wave_sums, total) - mine;   // (has barriers)
+    if (total != nnz) return false;
+    uint32_t run = (uint32_t)before;   // nnz is below 2^31
+#pragma unroll
+    for (int u = 0; u < PER / 4; ++u) {
+        const uint4 l = x[u];
+        own[u] = make_uint4(run, run + l.x, run + l.x + l.y, run + l.x + l.y + l.z);
+        run += l.x + l.y + l.z + l.w;
+    }
+    if (threadIdx.x == MERGE_BLOCK - 1) off[EMB_LENGTHS_DIRECT_BAGS] = run;   // (entries after the last bag hold nnz)
+    __syncthreads();
+    return true;
+}
+
+// For MERGE_ITEMS places j at once: the last of n ascending values, from lo on, that is at most j (lo itself if none is; the
+// number is counted from lo).  value(i) may be asked for i < n.
+template <typename Value>
+__device__ __forceinline__ void last_at_most(uint32_t n, const uint32_t (&j)[MERGE_ITEMS], uint32_t (&found)[MERGE_ITEMS],
+                                             const Value &value)
+{
+#pragma unroll
+    for (int k = 0; k < MERGE_ITEMS; ++k) found[k] = 0;
+    for (uint32_t step = 1u << (31 - __clz((int)n)); step >= 1; step >>= 1) {   // uniform
+#pragma unroll
+        for (int k = 0; k < MERGE_ITEMS; ++k) {
+            const uint32_t next = found[k] + step;
+            if (next < n && value(k, next) <= j[k]) found[k] = next;
+        }
+    }
+}
+
+// Tile `number` of a small step, from raw IDs (hashed here as the lookup does).  lengths != NULL: up to
+// EMB_LENGTHS_DIRECT_BAGS bags, given by their lengths; else MAKE_OFFSETS: `offsets` are sums within tiles
+// (emb_offsets_tile_sums) of at most MERGE_BLOCK tiles, whose prefix sums are taken here; else offsets as
+// emb_offset_at takes them, and table_start and ctrl are set up already.
+template <bool MAKE_OFFSETS>
+__device__ __forceinline__ void tile_sort_raw(const TileSortArgs &a, uint32_t number, const emb_table *__restrict__ tables,
+                                              int32_t T, int64_t B, int64_t nnz, const int64_t *__restrict__ raw,
+                                              const int32_t *__restrict__ lengths, const int64_t *__restrict__ offsets,
+                                              const int64_t *__restrict__ tile_prefix, const int64_t *__restrict__ table_start,
+                                              const BwdCtrl *ctrl)
+{
+    __shared__ TileSortLds lds;
+    __shared__ int64_t wave_sums[MERGE_WAVES];
+    uint32_t *const off = reinterpret_cast<uint32_t *>(&lds);
+    uint32_t *const prefix = off + TILE_SAMPLES;
+    const uint32_t gid = number * MERGE_BLOCK + threadIdx.x;
+    if (gid < a.n_flags) a.span_flags[gid] = 0u;
+    // first record of bag i, where it is not in LDS already (sums that are no offsets give a number like any other: the
+    // backward is aborted then)
+    auto bag_start = [&](int64_t i) -> uint32_t {
+        if (MAKE_OFFSETS) return (uint32_t)offsets[i] + (i > 0 ? prefix[(i - 1) / EMB_OFFSETS_TILE] : 0u);
+        return (uint32_t)emb_offset_at(offsets, tile_prefix, i);
+    };
+    MergePart tile;
+    bool there;
+    if (MAKE_OFFSETS && lengths) {   // uniform
+        if (!tile_offsets_from_lengths(lengths, (uint32_t)(T * B), nnz, off, wave_sums)) return;
+        there = merge_part_in<MERGE_TILE, MERGE_BLOCK>(T, number, [&](int32_t t, uint32_t &s, uint32_t &e) {
+            s = off[t * (uint32_t)B];
+            e = off[(t + 1) * (uint32_t)B];
+        }, tile);
+    } else if (MAKE_OFFSETS) {
+        const int64_t n = (int64_t)T * B, k = threadIdx.x;
+        int64_t end = (k + 1) * EMB_OFFSETS_TILE, total;
+        if (end > n) end = n;
+        const int64_t v = k * EMB_OFFSETS_TILE < n ? offsets[end] : 0;   // the tile's total stands at its end
+        const int64_t inc = block_inclusive_scan<int64_t, MERGE_BLOCK>(v, wave_sums, total);
+        if (total != nnz) return;   // uniform; the lookup aborts the backward
+        prefix[k] = (uint32_t)(inc - v);
+        __syncthreads();
+        there = merge_part_in<MERGE_TILE, MERGE_BLOCK>(T, number, [&](int32_t t, uint32_t &s, uint32_t &e) {
+            s = bag_start(t * B);
+            e = bag_start((t + 1) * B);
+        }, tile);
+    } else {
+        there = merge_part_of<MERGE_TILE, MERGE_BLOCK>(table_start, T, number, ctrl, tile);
+    }
+    if (!there) return;   // uniform
+    const emb_table tb = tables[tile.table];
+    const uint32_t first_bag = tile.table * (uint32_t)B, n_bags = (uint32_t)B;   // (T * B fits 32 bits)
+    const uint32_t step = (n_bags + TILE_SAMPLES - 1) / TILE_SAMPLES;
+    if (!(MAKE_OFFSETS && lengths)) {
+        const uint64_t at = (uint64_t)threadIdx.x * step;
+        off[threadIdx.x] = at < n_bags ? bag_start((int64_t)first_bag + (int64_t)at) : 0xFFFFFFFFu;
+        __syncthreads();
+    }
+    const uint32_t start = tile.seg_start + tile.index * MERGE_TILE;
+    tile_sort<0>(a, tile, a.last ? (uint32_t)tb.row_base : 0u, lds,
+              [&](const uint32_t (&i)[MERGE_ITEMS], uint32_t count, uint32_t (&key)[MERGE_ITEMS], uint32_t (&pay)[MERGE_ITEMS]) {
+        uint64_t id[MERGE_ITEMS];
+        uint32_t j[MERGE_ITEMS], bag[MERGE_ITEMS];
+#pragma unroll
+        for (int k = 0; k < MERGE_ITEMS; ++k) {
+            j[k] = start + i[k];
+            id[k] = i[k] < count ? (uint64_t)raw[j[k]] : 0ull;
+        }
+        if (MAKE_OFFSETS && lengths) {
+            last_at_most(n_bags, j, bag, [&](int, uint32_t b) { return off[first_bag + b]; });
+        } else {
+            uint32_t part[MERGE_ITEMS];
+            last_at_most(TILE_SAMPLES, j, part, [&](int, uint32_t b) { return off[b]; });
+            last_at_most(step, j, bag, [&](int k, uint32_t b) {
+                const uint32_t at = part[k] * step + b;
+                return at < n_bags ? bag_start((int64_t)first_bag + at) : 0xFFFFFFFFu;
+            });
+#pragma unroll
+            for (int k = 0; k < MERGE_ITEMS; ++k) bag[k] += part[k] * step;
+        }
+#pragma unroll
+        for (int k = 0; k < MERGE_ITEMS; ++k) {
+            key[k] = (uint32_t)emb_fast_mod(emb_splitmix64(id[k] ^ tb.salt), (uint64_t)tb.num_rows, tb.mod_magic);
+            pay[k] = first_bag + bag[k];
+        }
+    });
 }
 
 // Every record's place in its table: its place in its own tile and, for each other tile of the table, the number
@@ -172,7 +366,8 @@ __global__ __launch_bounds__(MERGE_BLOCK) void tile_sort_kernel(const uint32_t *
 // order stable).  The tiles' keys go through LDS, PLACE_TILES tiles a round, and a thread bisects those for its record
 // side by side: a bisection is a chain of LDS reads that wait for each other (one in 4096 keys for eight records
 // a thread, one after the other, made 6 us of every 4096 records of the table).  The next round's keys are requested
-// while the current ones are searched.
+// while the current ones are searched.  Also clears the words of the list of distinct rows (list_flags, [list_tiles],
+// optional), which is the next launch (a step that is not merged has one such word, and nobody waits for it).
 __global__ __launch_bounds__(PLACE_BLOCK) void tile_merge_kernel(const uint32_t *__restrict__ keys_in,
                                                                  const uint32_t *__restrict__ pay_in,
                                                                  uint32_t *__restrict__ keys_out,
@@ -180,8 +375,11 @@ __global__ __launch_bounds__(PLACE_BLOCK) void tile_merge_kernel(const uint32_t 
                                                                  const int64_t *__restrict__ table_start, int32_t T,
                                                                  const emb_table *__restrict__ tables,
                                                                  uint32_t local_sentinel, uint32_t global_sentinel,
-                                                                 const BwdCtrl *ctrl)
+                                                                 unsigned long long *__restrict__ list_flags,
+                                                                 uint32_t list_tiles, const BwdCtrl *ctrl)
 {
+    const uint32_t gid = blockIdx.x * PLACE_BLOCK + threadIdx.x;
+    if (list_flags && gid < list_tiles) list_flags[gid] = 0ull;
     constexpr int ROUND = PLACE_TILES * MERGE_TILE;       // keys in LDS at a time
     constexpr int PER = ROUND / PLACE_BLOCK;              // of them a thread fetches
     static_assert(MERGE_TILE % PLACE_BLOCK == 0, "a part lies in one tile");

@@ -1161,6 +1161,59 @@ def test_training_forward_from_lengths_with_more_than_a_thousand_tiles_of_bags()
     assert np.array_equal(uk[:int(nu.item())].cpu().numpy(), np.unique(rows))
 
 
+@pytest.mark.parametrize("B,per_table", [
+    (1, [1024]), (1, [1025]), (1, [1, 0, 2]),              # one bag holds whole tiles of the sort
+    (256, [1024, 1023]), (257, [1024, 1025, 0, 3000]),     # bags found by bisection, as many as threads and one more
+    (4096, [5000]), (4097, [5000]),                        # the last number of bags whose offsets stand in LDS, one more
+    (1639, [0, 4096, 7, 2049, 1]),                         # ... tables that start inside a tile of lengths
+    (70_000, [1500, 2000]),                                # hardly any bag has a lookup
+    (4, [1] * 300 + [0] * 100 + [40] * 100),               # more tables than threads
+])
+@pytest.mark.parametrize("from_lengths", [True, False])
+def test_tiles_sorted_beside_the_training_lookup_give_the_bits_of_records_in_memory(B, per_table, from_lengths):
+    # The training lookup of a small step sorts its tiles from the raw IDs in workgroups of the same launch; the one-call
+    # backward sorts records that a launch before has written.  Same rows, bags and order, so no bit may differ.
+    T, D, R = len(per_table), 16, 3000
+    rng = np.random.default_rng(6100 + B + T)
+    lengths = np.concatenate([np.bincount(np.sort(rng.integers(0, B, size=n)), minlength=B) for n in per_table]).astype(np.int32)
+    off, _ = oracle.lengths_to_offsets(lengths)
+    nnz = int(off[-1])
+    raw = rng.integers(0, 1 << 64, size=nnz, dtype=np.uint64)
+    raw[rng.random(nnz) < 0.2] = raw[0]
+    salts = [int(x) for x in rng.integers(0, 1 << 62, size=T)]
+    table = (rng.standard_normal((R, D)) * 0.01).astype(np.float32)
+    dout = H.dev(rng.standard_normal((T, B, D)).astype(np.float32))
+    raw_d, off_d, len_d = H.dev(raw), H.dev(off), H.dev(lengths)
+
+    def route(train):
+        w = [H.dev(table) for _ in range(T)]
+        acc = [torch.zeros(R, dtype=torch.float32, device=H.DEV) for _ in range(T)]
+        ts = emb.TableSet(w, D, "f32", accum=acc, salts=salts, device=torch.device(H.DEV))
+        ws = torch.full((emb.emb_bag_backward_workspace_bytes(T, B, nnz, ts.total_rows, D, "f32"),), 0xA5, dtype=torch.uint8,
+                        device=H.DEV)
+        uk, uc = torch.zeros(nnz, dtype=torch.int64, device=H.DEV), torch.zeros(nnz, dtype=torch.int32, device=H.DEV)
+        nu, st = torch.zeros(1, dtype=torch.int64, device=H.DEV), torch.zeros(1, dtype=torch.int32, device=H.DEV)
+        out = torch.empty((T, B, D), dtype=torch.float32, device=H.DEV)
+        if not train:
+            rows = torch.empty(nnz, dtype=torch.int64, device=H.DEV)
+            emb.emb_bag_forward_hashed(ts, raw_d, off_d, B, "mean", out, rows, st)
+            emb.emb_bag_backward_rowwise_adagrad(ts, rows, off_d, B, "mean", dout, 0.01, 1e-8, ws, uk, uc, nu, st)
+        else:
+            if from_lengths:
+                emb.emb_bag_forward_train_lengths(ts, raw_d, len_d, B, "mean", out, torch.empty_like(off_d), ws, None, nu, st)
+            else:
+                emb.emb_bag_forward_train(ts, raw_d, off_d, B, "mean", out, ws, None, nu, st)
+            for _ in range(2):   # (sorting what is sorted changes nothing)
+                emb.emb_bag_backward_sort_prepared(ts, B, nnz, ws, uk, uc, nu, st)
+            emb.emb_bag_backward_update(ts, B, nnz, dout, 0.01, 1e-8, ws, nu, None, None)
+        torch.cuda.synchronize()
+        assert st.item() == 0
+        return [out, uk, uc, nu] + w + acc
+
+    for a, b in zip(route(True), route(False)):
+        assert torch.equal(a, b)
+
+
 def test_training_forward_from_lengths_without_bags():
     ts = emb.TableSet([torch.zeros((5, 16), dtype=torch.float32, device=H.DEV)], 16, "f32",
                       accum=[torch.zeros(5, dtype=torch.float32, device=H.DEV)], device=torch.device(H.DEV))
