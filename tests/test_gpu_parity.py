@@ -145,6 +145,51 @@ def test_forward_matches_oracle(D, dtype, mode):
     assert np.all(out.reshape(T * B, D)[lengths == 0] == 0.0)         # empty bags give exact zeros
 
 
+@pytest.mark.parametrize("D,dtype", [(4, "f32"), (8, "f32"), (16, "f32"), (12, "f32"), (32, "f32"), (64, "f32"), (100, "f32"), (128, "f32"),
+                                     (256, "f32"), (8, "bf16"), (48, "bf16"), (16, "int4"), (48, "int4"), (64, "int4"), (512, "int4"),
+                                     (16, "int8"), (80, "int8")])
+@pytest.mark.parametrize("B,mean", [(1, 8), (1, 700), (37, 8), (37, 17), (37, 40), (300, 33), (45_000, 11), (34_000, 19), (9_000, 62)])
+def test_forward_bags_shared_by_lane_groups_add_every_row_once(D, dtype, B, mean):
+    # few bags, and long ones in a batch that fills the chip: rows of a bag go to 2, 4 or 8 lane groups.  Small whole
+    # numbers make every order of the sum exact, so the lookup equals the oracle bit for bit, empty bags included.
+    if B > 1000 and D not in (4, 8, 16, 32):
+        B //= 8
+    rng = np.random.default_rng(9000 + D + B + mean)
+    T, R = 2, 700
+    quant = dtype in ("int8", "int4")
+    lengths = np.clip(rng.poisson(mean, size=T * B), 0, None).astype(np.int32)
+    lengths[0] = mean
+    if B > 1:
+        lengths[rng.integers(1, T * B, size=T * B // 20 + 1)] = 0
+        lengths[-1] = 4 * mean + 1
+    off, _ = oracle.lengths_to_offsets(lengths)
+    nnz = int(off[-1])
+    tables = []
+    for t in range(T):
+        x = rng.integers(0, 16, size=(R, D)).astype(np.float32)
+        if quant:
+            x[:, 0], x[:, 1] = 0, (255 if dtype == "int8" else 15)           # scale 1, whole bias
+            tables.append(oracle.quantize_rows(x + rng.integers(-20, 20, size=(R, 1)).astype(np.float32), dtype))
+        else:
+            tables.append(wl.f32_to_bf16_bits(x).reshape(R, D) if dtype == "bf16" else x)
+    ts = emb.TableSet([H.dev(t) for t in tables], D, dtype, salts=[3, 4], device=torch.device(H.DEV))
+    raw = rng.integers(0, 1 << 64, size=nnz, dtype=np.uint64)
+    rows = np.concatenate([oracle.hash_ids(raw[off[t * B]:off[(t + 1) * B]], 3 + t, R) for t in range(T)])
+    kw = {"D": D} if quant else {}
+    ref, _, _ = oracle.bag_forward(tables, dtype, rows, off, B, "sum", **kw)
+    out, st = H.gpu_forward(ts, rows, off, B, "sum")
+    assert st == 0 and np.array_equal(out.reshape(ref.shape), ref)
+    outs = torch.full((T, B, D), float("nan"), dtype=torch.float32, device=H.DEV)
+    offs = torch.full((T * B + 1,), -1, dtype=torch.int64, device=H.DEV)
+    rows_out = torch.full((nnz,), -1, dtype=torch.int64, device=H.DEV)
+    scratch = torch.empty(emb.emb_offsets_scratch_bytes(T * B), dtype=torch.uint8, device=H.DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    emb.emb_bag_forward_hashed_lengths(ts, H.dev(raw), H.dev(lengths), B, "sum", outs, offs, scratch, rows_out, status)
+    torch.cuda.synchronize()
+    assert status.item() == 0 and np.array_equal(offs.cpu().numpy(), off) and np.array_equal(rows_out.cpu().numpy(), rows)
+    assert np.array_equal(outs.cpu().numpy().reshape(ref.shape), ref)
+
+
 def test_forward_integer_valued_tables_are_bit_exact():
     # small integers make every fp32 summation order exact: GPU == oracle bit for bit
     rng = np.random.default_rng(31)
