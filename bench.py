@@ -40,19 +40,19 @@ def log(*a):
 # bytes or less are counted at their true size, so for kernels that issue those (4-byte accumulators,
 # 48-byte quantised rows) the scaled figure is an upper bound.
 PMC_TRAFFIC = {
-    "sources": "cc8ccae76fc23f5f",
+    "sources": "6feb529de9afa25f",
     "fetch_scale": 2.0,
     "write_scale": 1.0,
     "kib_per_launch": {     # workload -> kernel -> (FETCH_SIZE, WRITE_SIZE)
-        "3": {"bag_forward_train_kernel": (173382.2, 69672.3), "update_kernel": (240542.1, 324005.5)},
-        "3b": {"bag_forward_train_kernel": (90536.5, 74149.3), "update_kernel": (170009.3, 221182.5)},
-        "2": {"bag_forward_kernel<HASHED>": (172050.4, 33883.7), "bag_forward_kernel": (172201.8, 32768.0)},
-        "2u": {"bag_forward_kernel<HASHED>": (338208.7, 33800.3), "bag_forward_kernel": (338159.7, 32768.0)},
-        "2un": {"bag_forward_kernel": (339636.6, 32768.0)},
-        "2q4": {"bag_forward_quant_kernel": (112729.5, 33825.9)},
-        "2uq4": {"bag_forward_quant_kernel": (225088.3, 33896.5)},
-        "2uq4r": {"bag_forward_quant_kernel": (182160.4, 33858.6)},
-        "4": {"bag_forward_kernel<HASHED>": (52440.1, 8704.2)},
+        "3": {"bag_forward_train_kernel": (173371.2, 69677.4), "update_kernel": (240916.9, 324005.8)},
+        "3b": {"bag_forward_train_kernel": (90604.5, 74115.9), "update_kernel": (170603.5, 221075.1)},
+        "2": {"bag_forward_kernel<HASHED>": (172152.1, 33876.9), "bag_forward_kernel": (172409.5, 32768.0)},
+        "2u": {"bag_forward_kernel<HASHED>": (338201.3, 33803.0), "bag_forward_kernel": (338155.3, 32768.0)},
+        "2un": {"bag_forward_kernel": (339975.7, 32768.0)},
+        "2q4": {"bag_forward_quant_kernel": (107657.1, 33819.0)},
+        "2uq4": {"bag_forward_quant_kernel": (214897.9, 33894.5)},
+        "2uq4r": {"bag_forward_quant_kernel": (174203.3, 33843.8)},
+        "4": {"bag_forward_kernel<HASHED>": (47079.6, 8710.4)},
     },
 }
 
