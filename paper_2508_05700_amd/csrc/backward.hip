@@ -856,25 +856,24 @@ __device__ __forceinline__ void train_bag_scale(const int64_t *__restrict__ offs
     }
 }
 
-template <int LPR, int CPL, int UNROLL, bool BF16, typename KeyT, bool SHARED>
+template <int LPR, int CPL, int UNROLL, bool BF16, typename KeyT>
 __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
     const emb_table *__restrict__ tables, int32_t T, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ raw, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
     float *__restrict__ out, int64_t *__restrict__ rows_out, KeyT *__restrict__ keys, uint32_t *__restrict__ pay,
     float *__restrict__ bag_scale, BwdCtrl *ctrl, uint32_t *status, const int64_t *__restrict__ tile_prefix,
-    int64_t *__restrict__ offsets_out, int32_t split)
+    int64_t *__restrict__ offsets_out)
 {
     // tile_prefix != NULL: `offsets` are sums within tiles (emb_offset_at) and the final offsets go to offsets_out
-    if (!SHARED) split = 0;
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = TRAIN_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = TRAIN_BLOCK / LPR;
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     const uint32_t lb = emb_xcd_block(blockIdx.x, gridDim.x);
     const uint32_t t_raw = lb / blocks_per_table;
     const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
     const int t = tail ? T - 1 : (int)t_raw;
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * groups;
-    const int64_t b = b0 + (threadIdx.x >> lane_bits);
+    const int l = threadIdx.x % LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
     const bool live = b < B;
     const int64_t bag = (int64_t)t * B + b;
     const emb_table tb = tables[t];
@@ -882,7 +881,7 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
                           (int64_t)chunks_per_row * 16, rows_out, keys, pay, (uint32_t)bag};
     float *const out_row = out + bag * ((int64_t)chunks_per_row * F);
     if (live && l == 0) train_bag_scale(offsets, tile_prefix, bag, nnz, mode, bag_scale, ctrl, offsets_out);
-    gather_pool_bag<LPR, CPL, UNROLL, BF16>(split, src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
+    gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
                                             tile_prefix);
 }
 
@@ -895,30 +894,28 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_kernel(
 // for up to EMB_LENGTHS_DIRECT_BAGS bags.  The kernel makes the bounds itself, from `lengths` or from the sums in `offsets`
 // as bag_forward_kernel does, and whoever has a table's first or the batch's last bag writes what the set-up kernel
 // would have: table_start, the control block (the bags partition [0, nnz) iff the last one ends there).
-template <int LPR, int CPL, int UNROLL, bool BF16, bool MAKE_OFFSETS, bool SHARED>
+template <int LPR, int CPL, int UNROLL, bool BF16, bool MAKE_OFFSETS>
 __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_small_kernel(
     const emb_table *__restrict__ tables, int32_t T, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ raw, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
     float *__restrict__ out, int64_t *__restrict__ rows_out, float *__restrict__ bag_scale, BwdCtrl *ctrl, uint32_t *status,
     const int64_t *__restrict__ tile_prefix, int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths,
-    int64_t *__restrict__ table_start, int64_t *num_unique_out, uint32_t tile_blocks, TileSortArgs sort, int32_t split)
+    int64_t *__restrict__ table_start, int64_t *num_unique_out, uint32_t tile_blocks, TileSortArgs sort)
 {
-    if (!SHARED) split = 0;
     static_assert(TRAIN_BLOCK == MERGE_BLOCK, "both kinds of workgroups are of one launch");
     if (blockIdx.x < tile_blocks) {   // uniform
         tile_sort_raw<MAKE_OFFSETS>(sort, blockIdx.x, tables, T, B, nnz, raw, lengths, offsets, tile_prefix, table_start, ctrl);
         return;
     }
-    constexpr int GROUPS = TRAIN_BLOCK / LPR;                       // bags of the workgroup at most
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = TRAIN_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = TRAIN_BLOCK / LPR;
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     const uint32_t lb = emb_xcd_block(blockIdx.x - tile_blocks, gridDim.x - tile_blocks);   // (both are multiples of EMB_XCDS)
     const uint32_t t_raw = lb / blocks_per_table;
     const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
     const int t = tail ? T - 1 : (int)t_raw;
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * groups;
-    const int64_t b = b0 + (threadIdx.x >> lane_bits);
+    const int l = threadIdx.x % LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
     const bool live = b < B;
     const int64_t bag = (int64_t)t * B + b;
     const emb_table tb = tables[t];
@@ -931,8 +928,8 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_small_kernel(
         int64_t s, e;
         if (lengths) {   // uniform
             const int64_t left = B - b0;
-            emb_bounds_from_lengths<TRAIN_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < groups ? (int)left : groups,
-                                                         (threadIdx.x >> lane_bits), prefixes, wave_sums, status, s, e);
+            emb_bounds_from_lengths<TRAIN_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < GROUPS ? (int)left : GROUPS,
+                                                         threadIdx.x / LPR, prefixes, wave_sums, status, s, e);
         } else {
             emb_two_level_bounds<TRAIN_BLOCK>(offsets, (int64_t)T * B, live, bag, prefixes, wave_sums, s, e);
         }
@@ -950,10 +947,10 @@ __global__ __launch_bounds__(TRAIN_BLOCK) void bag_forward_train_small_kernel(
                 if (num_unique_out) *num_unique_out = 0;
             }
         }
-        gather_pool_split<LPR, CPL, UNROLL, BF16>(split, src, live, s, e, l, nnz, raw, chunks_per_row, mode, out_row, status);
+        gather_pool_range<LPR, CPL, UNROLL, BF16>(src, live, s, e, l, nnz, raw, chunks_per_row, mode, out_row, status);
     } else {
         if (live && l == 0) train_bag_scale(offsets, tile_prefix, bag, nnz, mode, bag_scale, ctrl, offsets_out);
-        gather_pool_bag<LPR, CPL, UNROLL, BF16>(split, src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
+        gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, live, bag, l, nnz, raw, offsets, chunks_per_row, mode, out_row, status,
                                                 tile_prefix);
     }
 }
@@ -968,9 +965,8 @@ template <typename KeyT, int LPR, int CPL, int UNROLL>
 int launch_train(bool bf16, const BwdArgs &a, const BwdLayout &L, const int64_t *raw, float *out, int64_t *rows_out,
                  int chunks)
 {
-    const int32_t split = emb_bag_split(LPR, a.T * a.B, a.nnz);
-    const int64_t groups = TRAIN_BLOCK / LPR >> split;
-    const int64_t per_table = (a.B + groups - 1) / groups;
+    constexpr int GROUPS = TRAIN_BLOCK / LPR;
+    const int64_t per_table = (a.B + GROUPS - 1) / GROUPS;
     const int64_t blocks = emb_round_up_xcds(per_table * a.T);
     if (blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     BwdCtrl *ctrl = reinterpret_cast<BwdCtrl *>(a.ws + L.ctrl);
@@ -987,13 +983,10 @@ int launch_train(bool bf16, const BwdArgs &a, const BwdLayout &L, const int64_t 
             const int32_t *lengths = make && (int64_t)a.T * a.B <= EMB_LENGTHS_DIRECT_BAGS ? a.lengths : nullptr;
             const int64_t tile_blocks = emb_round_up_xcds(tile_sort_blocks(a));   // (not above nnz and T together: both small)
 #define EMB_TRAIN_SMALL(BF, MAKE)                                                                                            \
-    with_split<LPR>(split, [&](auto shared) {                                                                                \
-        hipLaunchKernelGGL((bag_forward_train_small_kernel<LPR, CPL, UNROLL, BF, MAKE, decltype(shared)::value>),            \
-                           dim3((unsigned)(tile_blocks + blocks)), dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B,   \
-                           (uint32_t)per_table, a.nnz, raw, offsets, chunks, a.mode, out, rows_out, bag_scale, ctrl, a.status, \
-                           tile_prefix, a.offsets_out, lengths, table_start_of(a, L), a.num_unique_out, (uint32_t)tile_blocks, \
-                           tile_sort_args(a, L), split);                                                                     \
-    })
+    hipLaunchKernelGGL((bag_forward_train_small_kernel<LPR, CPL, UNROLL, BF, MAKE>), dim3((unsigned)(tile_blocks + blocks)), \
+                       dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets,     \
+                       chunks, a.mode, out, rows_out, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out, lengths,        \
+                       table_start_of(a, L), a.num_unique_out, (uint32_t)tile_blocks, tile_sort_args(a, L))
             if (blocks + tile_blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
             if (make) {
                 if (bf16) EMB_TRAIN_SMALL(true, true);
@@ -1008,12 +1001,9 @@ int launch_train(bool bf16, const BwdArgs &a, const BwdLayout &L, const int64_t 
         }
     }
 #define EMB_TRAIN(BF)                                                                                                        \
-    with_split<LPR>(split, [&](auto shared) {                                                                                \
-        hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, BF, KeyT, decltype(shared)::value>),                  \
-                           dim3((unsigned)blocks), dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, \
-                           a.nnz, raw, offsets, chunks, a.mode, out, rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix, \
-                           a.offsets_out, split);                                                                            \
-    })
+    hipLaunchKernelGGL((bag_forward_train_kernel<LPR, CPL, UNROLL, BF, KeyT>), dim3((unsigned)blocks), dim3(TRAIN_BLOCK), 0, \
+                       a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets, chunks, a.mode, out,      \
+                       rows_out, keys, pay, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out)
     if (bf16) EMB_TRAIN(true);
     else EMB_TRAIN(false);
 #undef EMB_TRAIN

@@ -141,21 +141,20 @@ constexpr int CF_BLOCK = 256;
 // straight from `lengths` if that is given (emb_bounds_from_lengths: up to EMB_LENGTHS_DIRECT_BAGS bags), else from
 // `offsets`, the sums within tiles of lengths (emb_two_level_bounds).  Every thread of the workgroup calls this; the
 // choice is uniform over the launch.  n_bags: of all tables; first, in_table: the workgroup's first bag, and the bags
-// of its table from there on; lane_bits: of a bag's lanes.
+// of its table from there on.
 constexpr int CB_LDS_BOUNDS = CF_BLOCK + 1, CB_LDS_SUMS = 2 * CF_BLOCK / EMB_WAVE;   // int64 words of LDS
 template <int LPR>
 __device__ __forceinline__ void cached_bag_bounds(const int64_t *__restrict__ offsets, const int32_t *__restrict__ lengths,
                                                   int64_t *__restrict__ offsets_out, int64_t n_bags, int64_t first,
-                                                  int64_t in_table, bool live, int64_t bag, int lane_bits, int l, int64_t *bounds,
+                                                  int64_t in_table, bool live, int64_t bag, int l, int64_t *bounds,
                                                   int64_t *wave_sums, uint32_t *status, int64_t &s, int64_t &e)
 {
-    constexpr int GROUPS = CF_BLOCK / LPR;   // bags of a workgroup at most
-    const int groups = CF_BLOCK >> lane_bits;
+    constexpr int GROUPS = CF_BLOCK / LPR;
     s = e = 0;
     if (offsets_out) {
         if (lengths)
-            emb_bounds_from_lengths<CF_BLOCK, GROUPS>(lengths, first, in_table < groups ? (int)in_table : groups,
-                                                      (threadIdx.x >> lane_bits), bounds, wave_sums, status, s, e);
+            emb_bounds_from_lengths<CF_BLOCK, GROUPS>(lengths, first, in_table < GROUPS ? (int)in_table : GROUPS,
+                                                      threadIdx.x / LPR, bounds, wave_sums, status, s, e);
         else
             emb_two_level_bounds<CF_BLOCK>(offsets, n_bags, live, bag, bounds, wave_sums, s, e);
         if (live && l == 0) {
@@ -169,7 +168,7 @@ __device__ __forceinline__ void cached_bag_bounds(const int64_t *__restrict__ of
 }
 static_assert(CF_BLOCK == Q_BLOCK, "the cached lookups over plain and quantised rows scan the same number of tiles");
 
-template <int LPR, int CPL, int UNROLL, bool BF16, bool SHARED>
+template <int LPR, int CPL, int UNROLL, bool BF16>
 __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_kernel(const char *__restrict__ table,
                                                                       const char *__restrict__ cache_rows,
                                                                       const CacheEntry *__restrict__ index,
@@ -181,20 +180,19 @@ __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_kernel(const char
                                                                       unsigned long long *hit_miss, uint32_t *status,
                                                                       bool hashed, uint64_t salt, uint64_t magic,
                                                                       int64_t *__restrict__ offsets_out,
-                                                                      const int32_t *__restrict__ lengths, int32_t split)
+                                                                      const int32_t *__restrict__ lengths)
 {
-    if (!SHARED) split = 0;
     __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = CF_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b = (int64_t)blockIdx.x * groups + (threadIdx.x >> lane_bits);
+    constexpr int GROUPS = CF_BLOCK / LPR;
+    const int l = threadIdx.x % LPR;
+    const int64_t b = (int64_t)blockIdx.x * GROUPS + threadIdx.x / LPR;
     CachedSource src{table,  cache_rows, index, (uint64_t)num_rows, (uint64_t)num_hot, (int64_t)chunks_per_row * 16,
                      status, 0u,         0u,    hashed,             salt,              magic};
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     int64_t s, e;
-    const int64_t b0 = (int64_t)blockIdx.x * groups;
-    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, B, b0, B - b0, b < B, b, lane_bits, l, bounds, wave_sums, status, s, e);
-    gather_pool_split<LPR, CPL, UNROLL, BF16>(split, src, b < B, s, e, l, nnz, rows, chunks_per_row, mode,
+    const int64_t b0 = (int64_t)blockIdx.x * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, B, b0, B - b0, b < B, b, l, bounds, wave_sums, status, s, e);
+    gather_pool_range<LPR, CPL, UNROLL, BF16>(src, b < B, s, e, l, nnz, rows, chunks_per_row, mode,
                                               out + b * ((int64_t)chunks_per_row * F), status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
@@ -205,25 +203,21 @@ int launch_cached(bool bf16, hipStream_t s, const char *table, const char *cache
                   const int64_t *offsets, int32_t chunks, int32_t mode, float *out, unsigned long long *hit_miss,
                   uint32_t *status, bool hashed, uint64_t salt, uint64_t magic, int64_t *offsets_out, const int32_t *lengths)
 {
-    const int32_t split = emb_bag_split(LPR, B, nnz);
-    const int64_t groups = CF_BLOCK / LPR >> split;
-    dim3 grid((unsigned)((B + groups - 1) / groups));
-    with_split<LPR>(split, [&](auto shared) {
-        constexpr bool SHARED = decltype(shared)::value;
-        if (bf16)
-            hipLaunchKernelGGL((bag_forward_cached_kernel<LPR, CPL, UNROLL, true, SHARED>), grid, dim3(CF_BLOCK), 0, s, table,
-                               cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, chunks, mode, out, hit_miss, status,
-                               hashed, salt, magic, offsets_out, lengths, split);
-        else
-            hipLaunchKernelGGL((bag_forward_cached_kernel<LPR, CPL, UNROLL, false, SHARED>), grid, dim3(CF_BLOCK), 0, s, table,
-                               cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, chunks, mode, out, hit_miss, status,
-                               hashed, salt, magic, offsets_out, lengths, split);
-    });
+    constexpr int GROUPS = CF_BLOCK / LPR;
+    dim3 grid((unsigned)((B + GROUPS - 1) / GROUPS));
+    if (bf16)
+        hipLaunchKernelGGL((bag_forward_cached_kernel<LPR, CPL, UNROLL, true>), grid, dim3(CF_BLOCK), 0, s, table,
+                           cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, chunks, mode, out, hit_miss, status,
+                           hashed, salt, magic, offsets_out, lengths);
+    else
+        hipLaunchKernelGGL((bag_forward_cached_kernel<LPR, CPL, UNROLL, false>), grid, dim3(CF_BLOCK), 0, s, table,
+                           cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, chunks, mode, out, hit_miss, status,
+                           hashed, salt, magic, offsets_out, lengths);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
 
-template <int LPR, int BITS, int UNROLL, bool SHARED>
+template <int LPR, int BITS, int UNROLL>
 __global__ __launch_bounds__(Q_BLOCK) void bag_forward_cached_quant_kernel(const char *__restrict__ table,
                                                                            const char *__restrict__ cache_rows,
                                                                            const CacheEntry *__restrict__ index,
@@ -235,19 +229,18 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_cached_quant_kernel(const
                                                                            unsigned long long *hit_miss, uint32_t *status,
                                                                            bool hashed, uint64_t salt, uint64_t magic,
                                                                            int64_t *__restrict__ offsets_out,
-                                                                           const int32_t *__restrict__ lengths, int32_t split)
+                                                                           const int32_t *__restrict__ lengths)
 {
-    if (!SHARED) split = 0;
     __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = Q_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b = (int64_t)blockIdx.x * groups + (threadIdx.x >> lane_bits);
+    constexpr int GROUPS = Q_BLOCK / LPR;
+    const int l = threadIdx.x % LPR;
+    const int64_t b = (int64_t)blockIdx.x * GROUPS + threadIdx.x / LPR;
     CachedSource src{table, cache_rows, index, (uint64_t)num_rows, (uint64_t)num_hot, row_bytes, status, 0u, 0u,
                      hashed, salt, magic};
     int64_t s, e;
-    const int64_t b0 = (int64_t)blockIdx.x * groups;
-    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, B, b0, B - b0, b < B, b, lane_bits, l, bounds, wave_sums, status, s, e);
-    gather_dequant_pool_split<LPR, BITS, UNROLL>(split, src, b < B, b, s, e, l, nnz, rows, D, mode, out, status);
+    const int64_t b0 = (int64_t)blockIdx.x * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, B, b0, B - b0, b < B, b, l, bounds, wave_sums, status, s, e);
+    gather_dequant_pool_range<LPR, BITS, UNROLL>(src, b < B, b, s, e, l, nnz, rows, D, mode, out, status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
 
@@ -260,14 +253,10 @@ int dispatch_cached_quant(int lpr, hipStream_t s, const char *table, const char 
 {
 #define EMB_CQ(L)                                                                                                   \
     do {                                                                                                            \
-        const int32_t split = emb_bag_split(L, B, nnz);                                                             \
-        const int64_t groups = Q_BLOCK / L >> split;                                                               \
-        with_split<L>(split, [&](auto shared) {                                                                     \
-            hipLaunchKernelGGL((bag_forward_cached_quant_kernel<L, BITS, 8, decltype(shared)::value>),              \
-                               dim3((unsigned)((B + groups - 1) / groups)), dim3(Q_BLOCK), 0, s, table, cache_rows, \
-                               index, num_rows, num_hot, B, nnz, rows, offsets, D, row_bytes, mode, out, hit_miss,  \
-                               status, hashed, salt, magic, offsets_out, lengths, split);                           \
-        });                                                                                                         \
+        constexpr int GROUPS = Q_BLOCK / L;                                                                         \
+        hipLaunchKernelGGL((bag_forward_cached_quant_kernel<L, BITS, 8>), dim3((unsigned)((B + GROUPS - 1) / GROUPS)), \
+                           dim3(Q_BLOCK), 0, s, table, cache_rows, index, num_rows, num_hot, B, nnz, rows, offsets, D, \
+                           row_bytes, mode, out, hit_miss, status, hashed, salt, magic, offsets_out, lengths);      \
         EMB_RETURN_IF_LAUNCH_FAILED();                                                                              \
         return EMB_OK;                                                                                              \
     } while (0)
@@ -304,53 +293,51 @@ __device__ __forceinline__ CachedSource cached_source_of(const emb_cached_table 
                         tb.mod_magic};
 }
 
-template <int LPR, int CPL, int UNROLL, bool BF16, bool SHARED>
+template <int LPR, int CPL, int UNROLL, bool BF16>
 __global__ __launch_bounds__(CF_BLOCK) void bag_forward_cached_tables_kernel(
     const emb_cached_table *__restrict__ tables, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ ids, const int64_t *__restrict__ offsets, int32_t chunks_per_row, int32_t mode,
     float *__restrict__ out, unsigned long long *hit_miss, uint32_t *status, bool hashed, int32_t T,
-    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths, int32_t split)
+    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths)
 {
-    if (!SHARED) split = 0;
     __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = CF_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = CF_BLOCK / LPR;
     const uint32_t t = blockIdx.x / blocks_per_table;   // the grid is exactly T * blocks_per_table
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b = (int64_t)(blockIdx.x % blocks_per_table) * groups + (threadIdx.x >> lane_bits);
+    const int l = threadIdx.x % LPR;
+    const int64_t b = (int64_t)(blockIdx.x % blocks_per_table) * GROUPS + threadIdx.x / LPR;
     const emb_cached_table tb = tables[t];
     CachedSource src = cached_source_of(tb, (int64_t)chunks_per_row * 16, status, hashed);
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     const int64_t bag = (int64_t)t * B + b;
     int64_t s, e;
-    const int64_t b0 = (int64_t)(blockIdx.x % blocks_per_table) * groups;
-    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, (int64_t)T * B, (int64_t)t * B + b0, B - b0, b < B, bag, lane_bits, l, bounds, wave_sums,
+    const int64_t b0 = (int64_t)(blockIdx.x % blocks_per_table) * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, (int64_t)T * B, (int64_t)t * B + b0, B - b0, b < B, bag, l, bounds, wave_sums,
                            status, s, e);
-    gather_pool_split<LPR, CPL, UNROLL, BF16>(split, src, b < B, s, e, l, nnz, ids, chunks_per_row, mode,
+    gather_pool_range<LPR, CPL, UNROLL, BF16>(src, b < B, s, e, l, nnz, ids, chunks_per_row, mode,
                                               out + bag * ((int64_t)chunks_per_row * F), status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
 
-template <int LPR, int BITS, int UNROLL, bool SHARED>
+template <int LPR, int BITS, int UNROLL>
 __global__ __launch_bounds__(Q_BLOCK) void bag_forward_cached_tables_quant_kernel(
     const emb_cached_table *__restrict__ tables, int64_t B, uint32_t blocks_per_table, int64_t nnz,
     const int64_t *__restrict__ ids, const int64_t *__restrict__ offsets, int32_t D, int64_t row_bytes, int32_t mode,
     float *__restrict__ out, unsigned long long *hit_miss, uint32_t *status, bool hashed, int32_t T,
-    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths, int32_t split)
+    int64_t *__restrict__ offsets_out, const int32_t *__restrict__ lengths)
 {
-    if (!SHARED) split = 0;
     __shared__ int64_t bounds[CB_LDS_BOUNDS], wave_sums[CB_LDS_SUMS];
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = Q_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = Q_BLOCK / LPR;
     const uint32_t t = blockIdx.x / blocks_per_table;
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b = (int64_t)(blockIdx.x % blocks_per_table) * groups + (threadIdx.x >> lane_bits);
+    const int l = threadIdx.x % LPR;
+    const int64_t b = (int64_t)(blockIdx.x % blocks_per_table) * GROUPS + threadIdx.x / LPR;
     const emb_cached_table tb = tables[t];
     CachedSource src = cached_source_of(tb, row_bytes, status, hashed);
     const int64_t bag = (int64_t)t * B + b;
     int64_t s, e;
-    const int64_t b0 = (int64_t)(blockIdx.x % blocks_per_table) * groups;
-    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, (int64_t)T * B, (int64_t)t * B + b0, B - b0, b < B, bag, lane_bits, l, bounds, wave_sums,
+    const int64_t b0 = (int64_t)(blockIdx.x % blocks_per_table) * GROUPS;
+    cached_bag_bounds<LPR>(offsets, lengths, offsets_out, (int64_t)T * B, (int64_t)t * B + b0, B - b0, b < B, bag, l, bounds, wave_sums,
                            status, s, e);
-    gather_dequant_pool_split<LPR, BITS, UNROLL>(split, src, b < B, bag, s, e, l, nnz, ids, D, mode, out, status);
+    gather_dequant_pool_range<LPR, BITS, UNROLL>(src, b < B, bag, s, e, l, nnz, ids, D, mode, out, status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
 
@@ -373,23 +360,19 @@ struct CachedTablesArgs {
 template <int LPR, int CPL, int UNROLL>
 int launch_cached_tables(const CachedTablesArgs &a, bool bf16)
 {
-    const int32_t split = emb_bag_split(LPR, a.T * a.B, a.nnz);
-    const int64_t groups = CF_BLOCK / LPR >> split;
-    const int64_t per_table = (a.B + groups - 1) / groups;
+    constexpr int GROUPS = CF_BLOCK / LPR;
+    const int64_t per_table = (a.B + GROUPS - 1) / GROUPS;
     if (per_table * a.T > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(per_table * a.T));
     const int32_t chunks = (int32_t)(a.row_bytes / 16);
-    with_split<LPR>(split, [&](auto shared) {
-        constexpr bool SHARED = decltype(shared)::value;
-        if (bf16)
-            hipLaunchKernelGGL((bag_forward_cached_tables_kernel<LPR, CPL, UNROLL, true, SHARED>), grid, dim3(CF_BLOCK), 0, a.s,
-                               a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, chunks, a.mode, a.out, a.hit_miss,
-                               a.status, a.hashed, a.T, a.offsets_out, a.lengths, split);
-        else
-            hipLaunchKernelGGL((bag_forward_cached_tables_kernel<LPR, CPL, UNROLL, false, SHARED>), grid, dim3(CF_BLOCK), 0, a.s,
-                               a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, chunks, a.mode, a.out, a.hit_miss,
-                               a.status, a.hashed, a.T, a.offsets_out, a.lengths, split);
-    });
+    if (bf16)
+        hipLaunchKernelGGL((bag_forward_cached_tables_kernel<LPR, CPL, UNROLL, true>), grid, dim3(CF_BLOCK), 0, a.s,
+                           a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, chunks, a.mode, a.out, a.hit_miss,
+                           a.status, a.hashed, a.T, a.offsets_out, a.lengths);
+    else
+        hipLaunchKernelGGL((bag_forward_cached_tables_kernel<LPR, CPL, UNROLL, false>), grid, dim3(CF_BLOCK), 0, a.s,
+                           a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, chunks, a.mode, a.out, a.hit_miss,
+                           a.status, a.hashed, a.T, a.offsets_out, a.lengths);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
@@ -397,16 +380,12 @@ int launch_cached_tables(const CachedTablesArgs &a, bool bf16)
 template <int LPR, int BITS>
 int launch_cached_tables_quant(const CachedTablesArgs &a)
 {
-    const int32_t split = emb_bag_split(LPR, a.T * a.B, a.nnz);
-    const int64_t groups = Q_BLOCK / LPR >> split;
-    const int64_t per_table = (a.B + groups - 1) / groups;
+    constexpr int GROUPS = Q_BLOCK / LPR;
+    const int64_t per_table = (a.B + GROUPS - 1) / GROUPS;
     if (per_table * a.T > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
-    with_split<LPR>(split, [&](auto shared) {
-        hipLaunchKernelGGL((bag_forward_cached_tables_quant_kernel<LPR, BITS, 8, decltype(shared)::value>),
-                           dim3((unsigned)(per_table * a.T)), dim3(Q_BLOCK), 0, a.s, a.tables, a.B, (uint32_t)per_table, a.nnz,
-                           a.ids, a.offsets, a.D, a.row_bytes, a.mode, a.out, a.hit_miss, a.status, a.hashed, a.T, a.offsets_out,
-                           a.lengths, split);
-    });
+    hipLaunchKernelGGL((bag_forward_cached_tables_quant_kernel<LPR, BITS, 8>), dim3((unsigned)(per_table * a.T)),
+                       dim3(Q_BLOCK), 0, a.s, a.tables, a.B, (uint32_t)per_table, a.nnz, a.ids, a.offsets, a.D,
+                       a.row_bytes, a.mode, a.out, a.hit_miss, a.status, a.hashed, a.T, a.offsets_out, a.lengths);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }

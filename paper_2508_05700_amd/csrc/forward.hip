@@ -38,7 +38,7 @@ struct TableSource {
 // offsets to offsets_out.  lengths != NULL: from the lengths (emb_bounds_from_lengths); else `offsets` holds the
 // sums of the bag lengths within tiles of EMB_OFFSETS_TILE lengths (emb_offsets_tile_sums) and the prefix sums of
 // the tile totals are taken inside the kernel (emb_two_level_bounds, at most FWD_BLOCK tiles).
-template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM, bool HASHED, bool MAKE_OFFSETS, bool SHARED>
+template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM, bool HASHED, bool MAKE_OFFSETS>
 __global__ __launch_bounds__(FWD_BLOCK) void bag_forward_kernel(const emb_table *__restrict__ tables, int32_t T,
                                                                 int64_t B, uint32_t blocks_per_table, int64_t nnz,
                                                                 const int64_t *__restrict__ rows,
@@ -46,20 +46,18 @@ __global__ __launch_bounds__(FWD_BLOCK) void bag_forward_kernel(const emb_table 
                                                                 int32_t chunks_per_row, int32_t mode,
                                                                 float *__restrict__ out, int64_t *__restrict__ rows_out,
                                                                 uint32_t *status, int64_t *__restrict__ offsets_out,
-                                                                const int32_t *__restrict__ lengths, int32_t split)
+                                                                const int32_t *__restrict__ lengths)
 {
-    if (!SHARED) split = 0;
-    constexpr int GROUPS = FWD_BLOCK / LPR;              // bags of the workgroup at most
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = FWD_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = FWD_BLOCK / LPR;
     __shared__ int64_t tile_prefix[MAKE_OFFSETS ? FWD_BLOCK + 1 : 1];
     __shared__ int64_t wave_sums[2 * FWD_BLOCK / EMB_WAVE];
     const uint32_t lb = emb_xcd_block(blockIdx.x, gridDim.x);
     const uint32_t t_raw = lb / blocks_per_table;
     const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
     const int t = tail ? T - 1 : (int)t_raw;
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * groups;
-    const int64_t b = b0 + (threadIdx.x >> lane_bits);
+    const int l = threadIdx.x % LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
     const emb_table tb = tables[t];
     constexpr int F = ChunkAcc<BF16>::FLOATS;
     const int64_t bag = (int64_t)t * B + b;
@@ -68,8 +66,8 @@ __global__ __launch_bounds__(FWD_BLOCK) void bag_forward_kernel(const emb_table 
     if (MAKE_OFFSETS) {
         if (lengths) {   // uniform
             const int64_t left = B - b0;
-            emb_bounds_from_lengths<FWD_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < groups ? (int)left : groups,
-                                                       (threadIdx.x >> lane_bits), tile_prefix, wave_sums, status, s, e);
+            emb_bounds_from_lengths<FWD_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < GROUPS ? (int)left : GROUPS,
+                                                       threadIdx.x / LPR, tile_prefix, wave_sums, status, s, e);
         } else {
             emb_two_level_bounds<FWD_BLOCK>(offsets, (int64_t)T * B, live, bag, tile_prefix, wave_sums, s, e);
         }
@@ -85,11 +83,11 @@ __global__ __launch_bounds__(FWD_BLOCK) void bag_forward_kernel(const emb_table 
     if (HASHED) {
         HashedTableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt, tb.mod_magic,
                               (int64_t)chunks_per_row * 16, rows_out};
-        gather_pool_split<LPR, CPL, UNROLL, BF16, STREAM>(split, src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row, status);
+        gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM>(src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row, status);
     } else {
         TableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, (int64_t)chunks_per_row * 16,
                         status};
-        gather_pool_split<LPR, CPL, UNROLL, BF16, STREAM>(split, src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row, status);
+        gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM>(src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row, status);
     }
 }
 
@@ -107,13 +105,13 @@ struct ForwardArgs {
     hipStream_t s;
 };
 
-template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM, bool SHARED>
-void launch_forward_variant(dim3 grid, uint32_t per_table, int32_t split, const ForwardArgs &a)
+template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM>
+void launch_forward_variant(dim3 grid, uint32_t per_table, const ForwardArgs &a)
 {
 #define EMB_FK(HASHED, MAKE)                                                                                          \
-    hipLaunchKernelGGL((bag_forward_kernel<LPR, CPL, UNROLL, BF16, STREAM, HASHED, MAKE, SHARED>), grid, dim3(FWD_BLOCK), 0, a.s, \
+    hipLaunchKernelGGL((bag_forward_kernel<LPR, CPL, UNROLL, BF16, STREAM, HASHED, MAKE>), grid, dim3(FWD_BLOCK), 0, a.s, \
                        a.tables, a.T, a.B, per_table, a.nnz, a.rows, a.offsets, a.chunks, a.mode, a.out, a.rows_out,  \
-                       a.status, a.offsets_out, a.lengths, split)
+                       a.status, a.offsets_out, a.lengths)
     if (a.hashed) {
         if (a.offsets_out) EMB_FK(true, true); else EMB_FK(true, false);
     } else {
@@ -125,14 +123,12 @@ void launch_forward_variant(dim3 grid, uint32_t per_table, int32_t split, const 
 template <int LPR, int CPL, int UNROLL>
 int launch_forward(bool bf16, const ForwardArgs &a)
 {
-    const int32_t split = emb_bag_split(LPR, a.T * a.B, a.nnz);
-    const int64_t groups = FWD_BLOCK / LPR >> split;
-    const int64_t per_table = (a.B + groups - 1) / groups;
+    constexpr int GROUPS = FWD_BLOCK / LPR;
+    const int64_t per_table = (a.B + GROUPS - 1) / GROUPS;
     const int64_t blocks = emb_round_up_xcds(per_table * a.T);
     if (blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
-#define EMB_FV(BF, ST) \
-    with_split<LPR>(split, [&](auto shared) { launch_forward_variant<LPR, CPL, UNROLL, BF, ST, decltype(shared)::value>(grid, (uint32_t)per_table, split, a); })
+#define EMB_FV(BF, ST) launch_forward_variant<LPR, CPL, UNROLL, BF, ST>(grid, (uint32_t)per_table, a)
     if (bf16) {
         if (a.stream) EMB_FV(true, true); else EMB_FV(true, false);
     } else {

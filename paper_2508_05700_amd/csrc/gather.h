@@ -261,39 +261,6 @@ static inline void emb_row_split(int chunks, int &lpr, int &cpl)
     while (cpl < need) cpl <<= 1;
 }
 
-// How many lane groups of LPR lanes share a bag: 1, 2, 4 or 8, returned as its logarithm; at most a wavefront together.
-// They take its rows in turn and their sums are added up at the end.  A group by itself walks its bag eight rows per trip to
-// memory, and a wavefront waits for the longest of its bags: few bags leave the chip to those chains, and with many the
-// lanes of the shorter bags idle.
-// Two lines, whole calls in us of lookups from raw IDs and lengths over eight tables, groups 1 / 2 / 4 / 8:
-//  - up to four wavefronts a SIMD in all, as long as a group keeps four rows (six of 128 bytes, twelve of 256 and more,
-//    of which a wavefront has fewer bags to wait for).  40 000 lookups of 64-byte rows, bags of 20
-//    7.2 / 6.6 / 6.5 / 6.5, of 60 11.5 / 7.5 / 6.4 / 6.5; INT4 rows of 64 values 11.9 / 7.5 / 6.6 / 6.6 and
-//    21.2 / 12.2 / 8.2 / 6.7; 256-byte rows, 60 7.4 / 6.4; 130 000 of 64 bytes, bags of 8 9.4 / 9.3 / 9.7 / 11.0;
-//  - else by the length of the bags, since a group costs a wavefront's start and its share of the sum: 1.3e6 lookups, 32-byte
-//    rows, bags of 8 19.8 / 20.9 / 23.3, 12 21.1 / 19.9 / 19.7, 32 26.1 / 19.9 / 17.7; 64-byte rows, 12 20.7 / 21.2, 20
-//    20.5 / 19.6 / 20.2, 50 21.5 / 20.6 / 19.0; 128-byte rows, 20 20.8 / 21.5, 32 20.3 / 20.0 / 21.8, 60 20.9 / 20.5 / 19.3;
-//    256 bytes, 20 31.3 / 33.1, 32 31.2 / 30.4 / 33.0, 60 31.9 / 30.0 / 29.5; 512 bytes, 32 59.0 / 59.3, 60 57.1 / 56.0.
-// Every lookup of a batch goes by this rule, so that those which promise the same bits have them (the one over tables of
-// different width does not: its workgroups are numbered before the batch is known, emb_table_shapes_init).
-static inline int32_t emb_bag_split(int lpr, int64_t n_bags, int64_t nnz)
-{
-    constexpr int64_t FEW = (int64_t)4 * 1024 * EMB_WAVE;   // lanes of four wavefronts a SIMD
-    constexpr int32_t LEAST[6] = {4, 4, 4, 6, 12, 12};      // rows of a group then, by the lanes of a row: 1, 2, 4, ... 32
-    // the mean length from which 2, 4, 8 groups share a bag in a batch that fills the chip, likewise
-    constexpr int32_t LONG[3][6] = {{10, 12, 18, 34, 32, 48}, {24, 30, 44, 60, 60, 0}, {56, 60, 0, 0, 0, 0}};
-    int32_t split = 0;
-    for (int i = 0, row = __builtin_ctz((unsigned)lpr); i < 3 && row < 6; ++i) {
-        const int32_t next = 2 << split;
-        if (lpr * next > EMB_WAVE) break;
-        const bool few = n_bags * lpr * next <= FEW && nnz >= n_bags * next * LEAST[row];
-        const bool fills = LONG[i][row] != 0 && nnz >= n_bags * LONG[i][row];
-        if (!few && !fills) break;
-        ++split;
-    }
-    return split;
-}
-
 // ---------------------------------------------------------------------------
 // The gather-pool loop shared by the plain and the cached pooled lookup.
 //
@@ -305,9 +272,8 @@ static inline int32_t emb_bag_split(int lpr, int64_t n_bags, int64_t nnz)
 // coalesced load; the lane that fetched an index resolves it to the address of
 // the row (Source::resolve: bounds check, and for the cached table the cache
 // probe) and the address is handed round (group_bcast), so every index is
-// read and resolved exactly once.  A lane only ever adds the chunks it owns; a
-// cross-lane sum is needed only where SPLIT groups share a bag (emb_bag_split): row
-// k of the bag is group k mod SPLIT's, and the groups' sums are added by a butterfly.
+// read and resolved exactly once.  No cross-lane reduction is needed: a lane
+// only ever adds the chunks it owns.
 //
 // What bounds it: on narrow rows the instructions around a row load, on wide ones
 // the rate of scattered lines.  So a row costs two moves, one address add, the load
@@ -377,57 +343,9 @@ __device__ __forceinline__ void gather_batch(int64_t left, const Rows &do_rows)
     }
 }
 
-// A kernel for batches whose bags are not shared knows so at compile time: run(std::true_type) or (std::false_type)
-// launches the one or the other (with one kernel for both, calls of 6 to 9 us took 0.1 to 0.3 us longer).
-template <int LPR, typename Run>
-static inline void with_split(int32_t split, const Run &run)
-{
-    if constexpr (LPR < EMB_WAVE) {
-        if (split != 0) return run(std::true_type());
-    }
-    run(std::false_type());
-}
-
-// The bits of a thread's number that are its place among the lanes of its bag.
-template <int LPR>
-__device__ __forceinline__ int bag_lane_bits(int32_t split)
-{
-    return __builtin_ctz((unsigned)LPR) + split;
-}
-
-// split: what emb_bag_split returns; at most MOST groups (a constant of the caller's rows).
-template <int MOST, typename Do>
-__device__ __forceinline__ void split_dispatch(int32_t split, const Do &run)
-{
-    if constexpr (MOST >= 8) {
-        if (split == 3) return run(std::integral_constant<int, 8>());
-    }
-    if constexpr (MOST >= 4) {
-        if (split == 2) return run(std::integral_constant<int, 4>());
-    }
-    if constexpr (MOST >= 2) {
-        if (split == 1) return run(std::integral_constant<int, 2>());
-    }
-    run(std::integral_constant<int, 1>());
-}
-
-// Adds up the sums of the SPLIT parts of a bag, LPR lanes each, at most a wavefront; every part gets the same bits.
-template <int LPR, int SPLIT, typename Each>
-__device__ __forceinline__ void split_sum(const Each &each)
-{
-    static_assert(SPLIT == 1 || LPR * SPLIT <= EMB_WAVE, "a bag is one wavefront's");
-    auto by = [&](auto d) {
-        each([](float v) { return v + __uint_as_float((uint32_t)__shfl_xor((int)__float_as_uint(v), decltype(d)::value, EMB_WAVE)); });
-    };
-    if constexpr (SPLIT >= 2) by(std::integral_constant<int, LPR>());
-    if constexpr (SPLIT >= 4) by(std::integral_constant<int, 2 * LPR>());
-    if constexpr (SPLIT >= 8) by(std::integral_constant<int, 4 * LPR>());
-    if constexpr (SPLIT >= 16) by(std::integral_constant<int, 8 * LPR>());
-}
-
 // The bag is given by its bounds: lookups [s, e) of `rows` (ignored unless live).
-template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM = false, int SPLIT = 1, typename Source>
-__device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_t s, int64_t e, int lane, int64_t nnz,
+template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM = false, typename Source>
+__device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_t s, int64_t e, int l, int64_t nnz,
                                                   const int64_t *__restrict__ rows, int32_t chunks_per_row,
                                                   int32_t mode, float *__restrict__ out_row, uint32_t *status)
 {
@@ -435,12 +353,11 @@ __device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_
     constexpr int IPL = (UNROLL > LPR) ? UNROLL / LPR : 1;  // indices fetched per lane per batch
     constexpr int IB = IPL * LPR;                           // indices per batch
     static_assert(IB % UNROLL == 0, "index batch must be whole unroll groups");
-    const int l = lane % LPR, part = lane / LPR;   // lane of the row, row of the SPLIT
 
     if (!live) {
         s = e = 0;
     } else if (s < 0 || e < s || e > nnz) {
-        if (lane == 0) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
+        if (l == 0) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
         s = e = 0;
     }
 
@@ -457,23 +374,23 @@ __device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_
     int64_t next[IPL];
 #pragma unroll
     for (int m = 0; m < IPL; ++m) {
-        const int64_t j = s + (m * LPR + l) * SPLIT + part;
+        const int64_t j = s + m * LPR + l;
         next[m] = j < e ? rows[j] : 0;
     }
-    for (int64_t base = s; base < e; base += IB * SPLIT) {
+    for (int64_t base = s; base < e; base += IB) {
         uint64_t mine[IPL];
 #pragma unroll
         for (int m = 0; m < IPL; ++m) {
-            const int64_t j = base + (m * LPR + l) * SPLIT + part;
+            const int64_t j = base + m * LPR + l;
             mine[m] = 0ull;
             if (j < e) mine[m] = src.resolve(next[m], j);
             if (mine[m] == 0ull) mine[m] = zero_row;
-            if (j + IB * SPLIT < e) next[m] = rows[j + IB * SPLIT];
+            if (j + IB < e) next[m] = rows[j + IB];
         }
         // (lane numbers of a group of up to 16 must be constants)
 #pragma unroll(LPR <= 16 ? IB / UNROLL : 1)
         for (int u = 0; u < IB / UNROLL; ++u) {
-            const int64_t left = (int64_t)((uint64_t)(e - base + (SPLIT - 1 - part)) / SPLIT) - u * UNROLL;
+            const int64_t left = e - base - u * UNROLL;
             if (left > 0)   // the group's lanes agree
                 gather_batch<UNROLL>(left, [&](auto n) {
                     gather_rows<LPR, CPL, decltype(n)::value, BF16, STREAM>(acc, mine, u * UNROLL, off);
@@ -481,13 +398,7 @@ __device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_
         }
     }
 
-    split_sum<LPR, SPLIT>([&](auto add) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c)
-#pragma unroll
-            for (int i = 0; i < ChunkAcc<BF16>::FLOATS; ++i) acc[c].a[i] = add(acc[c].a[i]);
-    });
-    if (!live || part != 0) return;
+    if (!live) return;
     const int64_t len = e - s;
     const bool mean = (mode == EMB_POOL_MEAN) && len > 0;
     const float flen = (float)len;
@@ -507,23 +418,10 @@ __device__ __forceinline__ void gather_pool_range(Source &src, bool live, int64_
     }
 }
 
-// The same with the bag's rows dealt to `split` lane groups (emb_bag_split; uniform over the launch).  lane: the thread's
-// number among the bag's lanes.
-template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM = false, typename Source>
-__device__ __forceinline__ void gather_pool_split(int32_t split, Source &src, bool live, int64_t s, int64_t e, int lane, int64_t nnz,
-                                                  const int64_t *__restrict__ rows, int32_t chunks_per_row, int32_t mode,
-                                                  float *__restrict__ out_row, uint32_t *status)
-{
-    split_dispatch<(CPL == 1 ? EMB_WAVE / LPR : 1)>(split, [&](auto n) {
-        gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM, decltype(n)::value>(src, live, s, e, lane, nnz, rows, chunks_per_row, mode,
-                                                                              out_row, status);
-    });
-}
-
 // The bag is number `bag` of `offsets`.  tile_prefix: the offsets are sums within tiles and these are the
 // tiles' prefix sums (emb_bag_bounds).
 template <int LPR, int CPL, int UNROLL, bool BF16, bool STREAM = false, typename Source>
-__device__ __forceinline__ void gather_pool_bag(int32_t split, Source &src, bool live, int64_t bag, int lane, int64_t nnz,
+__device__ __forceinline__ void gather_pool_bag(Source &src, bool live, int64_t bag, int l, int64_t nnz,
                                                 const int64_t *__restrict__ rows,
                                                 const int64_t *__restrict__ offsets, int32_t chunks_per_row,
                                                 int32_t mode, float *__restrict__ out_row, uint32_t *status,
@@ -531,6 +429,6 @@ __device__ __forceinline__ void gather_pool_bag(int32_t split, Source &src, bool
 {
     int64_t s = 0, e = 0;
     if (live) emb_bag_bounds(offsets, tile_prefix, bag, s, e);
-    gather_pool_split<LPR, CPL, UNROLL, BF16, STREAM>(split, src, live, s, e, lane, nnz, rows, chunks_per_row, mode, out_row,
+    gather_pool_range<LPR, CPL, UNROLL, BF16, STREAM>(src, live, s, e, l, nnz, rows, chunks_per_row, mode, out_row,
                                                       status);
 }

@@ -83,22 +83,21 @@ __device__ __forceinline__ void gather_dequant_rows(float (&acc)[Q_ELEMS], const
 // (Source::resolve, 0 = skip: a row of zeros), addresses are handed round, UNROLL
 // rows are requested before the first add.  `bag` indexes offsets and out.
 // The bag is given by its bounds: lookups [s, e) of `rows` (ignored unless live).
-template <int LPR, int BITS, int UNROLL, int SPLIT = 1, typename Source>
-__device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live, int64_t bag, int64_t s, int64_t e, int lane,
+template <int LPR, int BITS, int UNROLL, typename Source>
+__device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live, int64_t bag, int64_t s, int64_t e, int l,
                                                           int64_t nnz, const int64_t *__restrict__ rows, int32_t D,
                                                           int32_t mode, float *__restrict__ out, uint32_t *status)
 {
     constexpr int IPL = (UNROLL > LPR) ? UNROLL / LPR : 1;  // indices fetched per lane per batch
     constexpr int IB = IPL * LPR;                           // indices per batch
     static_assert(IB % UNROLL == 0, "index batch must be whole unroll groups");
-    const int l = lane % LPR, part = lane / LPR;   // lane of the row, row of the SPLIT
     const bool mine_elems = l * Q_ELEMS < D;         // lanes past the row (D/16 not a power of two) read its first codes
     const uint32_t code_off = 8u + (mine_elems ? (uint32_t)l * (BITS == 8 ? 16u : 8u) : 0u);
 
     if (!live) {
         s = e = 0;
     } else if (s < 0 || e < s || e > nnz) {
-        if (lane == 0) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
+        if (l == 0) emb_flag(status, EMB_STATUS_BAD_OFFSETS);
         s = e = 0;
     }
     float acc[Q_ELEMS];
@@ -109,22 +108,22 @@ __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live
     int64_t next[IPL];
 #pragma unroll
     for (int m = 0; m < IPL; ++m) {
-        const int64_t j = s + (m * LPR + l) * SPLIT + part;
+        const int64_t j = s + m * LPR + l;
         next[m] = j < e ? rows[j] : 0;
     }
-    for (int64_t base = s; base < e; base += IB * SPLIT) {
+    for (int64_t base = s; base < e; base += IB) {
         uint64_t mine[IPL];
 #pragma unroll
         for (int m = 0; m < IPL; ++m) {
-            const int64_t j = base + (m * LPR + l) * SPLIT + part;
+            const int64_t j = base + m * LPR + l;
             mine[m] = 0ull;
             if (j < e) mine[m] = src.resolve(next[m], j);
             if (mine[m] == 0ull) mine[m] = zero_row;
-            if (j + IB * SPLIT < e) next[m] = rows[j + IB * SPLIT];
+            if (j + IB < e) next[m] = rows[j + IB];
         }
 #pragma unroll(LPR <= 16 ? IB / UNROLL : 1)
         for (int u = 0; u < IB / UNROLL; ++u) {
-            const int64_t left = (int64_t)((uint64_t)(e - base + (SPLIT - 1 - part)) / SPLIT) - u * UNROLL;
+            const int64_t left = e - base - u * UNROLL;
             if (left > 0)
                 gather_batch<UNROLL>(left, [&](auto n) {
                     gather_dequant_rows<LPR, BITS, decltype(n)::value>(acc, mine, u * UNROLL, code_off);
@@ -132,11 +131,7 @@ __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live
         }
     }
 
-    split_sum<LPR, SPLIT>([&](auto add) {
-#pragma unroll
-        for (int i = 0; i < Q_ELEMS; ++i) acc[i] = add(acc[i]);
-    });
-    if (!live || !mine_elems || part != 0) return;
+    if (!live || !mine_elems) return;
     const int64_t len = e - s;
     const bool mean = (mode == EMB_POOL_MEAN) && len > 0;
     const float flen = (float)len;
@@ -149,20 +144,9 @@ __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live
     }
 }
 
-// The same with the bag's rows dealt to `split` lane groups (gather_pool_split).
-template <int LPR, int BITS, int UNROLL, typename Source>
-__device__ __forceinline__ void gather_dequant_pool_split(int32_t split, Source &src, bool live, int64_t bag, int64_t s, int64_t e, int lane,
-                                                          int64_t nnz, const int64_t *__restrict__ rows, int32_t D,
-                                                          int32_t mode, float *__restrict__ out, uint32_t *status)
-{
-    split_dispatch<EMB_WAVE / LPR>(split, [&](auto n) {
-        gather_dequant_pool_range<LPR, BITS, UNROLL, decltype(n)::value>(src, live, bag, s, e, lane, nnz, rows, D, mode, out, status);
-    });
-}
-
 // The bag is number `bag` of `offsets`.
 template <int LPR, int BITS, int UNROLL, typename Source>
-__device__ __forceinline__ void gather_dequant_pool_bag(int32_t split, Source &src, bool live, int64_t bag, int lane, int64_t nnz,
+__device__ __forceinline__ void gather_dequant_pool_bag(Source &src, bool live, int64_t bag, int l, int64_t nnz,
                                                         const int64_t *__restrict__ rows,
                                                         const int64_t *__restrict__ offsets, int32_t D, int32_t mode,
                                                         float *__restrict__ out, uint32_t *status)
@@ -172,7 +156,7 @@ __device__ __forceinline__ void gather_dequant_pool_bag(int32_t split, Source &s
         s = offsets[bag];
         e = offsets[bag + 1];
     }
-    gather_dequant_pool_split<LPR, BITS, UNROLL>(split, src, live, bag, s, e, lane, nnz, rows, D, mode, out, status);
+    gather_dequant_pool_range<LPR, BITS, UNROLL>(src, live, bag, s, e, l, nnz, rows, D, mode, out, status);
 }
 
 // Lanes per row: D/16 rounded up to a power of two.

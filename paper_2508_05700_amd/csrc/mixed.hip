@@ -7,7 +7,7 @@
 //
 // A workgroup serves bags of one table; emb_table_shapes_init numbers the
 // workgroups (first_block) so that a table whose rows need fewer lanes gets
-// fewer of them.  The gather loop is gather_pool_range (gather.h).
+// fewer of them.  The gather loop is gather_pool_bag (gather.h).
 //
 // Every die works on one stretch of those numbers (its L2 then holds few tables' hot rows), and the stretches
 // are cut so that the dies have the same amount of work (DieShares).
@@ -50,10 +50,8 @@ __device__ __forceinline__ void mixed_bags(const emb_table &tb, const emb_table_
     const int64_t b = (int64_t)local_block * GROUPS + threadIdx.x / LPR;
     const int32_t chunks = sh.D * (BF16 ? 2 : 4) / 16;
     PlainSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, (int64_t)chunks * 16, status};
-    const int64_t bag = (int64_t)t * B + b;
-    const bool live = b < B;
-    gather_pool_range<LPR, 1, 8, BF16>(src, live, live ? offsets[bag] : 0, live ? offsets[bag + 1] : 0, l, nnz, rows, chunks, mode,
-                                       out + sh.out_offset + b * sh.out_stride, status);
+    gather_pool_bag<LPR, 1, 8, BF16>(src, b < B, (int64_t)t * B + b, l, nnz, rows, offsets, chunks, mode,
+                                     out + sh.out_offset + b * sh.out_stride, status);
 }
 
 __global__ __launch_bounds__(MX_BLOCK) void bag_forward_mixed_kernel(const emb_table *__restrict__ tables,

@@ -130,7 +130,7 @@ struct HashedQuantTableSource {
 };
 
 // MAKE_OFFSETS: as in bag_forward_kernel (forward.hip).
-template <int LPR, int BITS, int UNROLL, bool HASHED, bool MAKE_OFFSETS, bool SHARED>
+template <int LPR, int BITS, int UNROLL, bool HASHED, bool MAKE_OFFSETS>
 __global__ __launch_bounds__(Q_BLOCK) void bag_forward_quant_kernel(const emb_table *__restrict__ tables, int32_t T,
                                                                     int64_t B, uint32_t blocks_per_table, int64_t nnz,
                                                                     const int64_t *__restrict__ rows,
@@ -139,20 +139,18 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_quant_kernel(const emb_ta
                                                                     float *__restrict__ out, uint32_t *status,
                                                                     int64_t *__restrict__ rows_out,
                                                                     int64_t *__restrict__ offsets_out,
-                                                                    const int32_t *__restrict__ lengths, int32_t split)
+                                                                    const int32_t *__restrict__ lengths)
 {
-    if (!SHARED) split = 0;
-    constexpr int GROUPS = Q_BLOCK / LPR;                // bags of the workgroup at most
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = Q_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = Q_BLOCK / LPR;
     __shared__ int64_t tile_prefix[MAKE_OFFSETS ? Q_BLOCK + 1 : 1];
     __shared__ int64_t wave_sums[2 * Q_BLOCK / EMB_WAVE];
     const uint32_t lb = emb_xcd_block(blockIdx.x, gridDim.x);
     const uint32_t t_raw = lb / blocks_per_table;
     const bool tail = t_raw >= (uint32_t)T;          // the grid is rounded up to whole dies
     const int t = tail ? T - 1 : (int)t_raw;
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * groups;
-    const int64_t b = b0 + (threadIdx.x >> lane_bits);
+    const int l = threadIdx.x % LPR;
+    const int64_t b0 = tail ? B : (int64_t)(lb % blocks_per_table) * GROUPS;
+    const int64_t b = b0 + threadIdx.x / LPR;
     const emb_table tb = tables[t];
     const int64_t bag = (int64_t)t * B + b;
     const bool live = b < B;
@@ -160,8 +158,8 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_quant_kernel(const emb_ta
     if (MAKE_OFFSETS) {
         if (lengths) {   // uniform
             const int64_t left = B - b0;
-            emb_bounds_from_lengths<Q_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < groups ? (int)left : groups,
-                                                     (threadIdx.x >> lane_bits), tile_prefix, wave_sums, status, s, e);
+            emb_bounds_from_lengths<Q_BLOCK, GROUPS>(lengths, (int64_t)t * B + b0, left < GROUPS ? (int)left : GROUPS,
+                                                     threadIdx.x / LPR, tile_prefix, wave_sums, status, s, e);
         } else {
             emb_two_level_bounds<Q_BLOCK>(offsets, (int64_t)T * B, live, bag, tile_prefix, wave_sums, s, e);
         }
@@ -176,10 +174,10 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_quant_kernel(const emb_ta
     if (HASHED) {
         HashedQuantTableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, tb.salt,
                                    tb.mod_magic, row_bytes, rows_out};
-        gather_dequant_pool_split<LPR, BITS, UNROLL>(split, src, live, bag, s, e, l, nnz, rows, D, mode, out, status);
+        gather_dequant_pool_range<LPR, BITS, UNROLL>(src, live, bag, s, e, l, nnz, rows, D, mode, out, status);
     } else {
         QuantTableSource src{reinterpret_cast<const char *>(tb.weights), (uint64_t)tb.num_rows, row_bytes, status};
-        gather_dequant_pool_split<LPR, BITS, UNROLL>(split, src, live, bag, s, e, l, nnz, rows, D, mode, out, status);
+        gather_dequant_pool_range<LPR, BITS, UNROLL>(src, live, bag, s, e, l, nnz, rows, D, mode, out, status);
     }
 }
 
@@ -188,18 +186,15 @@ int launch_quant_forward(hipStream_t s, const emb_table *tables, int32_t T, int6
                          const int64_t *offsets, int32_t D, int64_t row_bytes, int32_t mode, float *out,
                          uint32_t *status, bool hashed, int64_t *rows_out, int64_t *offsets_out, const int32_t *lengths)
 {
+    constexpr int GROUPS = Q_BLOCK / LPR;
     constexpr int UNROLL = 8;
-    const int32_t split = emb_bag_split(LPR, T * B, nnz);
-    const int64_t groups = Q_BLOCK / LPR >> split;
-    const int64_t per_table = (B + groups - 1) / groups;
+    const int64_t per_table = (B + GROUPS - 1) / GROUPS;
     const int64_t blocks = emb_round_up_xcds(per_table * T);
     if (blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
 #define EMB_QK(HASHED, MAKE)                                                                                         \
-    with_split<LPR>(split, [&](auto shared) {                                                                        \
-        hipLaunchKernelGGL((bag_forward_quant_kernel<LPR, BITS, UNROLL, HASHED, MAKE, decltype(shared)::value>),     \
-                           dim3((unsigned)blocks), dim3(Q_BLOCK), 0, s, tables, T, B, (uint32_t)per_table, nnz, rows, \
-                           offsets, D, row_bytes, mode, out, status, rows_out, offsets_out, lengths, split);         \
-    })
+    hipLaunchKernelGGL((bag_forward_quant_kernel<LPR, BITS, UNROLL, HASHED, MAKE>), dim3((unsigned)blocks), dim3(Q_BLOCK), \
+                       0, s, tables, T, B, (uint32_t)per_table, nnz, rows, offsets, D, row_bytes, mode, out, status, \
+                       rows_out, offsets_out, lengths)
     if (hashed) {
         if (offsets_out) EMB_QK(true, true); else EMB_QK(true, false);
     } else {

@@ -172,14 +172,13 @@ __global__ __launch_bounds__(SF_BLOCK) void bag_forward_staged_kernel(StagedSour
                                                                       const int64_t *__restrict__ offsets,
                                                                       int32_t chunks_per_row, int32_t mode,
                                                                       float *__restrict__ out,
-                                                                      unsigned long long *hit_miss, uint32_t *status,
-                                                                      int32_t split)
+                                                                      unsigned long long *hit_miss, uint32_t *status)
 {
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = SF_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
+    constexpr int GROUPS = SF_BLOCK / LPR;
     constexpr int F = ChunkAcc<BF16>::FLOATS;
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b = (int64_t)blockIdx.x * groups + (threadIdx.x >> lane_bits);
-    gather_pool_bag<LPR, CPL, UNROLL, BF16>(split, src, b < B, b, l, nnz, loc, offsets, chunks_per_row, mode,
+    const int l = threadIdx.x % LPR;
+    const int64_t b = (int64_t)blockIdx.x * GROUPS + threadIdx.x / LPR;
+    gather_pool_bag<LPR, CPL, UNROLL, BF16>(src, b < B, b, l, nnz, loc, offsets, chunks_per_row, mode,
                                             out + b * ((int64_t)chunks_per_row * F), status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
@@ -191,28 +190,27 @@ __global__ __launch_bounds__(Q_BLOCK) void bag_forward_staged_quant_kernel(Stage
                                                                            int32_t D, int32_t mode,
                                                                            float *__restrict__ out,
                                                                            unsigned long long *hit_miss,
-                                                                           uint32_t *status, int32_t split)
+                                                                           uint32_t *status)
 {
-    const int lane_bits = bag_lane_bits<LPR>(split), groups = Q_BLOCK >> lane_bits;   // of a bag's lanes; bags of the workgroup
-    const int l = threadIdx.x & ((1 << lane_bits) - 1);
-    const int64_t b = (int64_t)blockIdx.x * groups + (threadIdx.x >> lane_bits);
-    gather_dequant_pool_bag<LPR, BITS, UNROLL>(split, src, b < B, b, l, nnz, loc, offsets, D, mode, out, status);
+    constexpr int GROUPS = Q_BLOCK / LPR;
+    const int l = threadIdx.x % LPR;
+    const int64_t b = (int64_t)blockIdx.x * GROUPS + threadIdx.x / LPR;
+    gather_dequant_pool_bag<LPR, BITS, UNROLL>(src, b < B, b, l, nnz, loc, offsets, D, mode, out, status);
     cache_add_hit_miss(src.hits, src.misses, hit_miss);
 }
 
 template <int LPR, int CPL, int UNROLL>
 int launch_staged(const StagedArgs &a, bool bf16)
 {
-    const int32_t split = emb_bag_split(LPR, a.B, a.nnz);
-    const int64_t groups = SF_BLOCK / LPR >> split;
-    const dim3 grid((unsigned)((a.B + groups - 1) / groups));
+    constexpr int GROUPS = SF_BLOCK / LPR;
+    const dim3 grid((unsigned)((a.B + GROUPS - 1) / GROUPS));
     const int32_t chunks = (int32_t)(a.src.row_bytes / 16);
     if (bf16)
         hipLaunchKernelGGL((bag_forward_staged_kernel<LPR, CPL, UNROLL, true>), grid, dim3(SF_BLOCK), 0, a.s, a.src, a.B,
-                           a.nnz, a.loc, a.offsets, chunks, a.mode, a.out, a.hit_miss, a.status, split);
+                           a.nnz, a.loc, a.offsets, chunks, a.mode, a.out, a.hit_miss, a.status);
     else
         hipLaunchKernelGGL((bag_forward_staged_kernel<LPR, CPL, UNROLL, false>), grid, dim3(SF_BLOCK), 0, a.s, a.src, a.B,
-                           a.nnz, a.loc, a.offsets, chunks, a.mode, a.out, a.hit_miss, a.status, split);
+                           a.nnz, a.loc, a.offsets, chunks, a.mode, a.out, a.hit_miss, a.status);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }
@@ -220,11 +218,10 @@ int launch_staged(const StagedArgs &a, bool bf16)
 template <int LPR, int BITS>
 int launch_staged_quant(const StagedArgs &a)
 {
-    const int32_t split = emb_bag_split(LPR, a.B, a.nnz);
-    const int64_t groups = Q_BLOCK / LPR >> split;
-    hipLaunchKernelGGL((bag_forward_staged_quant_kernel<LPR, BITS, 8>), dim3((unsigned)((a.B + groups - 1) / groups)),
+    constexpr int GROUPS = Q_BLOCK / LPR;
+    hipLaunchKernelGGL((bag_forward_staged_quant_kernel<LPR, BITS, 8>), dim3((unsigned)((a.B + GROUPS - 1) / GROUPS)),
                        dim3(Q_BLOCK), 0, a.s, a.src, a.B, a.nnz, a.loc, a.offsets, a.D, a.mode, a.out, a.hit_miss,
-                       a.status, split);
+                       a.status);
     EMB_RETURN_IF_LAUNCH_FAILED();
     return EMB_OK;
 }

@@ -149,9 +149,9 @@ def test_forward_matches_oracle(D, dtype, mode):
                                      (256, "f32"), (8, "bf16"), (48, "bf16"), (16, "int4"), (48, "int4"), (64, "int4"), (512, "int4"),
                                      (16, "int8"), (80, "int8")])
 @pytest.mark.parametrize("B,mean", [(1, 8), (1, 700), (37, 8), (37, 17), (37, 40), (300, 33), (45_000, 11), (34_000, 19), (9_000, 62)])
-def test_forward_bags_shared_by_lane_groups_add_every_row_once(D, dtype, B, mean):
-    # few bags, and long ones in a batch that fills the chip: rows of a bag go to 2, 4 or 8 lane groups.  Small whole
-    # numbers make every order of the sum exact, so the lookup equals the oracle bit for bit, empty bags included.
+def test_forward_few_or_long_bags_add_every_row_once(D, dtype, B, mean):
+    # few bags, and long ones in a batch that fills the chip.  Small whole numbers make every order of the sum exact, so
+    # the lookup equals the oracle bit for bit, empty bags included.
     if B > 1000 and D not in (4, 8, 16, 32):
         B //= 8
     rng = np.random.default_rng(9000 + D + B + mean)
@@ -2602,6 +2602,46 @@ def test_cached_forward_over_several_tables_in_one_launch(dtype, D):
             torch.cuda.synchronize()
             assert np.array_equal(off2.cpu().numpy(), off) and torch.equal(o2, out) and torch.equal(hm2, hm)
             assert int(status.item()) == st_all
+
+
+@pytest.mark.parametrize("dtype,D,B,means", [
+    ("f32", 16, 300, (4, 40)), ("f32", 64, 4096, (28, 28, 28, 28)),     # tables of unlike lengths; many bags only together
+    ("bf16", 32, 300, (60, 2, 9)), ("int4", 64, 2000, (20, 3, 20)), ("int8", 48, 300, (12, 60))])
+def test_bags_keep_their_bits_whatever_tables_are_looked_up_beside_them(dtype, D, B, means):
+    # A bag's sum is taken in the order of its lookups.  A lookup over several tables, plain or cached, therefore gives the
+    # bits of one lookup per table, however many bags the other tables have and however long these are.
+    rng = np.random.default_rng(7300 + D + B)
+    T, R, salt = len(means), 3000, 5
+    quant = dtype in ("int8", "int4")
+    tabs = []
+    for _ in range(T):
+        x = rng.standard_normal((R, D)).astype(np.float32)
+        tab = oracle.quantize_rows(x, dtype) if quant else (wl.f32_to_bf16_bits(x).reshape(R, D) if dtype == "bf16" else x)
+        tabs.append(H.dev(tab))
+    hot = np.arange(0, R, 7, dtype=np.int64)
+    entries = []
+    for tab in tabs:
+        cache = torch.empty((hot.size, tab.shape[1]), dtype=tab.dtype, device=H.DEV)
+        index = torch.empty(emb.emb_cache_index_bytes(R), dtype=torch.uint8, device=H.DEV)
+        emb.emb_cache_build(int(tab.data_ptr()), R, D, dtype, H.dev(hot), cache, index)
+        entries.append((int(tab.data_ptr()), R, cache, index, hot.size, salt))
+    lengths = np.concatenate([rng.poisson(m, size=B) for m in means]).astype(np.int32)
+    off, _ = oracle.lengths_to_offsets(lengths)
+    rows = rng.integers(0, R, size=int(off[-1])).astype(np.int64)
+    out = torch.empty((T, B, D), dtype=torch.float32, device=H.DEV)
+    emb.emb_bag_forward_cached_tables(emb.CachedTables(entries, D, dtype, device=torch.device(H.DEV)), H.dev(rows), H.dev(off), B,
+                                      "sum", out)
+    torch.cuda.synchronize()
+    plain, _ = H.gpu_forward(emb.TableSet(tabs, D, dtype, device=torch.device(H.DEV)), rows, off, B, "sum")
+    plain = plain.reshape(T, B, D)
+    for t, (ptr, _, cache, index, K, _) in enumerate(entries):
+        r, o = rows[off[t * B]:off[(t + 1) * B]], off[t * B:(t + 1) * B + 1] - off[t * B]
+        one = torch.empty((1, B, D), dtype=torch.float32, device=H.DEV)
+        emb.emb_bag_forward_cached(ptr, R, D, dtype, cache, index, K, H.dev(r), H.dev(o), B, "sum", one)
+        torch.cuda.synchronize()
+        one_plain, _ = H.gpu_forward(emb.TableSet([tabs[t]], D, dtype, device=torch.device(H.DEV)), r, o, B, "sum")
+        assert np.array_equal(out[t].cpu().numpy(), one[0].cpu().numpy()), t
+        assert np.array_equal(plain[t], one_plain.reshape(B, D)) and np.array_equal(plain[t], one[0].cpu().numpy()), t
 
 
 @pytest.mark.parametrize("dtype,D,T,B", [("f32", 16, 3, 100_000), ("int4", 64, 1, 270_000), ("bf16", 32, 2, 2500)])
