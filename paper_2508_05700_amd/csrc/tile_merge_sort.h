@@ -34,14 +34,20 @@ struct MergePart {
 };
 
 // Part `b` of the tables' records cut into SIZE records each, table after table; false: there is none.  Every thread of
-// the workgroup calls this.  range(t, s, e): table t has records [s, e), a partition of [0, nnz) in order.
+// the workgroup calls this and gets the same answer.  range(t, s, e): table t has records [s, e), a partition of [0, nnz)
+// in order, unless `ctrl` (nullable) says that the backward is aborted: then there is no part.  That is read once for the
+// workgroup: the lookup that a tile is sorted beside may abort meanwhile, and wavefronts that each read it for themselves
+// could part before a barrier.
 template <int SIZE, int BLOCK, typename Range>
-__device__ __forceinline__ bool merge_part_in(int32_t T, uint32_t b, const Range &range, MergePart &part)
+__device__ __forceinline__ bool merge_part_in(int32_t T, uint32_t b, const Range &range, MergePart &part, const BwdCtrl *ctrl = nullptr)
 {
     __shared__ uint32_t wave_sums[BLOCK / EMB_WAVE];
     __shared__ MergePart found;
-    __shared__ uint32_t is_there;
-    if (threadIdx.x == 0) is_there = 0;
+    __shared__ uint32_t is_there, aborted;
+    if (threadIdx.x == 0) {
+        is_there = 0;
+        aborted = ctrl ? __hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    }
     uint32_t before = 0;
     for (int32_t t0 = 0; t0 < T; t0 += BLOCK) {
         const int32_t t = t0 + (int32_t)threadIdx.x;
@@ -61,7 +67,7 @@ __device__ __forceinline__ bool merge_part_in(int32_t T, uint32_t b, const Range
     }
     __syncthreads();
     part = found;
-    return is_there;   // uniform
+    return is_there && !aborted;   // uniform
 }
 
 // The same from table_start ([T + 1], a partition unless ctrl->abort is set); there is no part of an aborted backward.
@@ -69,12 +75,10 @@ template <int SIZE, int BLOCK>
 __device__ __forceinline__ bool merge_part_of(const int64_t *__restrict__ table_start, int32_t T, uint32_t b, const BwdCtrl *ctrl,
                                               MergePart &part)
 {
-    const uint32_t abort = ctrl->abort;   // (asked for together with the ranges)
-    const bool there = merge_part_in<SIZE, BLOCK>(T, b, [&](int32_t t, uint32_t &s, uint32_t &e) {
+    return merge_part_in<SIZE, BLOCK>(T, b, [&](int32_t t, uint32_t &s, uint32_t &e) {
         s = (uint32_t)table_start[t];
         e = (uint32_t)table_start[t + 1];
-    }, part);
-    return !abort && there;
+    }, part, ctrl);
 }
 
 constexpr uint32_t MERGE_DIGITS = 1u << MERGE_BITS_MAX;

@@ -1259,6 +1259,48 @@ def test_tiles_sorted_beside_the_training_lookup_give_the_bits_of_records_in_mem
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("per_table,B", [([5000, 0, 7000], 257), ([900], 40), ([40] * 300, 4), ([100_000], 3000)])
+def test_malformed_bags_of_a_small_training_step_leave_tables_and_workspace_sound(per_table, B):
+    # Tables whose records start and end where they should, and bags inside them that do not ascend: lookup workgroups abort
+    # the backward while others of their launch sort the tiles.  Nothing is written, and a well-formed step in the same
+    # workspace afterwards has the bits of one in a fresh workspace.
+    T, D, R = len(per_table), 16, 3000
+    rng = np.random.default_rng(6400 + B + T)
+    lengths = np.concatenate([np.bincount(np.sort(rng.integers(0, B, size=n)), minlength=B) for n in per_table]).astype(np.int32)
+    off, _ = oracle.lengths_to_offsets(lengths)
+    nnz = int(off[-1])
+    raw = H.dev(rng.integers(0, 1 << 64, size=nnz, dtype=np.uint64))
+    salts = list(range(T))
+    table = H.dev((rng.standard_normal((R, D)) * 0.01).astype(np.float32))
+    dout = H.dev(rng.standard_normal((T, B, D)).astype(np.float32))
+    out = torch.empty((T, B, D), dtype=torch.float32, device=H.DEV)
+
+    def fresh():
+        w, acc = [table.clone() for _ in range(T)], [torch.zeros(R, dtype=torch.float32, device=H.DEV) for _ in range(T)]
+        ts = emb.TableSet(w, D, "f32", accum=acc, salts=salts, device=torch.device(H.DEV))
+        return ts, w, acc, torch.full((emb.emb_bag_backward_workspace_bytes(T, B, nnz, ts.total_rows, D, "f32"),), 0xA5,
+                                      dtype=torch.uint8, device=H.DEV)
+
+    def step(ts, ws, offsets):
+        nu, st = torch.full((1,), -1, dtype=torch.int64, device=H.DEV), torch.zeros(1, dtype=torch.int32, device=H.DEV)
+        emb.emb_bag_forward_train(ts, raw, H.dev(offsets), B, "mean", out, ws, None, nu, st)
+        emb.emb_bag_backward_sort_prepared(ts, B, nnz, ws, None, None, nu, st)
+        emb.emb_bag_backward_update(ts, B, nnz, dout, 0.01, 1e-8, ws, nu, None, None)
+        torch.cuda.synchronize()
+        return int(st.item()), int(nu.item())
+
+    ts, w, acc, ws = fresh()
+    inner = np.setdiff1d(np.arange(1, T * B), np.arange(0, T * B + 1, B))          # not where a table starts
+    for bad_bags, value in ((inner[:1], nnz + 5), (inner[-1:], -1), (inner[::7], 0), (inner, None), (inner[len(inner) // 2:], 1 << 40)):
+        bad = off.copy()
+        bad[bad_bags] = rng.integers(0, nnz + 1, size=len(bad_bags)) if value is None else value
+        assert (np.diff(bad) < 0).any() and step(ts, ws, bad) == (emb.STATUS_BAD_OFFSETS, 0)
+        assert all(torch.equal(x, table) for x in w) and not any(bool(a.any()) for a in acc)
+    ts2, w2, acc2, ws2 = fresh()
+    assert step(ts, ws, off) == step(ts2, ws2, off)
+    assert all(torch.equal(a, b) for a, b in zip(w + acc, w2 + acc2))
+
+
 def test_training_forward_from_lengths_without_bags():
     ts = emb.TableSet([torch.zeros((5, 16), dtype=torch.float32, device=H.DEV)], 16, "f32",
                       accum=[torch.zeros(5, dtype=torch.float32, device=H.DEV)], device=torch.device(H.DEV))
