@@ -324,10 +324,6 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
                                                                int64_t *num_unique_out, uint32_t poll_limit,
                                                                uint32_t *status)
 {
-    if (ctrl->abort) {   // uniform; nobody is to wait for this tile
-        if (threadIdx.x == 0) sort_flag_store(flags + blockIdx.x, SORT_FLAG_FAILED);
-        return;
-    }
     __shared__ uint32_t wave_sums[SORT_WAVES];
     __shared__ uint32_t rows_before, lookback_failed;
     // the tile's runs in order: where each starts (and, after them, where the last one ends), and its place among the
@@ -344,6 +340,10 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
     if (base < n) {
         load_records<KeyT, SORT_ITEMS>(keys + base, k);
         if (base > 0) prev = keys[base - 1];
+    }
+    if (workgroup_aborted(ctrl)) {   // uniform, and asked together with the records; nobody is to wait for this tile
+        if (threadIdx.x == 0) sort_flag_store(flags + blockIdx.x, SORT_FLAG_FAILED);
+        return;
     }
     uint32_t f[SORT_ITEMS], c = 0;
 #pragma unroll
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void runs_list_kernel(const KeyT *__res
     __syncthreads();
     if (lookback_failed) {   // uniform: the numbering is unknown, nothing is written
         if (threadIdx.x == 0) {
-            ctrl->abort = 1;
+            atomicOr(&ctrl->abort, 1u);
             emb_flag(status, EMB_STATUS_SORT_ABANDONED);
         }
         return;

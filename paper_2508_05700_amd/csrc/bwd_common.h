@@ -11,6 +11,17 @@ struct BwdCtrl {
 };
 static_assert(sizeof(BwdCtrl) == 256, "control block is one 256-byte line");
 
+// Whether the backward is aborted, for kernels whose own launch may abort it: one thread reads the word, and every thread of
+// the workgroup gets its answer.  Wavefronts that each read it for themselves could part before a barrier.  Other kernels
+// find the word settled.
+__device__ __forceinline__ bool workgroup_aborted(const BwdCtrl *ctrl)
+{
+    __shared__ uint32_t word;
+    if (threadIdx.x == 0) word = __hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return word != 0;
+}
+
 constexpr int RADIX_BITS = 8;
 constexpr int RADIX = 1 << RADIX_BITS;
 constexpr int SORT_BLOCK = 512;

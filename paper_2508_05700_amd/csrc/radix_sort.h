@@ -349,7 +349,9 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_scatter_kernel(const KeyT *__
                                                                   BwdCtrl *ctrl, unsigned long long *flags,
                                                                   uint32_t poll_limit, uint32_t *status)
 {
-    if (ctrl->abort) {   // uniform; nobody is to wait for this tile
+    const SortTile tile = desc[blockIdx.x];   // (of an aborted backward it says nothing)
+    const bool aborted = LOOKBACK ? workgroup_aborted(ctrl) : ctrl->abort != 0;   // only a pass that waits for others may abort
+    if (aborted) {   // uniform; nobody is to wait for this tile
         if (LOOKBACK && threadIdx.x < RADIX) sort_flag_store(flags + (size_t)blockIdx.x * RADIX + threadIdx.x, SORT_FLAG_FAILED);
         return;
     }
@@ -359,7 +361,6 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_scatter_kernel(const KeyT *__
     __shared__ unsigned long long wave_sums[SORT_WAVES];
     __shared__ KeyT sk[SORT_TILE];
     __shared__ uint32_t sp[SORT_TILE];
-    const SortTile tile = desc[blockIdx.x];
     if (tile.count == 0) return;   // uniform over the workgroup
     const int lane = threadIdx.x & (EMB_WAVE - 1);
     const int wave = threadIdx.x / EMB_WAVE;
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_scatter_kernel(const KeyT *__
     __syncthreads();
     if (LOOKBACK && lookback_failed) {   // uniform: positions unknown, nothing is written
         if (threadIdx.x == 0) {
-            ctrl->abort = 1;
+            atomicOr(&ctrl->abort, 1u);
             emb_flag(status, EMB_STATUS_SORT_ABANDONED);
         }
         return;

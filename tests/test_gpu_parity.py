@@ -1513,6 +1513,30 @@ def test_backward_sort_wait_that_runs_out_abandons_the_backward_and_changes_noth
     _check_backward_against_oracle(tables, Rs + [1] * extra, rows, off, B, D, "sum", dout, "after an abandoned sort")
 
 
+def test_backward_sort_that_is_abandoned_while_workgroups_are_still_to_start():
+    # More workgroups a pass than the chip holds at once: those that start late find the backward aborted by others of their
+    # own launch, and all wavefronts of a workgroup have to see the same.
+    rng = np.random.default_rng(4473)
+    T, B, D, R, n = 24, 64, 4, 70_000, 250_000
+    off = np.sort(rng.integers(0, n + 1, size=(T, B - 1)), axis=1)
+    off = np.concatenate([off + n * np.arange(T)[:, None], n * np.arange(1, T + 1)[:, None]], axis=1).reshape(-1)
+    off = np.concatenate([[0], off]).astype(np.int64)
+    rows = rng.integers(0, R, size=n * T).astype(np.int64)
+    dout = rng.standard_normal((T, B, D)).astype(np.float32)
+    table = (rng.standard_normal((R, D)) * 0.01).astype(np.float32)
+    ts, w_dev, acc_dev = H.make_tableset([table] * T, "f32", with_accum=True)
+    for want_unique in (False, True):
+        emb.emb_debug_sort_poll_limit(0)
+        try:
+            g = H.gpu_backward(ts, rows, off, B, "sum", dout, 0.01, 1e-8, want_unique=want_unique)
+        finally:
+            emb.emb_debug_sort_poll_limit(-1)
+        assert g["status"] == emb.STATUS_SORT_ABANDONED
+        assert all(np.array_equal(w.cpu().numpy(), table) and not a.any().item() for w, a in zip(w_dev, acc_dev))
+    g = H.gpu_backward(ts, rows, off, B, "sum", dout, 0.01, 1e-8)
+    assert g["status"] == 0 and np.array_equal(g["unique_keys"], np.unique(rows + R * np.repeat(np.arange(T), n)))
+
+
 def _rows_with_run_lengths(rng, n, R, runs):
     """n row numbers below R: the first rows as often as `runs` says while that fits, the rest at random, shuffled."""
     hot = np.repeat(np.arange(len(runs)), runs)[:n]
