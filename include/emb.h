@@ -398,7 +398,8 @@ int emb_quantize_rows(const float *src_dev, int64_t num_rows, int32_t D, int32_t
  * The tables need accumulators (accum != NULL), the workspace is that of
  * emb_bag_backward_workspace_bytes and must stay untouched until the update
  * has run; T, D, dtype, B, nnz, tables and workspace are the same in the three
- * calls.  rows_out_dev is nullable.  dtype: EMB_F32 or EMB_BF16. */
+ * calls.  rows_out_dev is nullable and may be raw_dev (the row numbers then take
+ * the place of the IDs).  dtype: EMB_F32 or EMB_BF16. */
 int emb_bag_forward_train(const emb_table *tables_host, const emb_table *tables_dev, int32_t T,
                           int32_t D, int32_t dtype, const uint64_t *raw_dev,
                           const int64_t *offsets_dev, int64_t B, int64_t nnz, int32_t mode,

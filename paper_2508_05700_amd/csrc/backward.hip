@@ -982,19 +982,28 @@ int launch_train(bool bf16, const BwdArgs &a, const BwdLayout &L, const int64_t 
         if (a.small) {
             const int32_t *lengths = make && (int64_t)a.T * a.B <= EMB_LENGTHS_DIRECT_BAGS ? a.lengths : nullptr;
             const int64_t tile_blocks = emb_round_up_xcds(tile_sort_blocks(a));   // (not above nnz and T together: both small)
-#define EMB_TRAIN_SMALL(BF, MAKE)                                                                                            \
-    hipLaunchKernelGGL((bag_forward_train_small_kernel<LPR, CPL, UNROLL, BF, MAKE>), dim3((unsigned)(tile_blocks + blocks)), \
+            // row numbers that take the place of the raw IDs: the tiles are sorted before the lookup, not beside it
+            const char *const ids = reinterpret_cast<const char *>(raw), *const rows = reinterpret_cast<const char *>(rows_out);
+            const bool over_ids = rows && rows < ids + a.nnz * 8 && ids < rows + a.nnz * 8;
+#define EMB_TRAIN_SMALL(BF, MAKE, SORTING, LOOKING_UP)                                                                        \
+    hipLaunchKernelGGL((bag_forward_train_small_kernel<LPR, CPL, UNROLL, BF, MAKE>), dim3((unsigned)((SORTING) + (LOOKING_UP))), \
                        dim3(TRAIN_BLOCK), 0, a.stream, a.tables_dev, a.T, a.B, (uint32_t)per_table, a.nnz, raw, offsets,     \
                        chunks, a.mode, out, rows_out, bag_scale, ctrl, a.status, tile_prefix, a.offsets_out, lengths,        \
-                       table_start_of(a, L), a.num_unique_out, (uint32_t)tile_blocks, tile_sort_args(a, L))
+                       table_start_of(a, L), a.num_unique_out, (uint32_t)(SORTING), tile_sort_args(a, L))
+#define EMB_TRAIN_SMALL_EACH(BF, MAKE)                                                  \
+    do {                                                                                \
+        if (over_ids) EMB_TRAIN_SMALL(BF, MAKE, tile_blocks, 0);                        \
+        EMB_TRAIN_SMALL(BF, MAKE, over_ids ? (int64_t)0 : tile_blocks, blocks);         \
+    } while (0)
             if (blocks + tile_blocks > (int64_t)0x7FFFFFFF) return EMB_ERR_UNSUPPORTED;
             if (make) {
-                if (bf16) EMB_TRAIN_SMALL(true, true);
-                else EMB_TRAIN_SMALL(false, true);
+                if (bf16) EMB_TRAIN_SMALL_EACH(true, true);
+                else EMB_TRAIN_SMALL_EACH(false, true);
             } else {
-                if (bf16) EMB_TRAIN_SMALL(true, false);
-                else EMB_TRAIN_SMALL(false, false);
+                if (bf16) EMB_TRAIN_SMALL_EACH(true, false);
+                else EMB_TRAIN_SMALL_EACH(false, false);
             }
+#undef EMB_TRAIN_SMALL_EACH
 #undef EMB_TRAIN_SMALL
             EMB_RETURN_IF_LAUNCH_FAILED();
             return EMB_OK;

@@ -1259,6 +1259,42 @@ def test_tiles_sorted_beside_the_training_lookup_give_the_bits_of_records_in_mem
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("per_table,B", [([10_000] * 3, 512), ([90_000], 3000), ([130_000] * 2, 700)])
+@pytest.mark.parametrize("from_lengths", [True, False])
+def test_training_lookup_may_write_the_row_numbers_over_the_raw_ids(per_table, B, from_lengths):
+    # rows_out_dev is raw_dev: every ID is read before its row number takes its place, also by those who sort (the first two
+    # are small steps, whose tiles are sorted from the raw IDs).
+    T, D, R = len(per_table), 16, 3000
+    rng = np.random.default_rng(6500 + B + T)
+    lengths = np.concatenate([np.bincount(np.sort(rng.integers(0, B, size=n)), minlength=B) for n in per_table]).astype(np.int32)
+    off, _ = oracle.lengths_to_offsets(lengths)
+    nnz = int(off[-1])
+    raw = rng.integers(0, 1 << 64, size=nnz, dtype=np.uint64)
+    table = H.dev((rng.standard_normal((R, D)) * 0.01).astype(np.float32))
+    dout = H.dev(rng.standard_normal((T, B, D)).astype(np.float32))
+    off_d, len_d = H.dev(off), H.dev(lengths)
+
+    def step(in_place):
+        w, acc = [table.clone() for _ in range(T)], [torch.zeros(R, dtype=torch.float32, device=H.DEV) for _ in range(T)]
+        ts = emb.TableSet(w, D, "f32", accum=acc, salts=list(range(T)), device=torch.device(H.DEV))
+        ws = torch.empty(emb.emb_bag_backward_workspace_bytes(T, B, nnz, ts.total_rows, D, "f32"), dtype=torch.uint8, device=H.DEV)
+        nu, st = torch.zeros(1, dtype=torch.int64, device=H.DEV), torch.zeros(1, dtype=torch.int32, device=H.DEV)
+        out, ids = torch.empty((T, B, D), dtype=torch.float32, device=H.DEV), H.dev(raw)
+        rows = ids.view(torch.int64) if in_place else torch.empty(nnz, dtype=torch.int64, device=H.DEV)
+        if from_lengths:
+            emb.emb_bag_forward_train_lengths(ts, ids, len_d, B, "sum", out, torch.empty_like(off_d), ws, rows, nu, st)
+        else:
+            emb.emb_bag_forward_train(ts, ids, off_d, B, "sum", out, ws, rows, nu, st)
+        emb.emb_bag_backward_sort_prepared(ts, B, nnz, ws, None, None, nu, st)
+        emb.emb_bag_backward_update(ts, B, nnz, dout, 0.01, 1e-8, ws, nu, None, None)
+        torch.cuda.synchronize()
+        assert st.item() == 0
+        return [rows, out, nu] + w + acc
+
+    for a, b in zip(step(True), step(False)):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("per_table,B", [([5000, 0, 7000], 257), ([900], 40), ([40] * 300, 4), ([100_000], 3000)])
 def test_malformed_bags_of_a_small_training_step_leave_tables_and_workspace_sound(per_table, B):
     # Tables whose records start and end where they should, and bags inside them that do not ascend: lookup workgroups abort
