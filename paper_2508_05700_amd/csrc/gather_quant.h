@@ -14,6 +14,17 @@ __device__ __forceinline__ uint2 load_u2(const char *p)   // rows are in device 
     return make_uint2(v.x, v.y);
 }
 
+// 16 bytes of an INT4 row, from a lane's place on: lanes are 8 bytes apart, so every other address is a multiple of 8 only.
+// (Still one request: the vector unit loads 16 bytes from any multiple of 4.)
+constexpr int Q4_LANE_BYTES = Q_ELEMS / 2;
+typedef uint32_t emb_u4_codes __attribute__((ext_vector_type(4), aligned(8)));
+static_assert(Q4_LANE_BYTES % alignof(emb_u4_codes) == 0, "the type promises no more than a lane's address keeps");
+__device__ __forceinline__ uint4 load_codes(const char *p)
+{
+    const emb_u4_codes v = *(const EMB_GLOBAL emb_u4_codes *)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // 16 codes of a lane -> fp32.  INT4: masking every other nibble leaves one code per
 // byte, which converts with the byte-to-float instructions.
 template <int BITS>
@@ -52,7 +63,7 @@ __device__ __forceinline__ void gather_dequant_rows(float (&acc)[Q_ELEMS], const
     for (int i = 0; i < N; ++i) {
         const char *row = group_bcast_ptr<LPR>(mine[IPL == 1 ? 0 : (k0 + i) / LPR], (k0 + i) % LPR);
         if (BITS == 4) {
-            const uint4 v = load_chunk(row + code_off - 8);
+            const uint4 v = load_codes(row + code_off - Q4_LANE_BYTES);
             hdr[i] = make_uint2(v.x, v.y);
             w[i][0] = v.z;
             w[i][1] = v.w;
@@ -92,7 +103,7 @@ __device__ __forceinline__ void gather_dequant_pool_range(Source &src, bool live
     constexpr int IB = IPL * LPR;                           // indices per batch
     static_assert(IB % UNROLL == 0, "index batch must be whole unroll groups");
     const bool mine_elems = l * Q_ELEMS < D;         // lanes past the row (D/16 not a power of two) read its first codes
-    const uint32_t code_off = 8u + (mine_elems ? (uint32_t)l * (BITS == 8 ? 16u : 8u) : 0u);
+    const uint32_t code_off = 8u + (mine_elems ? (uint32_t)l * (BITS == 8 ? 16u : (uint32_t)Q4_LANE_BYTES) : 0u);
 
     if (!live) {
         s = e = 0;
