@@ -82,11 +82,14 @@ __device__ __forceinline__ bool merge_part_of(const int64_t *__restrict__ table_
 }
 
 constexpr uint32_t MERGE_DIGITS = 1u << MERGE_BITS_MAX;
-struct TileSortLds {
+struct alignas(sizeof(uint4)) TileSortLds {
     uint32_t cnt[MERGE_WAVES][MERGE_DIGITS];   // per-wavefront digit counts, then offsets inside the tile
     uint32_t sk[MERGE_TILE], sp[MERGE_TILE];
     uint32_t wave_sums[MERGE_WAVES];
 };
+// the counts are cleared, and offsets that stand in their place written, 16 bytes at a time
+static_assert(alignof(TileSortLds) % alignof(uint4) == 0 && offsetof(TileSortLds, cnt) % alignof(uint4) == 0 &&
+                  sizeof(TileSortLds::cnt[0]) % sizeof(uint4) == 0, "16-byte accesses of LDS");
 
 // How the tiles of a small step are sorted and where they go.
 struct TileSortArgs {
