@@ -145,12 +145,6 @@ __device__ __forceinline__ uint32_t emb_xcd_block(uint32_t linear_block, uint32_
 {
     return (linear_block % EMB_XCDS) * (grid_blocks / EMB_XCDS) + linear_block / EMB_XCDS;
 }
-// The same with every die's stretch taken from its end: for a kernel that goes over what the one before it went over.
-__device__ __forceinline__ uint32_t emb_xcd_block_reversed(uint32_t linear_block, uint32_t grid_blocks)
-{
-    const uint32_t per_die = grid_blocks / EMB_XCDS;
-    return (linear_block % EMB_XCDS) * per_die + (per_die - 1 - linear_block / EMB_XCDS);
-}
 
 __device__ __forceinline__ void emb_flag(uint32_t *status, uint32_t bit)
 {

@@ -347,12 +347,8 @@ __global__ __launch_bounds__(UPD_BLOCK) void update_kernel(const emb_table *__re
     const int lane = threadIdx.x & (EMB_WAVE - 1);
     const int g = lane / LPR;
     const int l = lane % LPR;
-    // Sorted records are table-major: one die works on one stretch of tables (emb_xcd_block), here from its end.  The
-    // lookup of the step went over the same tables from the start, and more rows than the memory-side cache holds (300
-    // of 256 MB for sixteen tables of 256-byte rows and 2.6e6 lookups): the tables it read last are still there, and
-    // those updated last are the first the next lookup asks for.  Same card, first to last / last to first: this kernel
-    // 216 and 200 / 200 and 185 us, the lookup of the next step 90 / 86 and 81.
-    const uint64_t wid = (uint64_t)emb_xcd_block_reversed(blockIdx.x, gridDim.x) * WAVES + wave;
+    // sorted records are table-major: one die works on one stretch of tables (emb_xcd_block)
+    const uint64_t wid = (uint64_t)emb_xcd_block(blockIdx.x, gridDim.x) * WAVES + wave;
     const uint64_t first = wid * UPD_SPAN;
     const bool in = first < n;
     const uint32_t i0 = (uint32_t)first;
