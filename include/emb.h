@@ -134,6 +134,8 @@ int emb_lengths_to_offsets(const int32_t *lengths_dev, int64_t n, int64_t *offse
  * rows are widened exactly and accumulated in fp32; rows of a quantised table
  * (EMB_INT8, EMB_INT4) contribute scale * code + bias, dequantised in fp32
  * while they are gathered; out is fp32 [T,B,D] and is fully overwritten.
+ * A bag's rows are added in the order of its lookups, here and in every other
+ * lookup below: its bits do not depend on the other bags of the batch.
  * rows_dev: i64[nnz]; offsets_dev: i64[T*B+1].
  * EMB_ERR_UNSUPPORTED if D*element_size is not a multiple of 16 or exceeds
  * 16384 bytes (quantised: D not a multiple of 16 or above 1024), or T > 65535.
