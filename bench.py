@@ -40,19 +40,19 @@ def log(*a):
 # bytes or less are counted at their true size, so for kernels that issue those (4-byte accumulators,
 # 48-byte quantised rows) the scaled figure is an upper bound.
 PMC_TRAFFIC = {
-    "sources": "6feb529de9afa25f",
+    "sources": "397ab73d7bc1cf73",
     "fetch_scale": 2.0,
     "write_scale": 1.0,
     "kib_per_launch": {     # workload -> kernel -> (FETCH_SIZE, WRITE_SIZE)
-        "3": {"bag_forward_train_kernel": (173371.2, 69677.4), "update_kernel": (240916.9, 324005.8)},
-        "3b": {"bag_forward_train_kernel": (90604.5, 74115.9), "update_kernel": (170603.5, 221075.1)},
-        "2": {"bag_forward_kernel<HASHED>": (172152.1, 33876.9), "bag_forward_kernel": (172409.5, 32768.0)},
-        "2u": {"bag_forward_kernel<HASHED>": (338201.3, 33803.0), "bag_forward_kernel": (338155.3, 32768.0)},
-        "2un": {"bag_forward_kernel": (339975.7, 32768.0)},
-        "2q4": {"bag_forward_quant_kernel": (107657.1, 33819.0)},
-        "2uq4": {"bag_forward_quant_kernel": (214897.9, 33894.5)},
-        "2uq4r": {"bag_forward_quant_kernel": (174203.3, 33843.8)},
-        "4": {"bag_forward_kernel<HASHED>": (47079.6, 8710.4)},
+        "3": {"bag_forward_train_kernel": (173346.8, 69745.4), "update_kernel": (240598.3, 324003.5)},
+        "3b": {"bag_forward_train_kernel": (90592.8, 74096.1), "update_kernel": (170049.5, 220965.9)},
+        "2": {"bag_forward_kernel<HASHED>": (172110.7, 33881.5), "bag_forward_kernel": (172148.3, 32768.0)},
+        "2u": {"bag_forward_kernel<HASHED>": (338204.7, 33799.2), "bag_forward_kernel": (338158.3, 32768.0)},
+        "2un": {"bag_forward_kernel": (339593.3, 32768.0)},
+        "2q4": {"bag_forward_quant_kernel": (112578.4, 33834.0)},
+        "2uq4": {"bag_forward_quant_kernel": (224676.2, 33901.2)},
+        "2uq4r": {"bag_forward_quant_kernel": (182318.7, 33865.0)},
+        "4": {"bag_forward_kernel<HASHED>": (52440.7, 8704.3)},
     },
 }
 
